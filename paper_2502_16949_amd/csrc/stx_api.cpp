@@ -4,6 +4,7 @@
 #include <new>
 
 #include "stx_internal.h"
+#include "stx_rank.h"
 
 using namespace stx;
 
@@ -15,6 +16,7 @@ struct Layout {
     size_t ctrl, keys[3], pay[2], cix[2], table, table1, super, tile_heads, loss_partials, partials, gbuf[4], total;
     size_t tr_items, tr_dm_items, tr_fix_items, tr_counts, tr_m16, tr_m16t, tr_xt, tr_gyt;
     size_t colmap, rel_cnt;
+    size_t rank_q, rank_e, rank_q_bytes, rank_e_bytes;
     int map_words;
     int64_t rows_max, nnz_max, cols_max;
     int ld, out_dim, ntiles_max, fwd_blocks_max, n_gbuf;
@@ -107,6 +109,13 @@ Layout make_layout(const stx_config *c)
         L.tr_gyt = take((items + 1) * kProjRows * c->rel_dim * 2);
         L.rel_cnt = take((size_t)2 * c->n_rel * 4);
     }
+    if (c->model == STX_TRANSE || c->model == STX_TORUSE) {
+        L.rank_q_bytes = rank_filter_q_bytes(c->dist, c->dim, 32) ? kRankQBytes : 0;
+        L.rank_e_bytes = rank_filter_e_bytes(c->dist, c->dim, c->n_ent, 1);
+        if (L.rank_e_bytes > kRankEBytes) L.rank_e_bytes = kRankEBytes;
+        L.rank_q = take(L.rank_q_bytes);
+        L.rank_e = take(L.rank_e_bytes);
+    }
     L.total = off;
     return L;
 }
@@ -196,6 +205,10 @@ stx_status stx_create(const stx_config *cfg, void *workspace, size_t workspace_b
     c->tile_heads = (int32_t *)(base + L.tile_heads);
     c->loss_partials = (float *)(base + L.loss_partials);
     c->partials = (float *)(base + L.partials);
+    c->rank_q = base + L.rank_q;
+    c->rank_e = base + L.rank_e;
+    c->rank_q_bytes = L.rank_q_bytes;
+    c->rank_e_bytes = L.rank_e_bytes;
     for (int i = 0; i < 4; ++i) c->gbuf[i] = i < L.n_gbuf ? (float *)(base + L.gbuf[i]) : nullptr;
     const bool tr = cfg->model == STX_TRANSR;
     c->tr_items = tr ? (int32_t *)(base + L.tr_items) : nullptr;

@@ -21,6 +21,10 @@ constexpr int kSelfScanTiles = 512;   // up to this many sort tiles, scatter wor
 constexpr int kMapMaxWords = 2048;     // presence bitmap of the columns: kept when n_ent + n_rel <= 32 * this
 constexpr int kRelCntMax = 4096;       // TransR: rows per relation are counted while A is written when n_rel <= this
 constexpr int kMaxDim = 1024;
+// stx_rank on TransE / TorusE, distance kinds with a filtered sweep: bytes of a context's workspace that hold packed
+// queries and packed candidates (16 MB of a d = 128 table are 65,536 candidates; longer tables go in segments, which
+// the caches hold between the kernel that packs one and the sweep that reads it)
+constexpr size_t kRankQBytes = (size_t)48 << 20, kRankEBytes = (size_t)32 << 20;
 constexpr int kMaxProjDim = 256;        // TransR: dim and rel_dim are multiples of 32 up to this
 constexpr int kProjRows = 64;           // TransR: entries of one relation per work item of the two row products
 constexpr int kProjRowsDm = 256;        // ... and per work item of the product that forms dL/dM_r
@@ -198,6 +202,8 @@ struct stx_ctx {
     int32_t *tile_heads;           // [ntiles_max + 1]
     float *loss_partials;          // [fwd_blocks_max]
     float *partials;               // [(nnz_max/kSegTileMin + 2) * 2 * ld]
+    char *rank_q, *rank_e;         // TransE / TorusE: scratch of the filtered sweeps of stx_rank (stx_rank.h)
+    size_t rank_q_bytes, rank_e_bytes;
     float *gbuf[4];                // per-row buffers, rows_max x ld each (how many depends on the model)
     uint32_t *colmap[3];           // presence bitmaps of the columns (adjacent), or null when the table is too wide
     int map_words, map_cur;        // words per map (0: not kept); which map the next build fills (they rotate)

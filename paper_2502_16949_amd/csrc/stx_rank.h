@@ -1,0 +1,86 @@
+// What the kernels of link prediction share (stx_rank.hip, stx_rank_filter.hip): their arguments, the rows of a
+// query, and one step of a distance sum.
+#pragma once
+
+#include "stx_rowops.h"
+
+namespace stx {
+
+// One step of the distance sum (Sec. 4.3, 4.6), index order.  The L2 kinds use a fused multiply-add.
+template <int DIST>
+__device__ inline float rank_step(float acc, float y)
+{
+    if (DIST == STX_L1) return acc + fabsf(y);
+    if (DIST == STX_L2 || DIST == STX_L2_SQ) return __builtin_fmaf(y, y, acc);
+    const float f = __builtin_amdgcn_fractf(y);            // fractional part, always below 1
+    const float m = fminf(f, 1.0f - f);
+    return DIST == STX_TORUS_L1 ? acc + m : __builtin_fmaf(m, m, acc);
+}
+
+constexpr int kRankTables = 32;        // TransR: relations per launch
+struct RankIds {                       // (an argument of its own: indexed inside the struct that kernels copy and narrow,
+    int32_t g[kRankTables];            // it would put that copy in memory)
+};
+struct RankArgs {
+    const float *X;                    // TransE / TorusE: [E;R]; TransH: E.  Rows of dim floats
+    const float *D, *W;                // TransH: d_r and w_r, n_rel rows each
+    const int32_t *h, *r, *t;          // [nq]; r may be null: every query has relation 0
+    int64_t nq;
+    int32_t n_ent, n_rel;
+    int dim;
+    int32_t slice;                     // candidates per blockIdx.y, a multiple of kRankE
+    float *true_score;                 // [nq]: the true entity's sum until k_rank_finish
+    int32_t *n_less, *n_equal;         // [nq], cleared by k_rank_true
+    int32_t *bad;                      // counter of out-of-range indices
+    // TransR: blockIdx.z is one of up to kRankTables relations (RankIds); relation g owns the grouped queries
+    // [grp_offsets[g], + grp_counts[g]) (h, t and the outputs are grouped arrays) and table number blockIdx.z.
+    const int32_t *grp_counts, *grp_offsets;
+    int64_t table_stride;              // floats between the tables of consecutive blockIdx.z
+};
+
+// Narrows the arguments to the relation of this workgroup.
+__device__ inline void rank_group(RankArgs &a, const RankIds &ids)
+{
+    if (!a.grp_counts) return;
+    const int32_t g = ids.g[blockIdx.z];
+    const int32_t n = a.grp_counts[g];
+    const int64_t off = a.grp_offsets[g];
+    a.X += (int64_t)blockIdx.z * a.table_stride;
+    a.h += off; a.t += off;
+    a.true_score += off; a.n_less += off; a.n_equal += off;
+    a.nq = n;
+}
+
+// Clamped table rows of one query: q = h + r (tail side) or t - r (head side); the true entity is t or h.
+struct RankRows {
+    const float *pa, *pr, *ptrue;
+    int32_t itrue;
+    bool bad;
+};
+template <bool HEAD>
+__device__ inline RankRows rank_rows(const RankArgs &a, int64_t qi)
+{
+    int32_t ih = a.h[qi], ir = a.r ? a.r[qi] : 0, it = a.t[qi];
+    const bool bad = ih < 0 || ih >= a.n_ent || it < 0 || it >= a.n_ent || ir < 0 || ir >= a.n_rel;
+    ih = min(max(ih, 0), a.n_ent - 1);
+    it = min(max(it, 0), a.n_ent - 1);
+    ir = min(max(ir, 0), a.n_rel - 1);
+    return {a.X + (int64_t)(HEAD ? it : ih) * a.dim, a.X + ((int64_t)a.n_ent + ir) * a.dim,
+            a.X + (int64_t)(HEAD ? ih : it) * a.dim, HEAD ? ih : it, bad};
+}
+
+// ---- stx_rank_filter.hip ------------------------------------------------------------------------------
+// Scratch of a filtered sweep: packed queries with their thresholds; packed candidates (matrix-core kinds).  Sweeps
+// of more queries or candidates than fit go chunk by chunk.
+struct RankScratch {
+    char *q, *e;
+    size_t q_bytes, e_bytes;
+    float *q32;                        // TransR: fp32 query points of all grouped queries (else part of q)
+};
+size_t rank_filter_q_bytes(int dist, int width, int64_t queries);                 // 0: a kind without a filtered sweep
+size_t rank_filter_e_bytes(int dist, int width, int64_t candidates, int tables);
+// True scores and counts (not the final square roots) through the filter.  nz: 0, or the number of relations of a
+// TransR launch (blockIdx.z), which must fit the scratch in one piece.  false: not for this kind, nothing launched.
+bool rank_filtered(stx_ctx *, const RankArgs &, int side, const RankScratch &, int nz, const RankIds &);
+
+}  // namespace stx

@@ -13,9 +13,10 @@
 // registers, so every value fetched from LDS feeds eight steps.  Sums run over the row in index order in
 // one thread; the true entity's own sum is formed the same way, so it compares equal to itself.
 // Counts are integers: candidate slices of one query block add theirs with atomics, in any order.
+#include <algorithm>
 #include <new>
 
-#include "stx_rowops.h"
+#include "stx_rank.h"
 
 namespace stx {
 
@@ -23,51 +24,6 @@ constexpr int kRankQ = 128;            // queries per workgroup
 constexpr int kRankE = 128;            // candidates per tile
 constexpr int kRankJ = 32;             // floats of a row per staged chunk
 constexpr int kRankLd = kRankQ + 4;    // floats per LDS row: keeps float4 alignment, shifts banks by 4 per row
-
-// One step of the distance sum (Sec. 4.3, 4.6), index order.  The L2 kinds use a fused multiply-add.
-template <int DIST>
-__device__ inline float rank_step(float acc, float y)
-{
-    if (DIST == STX_L1) return acc + fabsf(y);
-    if (DIST == STX_L2 || DIST == STX_L2_SQ) return __builtin_fmaf(y, y, acc);
-    const float f = __builtin_amdgcn_fractf(y);            // fractional part, always below 1
-    const float m = fminf(f, 1.0f - f);
-    return DIST == STX_TORUS_L1 ? acc + m : __builtin_fmaf(m, m, acc);
-}
-
-struct RankArgs {
-    const float *X;                    // TransE / TorusE: [E;R]; TransH: E.  Rows of dim floats
-    const float *D, *W;                // TransH: d_r and w_r, n_rel rows each
-    const int32_t *h, *r, *t;          // [nq]; r may be null: every query has relation 0
-    int64_t nq;
-    int32_t n_ent, n_rel;
-    int dim;
-    int32_t slice;                     // candidates per blockIdx.y, a multiple of kRankE
-    float *true_score;                 // [nq]: the true entity's sum until k_rank_finish
-    int32_t *n_less, *n_equal;         // [nq], cleared by k_rank_true
-    int32_t *bad;                      // counter of out-of-range indices
-    // TransR: blockIdx.z walks the relations grp_first, grp_first + 1, ...; relation g owns the grouped queries
-    // [grp_offsets[g], + grp_counts[g]) (h, t and the outputs are grouped arrays) and table number blockIdx.z.
-    // With several relations per launch, those with more than grp_big queries are left to a launch of their own.
-    const int32_t *grp_counts, *grp_offsets;
-    int32_t grp_first, grp_big;
-    int64_t table_stride;              // floats between the tables of consecutive blockIdx.z
-};
-
-// Narrows the arguments to the relation of this workgroup; false: nothing to do.
-__device__ inline bool rank_group(RankArgs &a)
-{
-    if (!a.grp_counts) return true;
-    const int32_t g = a.grp_first + (int32_t)blockIdx.z;
-    const int32_t n = a.grp_counts[g];
-    if (n == 0 || (gridDim.z > 1 && n > a.grp_big)) return false;
-    const int64_t off = a.grp_offsets[g];
-    a.X += (int64_t)blockIdx.z * a.table_stride;
-    a.h += off; a.t += off;
-    a.true_score += off; a.n_less += off; a.n_equal += off;
-    a.nq = n;
-    return true;
-}
 
 // The 8 x 8 block of a thread: query u is block row (u < 4 ? 0 : 64) + 4 ty + (u & 3) of the workgroup's 128,
 // candidate v is (v < 4 ? 0 : 64) + 4 tx + (v & 3) of the tile's 128.
@@ -103,29 +59,12 @@ __device__ inline void rank_flush(const RankArgs &a, int64_t q0, int tx, int ty,
     }
 }
 
-// Clamped table rows of one query: q = h + r (tail side) or t - r (head side); the true entity is t or h.
-struct RankRows {
-    const float *pa, *pr, *ptrue;
-    bool bad;
-};
-template <bool HEAD>
-__device__ inline RankRows rank_rows(const RankArgs &a, int64_t qi)
-{
-    int32_t ih = a.h[qi], ir = a.r ? a.r[qi] : 0, it = a.t[qi];
-    const bool bad = ih < 0 || ih >= a.n_ent || it < 0 || it >= a.n_ent || ir < 0 || ir >= a.n_rel;
-    ih = min(max(ih, 0), a.n_ent - 1);
-    it = min(max(it, 0), a.n_ent - 1);
-    ir = min(max(ir, 0), a.n_rel - 1);
-    return {a.X + (int64_t)(HEAD ? it : ih) * a.dim, a.X + ((int64_t)a.n_ent + ir) * a.dim,
-            a.X + (int64_t)(HEAD ? ih : it) * a.dim, bad};
-}
-
 // One thread per query: the true entity's sum, formed step by step in index order exactly as the sweep forms
 // every candidate's, so that the true entity ties with itself there.  Also clears the query's counters.
 template <int DIST, bool HEAD>
-__global__ __launch_bounds__(kThreads) void k_rank_true(RankArgs a)
+__global__ __launch_bounds__(kThreads) void k_rank_true(RankArgs a, RankIds ids)
 {
-    if (!rank_group(a)) return;
+    rank_group(a, ids);
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= a.nq) return;
     const RankRows rw = rank_rows<HEAD>(a, i);
@@ -155,12 +94,12 @@ __global__ __launch_bounds__(kThreads) void k_rank_finish(float *true_score, int
 
 // (three waves per SIMD: the register budget that lets three workgroups share a compute unit)
 template <int DIST, bool HEAD>
-__global__ __launch_bounds__(kThreads, 3) void k_rank(RankArgs a)
+__global__ __launch_bounds__(kThreads, 3) void k_rank(RankArgs a, RankIds ids)
 {
     __shared__ __attribute__((aligned(16))) float s_q[kRankJ][kRankLd];
     __shared__ __attribute__((aligned(16))) float s_e[kRankJ][kRankLd];
 
-    if (!rank_group(a)) return;                           // (uniform over the workgroup)
+    rank_group(a, ids);
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;               // candidate / query position of the 8 x 8 block
     const int64_t q0 = (int64_t)blockIdx.x * kRankQ;
@@ -274,7 +213,7 @@ __device__ inline float rank_dot_row(const float *__restrict__ pw, const float *
 }
 
 template <int DIST, bool HEAD>
-__global__ __launch_bounds__(kThreads) void k_rank_true_h(RankArgs a)
+__global__ __launch_bounds__(kThreads) void k_rank_true_h(RankArgs a, RankIds)
 {
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
     if (i >= a.nq) return;
@@ -299,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void k_rank_true_h(RankArgs a)
 }
 
 template <int DIST, bool HEAD>
-__global__ __launch_bounds__(kThreads, 2) void k_rank_h(RankArgs a)
+__global__ __launch_bounds__(kThreads, 2) void k_rank_h(RankArgs a, RankIds)
 {
     __shared__ __attribute__((aligned(16))) float s_b[kRankJ][kRankLd];
     __shared__ __attribute__((aligned(16))) float s_w[kRankJ][kRankLd];
@@ -438,6 +377,7 @@ struct RankRWork {                      // partitions of the caller's work buffe
     int32_t *gless, *gequal;
     float *table;                       // n_tables tables of (n_ent + 1) x rel_dim: P_r, then r
     int n_tables;
+    RankScratch ws;                     // of the filtered sweeps (kinds that have one)
     size_t total;
 };
 constexpr int kRankBig = 1024;          // relations with more queries than this get a launch of their own
@@ -458,9 +398,16 @@ static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
     // relations with few queries are swept several per launch, each with a table of its own: up to 32, within 256 MiB
     const size_t table_bytes = (size_t)(cfg.n_ent + 1) * cfg.rel_dim * 4;
     const size_t fit = ((size_t)256 << 20) / table_bytes;
-    w.n_tables = (int)(fit < 1 ? 1 : (fit > 32 ? 32 : fit));
+    w.n_tables = (int)(fit < 1 ? 1 : (fit > kRankTables ? kRankTables : fit));
     if (w.n_tables > cfg.n_rel) w.n_tables = (int)cfg.n_rel;
     w.table = (float *)take(table_bytes * w.n_tables);
+    // one relation with all queries, or n_tables relations with up to kRankBig each
+    const int64_t few = nq < kRankBig ? nq : kRankBig, many = ((few + 31) / 32 * 32) * w.n_tables;
+    w.ws.q_bytes = rank_filter_q_bytes(cfg.dist, cfg.rel_dim, nq > many ? nq : many);
+    w.ws.e_bytes = rank_filter_e_bytes(cfg.dist, cfg.rel_dim, cfg.n_ent, w.n_tables);
+    w.ws.q = take(w.ws.q_bytes);
+    w.ws.e = take(w.ws.e_bytes);
+    w.ws.q32 = w.ws.q_bytes ? (float *)take((size_t)nq * cfg.rel_dim * 4) : nullptr;
     w.total = off;
     return w;
 }
@@ -475,14 +422,29 @@ __global__ __launch_bounds__(kThreads) void k_rr_clear(int32_t *counts, int32_t 
     if (i < n_rel) { counts[i] = 0; cursor[i] = 0; }
 }
 
+// Both grouping kernels count in LDS first (n_rel <= kRelCntMax): the hot relation of a Zipf distribution takes a
+// quarter of the queries, and one global atomic per query on its counter made them 76 us each at 20,466 queries.
 __global__ __launch_bounds__(kThreads) void k_rr_hist(const int32_t *h, const int32_t *r, const int32_t *t, int64_t nq,
                                                       int32_t n_ent, int32_t n_rel, int32_t *counts, int32_t *bad)
 {
+    __shared__ int32_t s_cnt[kRelCntMax];
+    const bool local = n_rel <= kRelCntMax;
+    if (local) {
+        for (int j = threadIdx.x; j < n_rel; j += kThreads) s_cnt[j] = 0;
+        __syncthreads();
+    }
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= nq) return;
-    const int32_t ih = h[i], ir = r[i], it = t[i];
-    if (ih < 0 || ih >= n_ent || it < 0 || it >= n_ent || ir < 0 || ir >= n_rel) atomicAdd(bad, 1);
-    atomicAdd(&counts[min(max(ir, 0), n_rel - 1)], 1);
+    if (i < nq) {
+        const int32_t ih = h[i], ir = r[i], it = t[i];
+        if (ih < 0 || ih >= n_ent || it < 0 || it >= n_ent || ir < 0 || ir >= n_rel) atomicAdd(bad, 1);
+        const int32_t g = min(max(ir, 0), n_rel - 1);
+        atomicAdd(local ? &s_cnt[g] : &counts[g], 1);
+    }
+    if (local) {
+        __syncthreads();
+        for (int j = threadIdx.x; j < n_rel; j += kThreads)
+            if (s_cnt[j]) atomicAdd(&counts[j], s_cnt[j]);
+    }
 }
 
 // offsets[i] = counts[0] + ... + counts[i-1], offsets[n_rel] = nq.  One workgroup.
@@ -506,10 +468,25 @@ __global__ __launch_bounds__(kThreads) void k_rr_scatter(const int32_t *h, const
                                                          int32_t n_ent, int32_t n_rel, const int32_t *offsets,
                                                          int32_t *cursor, int32_t *perm, int32_t *gh, int32_t *gt)
 {
+    __shared__ int32_t s_cnt[kRelCntMax];                 // queries of the workgroup per relation, then their first place
+    const bool local = n_rel <= kRelCntMax;
+    if (local) {
+        for (int j = threadIdx.x; j < n_rel; j += kThreads) s_cnt[j] = 0;
+        __syncthreads();
+    }
     const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
+    const int32_t ir = i < nq ? min(max(r[i], 0), n_rel - 1) : 0;
+    int32_t pos = 0;
+    if (i < nq) pos = atomicAdd(local ? &s_cnt[ir] : &cursor[ir], 1);
+    if (local) {
+        __syncthreads();
+        for (int j = threadIdx.x; j < n_rel; j += kThreads)
+            if (s_cnt[j]) s_cnt[j] = atomicAdd(&cursor[j], s_cnt[j]);
+        __syncthreads();
+        pos += s_cnt[ir];
+    }
     if (i >= nq) return;
-    const int32_t ir = min(max(r[i], 0), n_rel - 1);
-    const int32_t pos = offsets[ir] + atomicAdd(&cursor[ir], 1);
+    pos += offsets[ir];
     perm[pos] = (int32_t)i;
     gh[pos] = min(max(h[i], 0), n_ent - 1);
     gt[pos] = min(max(t[i], 0), n_ent - 1);
@@ -528,74 +505,84 @@ __global__ __launch_bounds__(kThreads) void k_rr_unpermute(const int32_t *perm, 
 }
 
 // T[e][a] = sum_j E[e][j] M[a][j] (index order, fused multiply-adds) for e < n_ent, a < k; T[n_ent][a] = rvec[a].
-// Tiled like the sweep: 128 entities x 128 outputs per workgroup, 8 x 8 per thread.
-// blockIdx.z walks the relations first, first + 1, ... as in the sweep (M, rvec: the whole tables).
-__global__ __launch_bounds__(kThreads, 3) void k_rr_project(const float *__restrict__ E, const float *__restrict__ M,
+// 128 entities x 128 outputs per workgroup, 64 x 64 per wavefront, on the fp32 matrix cores: a chain of
+// v_mfma_f32_32x32x2_f32 performs exactly the fused multiply-adds of an index-order loop, bit for bit (checked against
+// fmaf over the whole exponent range), at 118 TFLOP/s measured; as vector operations with 8 x 8 sums per thread the
+// same tiling reached 68.  dim and k are multiples of 32.  blockIdx.z: one of the relations ids (M, rvec: the
+// whole tables).
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+__global__ __launch_bounds__(kThreads, 2) void k_rr_project(const float *__restrict__ E, const float *__restrict__ M,
                                                             const float *__restrict__ rvec, int32_t n_ent, int dim, int k,
-                                                            float *__restrict__ T, const int32_t *__restrict__ counts,
-                                                            int32_t first, int32_t big, int64_t table_stride)
+                                                            float *__restrict__ T, RankIds ids,
+                                                            int64_t table_stride)
 {
     {
-        const int32_t g = first + (int32_t)blockIdx.z, n = counts[g];
-        if (n == 0 || (gridDim.z > 1 && n > big)) return;
+        const int32_t g = ids.g[blockIdx.z];
         M += (int64_t)g * k * dim;
         rvec += (int64_t)g * k;
         T += (int64_t)blockIdx.z * table_stride;
     }
     __shared__ __attribute__((aligned(16))) float s_m[kRankJ][kRankLd];
     __shared__ __attribute__((aligned(16))) float s_e[kRankJ][kRankLd];
-    const int tid = threadIdx.x, tx = tid & 15, ty = tid >> 4;
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l31 = lane & 31;
+    const int we = ((tid >> 6) & 1) * 64, wa = (tid >> 7) * 64;   // the wavefront's corner of the 128 x 128 block
     const int32_t e0 = (int32_t)blockIdx.x * kRankE;
     const int a0 = (int)blockIdx.y * kRankQ;
     const int sc = tid & (kRankQ - 1), sj = (tid >> 7) * 4;
-    const float *pm = M + (int64_t)min(a0 + sc, k - 1) * dim;
-    const float *pe = E + (int64_t)min(e0 + sc, n_ent - 1) * dim;
+    const float *pm = M + (int64_t)min(a0 + sc, k - 1) * dim + sj;
+    const float *pe = E + (int64_t)min(e0 + sc, n_ent - 1) * dim + sj;
     if (blockIdx.x == 0 && tid < kRankQ && a0 + tid < k) T[(int64_t)n_ent * k + a0 + tid] = rvec[a0 + tid];
-    float acc[8][8];
+    const bool work = a0 + wa < k;                        // (uniform over the wavefront)
+    floatx16 acc[2][2];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+    for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int v = 0; v < 8; ++v) acc[u][v] = 0.f;
+        for (int v = 0; v < 2; ++v)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[u][v][i] = 0.f;
+    float4 vm[4], ve[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) { vm[i] = ld4(pm + 8 * i); ve[i] = ld4(pe + 8 * i); }
     for (int j0 = 0; j0 < dim; j0 += kRankJ) {
-        float4 vm[4], ve[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int j = min(j0 + sj + 8 * i, dim - 4);
-            vm[i] = ld4(pm + j); ve[i] = ld4(pe + j);
-        }
         __syncthreads();
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int jj = sj + 8 * i;
-            float4 m4 = vm[i], e4 = ve[i];
-            if (j0 + jj >= dim) m4 = e4 = make_float4(0.f, 0.f, 0.f, 0.f);
-            s_m[jj][sc] = m4.x; s_m[jj + 1][sc] = m4.y; s_m[jj + 2][sc] = m4.z; s_m[jj + 3][sc] = m4.w;
-            s_e[jj][sc] = e4.x; s_e[jj + 1][sc] = e4.y; s_e[jj + 2][sc] = e4.z; s_e[jj + 3][sc] = e4.w;
+            s_m[jj][sc] = vm[i].x; s_m[jj + 1][sc] = vm[i].y; s_m[jj + 2][sc] = vm[i].z; s_m[jj + 3][sc] = vm[i].w;
+            s_e[jj][sc] = ve[i].x; s_e[jj + 1][sc] = ve[i].y; s_e[jj + 2][sc] = ve[i].z; s_e[jj + 3][sc] = ve[i].w;
         }
         __syncthreads();
-#pragma unroll 4
-        for (int jj = 0; jj < kRankJ; ++jj) {
-            const float4 ma = *reinterpret_cast<const float4 *>(&s_m[jj][ty * 4]);
-            const float4 mb = *reinterpret_cast<const float4 *>(&s_m[jj][64 + ty * 4]);
-            const float4 ea = *reinterpret_cast<const float4 *>(&s_e[jj][tx * 4]);
-            const float4 eb = *reinterpret_cast<const float4 *>(&s_e[jj][64 + tx * 4]);
-            const float mv[8] = {ma.x, ma.y, ma.z, ma.w, mb.x, mb.y, mb.z, mb.w};
-            const float ev[8] = {ea.x, ea.y, ea.z, ea.w, eb.x, eb.y, eb.z, eb.w};
+        if (j0 + kRankJ < dim) {                          // the next chunk travels while this one is multiplied
 #pragma unroll
-            for (int u = 0; u < 8; ++u)
+            for (int i = 0; i < 4; ++i) { vm[i] = ld4(pm + j0 + kRankJ + 8 * i); ve[i] = ld4(pe + j0 + kRankJ + 8 * i); }
+        }
+        if (!work) continue;
 #pragma unroll
-                for (int v = 0; v < 8; ++v) acc[u][v] = __builtin_fmaf(ev[v], mv[u], acc[u][v]);
+        for (int jj = 0; jj < kRankJ; jj += 2) {
+            float ev[2], mv[2];
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                ev[u] = s_e[jj + half][we + 32 * u + l31];
+                mv[u] = s_m[jj + half][wa + 32 * u + l31];
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int v = 0; v < 2; ++v) acc[u][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(ev[u], mv[v], acc[u][v], 0, 0, 0);
         }
     }
+    if (!work) return;
 #pragma unroll
-    for (int v = 0; v < 8; ++v) {
-        const int32_t e = e0 + (v < 4 ? 0 : 64) + tx * 4 + (v & 3);
-        if (e >= n_ent) continue;
+    for (int v = 0; v < 2; ++v) {
+        const int a = a0 + wa + 32 * v + l31;
+        if (a0 + wa + 32 * v >= k) break;
 #pragma unroll
-        for (int g = 0; g < 2; ++g) {                     // the thread's outputs: two runs of four consecutive a
-            const int a = a0 + g * 64 + ty * 4;
-            if (a < k) st4(T + (int64_t)e * k + a, make_float4(acc[4 * g][v], acc[4 * g + 1][v], acc[4 * g + 2][v], acc[4 * g + 3][v]));
-        }
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int32_t e = e0 + we + 32 * u + (i & 3) + 8 * (i >> 2) + 4 * half;
+                if (e < n_ent) T[(int64_t)e * k + a] = acc[u][v][i];
+            }
     }
 }
 
@@ -618,15 +605,15 @@ static RankShape rank_shape(int64_t nq, int32_t n_ent, int64_t min_tiles)
 }
 
 // k_rank_true, the sweep and (L2 kinds) the square root for one table and one list of queries.
-static void rank_sweep(stx_ctx *c, const RankArgs &a, const RankShape &sh, bool transh, int side, int nz = 1,
-                       bool finish = true)
+static void rank_sweep(stx_ctx *c, const RankArgs &a, const RankShape &sh, bool transh, int side, const RankIds &ids,
+                       int nz = 1, bool finish = true)
 {
     const dim3 grid(sh.grid.x, sh.grid.y, (unsigned)nz), qgrid(sh.qgrid.x, 1, (unsigned)nz);
 #define STX_RANK_GO(KT, KS, D, H)                                                                               \
     do {                                                                                                        \
-        hipLaunchKernelGGL((KT<D, H>), qgrid, dim3(kThreads), 0, c->stream, a);                                 \
+        hipLaunchKernelGGL((KT<D, H>), qgrid, dim3(kThreads), 0, c->stream, a, ids);                            \
         ProfScope prof(c, #KS);                                                                                 \
-        hipLaunchKernelGGL((KS<D, H>), grid, dim3(kThreads), 0, c->stream, a);                                  \
+        hipLaunchKernelGGL((KS<D, H>), grid, dim3(kThreads), 0, c->stream, a, ids);                             \
     } while (0)
 #define STX_RANK(D)                                                                                             \
     do {                                                                                                        \
@@ -656,8 +643,17 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
         const bool transh = c->cfg.model == STX_TRANSH;
         const RankShape sh = rank_shape(nq, n_ent, transh ? 4 : 2);   // TransH workgroups start with a dot product per query
         const RankArgs a{p->ent, transh ? p->rel : nullptr, transh ? p->w : nullptr, h, r, t, nq, n_ent, n_rel, c->cfg.dim,
-                         sh.slice, true_score, n_less, n_equal, bad, nullptr, nullptr, 0, 0, 0};
-        rank_sweep(c, a, sh, transh, side);
+                         sh.slice, true_score, n_less, n_equal, bad, nullptr, nullptr, 0};
+        // Small problems are not worth the filter's extra launches (about 10 us): the plain sweep, whose query blocks
+        // are padded to 128, does 28e12 steps a second.
+        const RankScratch ws{c->rank_q, c->rank_e, c->rank_q_bytes, c->rank_e_bytes, nullptr};
+        const double steps = (double)((nq + kRankQ - 1) / kRankQ * kRankQ) * n_ent * c->cfg.dim;
+        if (c->rank_q_bytes && steps >= 6e8 && rank_filtered(c, a, side, ws, 0, RankIds{})) {
+            if (c->cfg.dist == STX_L2)
+                hipLaunchKernelGGL((k_rank_finish<STX_L2>), sh.qgrid, dim3(kThreads), 0, c->stream, true_score, nq);
+            return hip_ok(hipGetLastError());
+        }
+        rank_sweep(c, a, sh, transh, side, RankIds{});
         return hip_ok(hipGetLastError());
     }
     // TransR: group the queries by relation, learn the group sizes (the one wait of this call), then one
@@ -670,7 +666,7 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
     hipLaunchKernelGGL(k_rr_scan, dim3(1), dim3(kThreads), 0, c->stream, w.counts, w.offsets, n_rel);
     hipLaunchKernelGGL(k_rr_scatter, qgrid, dim3(kThreads), 0, c->stream, h, r, t, nq, n_ent, n_rel, w.offsets, w.cursor,
                        w.perm, w.gh, w.gt);
-    int32_t *counts = new (std::nothrow) int32_t[(size_t)n_rel];
+    int32_t *counts = new (std::nothrow) int32_t[2 * (size_t)n_rel];   // and the order of the relations
     if (!counts) return STX_ERR_BAD_ARG;
     if (hipMemcpyAsync(counts, w.counts, (size_t)n_rel * 4, hipMemcpyDeviceToHost, c->stream) != hipSuccess ||
         hipStreamSynchronize(c->stream) != hipSuccess) {
@@ -678,27 +674,29 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
         return STX_ERR_HIP;
     }
     const int64_t stride = (int64_t)(n_ent + 1) * k;
-    // relations first, first + 1, ... first + nz - 1 in one set of launches; max_n: the largest group among them
-    auto sweep = [&](int32_t first, int nz, int64_t max_n, int32_t big) {
+    // Relations that occur, most queries first: neighbours in that order have similar numbers, so those with few can
+    // share launches whose shape suits all of them.  Relations with many queries get launches of their own.
+    int32_t *order = counts + n_rel, n_occ = 0;
+    for (int32_t rr = 0; rr < n_rel; ++rr)
+        if (counts[rr]) order[n_occ++] = rr;
+    std::sort(order, order + n_occ, [&](int32_t x, int32_t y) { return counts[x] != counts[y] ? counts[x] > counts[y] : x < y; });
+    for (int32_t i = 0; i < n_occ;) {
+        const int64_t max_n = counts[order[i]];
+        int nz = 1;
+        if (max_n <= kRankBig) nz = n_occ - i < w.n_tables ? n_occ - i : w.n_tables;
+        const RankShape sh = rank_shape(max_n, n_ent, 2);
+        const RankArgs a{w.table, nullptr, nullptr, w.gh, nullptr, w.gt, max_n, n_ent, 1, k, sh.slice, w.gts, w.gless,
+                   w.gequal, bad, w.counts, w.offsets, stride};
+        RankIds ids{};
+        for (int z = 0; z < nz; ++z) ids.g[z] = order[i + z];
+        i += nz;
         const dim3 pgrid((unsigned)((n_ent + kRankE - 1) / kRankE), (unsigned)((k + kRankQ - 1) / kRankQ), (unsigned)nz);
         {
             ProfScope prof(c, "k_rr_project");
             hipLaunchKernelGGL(k_rr_project, pgrid, dim3(kThreads), 0, c->stream, p->ent, p->proj, p->rel, n_ent, dim, k,
-                               w.table, w.counts, first, big, stride);
+                               w.table, ids, stride);
         }
-        const RankShape sh = rank_shape(max_n, n_ent, 2);
-        const RankArgs a{w.table, nullptr, nullptr, w.gh, nullptr, w.gt, max_n, n_ent, 1, k, sh.slice, w.gts, w.gless,
-                         w.gequal, bad, w.counts, w.offsets, first, big, stride};
-        rank_sweep(c, a, sh, false, side, nz, false);
-    };
-    for (int32_t rr = 0; rr < n_rel; ++rr)
-        if (counts[rr] > kRankBig) sweep(rr, 1, counts[rr], 0x7fffffff);
-    for (int32_t r0 = 0; r0 < n_rel; r0 += w.n_tables) {
-        const int nz = n_rel - r0 < w.n_tables ? n_rel - r0 : w.n_tables;
-        int64_t max_n = 0;
-        for (int z = 0; z < nz; ++z)
-            if (counts[r0 + z] <= kRankBig && counts[r0 + z] > max_n) max_n = counts[r0 + z];
-        if (max_n > 0) sweep(r0, nz, max_n, nz > 1 ? kRankBig : 0x7fffffff);
+        if (!rank_filtered(c, a, side, w.ws, nz, ids)) rank_sweep(c, a, sh, false, side, ids, nz, false);
     }
     if (c->cfg.dist == STX_L2) hipLaunchKernelGGL((k_rank_finish<STX_L2>), qgrid, dim3(kThreads), 0, c->stream, w.gts, nq);
     if (c->cfg.dist == STX_TORUS_L2)

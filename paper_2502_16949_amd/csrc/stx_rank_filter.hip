@@ -1,0 +1,974 @@
+// Link prediction through a filter: most candidates are ordered against the true entity by a cheap sum of known
+// error, and only those too close to it are summed exactly.
+//
+// The counts of stx_rank are defined by the fp32 sums of k_rank (index order, every step rounded as written there),
+// so they must come out as if every candidate had been summed that way.  A sum S' with a bound |S' - S| <= W on its
+// distance from the exact-order sum S decides the candidate whenever |S' - S_true| > W; with W about a thousandth of
+// the spread of the scores, one candidate in about a thousand is left, and those are recomputed: first as a tree sum
+// in fp32, whose own bound leaves only ties and near-ties, then, for these, in index order.  So the result is that of
+// the exhaustive fp32 sweep, bit for bit.  Wherever a bound is not finite (values out of range, infinities, NaN) the
+// candidate counts as undecided.
+//
+// Undecided pairs go to a list that k_rank_pairs works through.
+//
+// The plain sweep's rate is that of the vector ALU (two fp32 operations per element, five for the torus kind):
+// 59,071 queries x 15,000 entities at d = 128 (L1) took 3.85 ms a side and take 1.95; 256 x 4,000,000 (torus-L1) 10.2
+// and 4.2; 4,096 x 14,951 at d = 1024 (L2) 2.7 and 0.83.
+//
+//   L1, torus-L1   k_rank_sad: rows as 16-bit fixed point, two elements per vector operation (v_sad_u16 sums two
+//                  absolute differences; the torus kind wraps the difference by a 32-bit subtraction first).  The
+//                  bound is the sum of the roundings actually made in each row.
+//   L2, squared L2 k_rank_mfma: S = |q|^2 + |e|^2 - 2 q.e with q.e on the matrix cores, rows rounded to fp16 after
+//                  scaling by a power of two.  The bound is |q| |de| + |dq| |e| with the norms of the roundings made.
+#include "stx_rank.h"
+
+namespace stx {
+
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float floatx16 __attribute__((ext_vector_type(16)));
+#define STX_CONST_AS __attribute__((address_space(4)))      // uniform loads from here are scalar loads
+
+constexpr int kSadGroup = 16;          // queries per group of k_rank_sad: one accumulator each
+constexpr int kSadThreads = 512;
+constexpr int kListCap = 128;          // undecided pairs a wavefront collects before it recomputes them
+constexpr float kUnit = 5.9604645e-8f; // 2^-24
+
+struct FilterArgs {
+    RankArgs a;
+    int32_t q_first;                   // first query of this chunk (relations: 0)
+    int32_t q_cap;                     // queries per chunk and blockIdx.z, a multiple of 32
+    int32_t e_first, e_count;          // segment of candidates
+    int np;                            // 8-element pieces of a row: 2 per matrix-core step, the last may be padding
+    int nqb;                           // k_rank_prep: blocks (of 32) that prepare queries; the rest prepare candidates
+    float *q32;                        // [query]: its point, fp32
+    uint32_t *qt;                      // fixed point: [group][piece][dword][16 queries], two elements per dword
+    int2 *thr;                         // ... [query]: (sum below which a candidate is surely below, ... surely above)
+    float *scale;                      // ... [1]
+    uint4 *qf, *ef;                    // matrix cores: operand fragments [tile of 32 rows][step][lane]
+    float4 *qpar;                      // ... [query]: bound factors and threshold, see k_rank_prep
+    float *qscale;                     // ... [query]
+    float *eaux;                       // ... [tile of 32][64]: half the candidates' squared norms, scaled; then, from 32 on,
+                                       //     the tile's scale, largest norm, largest rounding, squared-norm term
+    int32_t slice;                     // sweeps: candidates (mfma) or query groups (sad) per blockIdx.y
+    int head;                          // side: q = t - r instead of h + r
+    int32_t *n_pairs;                  // undecided pairs found, cleared by k_rank_prep ...
+    uint2 *pairs;                      // ... and the pairs: (candidate | table << z_shift, position in the query arrays)
+    int32_t pair_cap;
+    int z_shift;                       // 32: one table
+};
+
+// Lane `lane`'s place among the set bits of a wavefront mask.
+__device__ inline int mask_rank(uint64_t m)
+{
+    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// ---- exact treatment of undecided pairs -------------------------------------------------------------------
+struct PairRows {
+    const float *pq, *pe;
+    uint32_t e;
+    int64_t q;
+    float st;
+};
+__device__ inline PairRows pair_rows(const FilterArgs &f, uint2 pr)
+{
+    RankArgs a = f.a;
+    uint32_t e = pr.x;
+    if (f.z_shift < 32) {
+        a.X += (int64_t)(e >> f.z_shift) * a.table_stride;
+        e &= (1u << f.z_shift) - 1u;
+    }
+    PairRows p;
+    p.e = e;
+    p.q = pr.y;
+    p.pq = f.q32 + (p.q - f.q_first) * a.dim;
+    p.pe = a.X + (int64_t)e * a.dim;
+    p.st = a.true_score[p.q];
+    return p;
+}
+// One term's difference as k_rank forms it (the factor +-1 is exact).
+__device__ inline float pair_diff(float sg, float qv, float ev) { return sg * (qv - ev); }
+
+// The index-order sum of one pair per lane.
+template <int DIST>
+__device__ inline void pair_exact(const FilterArgs &f, uint2 pr)
+{
+    const PairRows p = pair_rows(f, pr);
+    const float sg = f.head ? -1.f : 1.f;
+    const int dim = f.a.dim;
+    float acc = 0.f;
+    for (int j0 = 0; j0 < dim; j0 += 16) {
+        float4 vq[4], ve[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = min(j0 + 4 * u, dim - 4);
+            vq[u] = ld4(p.pq + j); ve[u] = ld4(p.pe + j);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (j0 + 4 * u < dim) {
+                acc = rank_step<DIST>(acc, pair_diff(sg, vq[u].x, ve[u].x));
+                acc = rank_step<DIST>(acc, pair_diff(sg, vq[u].y, ve[u].y));
+                acc = rank_step<DIST>(acc, pair_diff(sg, vq[u].z, ve[u].z));
+                acc = rank_step<DIST>(acc, pair_diff(sg, vq[u].w, ve[u].w));
+            }
+    }
+    if (acc < p.st) atomicAdd(&f.a.n_less[p.q], 1);
+    if (acc == p.st) atomicAdd(&f.a.n_equal[p.q], 1);
+}
+
+// Eight lanes per pair: a sum in another order, which decides all but ties and near-ties; these go to `ties`.
+template <int DIST>
+__device__ inline void pair_recheck(const FilterArgs &f, uint2 pr, bool in, int lane, uint2 *ties, int &n_ties)
+{
+    const PairRows p = pair_rows(f, pr);
+    const float sg = f.head ? -1.f : 1.f;
+    const int dim = f.a.dim;
+    const int32_t it = f.head ? f.a.h[p.q] : f.a.t[p.q];
+    const bool self = (int32_t)p.e == min(max(it, 0), f.a.n_ent - 1);
+    float s = 0.f;
+    for (int j0 = (lane & 7) * 4; j0 < dim; j0 += 128) {
+        float4 vq[4], ve[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int j = min(j0 + 32 * u, dim - 4);
+            vq[u] = ld4(p.pq + j); ve[u] = ld4(p.pe + j);
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (j0 + 32 * u < dim) {
+                s = rank_step<DIST>(s, pair_diff(sg, vq[u].x, ve[u].x));
+                s = rank_step<DIST>(s, pair_diff(sg, vq[u].y, ve[u].y));
+                s = rank_step<DIST>(s, pair_diff(sg, vq[u].z, ve[u].z));
+                s = rank_step<DIST>(s, pair_diff(sg, vq[u].w, ve[u].w));
+            }
+    }
+    s = group_sum<8>(s);
+    // The sum of the same rounded terms differs from this one by at most (dim / 8 + 6) 2^-24 of itself and from the
+    // index-order one by at most (dim + 2) 2^-24.
+    const float wd = ((float)dim * 1.126f + 16.f) * kUnit * s;
+    const bool less = !self && s + wd < p.st, tie = !self && !less && !(s - wd > p.st);
+    if ((lane & 7) == 0 && in) {
+        if (less) atomicAdd(&f.a.n_less[p.q], 1);
+        if (self && p.st == p.st) atomicAdd(&f.a.n_equal[p.q], 1);   // the very sum k_rank_prep formed
+    }
+    const uint64_t m = __ballot(tie && in && (lane & 7) == 0);
+    if (m >> lane & 1) ties[n_ties + mask_rank(m)] = pr;
+    n_ties += __builtin_popcountll(m);
+}
+
+// All undecided pairs of a sweep, many wavefronts in flight: bound by the latency and the bytes of the rows it reads.
+template <int DIST>
+__global__ __launch_bounds__(kThreads) void k_rank_pairs(FilterArgs f)
+{
+    __shared__ uint2 s_ties[4][72];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int n = min(*f.n_pairs, f.pair_cap), step = (int)gridDim.x * 32;
+    int n_ties = 0;
+    for (int i0 = ((int)blockIdx.x * 4 + wave) * 8; i0 < n; i0 += step) {
+        const int i = i0 + (lane >> 3);
+        pair_recheck<DIST>(f, f.pairs[min(i, n - 1)], i < n, lane, s_ties[wave], n_ties);
+        if (n_ties >= 64) {
+            pair_exact<DIST>(f, s_ties[wave][lane]);
+            n_ties -= 64;
+            if (lane < n_ties) s_ties[wave][lane] = s_ties[wave][64 + lane];
+        }
+    }
+    if (lane < n_ties) pair_exact<DIST>(f, s_ties[wave][lane]);
+}
+
+// A wavefront's collected pairs move to the list of the sweep; when that is full they are treated here, one per lane.
+template <int DIST>
+__device__ inline void flush_pairs(const FilterArgs &f, const uint2 *list, int cnt, int lane)
+{
+    int base = 0;
+    if (lane == 0) base = atomicAdd(f.n_pairs, cnt);
+    base = __builtin_amdgcn_readfirstlane(base);
+    for (int i = lane; i < cnt; i += 64) {
+        if (base + i < f.pair_cap) f.pairs[base + i] = list[i];
+        else pair_exact<DIST>(f, list[i]);
+    }
+}
+
+__device__ inline float max_group8(float v)
+{
+#pragma unroll
+    for (int m = 4; m >= 1; m >>= 1) v = fmaxf(v, __shfl_xor(v, m, 8));
+    return v;
+}
+// The power of two that brings `mx` to [64, 128); 1 for zero.  ok: mx lies where squares and products of rows stay
+// far from the ends of the fp32 range (elsewhere the bounds below would not hold, and nothing is decided by them).
+__device__ inline float pow2_scale(float mx, bool &ok)
+{
+    ok = mx == 0.f || (mx > 1e-12f && mx < 1e12f);
+    if (!ok || mx == 0.f) return 1.f;
+    return ldexpf(1.f, 6 - ilogbf(mx));
+}
+// Relative error of half a squared norm formed by eight lanes, and of the few roundings around it.
+__device__ inline float norm_slack(int np) { return 0.5f * kUnit * (float)(np + 24); }
+// Eight elements of a row, zeros past its end.
+__device__ inline void load8(const float *p, int j, int dim, float (&v)[8])
+{
+    const float4 x = j < dim ? ld4(p + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 y = j + 4 < dim ? ld4(p + j + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
+}
+// Eight elements scaled and rounded to fp16; adds the squares of the scaled values and of the roundings.
+__device__ inline uint4 half_piece(const float (&v)[8], float sc, float &n2, float &d2)
+{
+    half8 h;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const float x = v[i] * sc;                         // exact: sc is a power of two
+        h[i] = (_Float16)x;
+        const float d = x - (float)h[i];                   // exact
+        n2 = __builtin_fmaf(x, x, n2);
+        d2 = __builtin_fmaf(d, d, d2);
+    }
+    return __builtin_bit_cast(uint4, h);
+}
+// One element as 16-bit fixed point; adds the rounding made (in units of the last place).
+template <bool TORUS>
+__device__ inline uint32_t fixed16(float v, float sc, bool upper_q, float &res)
+{
+    if (TORUS) {
+        // the phase; a difference of unwrapped values as fp32 forms it is off by at most 2^-24 (|q| + |e|), the
+        // fractional part itself by 2^-24.  The upper half of a query's dword loses the borrow of the lower half's
+        // subtraction, 0 or 1 units: it is stored half a unit up and half a unit is added to its rounding.
+        const float x = __builtin_amdgcn_fractf(v) * 65536.f + (upper_q ? 0.5f : 0.f);
+        const float k = rintf(x);
+        res += fabsf(x - k) + 0.02f + fabsf(v) * (65536.f * 1.01f * kUnit) + (upper_q ? 0.5f : 0.f);
+        return (uint32_t)(int)k & 0xffffu;
+    }
+    const float k = fminf(fmaxf(rintf(v * sc), -32768.f), 32767.f);
+    res += fabsf(__builtin_fmaf(v, sc, -k)) * 1.0001f;
+    return (uint32_t)((int)k + 32768);
+}
+
+// ---- scale of the L1 kind ---------------------------------------------------------------------------------
+// The largest element among up to 128 queries' points and true entities sets the range of the fixed-point numbers.
+// (Elements beyond it are clamped; what that loses is part of their row's bound.)  One workgroup.
+template <bool HEAD>
+__global__ __launch_bounds__(1024) void k_rank_scale(RankArgs a, float *scale)
+{
+    __shared__ float s_mx[16];
+    const int u = (int)threadIdx.x >> 3, l8 = (int)threadIdx.x & 7;
+    const int64_t q = a.nq <= 128 ? min((int64_t)u, a.nq - 1) : (int64_t)u * (a.nq / 128);
+    const RankRows rw = rank_rows<HEAD>(a, q);
+    float mx = 0.f;
+    for (int j = l8 * 4; j < a.dim; j += 32) {
+        const float4 va = ld4(rw.pa + j), vr = ld4(rw.pr + j), ve = ld4(rw.ptrue + j);
+        const float4 q4 = HEAD ? sub4(va, vr) : add4(va, vr);
+        mx = fmaxf(fmaxf(fmaxf(mx, fabsf(q4.x)), fmaxf(fabsf(q4.y), fabsf(q4.z))), fabsf(q4.w));
+        mx = fmaxf(fmaxf(fmaxf(mx, fabsf(ve.x)), fmaxf(fabsf(ve.y), fabsf(ve.z))), fabsf(ve.w));
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
+    if ((threadIdx.x & 63) == 0) s_mx[threadIdx.x >> 6] = mx;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s_mx[i]);
+        *scale = (mx > 1e-12f && mx < 1e12f) ? 32767.f / mx : 1.f;
+    }
+}
+
+// ---- preparation ------------------------------------------------------------------------------------------
+// Blocks of 32 queries: the true entity's sum in index order (one lane per query walks the terms out of LDS), cleared
+// counters, and the packed query with its thresholds.  Matrix-core kinds: further blocks of 32 candidates each.
+// Eight threads per row.  Bound by the latency of its few dependent passes; the rows come from the caches.
+template <int DIST, bool HEAD>
+__global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds ids)
+{
+    constexpr bool SAD = DIST == STX_L1 || DIST == STX_TORUS_L1, TORUS = DIST == STX_TORUS_L1;
+    RankArgs a = f.a;
+    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) *f.n_pairs = 0;
+    rank_group(a, ids);
+    __shared__ float s_y[32][65];
+    __shared__ float s_t[32];
+    __shared__ float s_r[8];
+    const int tid = threadIdx.x, u = tid >> 3, l8 = tid & 7, dim = a.dim;
+    const int z = (int)blockIdx.z;
+    if ((int)blockIdx.x < f.nqb) {
+        const int64_t ql = (int64_t)blockIdx.x * 32 + u;       // within the chunk
+        const int64_t q = f.q_first + ql;
+        const int64_t nq = min(a.nq - f.q_first, (int64_t)f.q_cap);
+        if ((int64_t)blockIdx.x * 32 >= nq) return;            // (uniform)
+        const RankRows rw = rank_rows<HEAD>(a, min(q, a.nq - 1));
+        if (rw.bad && l8 == 0 && ql < nq) atomicAdd(a.bad, 1);
+        float mx = 0.f, acc = 0.f;
+        float *q32 = f.q32 + (ql + (a.true_score - f.a.true_score)) * dim;
+        for (int j0 = 0; j0 < dim; j0 += 64) {
+            float va[8], vr[8], ve[8];
+            const int j = j0 + l8 * 8;
+            load8(rw.pa, j, dim, va);
+            load8(rw.pr, j, dim, vr);
+            load8(rw.ptrue, j, dim, ve);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const float qv = HEAD ? va[i] - vr[i] : va[i] + vr[i];
+                mx = fmaxf(mx, fabsf(qv));
+                s_y[u][l8 * 8 + i] = HEAD ? ve[i] - qv : qv - ve[i];
+                va[i] = qv;
+            }
+            if (ql < nq) {
+                if (j < dim) st4(q32 + j, make_float4(va[0], va[1], va[2], va[3]));
+                if (j + 4 < dim) st4(q32 + j + 4, make_float4(va[4], va[5], va[6], va[7]));
+            }
+            __syncthreads();
+            if (tid < 32) {
+                const int n = min(64, dim - j0);
+                if (n == 64) {
+#pragma unroll 16
+                    for (int jj = 0; jj < 64; ++jj) acc = rank_step<DIST>(acc, s_y[tid][jj]);
+                } else {
+                    for (int jj = 0; jj < n; ++jj) acc = rank_step<DIST>(acc, s_y[tid][jj]);
+                }
+            }
+            __syncthreads();
+        }
+        if (tid < 32) {
+            s_t[tid] = acc;
+            const int64_t qq = f.q_first + (int64_t)blockIdx.x * 32 + tid;
+            if ((int64_t)blockIdx.x * 32 + tid < nq) {
+                a.true_score[qq] = acc;
+                a.n_less[qq] = 0;
+                a.n_equal[qq] = 0;
+            }
+        }
+        __syncthreads();
+        const float st = s_t[u];
+        if (SAD) {
+            const float sc = TORUS ? 65536.f : *f.scale;
+            const int64_t grp = ql >> 4;
+            float res = 0.f;
+            for (int p = l8; p < f.np; p += 8) {
+                float va[8], vr[8];
+                load8(rw.pa, p * 8, dim, va);
+                load8(rw.pr, p * 8, dim, vr);
+                uint32_t k[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) {
+                    // (past the row's end query and candidate hold the same number and add nothing, rounding aside)
+                    k[i] = fixed16<TORUS>(HEAD ? va[i] - vr[i] : va[i] + vr[i], sc, (i & 1) != 0, res);
+                    if (TORUS) k[i] ^= 0x8000u;                // half a turn up: the sweep measures from there
+                }
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    f.qt[((grp * f.np + p) * 4 + i) * kSadGroup + (ql & 15)] = k[2 * i] | k[2 * i + 1] << 16;
+            }
+            res = group_sum<8>(res);
+            if (l8 == 0) {
+                int2 thr = make_int2(-(1 << 30), -(1 << 30));  // past the last query: nothing is below, nothing undecided
+                if (ql < nq) {
+                    // the index-order sum is within (dim + 8) 2^-24 of the sum of its terms' exact values
+                    const double t = (double)st * (double)sc, rel = 1.02 * (dim + 8) * (double)kUnit;
+                    const double lo = t * (1.0 - rel) - (double)res * 1.001, hi = t * (1.0 + rel) + (double)res * 1.001;
+                    thr.x = lo > -1e8 && lo < 5e8 ? (int)floor(lo) - 1 : -(1 << 29);
+                    thr.y = hi > -1e8 && hi < 5e8 ? (int)ceil(hi) + 1 : 1 << 29;
+                    if (thr.y == 1 << 29) thr.x = -(1 << 29);
+                }
+                f.thr[ql] = thr;
+            }
+            return;
+        }
+        bool ok;
+        mx = max_group8(mx);
+        const float sc = pow2_scale(mx, ok);
+        float n2 = 0.f, d2 = 0.f;
+        uint4 *dst = f.qf + ((int64_t)z * (f.q_cap / 32) + blockIdx.x) * (f.np / 2) * 64;
+        for (int p = l8; p < f.np; p += 8) {
+            float va[8], vr[8], q8[8];
+            load8(rw.pa, p * 8, dim, va);
+            load8(rw.pr, p * 8, dim, vr);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) q8[i] = HEAD ? va[i] - vr[i] : va[i] + vr[i];
+            dst[(p >> 1) * 64 + u + 32 * (p & 1)] = half_piece(q8, sc, n2, d2);
+        }
+        n2 = group_sum<8>(n2);
+        d2 = group_sum<8>(d2);
+        if (l8 == 0) {
+            // In units scaled by sc (and, in the sweep, by the candidate tile's scale), with t = q.e - |e|^2/2 - tau and
+            // tau = (|q|^2 - S_true)/2, a candidate is below the true entity when t > 0.  What is computed differs by
+            //   the fp16 roundings        |q| |de| + |dq| (|e| + |de|)
+            //   the fp32 sums of the matrix cores: one instruction at most 2.5 * 2^-24 (|C| + sum |p|) (measured: 1.6),
+            //                             |C| up to |e|^2/2 + |tau| + |q| |e|
+            //   the norms and tau         fp32 sums of |q|^2 and |e|^2 in chains of dim / 8, a few more roundings
+            //   the index-order sums      (dim + 8) 2^-24 S_true / 2
+            const float eps = 2.5f * kUnit * (float)(f.np / 2 + 2), kap = norm_slack(f.np);
+            float4 par;
+            const float qn = sqrtf(n2) * 1.0001f, dq = sqrtf(d2) * 1.002f;
+            const float qq = n2 / sc;                          // sc |q|^2 in true units
+            par.x = dq * 1.001f + eps * qn;                    // times the tile's largest norm
+            par.y = qn;                                        // times the tile's largest rounding
+            par.z = 0.5f * (qq - st * sc);                     // tau
+            par.w = kap * (qq + st * sc) + eps * fabsf(par.z) + 0.51f * (float)(dim + 8) * kUnit * (st * sc);
+            if (!ok || !(par.w < 1e30f)) par.w = __builtin_inff();
+            if (ql >= nq) par = make_float4(0.f, 0.f, 3e37f, 0.f);
+            f.qpar[(int64_t)z * f.q_cap + ql] = par;
+            f.qscale[(int64_t)z * f.q_cap + ql] = sc;
+        }
+        return;
+    }
+    if (SAD) return;
+    // ---- 32 candidates: tile number et of the segment -----------------------------------------------------
+    const int et = (int)blockIdx.x - f.nqb;
+    const int64_t e = (int64_t)f.e_first + (int64_t)et * 32 + u;
+    const int64_t tiles = ((int64_t)f.e_count + 31) / 32;
+    const bool in = e < a.n_ent;
+    const float *pe = a.X + min(e, (int64_t)a.n_ent - 1) * dim;
+    float mx = 0.f;
+    for (int j = l8 * 4; j < dim; j += 32) {
+        const float4 v = ld4(pe + j);
+        mx = fmaxf(fmaxf(fmaxf(mx, fabsf(v.x)), fmaxf(fabsf(v.y), fabsf(v.z))), fabsf(v.w));
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
+    if ((tid & 63) == 0) s_r[tid >> 6] = mx;
+    __syncthreads();
+    mx = fmaxf(fmaxf(s_r[0], s_r[1]), fmaxf(s_r[2], s_r[3]));
+    bool ok;
+    const float sc = pow2_scale(mx, ok);
+    float n2 = 0.f, d2 = 0.f;
+    uint4 *dst = f.ef + ((int64_t)z * tiles + et) * (f.np / 2) * 64;
+    for (int p = l8; p < f.np; p += 8) {
+        float v[8];
+        load8(pe, p * 8, dim, v);
+        uint4 h = half_piece(v, sc, n2, d2);
+        if (!in) h = make_uint4(0u, 0u, 0u, 0u);
+        dst[(p >> 1) * 64 + u + 32 * (p & 1)] = h;
+    }
+    n2 = group_sum<8>(n2);
+    d2 = group_sum<8>(d2);
+    if (l8 == 0) {
+        s_t[u] = n2;
+        s_y[0][u] = d2;
+        f.eaux[((int64_t)z * tiles + et) * 64 + u] = in ? 0.5f * n2 / sc : 3e37f;   // past the end: never below
+    }
+    __syncthreads();
+    if (tid < 32) {
+        float m2 = s_t[tid], dd = s_y[0][tid];
+        bool fin = m2 < 1e30f && dd < 1e30f;                   // (false for NaN)
+#pragma unroll
+        for (int m = 16; m >= 1; m >>= 1) {
+            m2 = fmaxf(m2, __shfl_xor(m2, m, 32));
+            dd = fmaxf(dd, __shfl_xor(dd, m, 32));
+        }
+        fin = (__ballot(fin) & 0xffffffffull) == 0xffffffffull;
+        if (tid == 0) {
+            const float kap = norm_slack(f.np) + 1.25f * kUnit * (float)(f.np / 2 + 2);
+            float4 t = make_float4(sc, sqrtf(m2) * 1.0001f, sqrtf(dd) * 1.002f, kap * m2 / sc);
+            if (!fin || !ok) t.y = t.z = t.w = __builtin_inff();
+            st4(f.eaux + ((int64_t)z * tiles + et) * 64 + 32, t);
+        }
+    }
+}
+
+// ---- L1 kinds: fixed point ----------------------------------------------------------------------------------
+// A workgroup keeps 64 C candidates (C per lane) in LDS as 16-bit pairs; its wavefronts walk groups of 16 queries,
+// whose packed values are wavefront-uniform and come through scalar loads, so the inner step is one vector operation
+// per two elements (two for the torus kind) with one 16-byte LDS read per 64 C of them.  Bound by the rate of
+// v_sad_u16 (half that of an fp32 addition: 36 against 62 T lane-operations per second measured).
+template <int DIST, int C>
+__global__ __launch_bounds__(kSadThreads) void k_rank_sad(FilterArgs f)
+{
+    constexpr bool TORUS = DIST == STX_TORUS_L1;
+    constexpr int NE = 64 * C, NW = kSadThreads / 64;
+    extern __shared__ __align__(16) unsigned char s_arena[];
+    const RankArgs &a = f.a;
+    const int np = f.np;
+    uint4 *s_e = reinterpret_cast<uint4 *>(s_arena);                           // [piece][candidate]
+    uint2 *s_list = reinterpret_cast<uint2 *>(s_e + (size_t)np * NE);          // [wavefront][kListCap]
+    uint64_t *s_mask = reinterpret_cast<uint64_t *>(s_list + NW * kListCap);   // [wavefront][16 C]
+    float *s_res = reinterpret_cast<float *>(s_mask + NW * kSadGroup * C);     // [candidate]
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int64_t e0 = (int64_t)blockIdx.x * NE;
+    const float sc = TORUS ? 65536.f : *f.scale;
+    if (tid < NE) s_res[tid] = 0.f;
+    __syncthreads();
+    // staging: four pieces (128 bytes) of a row per four consecutive threads
+    for (int i = tid; i < ((np + 3) / 4) * 4 * NE; i += kSadThreads) {
+        const int c = (i >> 2) & (NE - 1), p = (i / (4 * NE)) * 4 + (i & 3);
+        if (p >= np) continue;
+        float v[8], res = 0.f;
+        load8(a.X + min(e0 + c, (int64_t)a.n_ent - 1) * a.dim, p * 8, a.dim, v);
+        uint32_t k[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) k[q] = fixed16<TORUS>(v[q], sc, false, res);
+        s_e[p * NE + c] = make_uint4(k[0] | k[1] << 16, k[2] | k[3] << 16, k[4] | k[5] << 16, k[6] | k[7] << 16);
+        atomicAdd(&s_res[c], res);
+    }
+    __syncthreads();
+    // the largest rounding of the wavefront's candidates, in whole units
+    float res = 0.f;
+    uint64_t valid[C];
+    bool finite = true;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        const float r = s_res[c * 64 + lane];
+        finite = finite && r < 1e8f;
+        res = fmaxf(res, r);
+        valid[c] = __ballot(e0 + c * 64 + lane < a.n_ent);
+    }
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) res = fmaxf(res, __shfl_xor(res, m, 64));
+    int er = __builtin_amdgcn_readfirstlane((int)ceilf(res * 1.001f) + 1);
+    if (!__all(finite)) er = 1 << 29;
+
+    const int64_t ngroups = ((int64_t)min(a.nq - f.q_first, (int64_t)f.q_cap) + kSadGroup - 1) / kSadGroup;
+    const int64_t g_end = min((int64_t)(blockIdx.y + 1) * f.slice, ngroups);
+    uint2 *list = s_list + wave * kListCap;
+    uint64_t *masks = s_mask + wave * kSadGroup * C;
+    int cnt = 0;
+    for (int64_t g = (int64_t)blockIdx.y * f.slice + wave; g < g_end; g += NW) {
+        const STX_CONST_AS uint32_t *qp = (const STX_CONST_AS uint32_t *)(f.qt + g * np * (4 * kSadGroup));
+        uint32_t acc[C][kSadGroup];
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+            for (int q = 0; q < kSadGroup; ++q) acc[c][q] = 0u;
+        for (int p = 0; p < np; ++p) {
+            uint4 ev[C];
+#pragma unroll
+            for (int c = 0; c < C; ++c) ev[c] = s_e[p * NE + c * 64 + lane];
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int q = 0; q < kSadGroup; ++q) {
+                    const uint32_t qv = qp[(p * 4 + k) * kSadGroup + q];
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        const uint32_t e = k == 0 ? ev[c].x : k == 1 ? ev[c].y : k == 2 ? ev[c].z : ev[c].w;
+                        if (TORUS) acc[c][q] = __builtin_amdgcn_sad_u16(qv - e, 0x80008000u, acc[c][q]);
+                        else acc[c][q] = __builtin_amdgcn_sad_u16(qv, e, acc[c][q]);
+                    }
+                }
+        }
+        const STX_CONST_AS int2 *thr = (const STX_CONST_AS int2 *)(f.thr + g * kSadGroup);
+        int lessv = 0;
+        uint32_t dirty = 0;
+#pragma unroll
+        for (int q = 0; q < kSadGroup; ++q) {
+            const int lo = thr[q].x - er, hi = thr[q].y + er;
+            int n = 0;
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                const uint64_t lm = __ballot((int)acc[c][q] < lo) & valid[c];
+                const uint64_t um = __ballot((int)acc[c][q] <= hi) & valid[c] & ~lm;
+                n += __builtin_popcountll(lm);
+                if (um) {
+                    masks[q * C + c] = um;
+                    dirty |= 1u << (q * C + c);
+                }
+            }
+            lessv = lane == q ? n : lessv;
+        }
+        const int64_t q0 = f.q_first + g * kSadGroup;
+        if (lane < kSadGroup && lessv) atomicAdd(&a.n_less[q0 + lane], lessv);
+        while (dirty) {
+            const int i = __builtin_ctz(dirty);
+            dirty &= dirty - 1;
+            const uint64_t m = masks[i];
+            if (m >> lane & 1) list[cnt + mask_rank(m)] = make_uint2((uint32_t)(e0 + (i % C) * 64 + lane), (uint32_t)(q0 + i / C));
+            cnt += __builtin_popcountll(m);
+            if (cnt > kListCap - 64) {
+                flush_pairs<DIST>(f, list, cnt, lane);
+                cnt = 0;
+            }
+        }
+    }
+    if (cnt) flush_pairs<DIST>(f, list, cnt, lane);
+}
+
+// ---- L2 kinds: matrix cores -----------------------------------------------------------------------------------
+// A wavefront keeps QF blocks of 32 queries (all KS steps of their rows) in registers; its workgroup's four wavefronts
+// share a stream of candidates, 32 to a tile, in operand order: a step of a tile is one contiguous kilobyte.  The
+// stream goes to LDS by direct loads, a chunk of CK kilobytes at a time, each wavefront fetching a quarter, NB - 1
+// chunks ahead (one barrier per chunk): with every wavefront reading the stream into its own registers, eight steps
+// ahead, the same 4,096 x 14,951 sweep at d = 1024 waited for memory most of the time (540 us).
+// v_mfma_f32_32x32x16_f16: rows are candidates, columns (lanes) queries; the accumulator starts at
+// -(|e|^2/2 + tau), so its sign is the decision.
+template <int KS>
+struct MfmaShape {
+    // kilobytes per chunk, chunks in LDS (64 KB at most: two workgroups per compute unit)
+    static constexpr int CK = KS <= 16 ? (32 % KS == 0 ? 32 : 24) : (KS % 16 == 0 ? 16 : 12);
+    static constexpr int NB = KS <= 16 ? 2 : 4;
+};
+
+// One kilobyte from global memory straight into LDS (16 bytes per lane, in lane order).  Completion is counted by
+// vmcnt like any load; the waits are placed by hand below.
+__device__ inline void load_lds_1k(const uint4 *g, uint32_t lds)
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+}
+
+__device__ inline void load_lds_256(const float *g, uint32_t lds)             // ... 256 bytes, four per lane
+{
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+}
+
+template <int QF, int KS, int WPE>
+__global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankIds ids)
+{
+    constexpr int CK = MfmaShape<KS>::CK, NB = MfmaShape<KS>::NB, LW = CK / 4;
+    constexpr int TPC = KS <= CK ? CK / KS : 1, CPT = KS <= CK ? 1 : KS / CK;   // tiles per chunk / chunks per tile
+    constexpr int LA = TPC > 4 ? TPC / 4 : 1;                                   // auxiliary loads per wavefront and chunk
+    __shared__ __align__(1024) uint4 s_ring[NB][CK][64];
+    __shared__ __align__(256) float s_aux[NB][TPC][64];
+    __shared__ uint2 s_list[4][kListCap];
+    RankArgs a = f.a;
+    rank_group(a, ids);
+    const int lane = threadIdx.x & 63, half = lane >> 5, z = (int)blockIdx.z;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int nq = (int)min(a.nq - f.q_first, (int64_t)f.q_cap);
+    if ((int)blockIdx.x * 4 * QF * 32 >= nq) return;
+    const int q_base = f.q_first + (int)(a.true_score - f.a.true_score);       // position of the chunk in the query arrays
+    const uint32_t zbits = f.z_shift < 32 ? (uint32_t)z << f.z_shift : 0u;
+    // Wavefronts with queries of their own: four, or two or one where the workgroup's queries are few; the others take
+    // the same queries and every second or fourth tile of a chunk (of one tile: nothing, they only fetch).
+    const int left = (nq - (int)blockIdx.x * 128 * QF + 32 * QF - 1) / (32 * QF), wq = left > 2 ? 4 : left > 1 ? 2 : 1;
+    const int parts = 4 / wq, part = wave / wq;
+    const int qb = ((int)blockIdx.x * 4 + wave % wq) * QF;                     // first block of 32 queries
+    const bool works = qb * 32 < nq && (TPC > 1 || part == 0);
+    const int tiles = (f.e_count + 31) / 32;
+    const int t0 = (int)blockIdx.y * f.slice, t1 = min(t0 + f.slice, tiles);
+    const uint4 *src = f.ef + ((int64_t)z * tiles + t0) * KS * 64 + wave * LW * 64 + lane;
+    const int chunks = ((t1 - t0) * KS + CK - 1) / CK;
+    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&s_ring[0][0][0];
+    const uint32_t ring_aux = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&s_aux[0][0][0];
+    const float *aux = f.eaux + ((int64_t)z * tiles + t0) * 64 + lane;
+    auto fetch = [&](int c, int slot) {                                        // (past the end: the last chunk once more)
+        const uint4 *g = src + (int64_t)min(c, chunks - 1) * CK * 64;
+#pragma unroll
+        for (int i = 0; i < LW; ++i) load_lds_1k(g + i * 64, ring + (uint32_t)((slot * CK + wave * LW + i) * 1024));
+        const float *ga = aux + (int64_t)(CPT > 1 ? min(c, chunks - 1) / CPT : min(c, chunks - 1) * TPC) * 64;
+#pragma unroll
+        for (int i = 0; i < LA; ++i) {                                         // (fewer tiles than wavefronts: some fetch the same)
+            const int tile = (wave + 4 * i) % TPC;
+            load_lds_256(ga + tile * 64, ring_aux + (uint32_t)((slot * TPC + tile) * 256));
+        }
+    };
+    half8 qf[QF][KS];
+    float p_x[QF], p_y[QF], p_z[QF], p_w[QF], p_s[QF];
+#pragma unroll
+    for (int q = 0; q < QF; ++q) {
+        const int blk = min(qb + q, (nq + 31) / 32 - 1);                       // past the end: repeated, made to count nothing
+        const uint4 *qs = f.qf + ((int64_t)z * (f.q_cap / 32) + blk) * KS * 64 + lane;
+#pragma unroll
+        for (int k = 0; k < KS; ++k) qf[q][k] = __builtin_bit_cast(half8, qs[k * 64]);
+        const int64_t qi = (int64_t)z * f.q_cap + blk * 32 + (lane & 31);
+        float4 par = f.qpar[qi];
+        p_s[q] = f.qscale[qi];
+        if (qb + q > blk) { par = make_float4(0.f, 0.f, 3e37f, 0.f); p_s[q] = 1.f; }
+        p_x[q] = par.x; p_y[q] = par.y; p_z[q] = par.z; p_w[q] = par.w;
+    }
+    int less[QF];
+#pragma unroll
+    for (int q = 0; q < QF; ++q) less[q] = 0;
+    int cnt = 0, t = t0;
+    floatx16 acc[QF];
+    float w[QF];
+    auto begin_tile = [&](const float *ta) {
+        const float4 et = ld4(ta + 32);
+        float4 cn[4];
+#pragma unroll
+        for (int g = 0; g < 4; ++g) cn[g] = ld4(ta + half * 4 + 8 * g);
+#pragma unroll
+        for (int q = 0; q < QF; ++q) {
+            w[q] = __builtin_fmaf(p_x[q], et.y, __builtin_fmaf(p_y[q], et.z, __builtin_fmaf(p_w[q], et.x, p_s[q] * et.w))) * 1.0001f;
+            const float tau = -p_z[q] * et.x, ns = -p_s[q];
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                acc[q][4 * g] = __builtin_fmaf(cn[g].x, ns, tau);
+                acc[q][4 * g + 1] = __builtin_fmaf(cn[g].y, ns, tau);
+                acc[q][4 * g + 2] = __builtin_fmaf(cn[g].z, ns, tau);
+                acc[q][4 * g + 3] = __builtin_fmaf(cn[g].w, ns, tau);
+            }
+        }
+    };
+    auto end_tile = [&] {
+        uint32_t und = 0;                                                      // the lane's undecided sums: bit 31 - 16 q - i
+#pragma unroll
+        for (int q = QF - 1; q >= 0; --q) {
+            uint32_t neg = 0, near = 0;                                        // signs of t and of |t| - w
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const float v = acc[q][i];
+                neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(v), 31);
+                near = __builtin_amdgcn_alignbit(near, __float_as_uint(fabsf(v) - w[q]), 31);
+            }
+            if (!(w[q] < 1e37f)) near = 0xffffu;                               // no bound: nothing is decided
+            less[q] += 16 - __builtin_popcount(neg | near);
+            und |= near << (16 * (1 - q));
+        }
+        while (__any(und != 0)) {
+            const int i = __builtin_clz(und | 1u);
+            const int e = f.e_first + t * 32 + (i & 3) + 8 * ((i >> 2) & 3) + 4 * half, q = (qb + i / 16) * 32 + (lane & 31);
+            const uint64_t m = __ballot(und != 0 && e < a.n_ent && q < nq);
+            und &= ~(0x80000000u >> i);
+            if (m >> lane & 1) s_list[wave][cnt + mask_rank(m)] = make_uint2((uint32_t)e | zbits, (uint32_t)(q_base + q));
+            cnt += __builtin_popcountll(m);
+            if (cnt > kListCap - 64) {
+                flush_pairs<STX_L2>(f, s_list[wave], cnt, lane);
+                cnt = 0;
+            }
+        }
+    };
+#pragma unroll
+    for (int c = 0; c < NB - 1; ++c) fetch(c, c);
+    for (int c0 = 0; c0 < chunks; c0 += CPT) {
+#pragma unroll
+        for (int cc = 0; cc < CPT; ++cc) {
+            const int c = c0 + cc;
+            // this wavefront's quarter of chunk c has landed when at most the later NB - 2 chunks' loads are outstanding
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((NB - 2) * (LW + LA)) : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(c + NB - 1, (c + NB - 1) % NB);          // over the chunk that every wavefront is done with
+            if (!works) continue;
+            const uint4 (*chunk)[64] = s_ring[c % NB];
+            if (CPT > 1) {
+                if (cc == 0) begin_tile(s_aux[c % NB][0]);
+#pragma unroll
+                for (int k = 0; k < CK; ++k) {
+                    const half8 e8 = __builtin_bit_cast(half8, chunk[k][lane]);
+#pragma unroll
+                    for (int q = 0; q < QF; ++q)
+                        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(e8, qf[q][cc * CK + k], acc[q], 0, 0, 0);
+                }
+            } else {
+#pragma unroll 1
+                for (int tt = part; tt < TPC; tt += parts) {
+                    t = t0 + c * TPC + tt;
+                    if (t >= t1) break;
+                    begin_tile(s_aux[c % NB][tt]);
+#pragma unroll
+                    for (int k = 0; k < KS; ++k) {
+                        const half8 e8 = __builtin_bit_cast(half8, chunk[tt * KS + k][lane]);
+#pragma unroll
+                        for (int q = 0; q < QF; ++q)
+                            acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(e8, qf[q][k], acc[q], 0, 0, 0);
+                    }
+                    end_tile();
+                }
+            }
+        }
+        if (CPT > 1 && works) {
+            end_tile();
+            ++t;
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // (loads into LDS still in flight must not outlive the workgroup)
+    if (!works) return;
+    if (cnt) flush_pairs<STX_L2>(f, s_list[wave], cnt, lane);
+#pragma unroll
+    for (int q = 0; q < QF; ++q) {
+        const int n = less[q] + __shfl_xor(less[q], 32, 64);
+        const int qi = (qb + q) * 32 + lane;
+        if (lane < 32 && qi < nq && n) atomicAdd(&a.n_less[f.q_first + qi], n);
+    }
+}
+
+// ---- host ---------------------------------------------------------------------------------------------------
+static bool sad_kind(int dist) { return dist == STX_L1 || dist == STX_TORUS_L1; }
+static bool mfma_kind(int dist) { return dist == STX_L2 || dist == STX_L2_SQ; }
+static int sad_pieces(int width) { return (width + 7) / 8; }
+// Matrix-core steps of a row: the compiled counts, rows in between are padded with zeros.
+static int mfma_steps(int width)
+{
+    static const int kSteps[] = {1, 2, 3, 4, 6, 8, 12, 16, 24, 32, 48, 64};
+    for (int s : kSteps)
+        if (16 * s >= width) return s;
+    return 64;
+}
+static size_t mfma_query_bytes(int ks) { return (size_t)ks * 32 + sizeof(float4) + sizeof(float); }
+static size_t mfma_tile_bytes(int ks) { return (size_t)ks * 1024 + 256; }
+constexpr size_t kMfmaSlack = 32 * 1024 + 32 * 256;            // reads past the last tile
+
+size_t rank_filter_q_bytes(int dist, int width, int64_t queries)
+{
+    const int64_t q = (queries + 31) / 32 * 32;
+    size_t each = 0;
+    if (sad_kind(dist)) each = sad_pieces(width) * 16 + sizeof(int2);
+    else if (mfma_kind(dist)) each = mfma_query_bytes(mfma_steps(width));
+    else return 0;
+    each += (size_t)width * 4;
+    const size_t b = (q * each + 2048) * 3 / 2;               // and half as much again for the list of undecided pairs
+    return b > (size_t)4 << 20 ? b : (size_t)4 << 20;
+}
+size_t rank_filter_e_bytes(int dist, int width, int64_t candidates, int tables)
+{
+    return mfma_kind(dist) ? (size_t)((candidates + 31) / 32) * tables * mfma_tile_bytes(mfma_steps(width)) + kMfmaSlack : 0;
+}
+
+template <int QF, int KS, int WPE>
+static void go_mfma(stx_ctx *c, FilterArgs &f, int64_t nq, int nz, const RankIds &ids)
+{
+    const unsigned gx = (unsigned)((nq + 128 * QF - 1) / (128 * QF));
+    const int tiles = (f.e_count + 31) / 32;
+    // One round of the workgroups that fit the chip (starting one costs a few microseconds of dependent loads), up to
+    // four when a workgroup then still streams 256 steps: the last round is partly empty.
+    const int64_t slots = 256 * WPE, blocks = (int64_t)gx * nz;
+    int64_t rounds = (int64_t)tiles * KS * blocks / (slots * 256);
+    rounds = rounds < 1 ? 1 : rounds > 4 ? 4 : rounds;
+    int64_t slices = (slots * rounds + blocks - 1) / blocks;
+    int slice = (int)((tiles + slices - 1) / slices);
+    if (slice < 4) slice = 4;
+    slices = (tiles + slice - 1) / slice;
+    f.slice = slice;
+    ProfScope prof(c, "k_rank_mfma");
+    hipLaunchKernelGGL((k_rank_mfma<QF, KS, WPE>), dim3(gx, (unsigned)slices, (unsigned)nz), dim3(kThreads), 0, c->stream, f, ids);
+}
+template <int QF, int KS, int WPE>
+static void go_mfma_q(stx_ctx *c, FilterArgs &f, int64_t nq, int nz, const RankIds &ids)
+{
+    if (nq <= 128) go_mfma<1, KS, WPE>(c, f, nq, nz, ids);
+    else go_mfma<QF, KS, WPE>(c, f, nq, nz, ids);
+}
+template <int DIST, int C>
+static void go_sad(stx_ctx *c, FilterArgs &f, int64_t nq)
+{
+    const size_t lds = (size_t)f.np * 64 * C * 16 + (kSadThreads / 64) * ((size_t)kListCap * 8 + kSadGroup * C * 8) + 64 * C * 4;
+    static bool told = false;                                  // (per instantiation: more than 64 KB of LDS has to be asked for)
+    if (!told) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rank_sad<DIST, C>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+        told = true;
+    }
+    const int64_t groups = (nq + kSadGroup - 1) / kSadGroup;
+    const int64_t gx = ((int64_t)f.a.n_ent + 64 * C - 1) / (64 * C);
+    int64_t slices = (4096 + gx - 1) / gx;
+    int64_t slice = (groups + slices - 1) / slices;
+    const int64_t waves = kSadThreads / 64;
+    if (slice < 4 * waves) slice = 4 * waves;                  // staging pays off over a few groups per wavefront
+    slice = (slice + waves - 1) / waves * waves;
+    slices = (groups + slice - 1) / slice;
+    f.slice = (int32_t)slice;
+    ProfScope prof(c, "k_rank_sad");
+    hipLaunchKernelGGL((k_rank_sad<DIST, C>), dim3((unsigned)gx, (unsigned)slices), dim3(kSadThreads), lds, c->stream, f);
+}
+
+bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &ws, int nz, const RankIds &ids)
+{
+    const int dist = c->cfg.dist, width = a.dim;
+    const bool sad = sad_kind(dist) && nz == 0;
+    if (!sad && !mfma_kind(dist)) return false;
+    const int tables = nz > 0 ? nz : 1;
+    FilterArgs f{};
+    f.a = a;
+    f.head = side;
+    size_t q_each = ws.q32 ? 0 : (size_t)width * 4;
+    if (sad) {
+        f.np = sad_pieces(width);
+        q_each += (size_t)f.np * 16 + sizeof(int2);
+    } else {
+        f.np = 2 * mfma_steps(width);
+        q_each += mfma_query_bytes(f.np / 2);
+    }
+    // the list of undecided pairs takes a third of the query scratch; about one pair in a thousand to three hundred is
+    // undecided, so a sweep covers at most 300 pairs per place (beyond that pairs are treated inside the sweep)
+    f.pair_cap = (int32_t)(ws.q_bytes / 3 / sizeof(uint2));
+    f.z_shift = 32;
+    if (nz > 0) {
+        f.z_shift = 26;
+        if (a.n_ent >= 1 << 26 || nz > kRankTables) return false;
+    }
+    const int64_t span = (int64_t)f.pair_cap * (sad ? 1000 : 300);
+    int64_t cap = (int64_t)((ws.q_bytes - (size_t)f.pair_cap * sizeof(uint2) - 1024) / q_each / tables) / 32 * 32;
+    if (sad && cap > span / a.n_ent / 32 * 32) cap = span / a.n_ent / 32 * 32;
+    if (sad && cap < 32) cap = 32;
+    if (cap > (a.nq + 31) / 32 * 32) cap = (a.nq + 31) / 32 * 32;
+    if (cap < 32 || (nz > 0 && cap < a.nq)) return false;
+    f.q_cap = (int32_t)cap;
+    char *q = ws.q;
+    f.n_pairs = (int32_t *)q;
+    f.pairs = (uint2 *)(q + 256);
+    q += 256 + (size_t)f.pair_cap * sizeof(uint2);
+    q += -(uintptr_t)q & 255u;
+    f.q32 = ws.q32;
+    if (!f.q32) {
+        f.q32 = (float *)q;
+        q += (size_t)cap * width * 4;
+    }
+    if (sad) {
+        f.scale = (float *)q;
+        f.thr = (int2 *)(q + 256);
+        f.qt = (uint32_t *)(f.thr + cap);
+    } else {
+        f.qf = (uint4 *)q;
+        f.qpar = (float4 *)(f.qf + (size_t)cap * tables * (f.np / 2) * 2);
+        f.qscale = (float *)(f.qpar + (size_t)cap * tables);
+    }
+    int64_t seg = a.n_ent;                                     // candidates per segment (matrix cores)
+    if (!sad) {
+        int64_t tiles = (int64_t)((ws.e_bytes - kMfmaSlack) / mfma_tile_bytes(f.np / 2)) / tables;
+        const int64_t all = ((int64_t)a.n_ent + 31) / 32;
+        if (tiles < 1 || (nz > 0 && tiles < all)) return false;
+        if (tiles > all) tiles = all;
+        if (nz == 0 && tiles > span / cap / 32) tiles = span / cap / 32 > 0 ? span / cap / 32 : 1;
+        seg = tiles * 32;
+        f.ef = (uint4 *)ws.e;
+        f.eaux = (float *)(ws.e + (size_t)tiles * tables * (f.np / 2) * 1024 + 32 * 1024);
+    }
+    auto pairs = [&] {
+        ProfScope prof(c, "k_rank_pairs");
+        const dim3 grid(2048);                                 // eight workgroups per compute unit
+        if (dist == STX_L1) hipLaunchKernelGGL((k_rank_pairs<STX_L1>), grid, dim3(kThreads), 0, c->stream, f);
+        else if (dist == STX_TORUS_L1) hipLaunchKernelGGL((k_rank_pairs<STX_TORUS_L1>), grid, dim3(kThreads), 0, c->stream, f);
+        else hipLaunchKernelGGL((k_rank_pairs<STX_L2>), grid, dim3(kThreads), 0, c->stream, f);
+    };
+    auto prep = [&](int nqb, int neb) {
+        f.nqb = nqb;
+        const dim3 grid((unsigned)(nqb + neb), 1, (unsigned)tables);
+        ProfScope prof(c, "k_rank_prep");
+#define STX_PREP(D)                                                                                           \
+    if (side) hipLaunchKernelGGL((k_rank_prep<D, true>), grid, dim3(kThreads), 0, c->stream, f, ids);         \
+    else hipLaunchKernelGGL((k_rank_prep<D, false>), grid, dim3(kThreads), 0, c->stream, f, ids);
+        if (dist == STX_L1) { STX_PREP(STX_L1) }
+        else if (dist == STX_TORUS_L1) { STX_PREP(STX_TORUS_L1) }
+        else { STX_PREP(STX_L2) }
+#undef STX_PREP
+    };
+    if (sad && dist == STX_L1) {
+        if (side) hipLaunchKernelGGL((k_rank_scale<true>), dim3(1), dim3(1024), 0, c->stream, a, f.scale);
+        else hipLaunchKernelGGL((k_rank_scale<false>), dim3(1), dim3(1024), 0, c->stream, a, f.scale);
+    }
+    for (int64_t q0 = 0; q0 < a.nq; q0 += cap) {
+        const int64_t nq = a.nq - q0 < cap ? a.nq - q0 : cap;
+        const int nqb = (int)((nq + 31) / 32);
+        f.q_first = (int32_t)q0;
+        if (sad) {
+            prep(nqb, 0);
+            const bool narrow = width <= 256;                  // two candidates per lane while their tile leaves LDS for two workgroups
+            if (dist == STX_L1) { if (narrow) go_sad<STX_L1, 2>(c, f, nq); else go_sad<STX_L1, 1>(c, f, nq); }
+            else { if (narrow) go_sad<STX_TORUS_L1, 2>(c, f, nq); else go_sad<STX_TORUS_L1, 1>(c, f, nq); }
+            pairs();
+            continue;
+        }
+        for (int64_t e0 = 0; e0 < a.n_ent; e0 += seg) {
+            f.e_first = (int32_t)e0;
+            f.e_count = (int32_t)(a.n_ent - e0 < seg ? a.n_ent - e0 : seg);
+            const bool packed = q0 > 0 && seg >= a.n_ent;      // a table of one segment stays packed for the later chunks
+            // (packed and no queries cannot both hold: the first segment of a chunk always has queries to prepare)
+            const int nb_q = e0 == 0 ? nqb : 0, nb_e = packed ? 0 : (f.e_count + 31) / 32;
+            prep(nb_q, nb_e);
+            switch (f.np / 2) {
+            case 1: go_mfma_q<2, 1, 1>(c, f, nq, tables, ids); break;
+            case 2: go_mfma_q<2, 2, 2>(c, f, nq, tables, ids); break;
+            case 3: go_mfma_q<2, 3, 2>(c, f, nq, tables, ids); break;
+            case 4: go_mfma_q<2, 4, 2>(c, f, nq, tables, ids); break;
+            case 6: go_mfma_q<2, 6, 2>(c, f, nq, tables, ids); break;
+            case 8: go_mfma_q<2, 8, 2>(c, f, nq, tables, ids); break;
+            case 12: go_mfma_q<2, 12, 2>(c, f, nq, tables, ids); break;
+            case 16: go_mfma_q<2, 16, 2>(c, f, nq, tables, ids); break;
+            case 24: go_mfma_q<2, 24, 1>(c, f, nq, tables, ids); break;
+            case 32: go_mfma_q<2, 32, 1>(c, f, nq, tables, ids); break;
+            case 48: go_mfma<1, 48, 1>(c, f, nq, tables, ids); break;
+            default: go_mfma<1, 64, 1>(c, f, nq, tables, ids); break;
+            }
+            pairs();
+        }
+    }
+    return true;
+}
+
+}  // namespace stx

@@ -1,0 +1,92 @@
+"""The filtered sweeps of stx_rank (one large call) against the plain sweep, which small calls take: the same queries
+128 at a time must give the same true scores and the same counts, bit for bit.  The plain sweep itself is held against
+the oracle in test_gpu_rank.py."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2502_16949_amd import binding as B
+from tests import gpu_util as G
+
+pytestmark = pytest.mark.gpu
+
+FILTER_STEPS = 6e8       # queries (padded to 128) x entities x dim from which a call is filtered
+
+
+def _rank(ctx, p, h, r, t, side):
+    nq = len(h)
+    ts = torch.empty(nq, dtype=torch.float32, device=G.DEV)
+    less = torch.empty(nq, dtype=torch.int32, device=G.DEV)
+    equal = torch.empty_like(less)
+    B.stx_rank(ctx, p, h, r, t, side, ts, less, equal)
+    return ts, less, equal
+
+
+CASES = [
+    # dist, n_ent, dim, nq: row widths at and around the pieces of 8 and 16 elements, ragged tiles and query blocks
+    ("l1", 12_001, 16, 4_000), ("l1", 4_097, 128, 1_300), ("l1", 2_050, 260, 1_250), ("l1", 1_100, 1024, 700),
+    ("torus_l1", 40_000, 36, 700), ("torus_l1", 3_000, 200, 1_290), ("torus_l1", 1_500, 1000, 513),
+    ("l2", 12_001, 16, 4_000), ("l2", 30_000, 44, 600), ("l2", 4_129, 128, 1_300), ("l2", 9_000, 196, 385),
+    ("l2_sq", 2_050, 260, 1_250), ("l2", 1_300, 700, 800), ("l2", 1_100, 1024, 700),
+    ("l2", 500_000, 100, 33), ("l1", 200_000, 60, 5),     # few queries, several segments of candidates
+]
+
+
+@pytest.mark.parametrize("odd_rows", [False, True])
+@pytest.mark.parametrize("dist,n_ent,dim,nq", CASES)
+def test_filtered_counts_equal_the_plain_sweep(dist, n_ent, dim, nq, odd_rows):
+    assert -(-nq // 128) * 128.0 * n_ent * dim >= FILTER_STEPS
+    n_rel = 5
+    rng = np.random.default_rng(dim + n_ent)
+    X = rng.uniform(-1, 1, (n_ent + n_rel, dim)).astype(np.float32)
+    if odd_rows:                                          # rows the bounds cannot cover, and exact ties
+        X[7] = 1e30
+        X[8, dim // 2] = np.inf
+        X[9, 0] = np.nan
+        X[10] *= 1e-22
+        X[11] = 0.0
+        X[12] *= 300.0
+        X[13:13 + n_ent // 8] = X[n_ent - n_ent // 8:n_ent]
+    h = rng.integers(0, n_ent, nq).astype(np.int32)
+    t = rng.integers(0, n_ent, nq).astype(np.int32)
+    if odd_rows:
+        h[:4], t[:4] = [7, 9, 10, 11], [8, 20, 10, 12]
+    r = rng.integers(0, n_rel, nq).astype(np.int32)
+    hd, rd, td = G.dev_i32(h), G.dev_i32(r), G.dev_i32(t)
+    cfg = B.make_config("toruse" if dist.startswith("torus") else "transe", dist, n_ent, n_rel, dim, 8, 1)
+    ctx, p = B.Context(cfg, G.DEV), B.Params(G.dev_f32(X))
+    step = 128 if 128.0 * n_ent * dim < FILTER_STEPS else 0
+    for side in (B.STX_TAIL, B.STX_HEAD):
+        got = [x.cpu().numpy() for x in _rank(ctx, p, hd, rd, td, side)]
+        if step:
+            parts = [_rank(ctx, p, hd[i:i + step].clone(), rd[i:i + step].clone(), td[i:i + step].clone(), side)
+                     for i in range(0, nq, step)]
+            want = [torch.cat([x[k] for x in parts]).cpu().numpy() for k in range(3)]
+        else:                                             # entities in ranges small enough for the plain sweep
+            want = _by_ranges(cfg, X, h, r, t, side, n_ent, n_rel, dim, dist)
+        for g, w in zip(got, want):
+            assert np.array_equal(g, w, equal_nan=True)
+    assert B.stx_check_indices(ctx) == 0
+
+
+def _by_ranges(cfg, X, h, r, t, side, n_ent, n_rel, dim, dist):
+    """The counts of long tables from plain sweeps over tables of a part of the entities each, to which the entities
+    of the queries are added (and subtracted again)."""
+    nq, size = len(h), int(FILTER_STEPS / 128 / dim / 2)
+    own = np.concatenate([h, t])
+    less, equal, ts = np.zeros(nq, np.int64), np.zeros(nq, np.int64), None
+
+    def run(rows):
+        n = len(rows)
+        ctx = B.Context(B.make_config(cfg.model, cfg.dist, n, n_rel, dim, 8, 1), G.DEV)
+        p = B.Params(G.dev_f32(np.concatenate([X[rows], X[n_ent:]])))
+        q = np.arange(nq, dtype=np.int32)
+        return [x.cpu().numpy() for x in _rank(ctx, p, G.dev_i32(q), G.dev_i32(r), G.dev_i32(q + nq), side)]
+
+    ts, less0, equal0 = run(own)
+    for lo in range(0, n_ent, size):
+        part = np.arange(lo, min(lo + size, n_ent))
+        _, l, e = run(np.concatenate([own, part]))
+        less += l - less0
+        equal += e - equal0
+    return ts, less.astype(np.int32), equal.astype(np.int32)
