@@ -207,7 +207,7 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
     // One block of LDS for whichever part a workgroup plays (the parts' own arrays would add up and cost the
     // launch wavefronts per CU): the product's arrays below, or those of a body that rides.
     constexpr int GROUPS_ = kThreads / LPR, ROWF_ = ITERS * LPR * 4;
-    constexpr int OWN_LDS = (GROUPS_ * 2 * ROWF_ + (FUSED ? GROUPS_ * ROWF_ : 4) + 5 * GROUPS_) * 4;
+    constexpr int OWN_LDS = (GROUPS_ * 2 * ROWF_ + (FUSED ? GROUPS_ * ROWF_ : 4) + 3 * GROUPS_) * 4;
     constexpr int RIDE_LDS = RIDE == 0 ? 0
                              : (RIDE == 3 || RIDE == 5) ? kScatterLds
                              : (RIDE == 2 || RIDE == 4) ? emit_lds(true, RIDE == 4)
@@ -285,12 +285,10 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
     constexpr int ROWF = ITERS * LPR * 4;   // floats per staged row in LDS
     static_assert(GROUPS == GROUPS_ && ROWF == ROWF_, "sizes of the block of LDS");
     float (*s_part)[2][ROWF] = reinterpret_cast<float (*)[2][ROWF]>(s_arena);
-    // FUSED: table row and column of the run that leaves each chunk to the right; which chunk's they are for
-    // the stitched run that closes in a chunk (-1: none closes there)
+    // FUSED: table row and column of the run that leaves each chunk to the right
     float (*s_x)[FUSED ? ROWF : 4] = reinterpret_cast<float (*)[FUSED ? ROWF : 4]>(s_arena + GROUPS * 2 * ROWF * 4);
     int32_t *s_small = reinterpret_cast<int32_t *>(s_arena + (GROUPS * 2 * ROWF + (FUSED ? GROUPS * ROWF : 4)) * 4);
-    int32_t *s_info = s_small, *s_seg_first = s_small + GROUPS, *s_seg_last = s_small + 2 * GROUPS;
-    int32_t *s_col_last = s_small + 3 * GROUPS, *s_fin_src = s_small + 4 * GROUPS;
+    int32_t *s_info = s_small, *s_seg_last = s_small + GROUPS, *s_col_last = s_small + 2 * GROUPS;
 
     const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
     const int pk_sh = PACKED ? 31 - __clz(ld_src) : 0;
@@ -346,7 +344,6 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
                     st4(&s_part[grp][slot][(lig + it * LPR) * 4], acc.v[it]);
                 if (open_left) {
                     info |= HAS_FIRST | (open_right ? FIRST_CONT : 0);
-                    if (lig == 0) s_seg_first[grp] = cur_seg;
                 } else {
                     info |= HAS_LAST;
                     if (lig == 0) s_seg_last[grp] = cur_seg;
@@ -439,61 +436,48 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
         }
         flush(true);
     }
-    if (lig == 0) { s_info[grp] = info; s_fin_src[grp] = -1; }
+    if (lig == 0) s_info[grp] = info;
     __syncthreads();
 
-    // Stitch the chunk-crossing runs in chunk order (group 0 only; lanes keep their float4 slices).
-    if (grp == 0) {
-        bool have = false, started_in = false;
-        int32_t cur_seg = 0;
-        int cur_src = 0;                                   // chunk in which the current run began
+    // Stitch the chunk-crossing runs, each in chunk order and by a group of its own: the group in whose chunk a run
+    // ends adds up its pieces, from the chunk in which the run began (or from the tile's first, for a run that came
+    // in from an earlier workgroup).  One group walking all chunks took 250 cycles per chunk, 8,000 at 32 groups.
+    const int linfo = (int)(threadIdx.x & 63) < GROUPS ? s_info[threadIdx.x & 63] : 0;
+    const uint64_t m_cont = __ballot((linfo & FIRST_CONT) != 0), m_last = __ballot((linfo & HAS_LAST) != 0);
+    float *my_part = partials + (int64_t)block * 2 * ld_out;
+    // pieces of the run that reaches chunk g, oldest first; returns the chunk it began in, -1: an earlier workgroup's
+    auto run_sum = [&](int g, uint64_t before, Acc<ITERS> &cur) {
+        const uint64_t m = m_last & before;
+        const int s0 = m ? 63 - __clzll(m) : -1;
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it) cur.v[it] = ld4(&s_part[s0 < 0 ? 0 : s0][s0 < 0 ? 0 : 1][(lig + it * LPR) * 4]);
+        for (int h = s0 < 0 ? 1 : s0 + 1; h <= g; ++h) {
+            Acc<ITERS> p;
+#pragma unroll
+            for (int it = 0; it < ITERS; ++it) p.v[it] = ld4(&s_part[h][0][(lig + it * LPR) * 4]);
+            cur.add(p);
+        }
+        return s0;
+    };
+    if ((info & HAS_FIRST) && !(info & FIRST_CONT)) {      // a run ends inside this group's chunk
         Acc<ITERS> cur;
-        cur.zero();
-        float *my_part = partials + (int64_t)block * 2 * ld_out;
-        for (int g = 0; g < GROUPS; ++g) {
-            const int inf = s_info[g];
-            if (inf & HAS_FIRST) {
-                Acc<ITERS> p;
+        const int s0 = run_sum(grp, (1ull << grp) - 1ull, cur);
+        if (s0 < 0) {
+            store_row<LPR, ITERS>(my_part, d4, lig, cur);
+        } else if constexpr (FUSED) {
+            Acc<ITERS> x;
 #pragma unroll
-                for (int it = 0; it < ITERS; ++it) p.v[it] = ld4(&s_part[g][0][(lig + it * LPR) * 4]);
-                if (!have) {
-                    have = true; started_in = false; cur = p; cur_seg = s_seg_first[g];
-                } else {
-                    cur.add(p);
-                }
-                if (!(inf & FIRST_CONT)) {   // the run ends inside chunk g
-                    if (!started_in) {
-                        store_row<LPR, ITERS>(my_part, d4, lig, cur);   // began in an earlier workgroup
-                    } else if constexpr (FUSED) {   // left in chunk g's consumed slot; group g applies it below
-#pragma unroll
-                        for (int it = 0; it < ITERS; ++it) st4(&s_part[g][0][(lig + it * LPR) * 4], cur.v[it]);
-                        if (lig == 0) s_fin_src[g] = cur_src;
-                    } else {
-                        store_row<LPR, ITERS>(out_rows + (int64_t)cur_seg * ld_out, d4, lig, cur);
-                    }
-                    have = false;
-                }
-            }
-            if (inf & HAS_LAST) {
-                have = true; started_in = true; cur_seg = s_seg_last[g]; cur_src = g;
-#pragma unroll
-                for (int it = 0; it < ITERS; ++it) cur.v[it] = ld4(&s_part[g][1][(lig + it * LPR) * 4]);
-            }
+            for (int it = 0; it < ITERS; ++it) x.v[it] = ld4(&s_x[s0][(lig + it * LPR) * 4]);
+            apply_update<LPR, ITERS>(fused_row(fu, s_col_last[s0], ld_tab), d4, lig, x, cur, fu.lr, fu.mode, fu.stream);
+        } else {
+            store_row<LPR, ITERS>(out_rows + (int64_t)s_seg_last[s0] * ld_out, d4, lig, cur);
         }
-        if (have) store_row<LPR, ITERS>(my_part + (started_in ? ld_out : 0), d4, lig, cur);   // runs on into the next tile
     }
-    if constexpr (FUSED) {   // the stitched runs that closed inside the tile: one per group at most, applied in parallel
-        __syncthreads();
-        const int src = s_fin_src[grp];
-        if (src >= 0) {
-            Acc<ITERS> x, g;
-#pragma unroll
-            for (int it = 0; it < ITERS; ++it) {
-                x.v[it] = ld4(&s_x[src][(lig + it * LPR) * 4]);
-                g.v[it] = ld4(&s_part[grp][0][(lig + it * LPR) * 4]);
-            }
-            apply_update<LPR, ITERS>(fused_row(fu, s_col_last[src], ld_tab), d4, lig, x, g, fu.lr, fu.mode, fu.stream);
-        }
+    // the run that goes on into the next tile (then the tile is full); taken by a group that seldom has another
+    if (grp == 0 && ((m_cont | m_last) >> (GROUPS - 1) & 1)) {
+        Acc<ITERS> cur;
+        const int s0 = run_sum(GROUPS - 1, (1ull << (GROUPS - 1) << 1) - 1ull, cur);
+        store_row<LPR, ITERS>(my_part + (s0 < 0 ? 0 : ld_out), d4, lig, cur);
     }
 }
 
