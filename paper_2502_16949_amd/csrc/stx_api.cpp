@@ -110,7 +110,9 @@ Layout make_layout(const stx_config *c)
         L.rel_cnt = take((size_t)2 * c->n_rel * 4);
     }
     if (c->model == STX_TRANSE || c->model == STX_TORUSE) {
-        L.rank_q_bytes = rank_filter_q_bytes(c->dist, c->dim, 32) ? kRankQBytes : 0;
+        size_t q = (size_t)(c->n_ent + c->n_rel) * c->dim * 16;          // in proportion to the table, 2 MB at least
+        if (q < (size_t)2 << 20) q = (size_t)2 << 20;
+        L.rank_q_bytes = rank_filter_q_bytes(c->dist, c->dim, 32) ? (q < kRankQBytes ? q : kRankQBytes) : 0;
         L.rank_e_bytes = rank_filter_e_bytes(c->dist, c->dim, c->n_ent, 1);
         if (L.rank_e_bytes > kRankEBytes) L.rank_e_bytes = kRankEBytes;
         L.rank_q = take(L.rank_q_bytes);

@@ -49,11 +49,11 @@ __global__ __launch_bounds__(kThreads, ITERS == 1 ? 8 : 1) void k_forward_stacke
 
 // (rows of one float4 per lane: 64 registers, every workgroup of a large batch resident at once; wider rows hold
 // four rows of ITERS float4 per lane)
-template <int LPR, int ITERS, int DIST, bool PACKED, int NB>
-__global__ __launch_bounds__(kThreads, ITERS == 1 ? 8 : (ITERS == 2 ? 4 : 2)) void k_forward_fast(ForwardArgs a, int32_t *general_flag,
+template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE>
+__global__ __launch_bounds__(kThreads, ITERS == 1 ? (NB > 4 ? 4 : 8) : ITERS == 2 ? (NB > 1 ? 3 : 4) : 2) void k_forward_fast(ForwardArgs a, int32_t *general_flag,
                                                                                                  int32_t serial)
 {
-    forward_fast_body<LPR, ITERS, DIST, PACKED, NB>((int)blockIdx.x, a, general_flag, serial);
+    forward_fast_body<LPR, ITERS, DIST, PACKED, NB, MORE>((int)blockIdx.x, a, general_flag, serial);
 }
 
 // TransR in stx_train_step: the first kernel of the next batch's build (which also counts the rows per relation)
@@ -156,11 +156,10 @@ static void forward_go(stx_ctx *c, const stx_incidence *inc, const stx_params *p
     EmitAhead ea{};
     if (from_y && c->ahead.armed && !c->ahead.emit_done && c->ahead.args.rc.cur) ea = take_emit_ahead(c);
     const dim3 grid_e(grid.x + (unsigned)ea.ntiles);
-    // Few negatives per positive (four with rows of one float4 per lane, one with wider rows): the kernel that
-    // fetches the positive's rows once (forward_fast_body).  It covers negatives that keep the relation and one entity of their positive; when the
-    // batch was not drawn by the library's sampler in this build, the general kernel is enqueued behind it and runs
-    // only if the fast one met another kind of negative.
-    const bool fast = !from_y && inc->k <= fast_negatives<LPR, ITERS>();
+    // The kernel that fetches the positive's rows once (forward_fast_body) covers negatives that keep the relation and
+    // one entity of their positive; when the batch was not drawn by the library's sampler in this build, the general
+    // kernel is enqueued behind it and runs only if the fast one met another kind of negative.
+    const bool fast = !from_y;
     const bool sampled = c->sampled_inc == inc;
     int32_t *flag = c->ctrl + CTRL_GENERAL;
     const int32_t serial = fast ? ++c->fwd_serial : 0;
@@ -170,9 +169,13 @@ static void forward_go(stx_ctx *c, const stx_incidence *inc, const stx_params *p
 #define STX_FAST(D, P)                                                                                          \
     do {                                                                                                        \
         if (inc->k <= 1)                                                                                        \
-            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, 1>), grid, dim3(kThreads), 0, c->stream, fa, flag, serial); \
+            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, true, false), false>), grid, dim3(kThreads), 0, \
+                               c->stream, fa, flag, serial);                                                    \
+        else if (inc->k <= 4)                                                                                   \
+            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, false, false), (ITERS > 2)>), grid, dim3(kThreads), 0, \
+                               c->stream, fa, flag, serial);                                                    \
         else                                                                                                    \
-            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_negatives<LPR, ITERS>()>), grid, dim3(kThreads), 0, \
+            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, false, true), true>), grid, dim3(kThreads), 0, \
                                c->stream, fa, flag, serial);                                                    \
     } while (0)
 #define STX_FWD2(D)                                                                                             \

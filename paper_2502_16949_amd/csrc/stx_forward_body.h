@@ -69,17 +69,19 @@ __device__ inline void finish_loss_body(const float *__restrict__ partials, int 
 }
 
 // The forward step for batches whose negatives come from the sampler (Sec. 5.3: every negative keeps the relation
-// and one entity of its positive), at most NB negatives per positive.  One group per positive: its lanes fetch the
-// 3 + 3k column ids in ONE load (lane s < 3: id s of the positive; lane 3 + 3q + s: id s of negative q) and share
-// them by shuffles; then the positive's three rows and the ONE row in which each negative differs are requested
-// together (3 + k table rows instead of 3 + 3k), so a wavefront pays two dependent memory round trips in all.
+// and one entity of its positive).  One group per positive: its lanes fetch the 3 + 3 NB column ids of the positive
+// and its first NB negatives in ONE load (id j in lane j; two loads when the group has fewer lanes) and share them by
+// shuffles; then the positive's three rows and the ONE row in which each negative differs are requested together
+// (3 + k table rows instead of 3 + 3k), so a wavefront pays two dependent memory round trips.  Further negatives
+// follow NB at a time, their ids requested a batch ahead, so each batch costs one more.
 // x is formed by the same two roundings in the same order as a full gather would: the bits are those of
-// forward_stacked_body.  A group that finds another kind of negative (a caller's own) does nothing and stores
-// `serial` in *general_flag: the caller then runs the general kernel over those groups.
-template <int LPR, int ITERS, int DIST, bool PACKED, int NB>
+// forward_stacked_body.  A group that finds another kind of negative (a caller's own) stores `serial` in
+// *general_flag: the caller then runs the general kernel, which redoes the batch.
+// MORE: the batch may have more than NB negatives per positive (the loop costs registers).
+template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE>
 __device__ inline void forward_fast_body(const int block, const ForwardArgs &a, int32_t *general_flag, int32_t serial)
 {
-    static_assert(LPR >= 3 + 3 * NB, "one lane per column id");
+    constexpr int NI = (3 + 3 * NB + LPR - 1) / LPR;       // column ids per lane
     const int32_t *__restrict__ colidx = a.colidx;
     const float *__restrict__ X = a.X;
     const int32_t b = a.b, k = a.k;
@@ -92,50 +94,66 @@ __device__ inline void forward_fast_body(const int block, const ForwardArgs &a, 
     float hinge_sum = 0.f;
     if (i < b) {
         const int32_t row0 = b + i * k;
-        int32_t mine = 0;
-        if (lig < 3 + 3 * k) mine = colidx[lig < 3 ? 3 * (int64_t)i + lig : 3 * (int64_t)row0 + (lig - 3)];
-        const int32_t c0 = __shfl(mine, 0, LPR), c1 = __shfl(mine, 1, LPR), c2 = __shfl(mine, 2, LPR);
-        int32_t ce[NB];
-        unsigned tail_mask = 0;
-        bool shared = true;
+        int32_t mine[NI];                                  // id j of (positive, negatives of the batch) in lane j % LPR
 #pragma unroll
-        for (int q = 0; q < NB; ++q) {
-            const int32_t nh = __shfl(mine, 3 + 3 * q, LPR), nr = __shfl(mine, 4 + 3 * q, LPR), nt = __shfl(mine, 5 + 3 * q, LPR);
-            const bool ts = nh == c0;
-            ce[q] = ts ? nt : nh;
-            tail_mask |= ts ? 1u << q : 0u;
-            if (q < k) shared = shared && nr == c1 && (ts || nt == c2);
+        for (int u = 0; u < NI; ++u) {
+            const int j = lig + u * LPR;
+            mine[u] = 0;
+            if (j < 3 + 3 * min(k, NB)) mine[u] = colidx[j < 3 ? 3 * (int64_t)i + j : 3 * (int64_t)row0 + (j - 3)];
         }
-        if (shared) {
-            const float wr = a.rel_weight ? a.rel_weight[c1 - a.n_ent] : 1.0f;
-            // (lanes past the row's width hold zeros and take part in the reductions only)
-            RowVec<ITERS> hr, pr, pt, e[NB];
-            load_vec<LPR, ITERS>(X + (int64_t)c0 * dim, d4, lig, hr);
-            load_vec<LPR, ITERS>(X + (int64_t)c1 * dim, d4, lig, pr);
-            load_vec<LPR, ITERS>(X + (int64_t)c2 * dim, d4, lig, pt);
+        auto id = [&](int j) { return __shfl(mine[j / LPR], j % LPR, LPR); };
+        const int32_t c0 = id(0), c1 = id(1), c2 = id(2);
+        const float wr = a.rel_weight ? a.rel_weight[c1 - a.n_ent] : 1.0f;
+        // (lanes past the row's width hold zeros and take part in the reductions only)
+        RowVec<ITERS> hr, pr, pt, xp;
+        load_vec<LPR, ITERS>(X + (int64_t)c0 * dim, d4, lig, hr);
+        load_vec<LPR, ITERS>(X + (int64_t)c1 * dim, d4, lig, pr);
+        load_vec<LPR, ITERS>(X + (int64_t)c2 * dim, d4, lig, pt);
+        uint8_t *recs = reinterpret_cast<uint8_t *>(a.G);
+        float *gcoef = PACKED ? reinterpret_cast<float *>(recs + packed_coef_offset((int64_t)b * (1 + k), gstride)) : nullptr;
+        bool shared = true;
+        int n_active = 0;
+        float npos = 0.f, dpos = 0.f;
+        for (int q0 = 0; q0 == 0 || (MORE && q0 < k); q0 += NB) {
+            int32_t ce[NB];
+            unsigned tail_mask = 0;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const int32_t nh = id(3 + 3 * q), nr = id(4 + 3 * q), nt = id(5 + 3 * q);
+                const bool ts = nh == c0;
+                ce[q] = ts ? nt : nh;
+                tail_mask |= ts ? 1u << q : 0u;
+                if (q0 + q < k) shared = shared && nr == c1 && (ts || nt == c2);
+            }
+            RowVec<ITERS> e[NB];
 #pragma unroll
             for (int q = 0; q < NB; ++q)
-                if (q < k) {
+                if (q0 + q < k) {
                     // a row used once does not displace the others when the table is far larger than the caches
                     if (a.stream_rows) load_vec_stream<LPR, ITERS>(X + (int64_t)ce[q] * dim, d4, lig, e[q]);
                     else load_vec<LPR, ITERS>(X + (int64_t)ce[q] * dim, d4, lig, e[q]);
                 }
-            RowVec<ITERS> x;
+            if (MORE && q0 + NB < k) {                     // the next batch's ids, in the places of this one's
 #pragma unroll
-            for (int it = 0; it < ITERS; ++it) {
-                hr.v[it] = add4(hr.v[it], pr.v[it]);
-                x.v[it] = sub4(hr.v[it], pt.v[it]);
+                for (int u = 0; u < NI; ++u) {
+                    const int j = lig + u * LPR;
+                    if (j >= 3 && j < 3 + 3 * min(k - q0 - NB, NB)) mine[u] = colidx[3 * (int64_t)(row0 + q0 + NB) + (j - 3)];
+                }
             }
-            const float npos = row_distance<LPR, ITERS, DIST>(x);
-            const float dpos = wr * npos;
-            if (lig == 0) scores[i] = dpos;
-            uint8_t *recs = reinterpret_cast<uint8_t *>(a.G);
-            float *gcoef = PACKED ? reinterpret_cast<float *>(recs + packed_coef_offset((int64_t)b * (1 + k), gstride)) : nullptr;
-            int n_active = 0;
-            const RowVec<ITERS> xp = x;
+            if (q0 == 0) {
+#pragma unroll
+                for (int it = 0; it < ITERS; ++it) {
+                    hr.v[it] = add4(hr.v[it], pr.v[it]);
+                    xp.v[it] = sub4(hr.v[it], pt.v[it]);
+                }
+                npos = row_distance<LPR, ITERS, DIST>(xp);
+                dpos = wr * npos;
+                if (lig == 0) scores[i] = dpos;
+            }
 #pragma unroll
             for (int q = 0; q < NB; ++q)
-                if (q < k) {
+                if (q0 + q < k) {
+                    RowVec<ITERS> x;
 #pragma unroll
                     for (int it = 0; it < ITERS; ++it)
                         x.v[it] = (tail_mask >> q & 1u) ? sub4(hr.v[it], e[q].v[it]) : sub4(add4(e[q].v[it], pr.v[it]), pt.v[it]);
@@ -143,7 +161,7 @@ __device__ inline void forward_fast_body(const int block, const ForwardArgs &a, 
                     const float dneg = wr * nneg;
                     const float arg = (a.margin + dpos) - dneg;
                     const bool active = arg > 0.f;
-                    const int32_t row = row0 + q;
+                    const int32_t row = row0 + q0 + q;
                     if (lig == 0) scores[row] = dneg;
                     if (active) { hinge_sum += arg; ++n_active; }
                     if (PACKED)
@@ -151,13 +169,12 @@ __device__ inline void forward_fast_body(const int block, const ForwardArgs &a, 
                     else
                         write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)row * dim, d4, lig, x, active ? -a.scale * wr : 0.f, nneg);
                 }
-            if (PACKED)
-                write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, i, d4, lig, xp, (float)n_active * a.scale * wr);
-            else
-                write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)i * dim, d4, lig, xp, (float)n_active * a.scale * wr, npos);
-        } else if (lig == 0 && general_flag) {
-            *general_flag = serial;
         }
+        if (PACKED)
+            write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, i, d4, lig, xp, (float)n_active * a.scale * wr);
+        else
+            write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)i * dim, d4, lig, xp, (float)n_active * a.scale * wr, npos);
+        if (!shared && lig == 0 && general_flag) *general_flag = serial;
     }
     if (lig == 0) s_loss[grp] = hinge_sum;
     __syncthreads();
@@ -279,24 +296,16 @@ __device__ inline void forward_stacked_body(const int block, const ForwardArgs &
 
 namespace stx {
 
-// Most negatives per positive that forward_fast_body takes with groups of LPR lanes (one lane per column id) and
-// ITERS float4 per lane (wide rows: one, or the rows in flight would not fit the registers).
-template <int LPR, int ITERS = 1>
-constexpr int fast_negatives() { return (LPR >= 16 && ITERS == 1) ? 4 : 1; }
+// Negatives that forward_fast_body holds at a time, for k of them per positive: as many rows in flight as the
+// registers allow (rows of ITERS float4 per lane, the positive's three beside them).
+constexpr int fast_batch(int iters, bool k1, bool many) { return k1 ? 1 : iters == 1 ? (many ? 8 : 4) : iters == 2 ? 4 : 2; }
 
-// The forward step inside the launches of stx_train_step, whose negatives are the sampler's: the fast body where the
-// row width and the number of negatives allow it.  K1: the launch was chosen for at most one negative per positive.
+// The forward step inside the launches of stx_train_step, whose negatives are the sampler's.  K1: the launch was
+// chosen for at most one negative per positive.
 template <int LPR, int ITERS, int DIST, bool PACKED, bool K1>
 __device__ inline void forward_step_body(const int block, const ForwardArgs &fa)
 {
-    if constexpr (ITERS == 1 && K1) {
-        forward_fast_body<LPR, 1, DIST, PACKED, 1>(block, fa, nullptr, 0);
-    } else if constexpr (ITERS == 1 && LPR >= 16) {
-        if (fa.k <= 4) forward_fast_body<LPR, 1, DIST, PACKED, 4>(block, fa, nullptr, 0);
-        else forward_stacked_body<LPR, ITERS, DIST, false, PACKED, K1>(block, fa);
-    } else {
-        forward_stacked_body<LPR, ITERS, DIST, false, PACKED, K1>(block, fa);
-    }
+    forward_fast_body<LPR, ITERS, DIST, PACKED, fast_batch(ITERS, K1, false), !K1>(block, fa, nullptr, 0);
 }
 
 }  // namespace stx
