@@ -182,19 +182,16 @@ stx_status stx_spmm_semiring(stx_ctx *ctx, const stx_incidence *inc, const stx_p
  * g->rows[s] = sum over the entries of segment s of gz[row] times the conjugated product of the row's
  * other two factors (head entry: conj(r) t | conj(r); relation entry: conj(h) t | conj(h); tail entry:
  * ComplEx conj(gz) h r, RotatE -gz; DistMult: the plain products), summed in the fixed order of
- * stx_backward.  work: 3 * n_rows * dim floats of device scratch owned by the caller (the per-row terms). */
+ * stx_backward.  work: 3 * n_rows * dim floats of device memory owned by the caller; required, but no longer
+ * touched: every entry's term is formed where it is summed.                                              */
 stx_status stx_spmm_semiring_t(stx_ctx *ctx, const stx_incidence *inc, const stx_params *p, int32_t kind,
                                const float *gz, float *work, stx_grads *g);
 
 /* stx_spmm_semiring_t for callers that cannot allocate device memory and have no work buffer to hand over
  * (code under HIP graph capture, serving loops, harnesses that forbid hipMalloc): the same kernels and the
- * same results bit for bit, with the per-row terms kept in a fixed array of STX_STATIC_WORK_BYTES bytes that
- * is part of the library's device code (every GPU the library runs on holds its own copy until the process
- * ends).  Calls no allocator.  The context's GPU must be the current device.
+ * same results bit for bit.  Calls no allocator and uses no memory of the library's own.
  * A batch with 3 * n_rows * dim * 4 > STX_STATIC_WORK_BYTES is refused with STX_ERR_STATIC_LIMIT before
- * anything is launched (at dim 128: up to 65,536 rows).  All calls on one GPU share the array, from every
- * context and thread: calls that overlap in time on one GPU race on it; calls on one stream do not.  Nothing
- * in it needs clearing between calls: every element a call reads it has written before.                  */
+ * anything is launched (at dim 128: up to 65,536 rows).                                                  */
 #define STX_STATIC_WORK_BYTES (96u << 20)
 stx_status stx_spmm_semiring_t_static(stx_ctx *ctx, const stx_incidence *inc, const stx_params *p, int32_t kind,
                                       const float *gz, stx_grads *g);

@@ -34,6 +34,7 @@
 #include "stx_forward_body.h"
 #include "stx_rowops.h"
 #include "stx_segw_body.h"
+#include "stx_semiring_ops.h"
 #include "stx_sort_body.h"
 #include "stx_transr_dm_body.h"
 
@@ -140,6 +141,16 @@ struct SegSecond {
     int fused_mode;            // ... in this mode
 };
 
+// Entries whose source row is not stored but formed where it is summed (template parameter SRC of k_seg_reduce).
+// SRC_SEMIRING + kind: dL/dZ row and the rows of the entry's two other columns (semiring_term).  Storing the three
+// terms of every matrix row for the product to read took a launch and ten row transfers per matrix row where this takes
+// nine: 47 + 6 us at 65,536 rows of 128 floats (ComplEx) as two kernels and the fix-up.
+enum { SRC_STORED = 0, SRC_SEMIRING = 1 };
+struct SrcArgs {
+    const int32_t *colidx;     // A's column ids, three per row
+    const float *X, *G;        // table and per-row rows, d4 float4 each
+};
+
 // table row <- x - lr * g, each product and difference rounded once, as in k_sgd_rows.
 template <int LPR, int ITERS>
 __device__ inline void apply_update(float *__restrict__ row, int d4, int lig, const Acc<ITERS> &x, const Acc<ITERS> &g,
@@ -193,17 +204,18 @@ __device__ inline void apply_update(float *__restrict__ row, int d4, int lig, co
 // first scatter pass of the next batch's sort comes along; 4 as 2, and that kernel counts the rows per relation;
 // 5 as 3, and TransR's dL/dM_r product comes along (its 128 registers still leave four workgroups on a CU, more
 // than such a batch gives this product).
-template <int LPR, int ITERS, bool PACKED, int CHUNK, bool FUSED, int RIDE>
+template <int LPR, int ITERS, bool PACKED, int CHUNK, bool FUSED, int RIDE, int SRC = SRC_STORED>
 __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && FUSED && RIDE != 4) ? 8 : 1) void k_seg_reduce(const int32_t *__restrict__ packed,
                                                          const int32_t *__restrict__ seg_id, int32_t e_begin,
                                                          int32_t e_end, const float *__restrict__ src_a,
                                                          const float *__restrict__ src_b, int32_t split,
-                                                         int ld_src, int tail_off, int d4, float *__restrict__ out_rows,
+                                                         int ld_src, int d4, float *__restrict__ out_rows,
                                                          int ld_out, float *__restrict__ partials, FusedArgs fu,
                                                          SegSecond sec, SegWriteRide sw, EmitAhead ea,
-                                                         ScatterAhead sca, DmRide dm)
+                                                         ScatterAhead sca, DmRide dm, SrcArgs sr = SrcArgs{})
 {
     constexpr bool RAW = RIDE != 0;
+    static_assert(SRC == SRC_STORED || (!RAW && !PACKED && ITERS == 1 && !FUSED), "formed rows: the plain product");
     // One block of LDS for whichever part a workgroup plays (the parts' own arrays would add up and cost the
     // launch wavefronts per CU): the product's arrays below, or those of a body that rides.
     constexpr int GROUPS_ = kThreads / LPR, ROWF_ = ITERS * LPR * 4;
@@ -269,7 +281,8 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
         const int c4 = (int)blockIdx.y * LPR;
         d4 = min(LPR, d4 - c4);
         if (PACKED) pk_off = c4;
-        else { src_a += 4 * c4; src_b += 4 * c4; }
+        else if (SRC == SRC_STORED) { src_a += 4 * c4; src_b += 4 * c4; }
+        else { sr.X += 4 * c4; sr.G += 4 * c4; }
         if (out_rows) out_rows += 4 * c4;
         partials += 4 * c4;
         if (fu.table) fu.table += 4 * c4;
@@ -278,7 +291,7 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
     constexpr int GROUPS = kThreads / LPR;
     // rows in flight per lane: dense rows cost 4*ITERS registers each; packed rows are a byte and a float,
     // so a whole chunk is fetched at once and the kernel pays one memory latency per chunk
-    constexpr int UNROLL = PACKED ? (FUSED ? 4 : (CHUNK < 8 ? CHUNK : 8)) : (ITERS == 1 ? (FUSED ? 4 : 8) : (ITERS == 2 ? 4 : 2));
+    constexpr int UNROLL = SRC != SRC_STORED ? 4 : PACKED ? (FUSED ? 4 : (CHUNK < 8 ? CHUNK : 8)) : (ITERS == 1 ? (FUSED ? 4 : 8) : (ITERS == 2 ? 4 : 2));
     constexpr int TILE = GROUPS * CHUNK;    // sorted entries per workgroup
     static_assert(CHUNK <= LPR && CHUNK % UNROLL == 0, "one entry per lane per chunk");
     constexpr int VROWS = PACKED ? 1 : UNROLL;
@@ -317,6 +330,16 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
             if (FUSED && lig < CHUNK && ec0 + lig < ec1)
                 colv = fu.cols_sorted ? fu.cols_sorted[ec0 + lig] : fu.touched_cols[seg_id[ec0 + lig]];
             if (ec1 < e_end) right_head = (packed[ec1] & 2) != 0;
+        }
+        int32_t o1 = 0, o2 = 0;                            // SRC: the other two columns of this lane's entry's row
+        if constexpr (SRC != SRC_STORED) {
+            if (lig < CHUNK && ec0 + lig < ec1) {
+                const int32_t *cx = sr.colidx + 3 * (int64_t)((uint32_t)meta >> 2);
+                const int32_t c0 = cx[0], c1 = cx[1], c2 = cx[2];
+                const bool rel = ec0 + lig >= split;
+                o1 = (meta & 1) || rel ? c0 : c1;
+                o2 = (meta & 1) ? c1 : c2;
+            }
         }
         Acc<ITERS> xcur;                                   // FUSED: table row of the run that is being summed
         int32_t colcur = 0;
@@ -359,6 +382,7 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
 
         for (int j0 = 0; j0 < n; j0 += UNROLL) {
             Acc<ITERS> v[VROWS];
+            Acc<ITERS> va[SRC != SRC_STORED ? UNROLL : 1], vb[SRC != SRC_STORED ? UNROLL : 1];
             Acc<ITERS> xr[FUSED ? UNROLL : 1];
             int32_t mu[UNROLL], cu[UNROLL];
             uint8_t sb[UNROLL][ITERS];
@@ -389,10 +413,14 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
                         sb[u][it] = j < d4 ? pb[it * LPR] : (uint8_t)0;
                     }
                     cf[u] = src_b[row];
+                } else if constexpr (SRC != SRC_STORED) {
+                    const int32_t c1 = __shfl(o1, (j0 + u) & (LPR - 1), LPR), c2 = __shfl(o2, (j0 + u) & (LPR - 1), LPR);
+                    load_row_stream<LPR, ITERS>(sr.G + (uint64_t)row * (uint32_t)ld_tab, d4, lig, v[u]);
+                    load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c1 * (uint32_t)ld_tab, d4, lig, va[u]);
+                    if (SRC != SRC_SEMIRING + SR_ROTATE)
+                        load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c2 * (uint32_t)ld_tab, d4, lig, vb[u]);
                 } else {   // entries before `split` read src_a, the rest src_b (entity vs relation columns)
-                    // (tail_off: where the rows that tail entries read sit, relative to the head entries' rows)
-                    load_row<LPR, ITERS>((ec0 + j0 + u < split ? src_a : src_b) + (uint64_t)row * (uint32_t)ld_src + ((mu[u] & 1) ? tail_off : 0),
-                                         d4, lig, v[u]);
+                    load_row<LPR, ITERS>((ec0 + j0 + u < split ? src_a : src_b) + (uint64_t)row * (uint32_t)ld_src, d4, lig, v[u]);
                 }
             }
 #pragma unroll
@@ -419,6 +447,10 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
                             acc.v[it].z = __builtin_fmaf(c, (float)((int)(b << 26) >> 30), acc.v[it].z);
                             acc.v[it].w = __builtin_fmaf(c, (float)((int)(b << 24) >> 30), acc.v[it].w);
                         }
+                    } else if constexpr (SRC != SRC_STORED) {
+                        Acc<ITERS> tm;
+                        tm.v[0] = semiring_term<SRC - SRC_SEMIRING>(v[u].v[0], va[u].v[0], vb[u].v[0], (mu[u] & 1) != 0);
+                        acc.add(tm);
                     } else {
                         Acc<ITERS> &vu = v[u];
                         if (mu[u] & 1) {
@@ -732,7 +764,7 @@ __global__ __launch_bounds__(kThreads) void k_sgd_rows(const int32_t *__restrict
 template <int LPR, int ITERS>
 static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_t e_end, const float *src_a,
                    const float *src_b, int32_t split, int ld_src, int width, float *out_rows, int ld_out,
-                   bool packed_src, const FusedArgs *fused, const SegSecondHost *second, int tail_off)
+                   bool packed_src, const FusedArgs *fused, const SegSecondHost *second)
 {
     // Entries per lane group: short chunks shorten every group's serial walk when the whole product is
     // small (latency bound); long ones mean fewer partial rows when it is large (bandwidth bound).
@@ -808,7 +840,7 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
             ProfScope prof(c, "k_seg_reduce");                                                                  \
             hipLaunchKernelGGL((k_seg_reduce<LPR, 1, P, CH, F, 0>), grid, dim3(kThreads), 0, c->stream,         \
                                inc->at_packed, inc->at_seg_id, e_begin, e_end, src_a, src_b, split, ld_src,     \
-                               tail_off, width / 4, out_rows, ld_out, c->partials, fu, sec, no_segw, r_emit,    \
+                               width / 4, out_rows, ld_out, c->partials, fu, sec, no_segw, r_emit,    \
                                r_scat, r_dm);                                                                   \
         }                                                                                                       \
         if (ntiles > 1) {                                                                                       \
@@ -828,7 +860,7 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
 #define STX_SEG_R(P, CH, F, R)                                                                                  \
     hipLaunchKernelGGL((k_seg_reduce<LPR, ITERS, P, CH, F, (F && ITERS == 1 && !(R == 5 && (P || LPR > 32))) ? R : 0>), \
                        dim3(ntiles + segw_blocks + r_blocks), dim3(kThreads), 0, c->stream, segw.args.pay,      \
-                       segw.args.keys, e_begin, e_end, src_a, src_b, split, ld_src, tail_off, width / 4,        \
+                       segw.args.keys, e_begin, e_end, src_a, src_b, split, ld_src, width / 4,        \
                        out_rows, ld_out, c->partials, fu, sec, segw, r_emit, r_scat, r_dm)
 #define STX_SEG_F(CH, F, R)                                                                                     \
     hipLaunchKernelGGL((k_seg_fixup<LPR, ITERS, CH, F, (F && ITERS == 1 && !(R == 3 && LPR > 32)) ? R : 0>), dim3(ntiles + f_blocks), \
@@ -846,7 +878,7 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
             else                                                                                                \
                 hipLaunchKernelGGL((k_seg_reduce<LPR, ITERS, P, CH, F, 0>), dim3(ntiles), dim3(kThreads), 0,    \
                                    c->stream, inc->at_packed, inc->at_seg_id, e_begin, e_end, src_a, src_b,     \
-                                   split, ld_src, tail_off, width / 4, out_rows, ld_out, c->partials, fu, sec,  \
+                                   split, ld_src, width / 4, out_rows, ld_out, c->partials, fu, sec,  \
                                    no_segw, r_emit, r_scat, r_dm);                                              \
         }                                                                                                       \
         if (ntiles > 1) {                                                                                       \
@@ -887,7 +919,7 @@ static void sgd_go(stx_ctx *c, const stx_incidence *inc, const SgdTables &T, con
 stx_status launch_seg_reduce(stx_ctx *c, const stx_incidence *inc, int64_t e_begin, int64_t e_end,
                              const float *src_a, const float *src_b, int64_t split, int ld_src, int width,
                              float *out_rows, int ld_out, bool packed_src, const SegFusedHost *fh,
-                             const SegSecondHost *second, int tail_off)
+                             const SegSecondHost *second)
 {
     if (e_end <= e_begin) return STX_OK;
     Launch L = row_launch(width);
@@ -897,7 +929,54 @@ stx_status launch_seg_reduce(stx_ctx *c, const stx_incidence *inc, int64_t e_beg
     if (fh) { fu.table = fh->table; fu.table_b = fh->table_b; fu.n_split = fh->n_split; fu.lr = fh->lr; fu.mode = fh->mode; }
     const FusedArgs *fused = fh ? &fu : nullptr;
     STX_DISPATCH_ROW(L, seg_go, c, inc, (int32_t)e_begin, (int32_t)e_end, src_a, src_b, (int32_t)split, ld_src, width,
-                     out_rows, ld_out, packed_src, fused, second, packed_src ? 0 : tail_off);
+                     out_rows, ld_out, packed_src, fused, second);
+    return hip_ok(hipGetLastError());
+}
+
+template <int LPR, int ITERS>
+static void semiring_t_go(stx_ctx *c, const stx_incidence *inc, const float *X, int kind, const float *gz, float *out_rows)
+{
+    constexpr int CH_LONG = LPR == 64 ? 64 : (LPR < 32 ? LPR : 32), CH_SHORT = LPR < 16 ? LPR : 16;
+    constexpr int GROUPS = kThreads / LPR;
+    const int32_t nnz = (int32_t)inc->nnz;
+    const bool small = nnz <= (1 << 20);
+    const int tile = GROUPS * (small ? CH_SHORT : CH_LONG), ntiles = (nnz + tile - 1) / tile;
+    const dim3 grid((unsigned)ntiles, (unsigned)ITERS);    // wide rows: column slices of one float4 per lane
+    const int d4 = c->cfg.dim / 4;
+    const FusedArgs fu{};
+    const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
+    const SrcArgs sr{inc->a_colidx, X, gz};
+#define STX_SR_T(K, CH)                                                                                         \
+    hipLaunchKernelGGL((k_seg_reduce<LPR, 1, false, CH, false, 0, SRC_SEMIRING + K>), grid, dim3(kThreads), 0,  \
+                       c->stream, inc->at_packed, inc->at_seg_id, 0, nnz, nullptr, nullptr,                     \
+                       (int32_t)(2 * inc->n_rows), 0, d4, out_rows, c->ld, c->partials, fu, sec,             \
+                       SegWriteRide{}, EmitAhead{}, ScatterAhead{}, DmRide{}, sr)
+#define STX_SR_T2(K) do { if (small) STX_SR_T(K, CH_SHORT); else STX_SR_T(K, CH_LONG); } while (0)
+    {
+        ProfScope prof(c, "k_seg_reduce");
+        if (kind == SR_DISTMULT) STX_SR_T2(SR_DISTMULT);
+        else if (kind == SR_COMPLEX) STX_SR_T2(SR_COMPLEX);
+        else STX_SR_T2(SR_ROTATE);
+    }
+#undef STX_SR_T2
+#undef STX_SR_T
+    if (ntiles <= 1) return;
+    ProfScope prof(c, "k_seg_fixup");
+#define STX_SR_F(CH)                                                                                            \
+    hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, false, 0>), grid, dim3(kThreads), 0, c->stream, inc->at_packed, \
+                       inc->at_seg_id, inc->at_seg_ptr, 0, nnz, d4, out_rows, c->ld, c->partials, fu, sec,      \
+                       ScatterAhead{}, HistAhead{}, DmRide{}, EmitAhead{})
+    if (small) STX_SR_F(CH_SHORT);
+    else STX_SR_F(CH_LONG);
+#undef STX_SR_F
+}
+
+stx_status launch_semiring_t(stx_ctx *c, const stx_incidence *inc, const stx_params *p, int kind, const float *gz,
+                             float *out_rows)
+{
+    if (inc->n_rows == 0) return STX_OK;
+    Launch L = row_launch(c->cfg.dim);
+    STX_DISPATCH_ROW(L, semiring_t_go, c, inc, p->ent, kind, gz, out_rows);
     return hip_ok(hipGetLastError());
 }
 

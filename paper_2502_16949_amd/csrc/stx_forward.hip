@@ -50,7 +50,7 @@ __global__ __launch_bounds__(kThreads, ITERS == 1 ? 8 : 1) void k_forward_stacke
 // (rows of one float4 per lane: 64 registers, every workgroup of a large batch resident at once; wider rows hold
 // four rows of ITERS float4 per lane)
 template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE>
-__global__ __launch_bounds__(kThreads, ITERS == 1 ? (NB > 4 ? 4 : 8) : ITERS == 2 ? (NB > 1 ? 3 : 4) : 2) void k_forward_fast(ForwardArgs a, int32_t *general_flag,
+__global__ __launch_bounds__(kThreads, ITERS == 1 ? (NB == 1 || (PACKED && !MORE) ? 8 : PACKED ? 6 : 5) : ITERS == 2 ? (NB > 1 ? 3 : 4) : 2) void k_forward_fast(ForwardArgs a, int32_t *general_flag,
                                                                                                  int32_t serial)
 {
     forward_fast_body<LPR, ITERS, DIST, PACKED, NB, MORE>((int)blockIdx.x, a, general_flag, serial);
@@ -169,13 +169,13 @@ static void forward_go(stx_ctx *c, const stx_incidence *inc, const stx_params *p
 #define STX_FAST(D, P)                                                                                          \
     do {                                                                                                        \
         if (inc->k <= 1)                                                                                        \
-            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, true, false), false>), grid, dim3(kThreads), 0, \
+            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, true), false>), grid, dim3(kThreads), 0, \
                                c->stream, fa, flag, serial);                                                    \
         else if (inc->k <= 4)                                                                                   \
-            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, false, false), (ITERS > 2)>), grid, dim3(kThreads), 0, \
+            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, false), (ITERS > 2)>), grid, dim3(kThreads), 0, \
                                c->stream, fa, flag, serial);                                                    \
         else                                                                                                    \
-            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, false, true), true>), grid, dim3(kThreads), 0, \
+            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, false), true>), grid, dim3(kThreads), 0, \
                                c->stream, fa, flag, serial);                                                    \
     } while (0)
 #define STX_FWD2(D)                                                                                             \

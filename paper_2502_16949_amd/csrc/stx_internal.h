@@ -334,7 +334,6 @@ stx_status launch_read_sectors(stx_ctx *, const void *src, int64_t n_slots, int 
 // and src_b the rows' coefficients.
 // second: another product of the same row width over the entries [e_begin, e_end), all reading `src`, that
 // runs in the same two launches (its workgroups follow the first product's).
-// tail_off (dense source rows only): entries with value -1 read their row tail_off floats further on.
 // fused: no gradient row is written; the table row of the column (rows of `width` floats; `table` for
 // columns below n_split, row column - n_split of `table_b` for the others) becomes row - lr * gradient
 // instead (mode 1: then its fractional part; mode 2: then rescaled to unit length).  The second
@@ -355,13 +354,15 @@ struct SegFusedHost {
 stx_status launch_seg_reduce(stx_ctx *, const stx_incidence *, int64_t e_begin, int64_t e_end, const float *src_a,
                              const float *src_b, int64_t split, int ld_src, int width, float *out_rows, int ld_out,
                              bool packed_src = false, const SegFusedHost *fused = nullptr,
-                             const SegSecondHost *second = nullptr, int tail_off = 0);
+                             const SegSecondHost *second = nullptr);
 struct SgdTables {
     float *table_a; int width_a; int mode_a;   // columns [0, n_split)
     int64_t n_split;
     float *table_b; int width_b;               // columns >= n_split, gradient in the same rows array (may be null)
     float *table_w; int mode_w;                // columns >= n_split, gradient in w_rows, width_a (may be null)
 };
+// the backward of a semiring product: every entry's term formed where it is summed
+stx_status launch_semiring_t(stx_ctx *, const stx_incidence *, const stx_params *, int kind, const float *gz, float *out_rows);
 stx_status launch_sgd_rows(stx_ctx *, const stx_incidence *, const SgdTables &, const float *grad_rows,
                            const float *w_rows, float lr);
 stx_status launch_forward_from_y(stx_ctx *, const stx_incidence *, const stx_params *, float *scores, float *loss);
@@ -371,10 +372,6 @@ stx_status launch_rank(stx_ctx *, const stx_params *, const int32_t *h, const in
 size_t rank_work_bytes(const stx_ctx *, int64_t nq);   // scratch launch_rank needs for nq queries (0 unless TransR)
 // stx_semiring.hip
 stx_status launch_semiring(stx_ctx *, const stx_incidence *, const stx_params *, int kind, float *z_out);
-stx_status launch_semiring_t(stx_ctx *, const stx_incidence *, const stx_params *, int kind, const float *gz,
-                             float *work, float *out_rows);
-// device address, on the current GPU, of the library's fixed scratch array of STX_STATIC_WORK_BYTES bytes
-stx_status static_work(float **out);
 // stx_transr.hip
 stx_status launch_transr_project(stx_ctx *, const stx_incidence *, const stx_params *);
 // the forward pass, dL/dy, dL/dx and the tiles of the dM product in one kernel, for the shapes transr_fused_ok names
