@@ -555,6 +555,14 @@ static stx_status run_backward(stx_ctx *ctx, const stx_incidence *inc, const stx
     float *rows = lr ? nullptr : g->rows;
     if (stacked(ctx)) {   // dL/dX = A^T G over all columns of X = [E;R] (Appendix G)
         const bool pk = packed_grad(ctx);
+        if (inc->n_rows > 0 && formed_rows(ctx, inc->n_rows)) {   // the rows of dL/dx were not stored: formed again here
+            float *out = lr ? formed_buffers(ctx, inc->n_rows).grads : g->rows;
+            const stx_status s = launch_seg_formed(ctx, inc, p, out, ctx->ld);
+            if (s != STX_OK || !lr) return s;
+            const SgdTables T{p->ent, dim, ctx->cfg.model == STX_TORUSE ? 1 : 0, ctx->cfg.n_ent + ctx->cfg.n_rel, nullptr,
+                              dim, nullptr, 0};
+            return launch_sgd_rows(ctx, inc, T, out, nullptr, *lr);
+        }
         const SegFusedHost fh{p->ent, nullptr, 0x7fffffff, lr ? *lr : 0.f, ctx->cfg.model == STX_TORUSE ? 1 : 0};
         const float *coefs = pk ? reinterpret_cast<const float *>(reinterpret_cast<const char *>(ctx->gbuf[0]) +
                                                                   packed_coef_offset(inc->n_rows, packed_stride(dim)))
@@ -671,7 +679,8 @@ stx_status stx_train_step(stx_ctx *ctx, const stx_batch *bt, stx_incidence *inc,
     StepFusion fusion{p, scores, loss, false, false, 0, 1.0f, b > 0 ? bt->next : nullptr, nullptr};
     // the fused transposed product of one float4 per lane can run the build's last kernel in its own launch
     // (TransR: when its work items come from the rows-per-relation counts, not from the segment lists)
-    ctx->segw.allowed = (ctx->cfg.model != STX_TRANSR || ctx->rel_cnt[0] != nullptr) && row_launch(ctx->cfg.dim).iters == 1;
+    ctx->segw.allowed = (ctx->cfg.model != STX_TRANSR || ctx->rel_cnt[0] != nullptr) && row_launch(ctx->cfg.dim).iters == 1 &&
+                        !formed_rows(ctx, inc->n_rows);
     s = launch_build(ctx, bt->h, bt->r, bt->t, nullptr, nullptr, b, k, inc, &sa, &fusion);
     ctx->segw.allowed = false;
     // a stage of the next build that no launch took along: the buffers go back to their roles

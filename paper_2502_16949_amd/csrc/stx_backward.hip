@@ -145,11 +145,31 @@ struct SegSecond {
 // SRC_SEMIRING + kind: dL/dZ row and the rows of the entry's two other columns (semiring_term).  Storing the three
 // terms of every matrix row for the product to read took a launch and ten row transfers per matrix row where this takes
 // nine: 47 + 6 us at 65,536 rows of 128 floats (ComplEx) as two kernels and the fix-up.
-enum { SRC_STORED = 0, SRC_SEMIRING = 1 };
+// SRC_DIFF + distance kind (formed_rows): x of the row, from the table rows of the entry's own column and the row's other
+// two, times the row's coefficient through the distance's derivative.  In 64-float slices, one after the other
+// (blockIdx.y), so that the slice of the table all workgroups read at a time stays in the L2 caches; columns and
+// coefficient come as one 16-byte record per sorted entry (k_seg_records).
+enum { SRC_STORED = 0, SRC_SEMIRING = 1, SRC_DIFF = 8 };
 struct SrcArgs {
-    const int32_t *colidx;     // A's column ids, three per row
-    const float *X, *G;        // table and per-row rows, d4 float4 each
+    const int32_t *colidx;     // semiring: A's column ids, three per row
+    const float *X, *G;        // table and (semiring) per-row rows, d4 float4 each
+    const int4 *recs;          // formed rows: sorted records
 };
+
+// recs[e] = (column of sorted entry e, the other two columns of its row in row order, the row's coefficient).
+__global__ __launch_bounds__(kThreads) void k_seg_records(const int32_t *__restrict__ packed, const int32_t *__restrict__ colidx,
+                                                          const float *__restrict__ coefs, int32_t nnz, int32_t split,
+                                                          int4 *__restrict__ recs)
+{
+    const int32_t e = (int32_t)blockIdx.x * kThreads + threadIdx.x;
+    if (e >= nnz) return;
+    const int32_t m = packed[e];
+    const uint32_t row = (uint32_t)m >> 2;
+    const int32_t *cx = colidx + 3 * (int64_t)row;
+    const int32_t c0 = cx[0], c1 = cx[1], c2 = cx[2];
+    const bool tail = m & 1, rel = e >= split;
+    recs[e] = make_int4(tail ? c2 : rel ? c1 : c0, tail || rel ? c0 : c1, tail ? c1 : c2, __float_as_int(coefs[row]));
+}
 
 // table row <- x - lr * g, each product and difference rounded once, as in k_sgd_rows.
 template <int LPR, int ITERS>
@@ -216,6 +236,7 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
 {
     constexpr bool RAW = RIDE != 0;
     static_assert(SRC == SRC_STORED || (!RAW && !PACKED && ITERS == 1 && !FUSED), "formed rows: the plain product");
+    constexpr bool DIFF = SRC >= SRC_DIFF, SEMI = SRC != SRC_STORED && !DIFF;
     // One block of LDS for whichever part a workgroup plays (the parts' own arrays would add up and cost the
     // launch wavefronts per CU): the product's arrays below, or those of a body that rides.
     constexpr int GROUPS_ = kThreads / LPR, ROWF_ = ITERS * LPR * 4;
@@ -282,7 +303,7 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
         d4 = min(LPR, d4 - c4);
         if (PACKED) pk_off = c4;
         else if (SRC == SRC_STORED) { src_a += 4 * c4; src_b += 4 * c4; }
-        else { sr.X += 4 * c4; sr.G += 4 * c4; }
+        else { sr.X += 4 * c4; if (SEMI) sr.G += 4 * c4; }
         if (out_rows) out_rows += 4 * c4;
         partials += 4 * c4;
         if (fu.table) fu.table += 4 * c4;
@@ -332,7 +353,15 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
             if (ec1 < e_end) right_head = (packed[ec1] & 2) != 0;
         }
         int32_t o1 = 0, o2 = 0;                            // SRC: the other two columns of this lane's entry's row
-        if constexpr (SRC != SRC_STORED) {
+        int32_t own = 0;                                   // DIFF: its column and its row's coefficient
+        float cs = 0.f;
+        if constexpr (DIFF) {
+            if (lig < CHUNK && ec0 + lig < ec1) {
+                const int4 rc = sr.recs[ec0 + lig];
+                own = rc.x; o1 = rc.y; o2 = rc.z; cs = __int_as_float(rc.w);
+            }
+        }
+        if constexpr (SEMI) {
             if (lig < CHUNK && ec0 + lig < ec1) {
                 const int32_t *cx = sr.colidx + 3 * (int64_t)((uint32_t)meta >> 2);
                 const int32_t c0 = cx[0], c1 = cx[1], c2 = cx[2];
@@ -413,7 +442,18 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
                         sb[u][it] = j < d4 ? pb[it * LPR] : (uint8_t)0;
                     }
                     cf[u] = src_b[row];
-                } else if constexpr (SRC != SRC_STORED) {
+                } else if constexpr (DIFF) {
+                    const int src = (j0 + u) & (LPR - 1);
+                    const int32_t c1 = __shfl(o1, src, LPR), c2 = __shfl(o2, src, LPR);
+                    cf[u] = __shfl(cs, src, LPR);
+                    const int32_t c0 = __shfl(own, src, LPR);
+                    if ((mu[u] & 2) || j0 + u == 0)        // a run begins (or goes on) here: its column's own row
+                        load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c0 * (uint32_t)ld_tab, d4, lig, v[u]);
+                    if (cf[u] != 0.f) {                    // (a row of inactive pairs adds nothing)
+                        load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c1 * (uint32_t)ld_tab, d4, lig, va[u]);
+                        load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c2 * (uint32_t)ld_tab, d4, lig, vb[u]);
+                    }
+                } else if constexpr (SEMI) {
                     const int32_t c1 = __shfl(o1, (j0 + u) & (LPR - 1), LPR), c2 = __shfl(o2, (j0 + u) & (LPR - 1), LPR);
                     load_row_stream<LPR, ITERS>(sr.G + (uint64_t)row * (uint32_t)ld_tab, d4, lig, v[u]);
                     load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c1 * (uint32_t)ld_tab, d4, lig, va[u]);
@@ -447,7 +487,20 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
                             acc.v[it].z = __builtin_fmaf(c, (float)((int)(b << 26) >> 30), acc.v[it].z);
                             acc.v[it].w = __builtin_fmaf(c, (float)((int)(b << 24) >> 30), acc.v[it].w);
                         }
-                    } else if constexpr (SRC != SRC_STORED) {
+                    } else if constexpr (DIFF) {
+                        // x = (h + r) - t, rounded as the forward pass rounds it (a sum has the same bits either way
+                        // round); then the derivative times the coefficient, as write_grad_row would have stored it
+                        if ((mu[u] & 2) || jj == 0) xcur = v[u];
+                        if (cf[u] != 0.f) {
+                            const bool tail = mu[u] & 1;
+                            const float4 x = tail ? sub4(add4(va[u].v[0], vb[u].v[0]), xcur.v[0])
+                                                  : sub4(add4(xcur.v[0], va[u].v[0]), vb[u].v[0]);
+                            const float c = cf[u];
+                            constexpr int DIST = DIFF ? SRC - SRC_DIFF : 0;
+                            const float4 g = make_float4(dterm<DIST>(x.x, c), dterm<DIST>(x.y, c), dterm<DIST>(x.z, c), dterm<DIST>(x.w, c));
+                            acc.v[0] = tail ? sub4(acc.v[0], g) : add4(acc.v[0], g);
+                        }
+                    } else if constexpr (SEMI) {
                         Acc<ITERS> tm;
                         tm.v[0] = semiring_term<SRC - SRC_SEMIRING>(v[u].v[0], va[u].v[0], vb[u].v[0], (mu[u] & 1) != 0);
                         acc.add(tm);
@@ -945,7 +998,7 @@ static void semiring_t_go(stx_ctx *c, const stx_incidence *inc, const float *X, 
     const int d4 = c->cfg.dim / 4;
     const FusedArgs fu{};
     const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
-    const SrcArgs sr{inc->a_colidx, X, gz};
+    const SrcArgs sr{inc->a_colidx, X, gz, nullptr};
 #define STX_SR_T(K, CH)                                                                                         \
     hipLaunchKernelGGL((k_seg_reduce<LPR, 1, false, CH, false, 0, SRC_SEMIRING + K>), grid, dim3(kThreads), 0,  \
                        c->stream, inc->at_packed, inc->at_seg_id, 0, nnz, nullptr, nullptr,                     \
@@ -969,6 +1022,42 @@ static void semiring_t_go(stx_ctx *c, const stx_incidence *inc, const float *X, 
     if (small) STX_SR_F(CH_SHORT);
     else STX_SR_F(CH_LONG);
 #undef STX_SR_F
+}
+
+stx_status launch_seg_formed(stx_ctx *c, const stx_incidence *inc, const stx_params *p, float *out_rows, int ld_out)
+{
+    constexpr int LPR = 16, CH = 16, TILE = kThreads / LPR * CH;
+    const int32_t nnz = (int32_t)inc->nnz, split = (int32_t)(2 * inc->n_rows);
+    const FormedRows fr = formed_buffers(c, inc->n_rows);
+    {
+        ProfScope prof(c, "k_seg_records");
+        hipLaunchKernelGGL(k_seg_records, dim3((unsigned)((nnz + kThreads - 1) / kThreads)), dim3(kThreads), 0, c->stream,
+                           inc->at_packed, inc->a_colidx, fr.coefs, nnz, split, fr.recs);
+    }
+    const int d4 = c->cfg.dim / 4, ntiles = (nnz + TILE - 1) / TILE;
+    const dim3 grid((unsigned)ntiles, (unsigned)((d4 + LPR - 1) / LPR));
+    const FusedArgs fu{};
+    const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
+    const SrcArgs sr{nullptr, p->ent, nullptr, fr.recs};
+#define STX_FORMED(D)                                                                                           \
+    hipLaunchKernelGGL((k_seg_reduce<LPR, 1, false, CH, false, 0, SRC_DIFF + D>), grid, dim3(kThreads), 0,      \
+                       c->stream, inc->at_packed, inc->at_seg_id, 0, nnz, nullptr, nullptr, split, 0, d4,       \
+                       out_rows, ld_out, c->partials, fu, sec, SegWriteRide{}, EmitAhead{}, ScatterAhead{},     \
+                       DmRide{}, sr)
+    {
+        ProfScope prof(c, "k_seg_reduce");
+        if (c->cfg.dist == STX_L2) STX_FORMED(STX_L2);
+        else if (c->cfg.dist == STX_L2_SQ) STX_FORMED(STX_L2_SQ);
+        else STX_FORMED(STX_TORUS_L2);
+    }
+#undef STX_FORMED
+    if (ntiles > 1) {
+        ProfScope prof(c, "k_seg_fixup");
+        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, false, 0>), grid, dim3(kThreads), 0, c->stream, inc->at_packed,
+                           inc->at_seg_id, inc->at_seg_ptr, 0, nnz, d4, out_rows, ld_out, c->partials, fu, sec,
+                           ScatterAhead{}, HistAhead{}, DmRide{}, EmitAhead{});
+    }
+    return hip_ok(hipGetLastError());
 }
 
 stx_status launch_semiring_t(stx_ctx *c, const stx_incidence *inc, const stx_params *p, int kind, const float *gz,

@@ -166,13 +166,17 @@ __device__ inline void forward_fast_body(const int block, const ForwardArgs &a, 
                     if (active) { hinge_sum += arg; ++n_active; }
                     if (PACKED)
                         write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, row, d4, lig, x, active ? -a.scale * wr : 0.f);
-                    else
+                    else if (a.coefs) {
+                        if (lig == 0) a.coefs[row] = coef_scale<DIST>(active ? -a.scale * wr : 0.f, nneg);
+                    } else
                         write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)row * dim, d4, lig, x, active ? -a.scale * wr : 0.f, nneg);
                 }
         }
         if (PACKED)
             write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, i, d4, lig, xp, (float)n_active * a.scale * wr);
-        else
+        else if (a.coefs) {
+            if (lig == 0) a.coefs[i] = coef_scale<DIST>((float)n_active * a.scale * wr, npos);
+        } else
             write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)i * dim, d4, lig, xp, (float)n_active * a.scale * wr, npos);
         if (!shared && lig == 0 && general_flag) *general_flag = serial;
     }
@@ -270,7 +274,9 @@ __device__ inline void forward_stacked_body(const int block, const ForwardArgs &
                     if (PACKED)
                         write_grad_row_packed<LPR, ITERS, DIST>(reinterpret_cast<uint8_t *>(G), gstride, gcoef, row, d4,
                                                                 lig, xn[q], active ? -scale * wr : 0.f);
-                    else
+                    else if (!FROM_Y && a.coefs) {
+                        if (lig == 0) a.coefs[row] = coef_scale<DIST>(active ? -scale * wr : 0.f, nneg);
+                    } else
                         write_grad_row<LPR, ITERS, DIST>(G + row * dim, d4, lig, xn[q], active ? -scale * wr : 0.f,
                                                          nneg);
                 }
@@ -279,7 +285,9 @@ __device__ inline void forward_stacked_body(const int block, const ForwardArgs &
         if (PACKED)
             write_grad_row_packed<LPR, ITERS, DIST>(reinterpret_cast<uint8_t *>(G), gstride, gcoef, i, d4, lig, xp,
                                                     (float)n_active * scale * wr);
-        else
+        else if (!FROM_Y && a.coefs) {
+            if (lig == 0) a.coefs[i] = coef_scale<DIST>((float)n_active * scale * wr, npos);
+        } else
             write_grad_row<LPR, ITERS, DIST>(G + i * dim, d4, lig, xp, (float)n_active * scale * wr, npos);
     }
     if (lig == 0) s_loss[grp] = hinge_sum;

@@ -258,6 +258,7 @@ struct ForwardArgs {
     const float *rel_weight;   // fixed weight of every relation's distance, or null (gathered rows only)
     int32_t n_ent;
     int32_t stream_rows;       // the table is far larger than the caches: rows used once are fetched past them
+    float *coefs;              // dense kinds: only the rows' coefficients are stored, here (see formed_rows), or null
 };
 
 
@@ -355,6 +356,8 @@ stx_status launch_seg_reduce(stx_ctx *, const stx_incidence *, int64_t e_begin, 
                              const float *src_b, int64_t split, int ld_src, int width, float *out_rows, int ld_out,
                              bool packed_src = false, const SegFusedHost *fused = nullptr,
                              const SegSecondHost *second = nullptr);
+// TransE / TorusE with formed_rows: out_rows[segment] as launch_seg_reduce forms it, from the coefficients and the table
+stx_status launch_seg_formed(stx_ctx *, const stx_incidence *, const stx_params *, float *out_rows, int ld_out);
 struct SgdTables {
     float *table_a; int width_a; int mode_a;   // columns [0, n_split)
     int64_t n_split;
@@ -415,6 +418,31 @@ __host__ __device__ inline int64_t packed_coef_offset(int64_t rows, int stride) 
 inline int big_tables(const stx_ctx *c)
 {
     return (c->cfg.n_ent + c->cfg.n_rel) * (int64_t)c->cfg.dim * 4 > ((int64_t)128 << 20) ? 1 : 0;
+}
+
+// Dense kinds of TransE / TorusE: dL/dx of a row is its x times a coefficient (through the distance's derivative), and
+// x = h + r - t can be formed again where the transposed product sums it, from two more table rows, instead of being
+// stored by the forward pass and read three times.  That pays when the stored rows are beyond the last-level cache
+// while a 64-float slice of the whole table fits the L2 caches, slice by slice (every die's 4 MB; popular rows make
+// somewhat larger ones do).  The update cannot be fused then: other workgroups still read the rows it would replace.
+inline bool formed_rows(const stx_ctx *c, int64_t n_rows)
+{
+    const bool stacked = c->cfg.model == STX_TRANSE || c->cfg.model == STX_TORUSE;
+    const int64_t cols = c->cfg.n_ent + c->cfg.n_rel, row = (int64_t)c->cfg.dim * 4;
+    return stacked && !packed_grad(c) && cols * 256 <= ((int64_t)6 << 20) && n_rows * row >= ((int64_t)192 << 20) &&
+           // room in the buffer of those rows for what replaces them: coefficients, sorted records, gradient rows
+           n_rows * (4 + 48) + (cols + 1) * row + 1024 <= c->rows_max * row;
+}
+struct FormedRows {
+    float *coefs;              // [n_rows]
+    int4 *recs;                // [3 n_rows], per sorted entry: its column, the row's other two columns, the coefficient
+    float *grads;              // gradient rows of the touched columns, ld floats each (when the update follows at once)
+};
+inline FormedRows formed_buffers(const stx_ctx *c, int64_t n_rows)
+{
+    char *b = (char *)c->gbuf[0];
+    const int64_t o1 = (n_rows * 4 + 255) / 256 * 256, o2 = o1 + (n_rows * 48 + 255) / 256 * 256;
+    return {(float *)b, (int4 *)(b + o1), (float *)(b + o2)};
 }
 
 inline stx_status hip_ok(hipError_t e) { return e == hipSuccess ? STX_OK : STX_ERR_HIP; }
