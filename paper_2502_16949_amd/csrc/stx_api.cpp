@@ -233,6 +233,7 @@ stx_status stx_create(const stx_config *cfg, void *workspace, size_t workspace_b
     c->dm_ride = DmRideState{};
     c->step_colidx = nullptr;
     c->step_colidx_inc = nullptr;
+    c->form_rows = false;
     c->defer_finish = false;
     c->fin_n = 0;
     c->fin_scale = 1.0f;
@@ -555,7 +556,7 @@ static stx_status run_backward(stx_ctx *ctx, const stx_incidence *inc, const stx
     float *rows = lr ? nullptr : g->rows;
     if (stacked(ctx)) {   // dL/dX = A^T G over all columns of X = [E;R] (Appendix G)
         const bool pk = packed_grad(ctx);
-        if (inc->n_rows > 0 && formed_rows(ctx, inc->n_rows)) {   // the rows of dL/dx were not stored: formed again here
+        if (inc->n_rows > 0 && ctx->form_rows) {   // the rows of dL/dx were not stored: formed again here
             float *out = lr ? formed_buffers(ctx, inc->n_rows).grads : g->rows;
             const stx_status s = launch_seg_formed(ctx, inc, p, out, ctx->ld);
             if (s != STX_OK || !lr) return s;
@@ -673,6 +674,10 @@ stx_status stx_train_step(stx_ctx *ctx, const stx_batch *bt, stx_incidence *inc,
     inc->n_rows = (int64_t)b * (1 + k);
     inc->nnz = 3 * inc->n_rows;
     ctx->fwd_inc = nullptr;
+    // (only here: between the separate calls the caller may change the tables, and a gradient is that of the tables
+    // the forward pass saw)
+    ctx->form_rows = formed_rows(ctx, inc->n_rows);
+    struct Reset { bool &b; ~Reset() { b = false; } } reset{ctx->form_rows};
     SampleArgs sa{bt->neg_h, bt->neg_t, bt->seed,
                   (bt->epoch * (uint64_t)bt->m_total + (uint64_t)bt->global_offset) * (uint64_t)k};
     // (the next batch's first build kernels may ride in this step's launches: the build prepares them)
@@ -680,7 +685,7 @@ stx_status stx_train_step(stx_ctx *ctx, const stx_batch *bt, stx_incidence *inc,
     // the fused transposed product of one float4 per lane can run the build's last kernel in its own launch
     // (TransR: when its work items come from the rows-per-relation counts, not from the segment lists)
     ctx->segw.allowed = (ctx->cfg.model != STX_TRANSR || ctx->rel_cnt[0] != nullptr) && row_launch(ctx->cfg.dim).iters == 1 &&
-                        !formed_rows(ctx, inc->n_rows);
+                        !ctx->form_rows;
     s = launch_build(ctx, bt->h, bt->r, bt->t, nullptr, nullptr, b, k, inc, &sa, &fusion);
     ctx->segw.allowed = false;
     // a stage of the next build that no launch took along: the buffers go back to their roles

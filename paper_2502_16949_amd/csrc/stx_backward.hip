@@ -449,7 +449,7 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
                     const int32_t c0 = __shfl(own, src, LPR);
                     if ((mu[u] & 2) || j0 + u == 0)        // a run begins (or goes on) here: its column's own row
                         load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c0 * (uint32_t)ld_tab, d4, lig, v[u]);
-                    if (cf[u] != 0.f) {                    // (a row of inactive pairs adds nothing)
+                    if (__float_as_uint(cf[u])) {          // (+0, a row of inactive pairs, adds nothing)
                         load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c1 * (uint32_t)ld_tab, d4, lig, va[u]);
                         load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c2 * (uint32_t)ld_tab, d4, lig, vb[u]);
                     }
@@ -491,7 +491,7 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
                         // x = (h + r) - t, rounded as the forward pass rounds it (a sum has the same bits either way
                         // round); then the derivative times the coefficient, as write_grad_row would have stored it
                         if ((mu[u] & 2) || jj == 0) xcur = v[u];
-                        if (cf[u] != 0.f) {
+                        if (__float_as_uint(cf[u])) {
                             const bool tail = mu[u] & 1;
                             const float4 x = tail ? sub4(add4(va[u].v[0], vb[u].v[0]), xcur.v[0])
                                                   : sub4(add4(xcur.v[0], va[u].v[0]), vb[u].v[0]);
@@ -969,6 +969,36 @@ static void sgd_go(stx_ctx *c, const stx_incidence *inc, const SgdTables &T, con
                        T.table_b, T.width_b / 4, T.table_w, T.mode_w, grad_rows, w_rows, c->ld, lr, big_tables(c));
 }
 
+// Stored rows of a batch that stx_train_step would form (formed_rows): the tiles and slices of launch_seg_formed, so
+// that the sums have the same bits.
+static void seg_slices(stx_ctx *c, const stx_incidence *inc, const float *src, int width, float *out_rows, int ld_out,
+                       const FusedArgs *fused)
+{
+    constexpr int LPR = 16, CH = 16, TILE = kThreads / LPR * CH;
+    const int32_t nnz = (int32_t)inc->nnz;
+    const int d4 = width / 4, ntiles = (nnz + TILE - 1) / TILE;
+    const dim3 grid((unsigned)ntiles, (unsigned)((d4 + LPR - 1) / LPR));
+    const FusedArgs fu = fused ? *fused : FusedArgs{};
+    const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
+#define STX_SLICES(F)                                                                                           \
+    do {                                                                                                        \
+        {                                                                                                       \
+            ProfScope prof(c, "k_seg_reduce");                                                                  \
+            hipLaunchKernelGGL((k_seg_reduce<LPR, 1, false, CH, F, 0>), grid, dim3(kThreads), 0, c->stream,     \
+                               inc->at_packed, inc->at_seg_id, 0, nnz, src, src, nnz, width, d4, out_rows,      \
+                               ld_out, c->partials, fu, sec, SegWriteRide{}, EmitAhead{}, ScatterAhead{},       \
+                               DmRide{});                                                                       \
+        }                                                                                                       \
+        ProfScope prof(c, "k_seg_fixup");                                                                       \
+        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, F, 0>), grid, dim3(kThreads), 0, c->stream, inc->at_packed, \
+                           inc->at_seg_id, inc->at_seg_ptr, 0, nnz, d4, out_rows, ld_out, c->partials, fu, sec, \
+                           ScatterAhead{}, HistAhead{}, DmRide{}, EmitAhead{});                                 \
+    } while (0)
+    if (fused) STX_SLICES(true);
+    else STX_SLICES(false);
+#undef STX_SLICES
+}
+
 stx_status launch_seg_reduce(stx_ctx *c, const stx_incidence *inc, int64_t e_begin, int64_t e_end,
                              const float *src_a, const float *src_b, int64_t split, int ld_src, int width,
                              float *out_rows, int ld_out, bool packed_src, const SegFusedHost *fh,
@@ -981,6 +1011,10 @@ stx_status launch_seg_reduce(stx_ctx *c, const stx_incidence *inc, int64_t e_beg
                  big_tables(c)};
     if (fh) { fu.table = fh->table; fu.table_b = fh->table_b; fu.n_split = fh->n_split; fu.lr = fh->lr; fu.mode = fh->mode; }
     const FusedArgs *fused = fh ? &fu : nullptr;
+    if (formed_rows(c, inc->n_rows)) {
+        seg_slices(c, inc, src_a, width, out_rows, ld_out, fused);
+        return hip_ok(hipGetLastError());
+    }
     STX_DISPATCH_ROW(L, seg_go, c, inc, (int32_t)e_begin, (int32_t)e_end, src_a, src_b, (int32_t)split, ld_src, width,
                      out_rows, ld_out, packed_src, fused, second);
     return hip_ok(hipGetLastError());

@@ -152,7 +152,7 @@ static void forward_go(stx_ctx *c, const stx_incidence *inc, const stx_params *p
     const ForwardArgs fa{inc->a_colidx, p->ent, inc->b, inc->k, width, c->cfg.margin, scale, scores, c->gbuf[0],
                          packed_stride(c->cfg.dim), c->loss_partials, from_y ? nullptr : p->rel_weight,
                          (int32_t)c->cfg.n_ent, from_y ? 0 : big_tables(c),
-                         !from_y && formed_rows(c, inc->n_rows) ? formed_buffers(c, inc->n_rows).coefs : nullptr};
+                         !from_y && c->form_rows ? formed_buffers(c, inc->n_rows).coefs : nullptr};
     // (the next batch's first build kernel, if one is due and counts rows per relation as TransR's do)
     EmitAhead ea{};
     if (from_y && c->ahead.armed && !c->ahead.emit_done && c->ahead.args.rc.cur) ea = take_emit_ahead(c);

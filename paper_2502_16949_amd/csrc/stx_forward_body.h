@@ -35,6 +35,15 @@ __device__ inline void write_grad_row(float *__restrict__ g, int d4, int lig, co
     }
 }
 
+// The coefficient of a row that is formed again where it is summed.  +0 there means that the row adds nothing and is
+// not fetched; an inactive row with an infinity or a NaN in it keeps -0, as its stored products would be NaN.
+template <int DIST>
+__device__ inline float formed_coef(float coef, float dist)
+{
+    const float cs = coef_scale<DIST>(coef, dist);
+    return cs != 0.f ? cs : fabsf(dist) < __builtin_inff() ? 0.f : -0.f;
+}
+
 // Sum of the per-workgroup loss partials in a fixed order (one workgroup, after the forward kernel).
 // ARENA: the body's LDS array lives in the kFinishLds bytes at `lds` (8-byte aligned) instead of its own.
 template <bool ARENA = false>
@@ -167,7 +176,7 @@ __device__ inline void forward_fast_body(const int block, const ForwardArgs &a, 
                     if (PACKED)
                         write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, row, d4, lig, x, active ? -a.scale * wr : 0.f);
                     else if (a.coefs) {
-                        if (lig == 0) a.coefs[row] = coef_scale<DIST>(active ? -a.scale * wr : 0.f, nneg);
+                        if (lig == 0) a.coefs[row] = formed_coef<DIST>(active ? -a.scale * wr : 0.f, nneg);
                     } else
                         write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)row * dim, d4, lig, x, active ? -a.scale * wr : 0.f, nneg);
                 }
@@ -175,7 +184,7 @@ __device__ inline void forward_fast_body(const int block, const ForwardArgs &a, 
         if (PACKED)
             write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, i, d4, lig, xp, (float)n_active * a.scale * wr);
         else if (a.coefs) {
-            if (lig == 0) a.coefs[i] = coef_scale<DIST>((float)n_active * a.scale * wr, npos);
+            if (lig == 0) a.coefs[i] = formed_coef<DIST>((float)n_active * a.scale * wr, npos);
         } else
             write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)i * dim, d4, lig, xp, (float)n_active * a.scale * wr, npos);
         if (!shared && lig == 0 && general_flag) *general_flag = serial;
@@ -275,7 +284,7 @@ __device__ inline void forward_stacked_body(const int block, const ForwardArgs &
                         write_grad_row_packed<LPR, ITERS, DIST>(reinterpret_cast<uint8_t *>(G), gstride, gcoef, row, d4,
                                                                 lig, xn[q], active ? -scale * wr : 0.f);
                     else if (!FROM_Y && a.coefs) {
-                        if (lig == 0) a.coefs[row] = coef_scale<DIST>(active ? -scale * wr : 0.f, nneg);
+                        if (lig == 0) a.coefs[row] = formed_coef<DIST>(active ? -scale * wr : 0.f, nneg);
                     } else
                         write_grad_row<LPR, ITERS, DIST>(G + row * dim, d4, lig, xn[q], active ? -scale * wr : 0.f,
                                                          nneg);
@@ -286,7 +295,7 @@ __device__ inline void forward_stacked_body(const int block, const ForwardArgs &
             write_grad_row_packed<LPR, ITERS, DIST>(reinterpret_cast<uint8_t *>(G), gstride, gcoef, i, d4, lig, xp,
                                                     (float)n_active * scale * wr);
         else if (!FROM_Y && a.coefs) {
-            if (lig == 0) a.coefs[i] = coef_scale<DIST>((float)n_active * scale * wr, npos);
+            if (lig == 0) a.coefs[i] = formed_coef<DIST>((float)n_active * scale * wr, npos);
         } else
             write_grad_row<LPR, ITERS, DIST>(G + i * dim, d4, lig, xp, (float)n_active * scale * wr, npos);
     }

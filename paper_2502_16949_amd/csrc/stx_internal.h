@@ -222,6 +222,7 @@ struct stx_ctx {
     const stx_incidence *step_colidx_inc;   // ... of this incidence
     // stx_train_step: the final sum of the loss is not launched by the forward pass but rides in the first
     // launch of the backward pass (nothing in between needs it), when that launch can take it along
+    bool form_rows;                // this step's rows of dL/dx are formed where they are summed (see formed_rows)
     bool defer_finish;
     int fin_n;                     // loss partials waiting to be summed (0: none)
     float fin_scale;
@@ -425,6 +426,8 @@ inline int big_tables(const stx_ctx *c)
 // stored by the forward pass and read three times.  That pays when the stored rows are beyond the last-level cache
 // while a 64-float slice of the whole table fits the L2 caches, slice by slice (every die's 4 MB; popular rows make
 // somewhat larger ones do).  The update cannot be fused then: other workgroups still read the rows it would replace.
+// stx_train_step forms rows; the separate calls store theirs, and sum batches of these sizes in the same tiles, so that
+// both give the same bits.
 inline bool formed_rows(const stx_ctx *c, int64_t n_rows)
 {
     const bool stacked = c->cfg.model == STX_TRANSE || c->cfg.model == STX_TORUSE;

@@ -193,7 +193,7 @@ bool launch_fwd_hist(stx_ctx *c, const stx_incidence *inc, StepFusion *f, const 
     const bool stacked = c->cfg.model == STX_TRANSE || c->cfg.model == STX_TORUSE;
     const bool transh = c->cfg.model == STX_TRANSH;
     const Launch L = row_launch(c->cfg.dim);
-    if (!(stacked || transh) || L.iters != 1 || inc->n_rows == 0 || formed_rows(c, inc->n_rows)) return false;
+    if (!(stacked || transh) || L.iters != 1 || inc->n_rows == 0 || c->form_rows) return false;
     f->scale = 1.0f;
     if (c->cfg.reduce == STX_MEAN && inc->k > 0) f->scale = 1.0f / (float)((int64_t)inc->b * inc->k);
     const int groups = kThreads / L.lpr;
@@ -238,7 +238,7 @@ bool launch_fwd_scatter(stx_ctx *c, const stx_incidence *inc, StepFusion *f, con
     const bool stacked = c->cfg.model == STX_TRANSE || c->cfg.model == STX_TORUSE;
     const bool transh = c->cfg.model == STX_TRANSH;
     const Launch L = row_launch(c->cfg.dim);
-    if (!(stacked || transh) || L.iters != 1 || inc->n_rows == 0 || formed_rows(c, inc->n_rows)) return false;
+    if (!(stacked || transh) || L.iters != 1 || inc->n_rows == 0 || c->form_rows) return false;
     f->scale = 1.0f;
     if (c->cfg.reduce == STX_MEAN && inc->k > 0) f->scale = 1.0f / (float)((int64_t)inc->b * inc->k);
     const int groups = kThreads / L.lpr;
