@@ -829,11 +829,8 @@ template <int DIST, int C>
 static void go_sad(stx_ctx *c, FilterArgs &f, int64_t nq)
 {
     const size_t lds = (size_t)f.np * 64 * C * 16 + (kSadThreads / 64) * ((size_t)kListCap * 8 + kSadGroup * C * 8) + 64 * C * 4;
-    static bool told = false;                                  // (per instantiation: more than 64 KB of LDS has to be asked for)
-    if (!told) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rank_sad<DIST, C>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-        told = true;
-    }
+    // (more than 64 KB of LDS has to be asked for, on every device that runs the kernel)
+    (void)hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rank_sad<DIST, C>), hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     const int64_t groups = (nq + kSadGroup - 1) / kSadGroup;
     const int64_t gx = ((int64_t)f.a.n_ent + 64 * C - 1) / (64 * C);
     int64_t slices = (4096 + gx - 1) / gx;
