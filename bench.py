@@ -50,8 +50,6 @@ TRAFFIC_BYTES = {("toruse", "k_seg_reduce", True): 1133.94e6 + 623.18e6,
                  ("toruse", "k_forward_stacked", False): 693.55e6 + 53.52e6,
                  ("toruse", "k_seg_reduce", False): 561.76e6 + 532.18e6,
                  ("toruse", "k_sgd_rows", False): 1056.94e6 + 526.37e6,
-                 # mean of the two batches of an epoch (393,216 and 89,926 positives), like the timed mean
-                 ("paper_transe", "k_seg_reduce", True): (9761.85e6 + 104.19e6 + 2281.04e6 + 99.90e6) / 2,
                  # with the look-ahead (the next batch's first build kernels ride in these launches)
                  ("mid", "k_seg_reduce", "rides"): 28.04e6 + 17.01e6,
                  ("mid", "k_fwd_scatter", "rides"): 27.44e6 + 9.25e6,
@@ -61,10 +59,7 @@ TRAFFIC_BYTES = {("toruse", "k_seg_reduce", True): 1133.94e6 + 623.18e6,
                  ("transh", "k_seg_fixup", "rides"): 4.06e6 + 0.48e6,
                  ("transr", "k_transr_fused", "rides"): 40.20e6 + 52.83e6,
                  ("transr", "k_seg_reduce", "rides"): 89.66e6 + 31.35e6,
-                 ("transr", "k_seg_fixup", "rides"): 9.78e6 + 1.26e6,
-                 # the other modes (profiles/semiring_complex_*_kernel_trace.txt, profiles/rank_mid_kernel_trace.txt)
-                 ("semiring complex", "mid", "k_semiring_terms"): 66.64e6 + 100.66e6,
-                 ("semiring complex", "toruse", "k_semiring_terms"): 1560.16e6 + 2013.27e6}
+                 ("transr", "k_seg_fixup", "rides"): 9.78e6 + 1.26e6}
 
 
 def parse():
@@ -162,10 +157,10 @@ def kernel_work(wl, kernel, rows, touched, fused=False, rides=False, segw=False)
         return touched * 3 * row, "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_semiring":          # three gathered rows + ids in, the product row out
         return rows * (3 * row + 12 + row), "GB/s", "hbm", HBM_PEAK_GBS
-    if kernel == "k_semiring_terms":    # three gathered rows, the dL/dZ row and ids in, three term rows out
-        return rows * (4 * row + 12 + 3 * row), "GB/s", "hbm", HBM_PEAK_GBS
-    if kernel == "k_seg_reduce_terms":  # the transposed product over the term rows: one row per entry in, one per column out
-        return nnz * (row + 4) + touched * row, "GB/s", "hbm", HBM_PEAK_GBS
+    if kernel == "k_seg_reduce_terms":  # semiring backward: the dL/dZ row, the entry's two other table rows and ids in
+        return nnz * (3 * row + 16) + touched * row, "GB/s", "hbm", HBM_PEAK_GBS
+    if kernel == "k_seg_reduce_formed":  # x formed again: the entry's two other table rows and its record in, the
+        return nnz * (2 * row + 20) + touched * 2 * row, "GB/s", "hbm", HBM_PEAK_GBS    # column's own row once
     if kernel == "k_scatter":
         return nnz * 16, "GB/s", "hbm", HBM_PEAK_GBS      # key + payload in, key + payload out
     # TransR's three products: 2*d*k flop per row against ~2 KB of row traffic is ~20 flop per byte, far left of
@@ -341,7 +336,7 @@ def bench_semiring(args, wl, dev):
     z = torch.empty(rows, wl.dim, dtype=torch.float32, device=dev)
     gz = torch.rand(rows, wl.dim, dtype=torch.float32, device=dev) - 0.5
     work = torch.empty(3 * rows * wl.dim, dtype=torch.float32, device=dev)
-    kernel = args.kernel or "k_semiring_terms"
+    kernel = args.kernel or "k_seg_reduce"
     for _ in range(args.warmup):
         B.stx_spmm_semiring(ctx, inc, params, kind, z)
         B.stx_spmm_semiring_t(ctx, inc, params, kind, gz, work, grads)
@@ -444,9 +439,12 @@ class Job:
         # batches whose first build kernels can run inside the previous step's launches (see stx_batch.next)
         self.rides = (self.one_call and lookahead and (wl.model != "transr" or wl.n_rel <= 4096)
                       and wl.n_ent + wl.n_rel <= 65536 and 3 * wl.rows_per_batch <= (1 << 19) and wl.dim <= 256)
+        # the step forms the rows of dL/dx where they are summed (the library's rule for dense kinds, on a full batch)
+        self.formed = (self.one_call and wl.model in ("transe", "toruse") and wl.dist not in ("l1", "torus_l1")
+                       and (wl.n_ent + wl.n_rel) * 256 <= 6 << 20 and wl.rows_per_batch * wl.dim * 4 >= 192 << 20)
         # the one-call step leaves the last kernel of the build to the launch of the transposed product (rows of
         # one float4 per lane; TransR when its work items come from the rows-per-relation counts)
-        self.segw = self.one_call and (wl.model != "transr" or wl.n_rel <= 4096) and wl.dim <= 256
+        self.segw = not self.formed and self.one_call and (wl.model != "transr" or wl.n_rel <= 4096) and wl.dim <= 256
         self.h, self.r, self.t = W.make_graph(wl)
         self.tabs = W.make_tables(wl)
         hd, rd, td = (torch.from_numpy(a).to(dev) for a in (self.h, self.r, self.t))
@@ -570,18 +568,23 @@ class Job:
         could move, the measured traffic where a profile has it, and the roof the figures are held against."""
         wl = self.wl
         u = touched * mean_rows / wl.rows_per_batch
-        w, unit, bound, peak = kernel_work(wl, kname, mean_rows, u, self.fused, self.rides, self.segw)
+        formed = self.formed and kname == "k_seg_reduce"
+        w, unit, bound, peak = kernel_work(wl, kname + "_formed" if formed else kname, mean_rows, u, self.fused, self.rides,
+                                           self.segw)
         ach = w / (us * 1e-6) / (1e9 if unit == "GB/s" else 1e12) if us > 0 else 0.0
         e = {"bound": bound, "kernel": kname, "achieved": round(ach, 1), "peak": peak, "unit": unit,
              "frac": round(ach / peak, 4),
              "traffic": TRAFFIC_BYTES.get((wl.name, kname, "rides" if self.rides else self.fused)),
              "work_per_launch": int(w), "avg_launch_us": round(us, 2), "roof": roof_of(wl, kname, us)}
-        bmin = kernel_min_bytes(wl, kname, mean_rows, u, self.fused)
+        bmin = None if formed else kernel_min_bytes(wl, kname, mean_rows, u, self.fused)
         if bmin is not None and us > 0:
             e["min_bytes_per_launch"] = int(bmin)
             e["achieved_min_bytes"] = round(bmin / (us * 1e-6) / 1e9, 1)
         if e["traffic"] and us > 0:
             e["achieved_traffic"] = round(e["traffic"] / (us * 1e-6) / 1e9, 1)
+        if formed:
+            e["note"] = ("rows of dL/dx formed where they are summed: nearly all of these bytes come from the L2 caches, which "
+                         "hold the 64-float slice of the table that is being read")
         if ach > peak and kname in ("k_forward_stacked", "k_fwd_scatter"):
             # the algorithmic figure counts three gathered table rows per matrix row; the kernel requests a positive's
             # rows once for all of its negatives and repeated rows come from the caches
