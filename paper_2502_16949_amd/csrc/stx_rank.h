@@ -77,6 +77,8 @@ struct RankScratch {
     size_t q_bytes, e_bytes;
     float *q32;                        // TransR: fp32 query points of all grouped queries (else part of q)
 };
+// Whether one table's sweep of these sizes is faster filtered than plain, given q_bytes of query scratch.
+bool rank_filter_pays(int dist, int64_t queries, int64_t n_ent, int width, size_t q_bytes);
 size_t rank_filter_q_bytes(int dist, int width, int64_t queries);                 // 0: a kind without a filtered sweep
 size_t rank_filter_e_bytes(int dist, int width, int64_t candidates, int tables);
 // True scores and counts (not the final square roots) through the filter.  nz: 0, or the number of relations of a

@@ -644,11 +644,9 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
         const RankShape sh = rank_shape(nq, n_ent, transh ? 4 : 2);   // TransH workgroups start with a dot product per query
         const RankArgs a{p->ent, transh ? p->rel : nullptr, transh ? p->w : nullptr, h, r, t, nq, n_ent, n_rel, c->cfg.dim,
                          sh.slice, true_score, n_less, n_equal, bad, nullptr, nullptr, 0};
-        // Small problems are not worth the filter's extra launches (about 10 us): the plain sweep, whose query blocks
-        // are padded to 128, does 28e12 steps a second.
         const RankScratch ws{c->rank_q, c->rank_e, c->rank_q_bytes, c->rank_e_bytes, nullptr};
-        const double steps = (double)((nq + kRankQ - 1) / kRankQ * kRankQ) * n_ent * c->cfg.dim;
-        if (c->rank_q_bytes && steps >= 6e8 && rank_filtered(c, a, side, ws, 0, RankIds{})) {
+        if (rank_filter_pays(c->cfg.dist, nq, n_ent, c->cfg.dim, c->rank_q_bytes) &&
+            rank_filtered(c, a, side, ws, 0, RankIds{})) {
             if (c->cfg.dist == STX_L2)
                 hipLaunchKernelGGL((k_rank_finish<STX_L2>), sh.qgrid, dim3(kThreads), 0, c->stream, true_score, nq);
             return hip_ok(hipGetLastError());

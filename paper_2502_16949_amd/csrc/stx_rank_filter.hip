@@ -796,6 +796,35 @@ size_t rank_filter_q_bytes(int dist, int width, int64_t queries)
     const size_t b = (q * each + 2048) * 3 / 2;               // and half as much again for the list of undecided pairs
     return b > (size_t)4 << 20 ? b : (size_t)4 << 20;
 }
+// Both sides as measured at 230 sizes over rows of 16 to 1,000 floats, tables of 1,000 to 1,500,000 entities and 1 to
+// 59,071 queries, in us a side; the rule took the slower filter at none of them.  The plain sweep: a serial walk of the row by the kernel of the true sums, then its steps, padded to
+// 128 queries and 32 floats.  The filter: launches and dependent passes for every chunk of queries that its scratch
+// holds, a little per query, then its steps; the matrix-core kinds also pack the table, which few queries do not repay
+// once it is past the caches (128 queries x 700,000 at d = 544: 2,290 plain, 2,790 filtered), and a small table gives
+// the fixed-point sweep too few candidates to share a query's load (8,000 x 1,000 at d = 256, L1: 177 plain, 597
+// filtered; 59,071 x 15,000 at d = 128: 3,850 and 1,950).
+bool rank_filter_pays(int dist, int64_t queries, int64_t n_ent, int width, size_t q_bytes)
+{
+    if (!q_bytes || (!sad_kind(dist) && !mfma_kind(dist))) return false;
+    const double q = (double)queries, n = (double)n_ent, w32 = (width + 31) / 32 * 32;
+    const double padded = (double)((queries + 127) / 128 * 128);
+    if (padded * n * width < 6e8) return false;                // a plain sweep of at most about 20 us
+    const bool narrow = width <= 32;
+    const double per_query = (double)rank_filter_q_bytes(dist, width, 1 << 20) / (1 << 20);   // the list's share included
+    double chunks = ceil(q * per_query / (double)q_bytes), pass = 25. + 0.1 * width, sweep;
+    if (sad_kind(dist)) {
+        const double listed = ceil(q * n / ((double)(q_bytes / 3 / sizeof(uint2)) * 1000.));   // as rank_filtered cuts them
+        if (chunks < listed) chunks = listed;
+        if (narrow) pass = 60.;
+        sweep = q * (n > 4096. ? n : 4096.) * w32 / (narrow ? 38e6 : dist == STX_TORUS_L1 ? 25e6 : 41e6);
+    } else {
+        const double wp = 16. * mfma_steps(width);
+        sweep = n * wp * (3.8e-6 + 0.018e-6 * (q < 128. ? q : 128.)) + n * (narrow ? 0.8e-6 * q : 0.012e-6 * wp * (q > 128. ? q - 128. : 0.));
+    }
+    const double filtered = chunks * pass + 0.003 * q + sweep;
+    const double plain = 0.6 * width + padded * n * w32 / (dist == STX_TORUS_L1 ? 12e6 : 28e6);
+    return filtered < plain;
+}
 size_t rank_filter_e_bytes(int dist, int width, int64_t candidates, int tables)
 {
     return mfma_kind(dist) ? (size_t)((candidates + 31) / 32) * tables * mfma_tile_bytes(mfma_steps(width)) + kMfmaSlack : 0;

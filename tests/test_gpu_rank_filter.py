@@ -10,7 +10,7 @@ from tests import gpu_util as G
 
 pytestmark = pytest.mark.gpu
 
-FILTER_STEPS = 6e8       # queries (padded to 128) x entities x dim from which a call is filtered
+FILTER_STEPS = 6e8       # queries (padded to 128) x entities x dim below which no call is filtered
 
 
 def _rank(ctx, p, h, r, t, side):
@@ -23,10 +23,11 @@ def _rank(ctx, p, h, r, t, side):
 
 
 CASES = [
+    # (sizes at which the rule that compares both sweeps' times takes the filter)
     # dist, n_ent, dim, nq: row widths at and around the pieces of 8 and 16 elements, ragged tiles and query blocks
-    ("l1", 12_001, 16, 4_000), ("l1", 4_097, 128, 1_300), ("l1", 2_050, 260, 1_250), ("l1", 1_100, 1024, 700),
+    ("l1", 60_001, 16, 8_000), ("l1", 4_097, 128, 1_300), ("l1", 2_050, 260, 1_250), ("l1", 1_100, 1024, 700),
     ("torus_l1", 40_000, 36, 700), ("torus_l1", 3_000, 200, 1_290), ("torus_l1", 1_500, 1000, 513),
-    ("l2", 12_001, 16, 4_000), ("l2", 30_000, 44, 600), ("l2", 4_129, 128, 1_300), ("l2", 9_000, 196, 385),
+    ("l2", 60_001, 16, 4_000), ("l2", 30_000, 44, 600), ("l2", 4_129, 128, 1_300), ("l2", 9_000, 196, 385),
     ("l2_sq", 2_050, 260, 1_250), ("l2", 1_300, 700, 800), ("l2", 1_100, 1024, 700),
     ("l2", 500_000, 100, 33), ("l1", 200_000, 60, 5),     # few queries, several segments of candidates
 ]
