@@ -1,0 +1,37 @@
+"""The forward kernel that fetches a positive's rows once, at numbers of negatives around the batches it holds at a time
+(four, two for rows of more than two float4 per lane), and the transposed product's stitching of runs that cross
+chunks, at few columns; against the oracle at the bars of the step test."""
+import numpy as np
+import pytest
+
+from oracle import stxo
+from paper_2502_16949_amd import binding as B
+from tests.test_gpu_stacked import _check_step, _problem
+
+pytestmark = pytest.mark.gpu
+
+
+# (Rows of 12 floats at least: table values reach 6 / sqrt(dim), and past 2 their last place, 2^-22, is more than the
+# absolute term 2^-23 of the step test's bar.)
+@pytest.mark.parametrize("k", [2, 3, 4, 5, 8, 9])
+@pytest.mark.parametrize("model,dist,dim", [("transe", "l2", 12), ("toruse", "torus_l1", 60), ("transe", "l1", 200),
+                                            ("transe", "l2", 260), ("toruse", "torus_l2", 516), ("transe", "l1", 1020)])
+def test_batches_of_negatives(model, dist, dim, k):
+    wl, tabs, bt = _problem(model, dist, 300, 7, 203, k, dim, seed=dim + k, zipf=1.1)
+    _check_step(wl, tabs, bt, model, dim, B.STX_SUM)
+    # the last negative of the last positive alone is of a kind that the kernel does not cover
+    nh, nt = bt.nh.copy(), bt.nt.copy()
+    nh[-1], nt[-1] = (bt.h[-1] + 1) % wl.n_ent, (bt.t[-1] + 1) % wl.n_ent
+    _check_step(wl, tabs, stxo.Batch(bt.h, bt.r, bt.t, nh, nt), model, dim, B.STX_SUM)
+
+
+# rows of 8, 16, 32 and 64 lanes; two entities: runs over many chunks and tiles; more: runs that end at
+# any place
+@pytest.mark.parametrize("dim", [32, 64, 128, 256])
+@pytest.mark.parametrize("n_ent,n_rel,b", [(2, 1, 700), (3, 2, 411), (40, 3, 1_025)])
+def test_runs_across_chunks(n_ent, n_rel, b, dim):
+    wl, tabs, bt = _problem("transe", "l2", n_ent, n_rel, b, 1, dim, seed=dim + b)
+    rng = np.random.default_rng(b)
+    h, t = (rng.integers(0, n_ent, b).astype(np.int32) for _ in range(2))
+    bt = stxo.Batch(h, bt.r, t, np.roll(h, 1), t)
+    _check_step(wl, tabs, bt, "transe", dim, B.STX_SUM)
