@@ -675,7 +675,8 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
         for (int g = 0; g < 4; ++g) cn[g] = ld4(ta + half * 4 + 8 * g);
 #pragma unroll
         for (int q = 0; q < QF; ++q) {
-            w[q] = __builtin_fmaf(p_x[q], et.y, __builtin_fmaf(p_y[q], et.z, __builtin_fmaf(p_w[q], et.x, p_s[q] * et.w))) * 1.0001f;
+            // (never zero: a zero query's sums against a tile of zero rows are exactly zero, and such ties are undecided)
+            w[q] = __builtin_fmaf(__builtin_fmaf(p_x[q], et.y, __builtin_fmaf(p_y[q], et.z, __builtin_fmaf(p_w[q], et.x, p_s[q] * et.w))), 1.0001f, 1e-37f);
             const float tau = -p_z[q] * et.x, ns = -p_s[q];
 #pragma unroll
             for (int g = 0; g < 4; ++g) {

@@ -13,12 +13,12 @@ pytestmark = pytest.mark.gpu
 FILTER_STEPS = 6e8       # queries (padded to 128) x entities x dim below which no call is filtered
 
 
-def _rank(ctx, p, h, r, t, side):
+def _rank(ctx, p, h, r, t, side, work=None):
     nq = len(h)
     ts = torch.empty(nq, dtype=torch.float32, device=G.DEV)
     less = torch.empty(nq, dtype=torch.int32, device=G.DEV)
     equal = torch.empty_like(less)
-    B.stx_rank(ctx, p, h, r, t, side, ts, less, equal)
+    B.stx_rank(ctx, p, h, r, t, side, ts, less, equal, work)
     return ts, less, equal
 
 
@@ -68,6 +68,50 @@ def test_filtered_counts_equal_the_plain_sweep(dist, n_ent, dim, nq, odd_rows):
         for g, w in zip(got, want):
             assert np.array_equal(g, w, equal_nan=True)
     assert B.stx_check_indices(ctx) == 0
+
+
+# Zero query points against whole tiles (32 candidates) of zero rows: every sum is exactly zero and so is every rounding.
+@pytest.mark.parametrize("dist", ["l2", "l2_sq"])
+@pytest.mark.parametrize("n_ent,dim,n_zero", [(4_129, 128, 1_000), (2_050, 260, 33), (4_129, 128, 4_129)])
+def test_zero_queries_tie_with_zero_rows(n_ent, dim, n_zero, dist):
+    nq, n_rel = 1_300, 3
+    assert -(-nq // 128) * 128.0 * n_ent * dim >= FILTER_STEPS
+    rng = np.random.default_rng(n_zero)
+    X = rng.uniform(-1, 1, (n_ent + n_rel, dim)).astype(np.float32)
+    X[:n_zero] = 0.0
+    X[n_ent:] = 0.0                                       # (the relations)
+    h, t = (rng.integers(0, n_zero, nq).astype(np.int32) for _ in range(2))
+    r = rng.integers(0, n_rel, nq).astype(np.int32)
+    ctx = B.Context(B.make_config("transe", dist, n_ent, n_rel, dim, 8, 1), G.DEV)
+    p = B.Params(G.dev_f32(X))
+    for side in (B.STX_TAIL, B.STX_HEAD):
+        ts, less, equal = (x.cpu().numpy() for x in _rank(ctx, p, G.dev_i32(h), G.dev_i32(r), G.dev_i32(t), side))
+        assert not ts.any() and not less.any() and np.all(equal == n_zero)
+
+
+@pytest.mark.parametrize("dist", ["l2", "l2_sq"])
+def test_transr_zero_projections_tie(dist):
+    # relation 0: a zero matrix, all candidates tie; relation 1: the rows of 70 zero entities do; relation 2: no zero
+    n_ent, dim, k, n_zero, nq = 1_000, 64, 32, 70, 300
+    rng = np.random.default_rng(4)
+    E = rng.uniform(-1, 1, (n_ent, dim)).astype(np.float32)
+    E[:n_zero] = 0.0
+    M = rng.uniform(-1, 1, (3, k, dim)).astype(np.float32)
+    M[0] = 0.0
+    R = np.zeros((3, k), np.float32)
+    R[2] = 1.0
+    h, t = (rng.integers(0, n_zero, nq).astype(np.int32) for _ in range(2))
+    r = (np.arange(nq) % 3).astype(np.int32)
+    ctx = B.Context(B.make_config("transr", dist, n_ent, 3, dim, 8, 1, rel_dim=k, flags=B.STX_FLAG_BF16_PROJ), G.DEV)
+    p = B.Params(G.dev_f32(E), G.dev_f32(R), proj=G.dev_f32(M))
+    work = torch.empty(B.stx_rank_work_bytes(ctx, nq) + 256, dtype=torch.uint8, device=G.DEV)
+    for side in (B.STX_TAIL, B.STX_HEAD):
+        ts, less, equal = (x.cpu().numpy() for x in _rank(ctx, p, G.dev_i32(h), G.dev_i32(r), G.dev_i32(t), side, work))
+        for rel, tied in ((0, n_ent), (1, n_zero)):
+            assert not ts[r == rel].any() and not less[r == rel].any() and np.all(equal[r == rel] == tied)
+        # zero rows all score |r|^2 = k (or its root)
+        assert np.all(equal[r == 2] == n_zero)
+        assert np.allclose(ts[r == 2], k if dist == "l2_sq" else np.sqrt(k), rtol=1e-6)
 
 
 def _by_ranges(cfg, X, h, r, t, side, n_ent, n_rel, dim, dist):
