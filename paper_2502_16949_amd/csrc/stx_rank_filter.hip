@@ -51,7 +51,7 @@ struct FilterArgs {
                                        //     the tile's scale, largest norm, largest rounding, squared-norm term
     int32_t slice;                     // sweeps: candidates (mfma) or query groups (sad) per blockIdx.y
     int head;                          // side: q = t - r instead of h + r
-    int32_t *n_pairs;                  // undecided pairs found, cleared by k_rank_prep ...
+    unsigned long long *n_pairs;       // undecided pairs found, cleared by k_rank_prep (a sweep may find up to 2^31 x 2^31) ...
     uint2 *pairs;                      // ... and the pairs: (candidate | table << z_shift, position in the query arrays)
     int32_t pair_cap;
     int z_shift;                       // 32: one table
@@ -163,7 +163,7 @@ __global__ __launch_bounds__(kThreads) void k_rank_pairs(FilterArgs f)
 {
     __shared__ uint2 s_ties[4][72];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = min(*f.n_pairs, f.pair_cap), step = (int)gridDim.x * 32;
+    const int n = (int)min(*f.n_pairs, (unsigned long long)f.pair_cap), step = (int)gridDim.x * 32;
     int n_ties = 0;
     for (int i0 = ((int)blockIdx.x * 4 + wave) * 8; i0 < n; i0 += step) {
         const int i = i0 + (lane >> 3);
@@ -181,11 +181,11 @@ __global__ __launch_bounds__(kThreads) void k_rank_pairs(FilterArgs f)
 template <int DIST>
 __device__ inline void flush_pairs(const FilterArgs &f, const uint2 *list, int cnt, int lane)
 {
-    int base = 0;
-    if (lane == 0) base = atomicAdd(f.n_pairs, cnt);
+    int base = 0;                                          // first place, pair_cap: none left
+    if (lane == 0) base = (int)min(atomicAdd(f.n_pairs, (unsigned long long)cnt), (unsigned long long)f.pair_cap);
     base = __builtin_amdgcn_readfirstlane(base);
     for (int i = lane; i < cnt; i += 64) {
-        if (base + i < f.pair_cap) f.pairs[base + i] = list[i];
+        if (i < f.pair_cap - base) f.pairs[base + i] = list[i];
         else pair_exact<DIST>(f, list[i]);
     }
 }
@@ -281,7 +281,7 @@ __global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds id
 {
     constexpr bool SAD = DIST == STX_L1 || DIST == STX_TORUS_L1, TORUS = DIST == STX_TORUS_L1;
     RankArgs a = f.a;
-    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) *f.n_pairs = 0;
+    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) *f.n_pairs = 0ull;
     rank_group(a, ids);
     __shared__ float s_y[32][65];
     __shared__ float s_t[32];
@@ -892,7 +892,8 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
         q_each += mfma_query_bytes(f.np / 2);
     }
     // the list of undecided pairs takes a third of the query scratch; about one pair in a thousand to three hundred is
-    // undecided, so a sweep covers at most 300 pairs per place (beyond that pairs are treated inside the sweep)
+    // undecided, so one table's sweep covers at most 1,000 pairs per place (fixed point; 32 queries at least) or 300
+    // (matrix cores).  Beyond the list, and TransR's sweeps cover any number, pairs are treated inside the sweep.
     f.pair_cap = (int32_t)(ws.q_bytes / 3 / sizeof(uint2));
     f.z_shift = 32;
     if (nz > 0) {
@@ -907,7 +908,7 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
     if (cap < 32 || (nz > 0 && cap < a.nq)) return false;
     f.q_cap = (int32_t)cap;
     char *q = ws.q;
-    f.n_pairs = (int32_t *)q;
+    f.n_pairs = (unsigned long long *)q;
     f.pairs = (uint2 *)(q + 256);
     q += 256 + (size_t)f.pair_cap * sizeof(uint2);
     q += -(uintptr_t)q & 255u;

@@ -114,6 +114,30 @@ def test_transr_zero_projections_tie(dist):
         assert np.allclose(ts[r == 2], k if dist == "l2_sq" else np.sqrt(k), rtol=1e-6)
 
 
+# More undecided pairs in one sweep than an int32 counts (every candidate ties): a chunk of fixed-point queries is
+# never smaller than 32, and a TransR relation is swept in one piece.
+def test_more_undecided_pairs_than_an_int32_counts():
+    n_ent, dim, nq = 68_000_000, 4, 32
+    assert nq * n_ent > 2**31
+    p = B.Params(torch.full((n_ent + 1, dim), 0.25, device=G.DEV))
+    ctx = B.Context(B.make_config("transe", "l1", n_ent, 1, dim, 8, 1), G.DEV)
+    q = torch.arange(nq, dtype=torch.int32, device=G.DEV)
+    _, less, equal = _rank(ctx, p, q, torch.zeros_like(q), q + 7, B.STX_TAIL)
+    assert not less.any() and bool((equal == n_ent).all())
+
+
+def test_more_undecided_pairs_than_an_int32_counts_transr():
+    n_ent, dim, nq = 125_000, 32, 17_500
+    assert nq * n_ent > 2**31
+    E = torch.rand(n_ent, dim, device=G.DEV)
+    p = B.Params(E, torch.zeros(1, dim, device=G.DEV), proj=torch.zeros(1, dim, dim, device=G.DEV))
+    ctx = B.Context(B.make_config("transr", "l2", n_ent, 1, dim, 8, 1, rel_dim=dim, flags=B.STX_FLAG_BF16_PROJ), G.DEV)
+    work = torch.empty(B.stx_rank_work_bytes(ctx, nq) + 256, dtype=torch.uint8, device=G.DEV)
+    q = torch.arange(nq, dtype=torch.int32, device=G.DEV)
+    _, less, equal = _rank(ctx, p, q, torch.zeros_like(q), q + 7, B.STX_TAIL, work)
+    assert not less.any() and bool((equal == n_ent).all())
+
+
 def _by_ranges(cfg, X, h, r, t, side, n_ent, n_rel, dim, dist):
     """The counts of long tables from plain sweeps over tables of a part of the entities each, to which the entities
     of the queries are added (and subtracted again)."""
