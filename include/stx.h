@@ -182,14 +182,19 @@ stx_status stx_spmm_semiring(stx_ctx *ctx, const stx_incidence *inc, const stx_p
  * g->rows[s] = sum over the entries of segment s of gz[row] times the conjugated product of the row's
  * other two factors (head entry: conj(r) t | conj(r); relation entry: conj(h) t | conj(h); tail entry:
  * ComplEx conj(gz) h r, RotatE -gz; DistMult: the plain products), summed in the fixed order of
- * stx_backward.  work: 3 * n_rows * dim floats of device memory owned by the caller; required, but no longer
- * touched: every entry's term is formed where it is summed.                                              */
+ * stx_backward.  work: 3 * n_rows * dim floats of device scratch owned by the caller.  Every entry's term is
+ * formed where it is summed, and work stays untouched, unless g->rows (as many rows as the batch can touch,
+ * min(nnz, n_ent + n_rel)) shares memory with gz or the table: the rows are formed in work then and copied.
+ * work itself shares no memory with the others.                                                          */
 stx_status stx_spmm_semiring_t(stx_ctx *ctx, const stx_incidence *inc, const stx_params *p, int32_t kind,
                                const float *gz, float *work, stx_grads *g);
 
 /* stx_spmm_semiring_t for callers that cannot allocate device memory and have no work buffer to hand over
  * (code under HIP graph capture, serving loops, harnesses that forbid hipMalloc): the same kernels and the
- * same results bit for bit.  Calls no allocator and uses no memory of the library's own.
+ * same results bit for bit.  Calls no allocator.  Where stx_spmm_semiring_t would use work, a fixed array of
+ * STX_STATIC_WORK_BYTES bytes that is part of the library's device code takes its place (every GPU the library
+ * runs on holds its own copy until the process ends; the context's GPU must be the current device): such calls
+ * race on it when they overlap in time on one GPU, from whatever context or thread; calls on one stream do not.
  * A batch with 3 * n_rows * dim * 4 > STX_STATIC_WORK_BYTES is refused with STX_ERR_STATIC_LIMIT before
  * anything is launched (at dim 128: up to 65,536 rows).                                                  */
 #define STX_STATIC_WORK_BYTES (96u << 20)

@@ -468,7 +468,7 @@ stx_status stx_spmm_semiring_t(stx_ctx *ctx, const stx_incidence *inc, const stx
     if (((uintptr_t)gz & 15u) || ((uintptr_t)work & 15u)) return STX_ERR_BAD_ARG;
     if (!stacked(ctx)) return STX_ERR_UNSUPPORTED;
     if ((s = check_a_current(ctx, inc)) != STX_OK) return s;
-    return launch_semiring_t(ctx, inc, p, kind, gz, g->rows);
+    return launch_semiring_t(ctx, inc, p, kind, gz, work, g->rows);
 }
 
 stx_status stx_spmm_semiring_t_static(stx_ctx *ctx, const stx_incidence *inc, const stx_params *p, int32_t kind,
@@ -484,7 +484,7 @@ stx_status stx_spmm_semiring_t_static(stx_ctx *ctx, const stx_incidence *inc, co
     if ((uint64_t)inc->n_rows * 3u * (uint64_t)ctx->cfg.dim * sizeof(float) > (uint64_t)STX_STATIC_WORK_BYTES)
         return STX_ERR_STATIC_LIMIT;
     if ((s = check_a_current(ctx, inc)) != STX_OK) return s;
-    return launch_semiring_t(ctx, inc, p, kind, gz, g->rows);
+    return launch_semiring_t(ctx, inc, p, kind, gz, nullptr, g->rows);
 }
 
 stx_status stx_rank_work_bytes(const stx_ctx *ctx, int64_t nq, size_t *bytes)

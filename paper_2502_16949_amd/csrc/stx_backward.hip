@@ -1094,10 +1094,9 @@ stx_status launch_seg_formed(stx_ctx *c, const stx_incidence *inc, const stx_par
     return hip_ok(hipGetLastError());
 }
 
-stx_status launch_semiring_t(stx_ctx *c, const stx_incidence *inc, const stx_params *p, int kind, const float *gz,
-                             float *out_rows)
+stx_status launch_semiring_product_t(stx_ctx *c, const stx_incidence *inc, const stx_params *p, int kind, const float *gz,
+                                     float *out_rows)
 {
-    if (inc->n_rows == 0) return STX_OK;
     Launch L = row_launch(c->cfg.dim);
     STX_DISPATCH_ROW(L, semiring_t_go, c, inc, p->ent, kind, gz, out_rows);
     return hip_ok(hipGetLastError());

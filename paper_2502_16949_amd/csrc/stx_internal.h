@@ -365,8 +365,10 @@ struct SgdTables {
     float *table_b; int width_b;               // columns >= n_split, gradient in the same rows array (may be null)
     float *table_w; int mode_w;                // columns >= n_split, gradient in w_rows, width_a (may be null)
 };
-// the backward of a semiring product: every entry's term formed where it is summed
-stx_status launch_semiring_t(stx_ctx *, const stx_incidence *, const stx_params *, int kind, const float *gz, float *out_rows);
+// the backward of a semiring product: every entry's term formed where it is summed (out_rows shares no memory with
+// gz or the table)
+stx_status launch_semiring_product_t(stx_ctx *, const stx_incidence *, const stx_params *, int kind, const float *gz,
+                                     float *out_rows);
 stx_status launch_sgd_rows(stx_ctx *, const stx_incidence *, const SgdTables &, const float *grad_rows,
                            const float *w_rows, float lr);
 stx_status launch_forward_from_y(stx_ctx *, const stx_incidence *, const stx_params *, float *scores, float *loss);
@@ -376,6 +378,9 @@ stx_status launch_rank(stx_ctx *, const stx_params *, const int32_t *h, const in
 size_t rank_work_bytes(const stx_ctx *, int64_t nq);   // scratch launch_rank needs for nq queries (0 unless TransR)
 // stx_semiring.hip
 stx_status launch_semiring(stx_ctx *, const stx_incidence *, const stx_params *, int kind, float *z_out);
+// work: 3 n_rows dim floats, used where out_rows shares memory with gz or the table; null: the library's fixed array
+stx_status launch_semiring_t(stx_ctx *, const stx_incidence *, const stx_params *, int kind, const float *gz,
+                             float *work, float *out_rows);
 // stx_transr.hip
 stx_status launch_transr_project(stx_ctx *, const stx_incidence *, const stx_params *);
 // the forward pass, dL/dy, dL/dx and the tiles of the dM product in one kernel, for the shapes transr_fused_ok names

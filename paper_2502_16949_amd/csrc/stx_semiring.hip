@@ -9,6 +9,8 @@
 // Backward for a real loss, given G = dL/dZ: every entry of a row receives G times the (conjugated)
 // product of the row's other two factors.  The transposed product (stx_backward.hip) forms that where it
 // sums the entries of a column.
+#include <mutex>
+
 #include "stx_semiring_ops.h"
 
 namespace stx {
@@ -65,6 +67,67 @@ stx_status launch_semiring(stx_ctx *c, const stx_incidence *inc, const stx_param
     if (inc->n_rows == 0) return STX_OK;
     Launch L = row_launch(c->cfg.dim);
     STX_DISPATCH_ROW(L, semiring_go, c, inc, p, kind, z_out);
+    return hip_ok(hipGetLastError());
+}
+
+// Scratch of stx_spmm_semiring_t_static for gradient rows that share memory with what the product reads.  Every GPU the
+// library runs on holds its own copy of the array, at its own address, until the process ends.  In host code the
+// array's name is only a handle for the symbol look-up below, never an address.
+static __device__ __align__(256) unsigned char scratch[STX_STATIC_WORK_BYTES];
+
+namespace {
+constexpr int kMaxDevices = 64;
+std::mutex g_scratch_mu;
+void *g_scratch_ptr[kMaxDevices];   // device address of `scratch` on each GPU, null until first asked for
+}  // namespace
+
+static stx_status static_work(float **out)
+{
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return STX_ERR_HIP;
+    if (dev < 0 || dev >= kMaxDevices) return STX_ERR_UNSUPPORTED;
+    std::lock_guard<std::mutex> lock(g_scratch_mu);
+    if (!g_scratch_ptr[dev]) {
+        void *ptr = nullptr;
+        if (hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)) != hipSuccess || !ptr) return STX_ERR_HIP;
+        g_scratch_ptr[dev] = ptr;
+    }
+    *out = static_cast<float *>(g_scratch_ptr[dev]);
+    return STX_OK;
+}
+
+// Gradient rows of the touched columns from where they were formed to where the caller wants them.
+__global__ __launch_bounds__(kThreads) void k_copy_touched(const float4 *__restrict__ src, const int32_t *__restrict__ n_touched,
+                                                           int row4, float4 *__restrict__ dst)
+{
+    const int64_t n = (int64_t)*n_touched * row4;
+    for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < n; i += (int64_t)gridDim.x * kThreads) dst[i] = src[i];
+}
+
+static bool overlap(const float *a, int64_t na, const float *b, int64_t nb)
+{
+    const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+    return x < y + (uintptr_t)nb * 4 && y < x + (uintptr_t)na * 4;
+}
+
+// The product reads dL/dZ and the table while other workgroups store gradient rows.  A caller may hand over gradient
+// rows that share memory with either (dL/dZ replaced in place): they are formed in `work` then, and copied.
+stx_status launch_semiring_t(stx_ctx *c, const stx_incidence *inc, const stx_params *p, int kind, const float *gz,
+                             float *work, float *out_rows)
+{
+    if (inc->n_rows == 0) return STX_OK;
+    const int64_t dim = c->cfg.dim, cols = c->cfg.n_ent + c->cfg.n_rel, n_out = (inc->nnz < cols ? inc->nnz : cols) * c->ld;
+    if (!overlap(out_rows, n_out, gz, inc->n_rows * dim) && !overlap(out_rows, n_out, p->ent, cols * dim))
+        return launch_semiring_product_t(c, inc, p, kind, gz, out_rows);
+    if (!work) {
+        const stx_status s = static_work(&work);
+        if (s != STX_OK) return s;
+    }
+    const stx_status s = launch_semiring_product_t(c, inc, p, kind, gz, work);
+    if (s != STX_OK) return s;
+    const int64_t blocks = (n_out / 4 + kThreads - 1) / kThreads;
+    hipLaunchKernelGGL(k_copy_touched, dim3((unsigned)(blocks < 2048 ? blocks : 2048)), dim3(kThreads), 0, c->stream,
+                       (const float4 *)work, inc->n_touched, c->ld / 4, (float4 *)out_rows);
     return hip_ok(hipGetLastError());
 }
 

@@ -110,3 +110,41 @@ def test_semiring_rejects_bad_arguments():
     with pytest.raises(B.StxError) as e:
         B.stx_spmm_semiring(mh.ctx, mh.inc, mh.params, B.STX_DISTMULT, z)
     assert e.value.status == B.STX_ERR_UNSUPPORTED
+
+
+# dL/dZ, or the table, in the memory that the gradient rows go to: both are read before any row is stored there.
+@pytest.mark.parametrize("shared", ["gz", "gz_shifted", "table"])
+@pytest.mark.parametrize("n_ent,n_rel,b,k,dim", [(3000, 40, 5000, 0, 128), (700, 9, 500, 1, 1024), (2000, 7, 333, 2, 36)])
+def test_semiring_backward_over_its_own_input(n_ent, n_rel, b, k, dim, shared):
+    wl, tabs, bt = _problem(n_ent, n_rel, b, k, dim, seed=b)
+    m = G.GpuModel(wl, tabs)
+    m.build(bt)
+    rows, n = m.inc.n_rows, m.inc.n_rows * dim
+    gz = G.dev_f32(np.random.default_rng(b).uniform(-1, 1, n))
+    work = torch.empty(3 * n, dtype=torch.float32, device=G.DEV)
+    table = m.params.ent.clone()
+    cols_max = min(m.inc.nnz, n_ent + n_rel)
+    room = torch.empty(n + (cols_max + 1) * dim, dtype=torch.float32, device=G.DEV)
+    off = (cols_max - 1) * dim if shared == "gz_shifted" else 0   # the last row that can be stored is dL/dZ's first
+    for kind, _ in KINDS:
+        B.stx_spmm_semiring_t(m.ctx, m.inc, m.params, kind, gz, work, m.grads)
+        u = int(m.inc.n_touched.item())
+        want = m.grads.rows.reshape(-1)[:u * dim].clone()
+        for static in (False, True):
+            if static and 3 * n * 4 > B.STX_STATIC_WORK_BYTES:
+                continue
+            g = B.Grads(m.ctx)
+            if shared == "table":
+                g.c.rows = m.params.ent.data_ptr()
+                src = gz
+            else:
+                g.c.rows = room.data_ptr()
+                src = room[off:off + n]
+                src.copy_(gz)
+            if static:
+                B.stx_spmm_semiring_t_static(m.ctx, m.inc, m.params, kind, src, g)
+            else:
+                B.stx_spmm_semiring_t(m.ctx, m.inc, m.params, kind, src, work, g)
+            got = (m.params.ent.reshape(-1) if shared == "table" else room)[:u * dim]
+            assert torch.equal(got, want), (kind, static)
+            m.params.ent.copy_(table)
