@@ -36,6 +36,7 @@ struct RankArgs {
     // [grp_offsets[g], + grp_counts[g]) (h, t and the outputs are grouped arrays) and table number blockIdx.z.
     const int32_t *grp_counts, *grp_offsets;
     int64_t table_stride;              // floats between the tables of consecutive blockIdx.z
+    const int32_t *gate;               // k_rank: nothing is done while this is zero; null: no such condition
 };
 
 // Narrows the arguments to the relation of this workgroup.
@@ -82,7 +83,13 @@ bool rank_filter_pays(int dist, int64_t queries, int64_t n_ent, int width, size_
 size_t rank_filter_q_bytes(int dist, int width, int64_t queries);                 // 0: a kind without a filtered sweep
 size_t rank_filter_e_bytes(int dist, int width, int64_t candidates, int tables);
 // True scores and counts (not the final square roots) through the filter.  nz: 0, or the number of relations of a
-// TransR launch (blockIdx.z), which must fit the scratch in one piece.  false: not for this kind, nothing launched.
-bool rank_filtered(stx_ctx *, const RankArgs &, int side, const RankScratch &, int nz, const RankIds &);
+// TransR launch (blockIdx.z), which must fit the scratch in one piece; queries: all of theirs.  false: not for this kind,
+// nothing launched.
+bool rank_filtered(stx_ctx *, const RankArgs &, int side, const RankScratch &, int nz, const RankIds &, int64_t queries);
+
+// ---- stx_rank.hip -------------------------------------------------------------------------------------
+// The plain sweep of queries [q0, q0 + nq) (TransR: of nz relations; q0 = 0), whose true sums are there and whose counters
+// are cleared, done on the GPU only where *gate is not zero by then.
+void rank_plain_behind(stx_ctx *, const RankArgs &, int side, int64_t q0, int64_t nq, int nz, const RankIds &, const int32_t *gate);
 
 }  // namespace stx

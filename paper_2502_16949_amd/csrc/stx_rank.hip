@@ -99,6 +99,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_rank(RankArgs a, RankIds ids)
     __shared__ __attribute__((aligned(16))) float s_q[kRankJ][kRankLd];
     __shared__ __attribute__((aligned(16))) float s_e[kRankJ][kRankLd];
 
+    if (a.gate && !*a.gate) return;
     rank_group(a, ids);
     const int tid = threadIdx.x;
     const int tx = tid & 15, ty = tid >> 4;               // candidate / query position of the 8 x 8 block
@@ -633,6 +634,32 @@ static void rank_sweep(stx_ctx *c, const RankArgs &a, const RankShape &sh, bool 
 #undef STX_RANK_GO
 }
 
+void rank_plain_behind(stx_ctx *c, const RankArgs &args, int side, int64_t q0, int64_t nq, int nz, const RankIds &ids,
+                       const int32_t *gate)
+{
+    RankArgs a = args;
+    if (!a.grp_counts) {
+        a.h += q0; a.r += q0; a.t += q0;
+        a.true_score += q0; a.n_less += q0; a.n_equal += q0;
+        a.nq = nq;
+    }
+    a.gate = gate;
+    // at most 4,096 workgroups, five rounds: far more would make the launch that returns at once a slow one
+    const RankShape sh = rank_shape(nq, a.n_ent, 2);
+    const int64_t tiles = ((int64_t)a.n_ent + kRankE - 1) / kRankE, qblocks = (int64_t)sh.grid.x * nz;
+    const int64_t slices = std::min((int64_t)sh.grid.y, std::max(4096 / qblocks, (int64_t)1));
+    a.slice = (int32_t)std::min((tiles + slices - 1) / slices * kRankE, (int64_t)0x7fffff80);
+    const dim3 grid(sh.grid.x, (unsigned)(((int64_t)a.n_ent + a.slice - 1) / a.slice), (unsigned)nz);
+    ProfScope prof(c, "k_rank");
+#define STX_BEHIND(D)                                                                                                do {                                                                                                                 if (side) hipLaunchKernelGGL((k_rank<D, true>), grid, dim3(kThreads), 0, c->stream, a, ids);                     else hipLaunchKernelGGL((k_rank<D, false>), grid, dim3(kThreads), 0, c->stream, a, ids);                     } while (0)
+    switch (c->cfg.dist) {                                 // the kinds that have a filtered sweep
+    case STX_L1: STX_BEHIND(STX_L1); break;
+    case STX_TORUS_L1: STX_BEHIND(STX_TORUS_L1); break;
+    default: STX_BEHIND(STX_L2); break;                    // (and squared L2: the same sums)
+    }
+#undef STX_BEHIND
+}
+
 stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const int32_t *r, const int32_t *t,
                        int64_t nq, int side, float *true_score, int32_t *n_less, int32_t *n_equal, void *work)
 {
@@ -643,10 +670,10 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
         const bool transh = c->cfg.model == STX_TRANSH;
         const RankShape sh = rank_shape(nq, n_ent, transh ? 4 : 2);   // TransH workgroups start with a dot product per query
         const RankArgs a{p->ent, transh ? p->rel : nullptr, transh ? p->w : nullptr, h, r, t, nq, n_ent, n_rel, c->cfg.dim,
-                         sh.slice, true_score, n_less, n_equal, bad, nullptr, nullptr, 0};
+                         sh.slice, true_score, n_less, n_equal, bad, nullptr, nullptr, 0, nullptr};
         const RankScratch ws{c->rank_q, c->rank_e, c->rank_q_bytes, c->rank_e_bytes, nullptr};
         if (rank_filter_pays(c->cfg.dist, nq, n_ent, c->cfg.dim, c->rank_q_bytes) &&
-            rank_filtered(c, a, side, ws, 0, RankIds{})) {
+            rank_filtered(c, a, side, ws, 0, RankIds{}, nq)) {
             if (c->cfg.dist == STX_L2)
                 hipLaunchKernelGGL((k_rank_finish<STX_L2>), sh.qgrid, dim3(kThreads), 0, c->stream, true_score, nq);
             return hip_ok(hipGetLastError());
@@ -684,9 +711,13 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
         if (max_n <= kRankBig) nz = n_occ - i < w.n_tables ? n_occ - i : w.n_tables;
         const RankShape sh = rank_shape(max_n, n_ent, 2);
         const RankArgs a{w.table, nullptr, nullptr, w.gh, nullptr, w.gt, max_n, n_ent, 1, k, sh.slice, w.gts, w.gless,
-                   w.gequal, bad, w.counts, w.offsets, stride};
+                   w.gequal, bad, w.counts, w.offsets, stride, nullptr};
         RankIds ids{};
-        for (int z = 0; z < nz; ++z) ids.g[z] = order[i + z];
+        int64_t queries = 0;
+        for (int z = 0; z < nz; ++z) {
+            ids.g[z] = order[i + z];
+            queries += counts[order[i + z]];
+        }
         i += nz;
         const dim3 pgrid((unsigned)((n_ent + kRankE - 1) / kRankE), (unsigned)((k + kRankQ - 1) / kRankQ), (unsigned)nz);
         {
@@ -694,7 +725,7 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
             hipLaunchKernelGGL(k_rr_project, pgrid, dim3(kThreads), 0, c->stream, p->ent, p->proj, p->rel, n_ent, dim, k,
                                w.table, ids, stride);
         }
-        if (!rank_filtered(c, a, side, w.ws, nz, ids)) rank_sweep(c, a, sh, false, side, ids, nz, false);
+        if (!rank_filtered(c, a, side, w.ws, nz, ids, queries)) rank_sweep(c, a, sh, false, side, ids, nz, false);
     }
     if (c->cfg.dist == STX_L2) hipLaunchKernelGGL((k_rank_finish<STX_L2>), qgrid, dim3(kThreads), 0, c->stream, w.gts, nq);
     if (c->cfg.dist == STX_TORUS_L2)

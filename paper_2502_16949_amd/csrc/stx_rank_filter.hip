@@ -9,7 +9,11 @@
 // the exhaustive fp32 sweep, bit for bit.  Wherever a bound is not finite (values out of range, infinities, NaN) the
 // candidate counts as undecided.
 //
-// Undecided pairs go to a list that k_rank_pairs works through.
+// Undecided pairs go to a list that k_rank_pairs works through; when it is full they are summed inside the sweep, one per
+// lane, at 20 to 130 times what a pair costs the plain sweep.  How many there are depends on the values: a sweep that
+// finds more than that can pay for (many equal rows, rows far outside the others' range) stops, and the plain sweep, which
+// is always launched behind it and otherwise returns at once, does the whole chunk.  59,071 queries x 15,000 equal rows at
+// d = 128 (L1) took 180 ms a side without that; the plain sweep takes 4.2.
 //
 // The plain sweep's rate is that of the vector ALU (two fp32 operations per element, five for the torus kind):
 // 59,071 queries x 15,000 entities at d = 128 (L1) took 3.85 ms a side and take 1.95; 256 x 4,000,000 (torus-L1) 10.2
@@ -20,6 +24,8 @@
 //                  bound is the sum of the roundings actually made in each row.
 //   L2, squared L2 k_rank_mfma: S = |q|^2 + |e|^2 - 2 q.e with q.e on the matrix cores, rows rounded to fp16 after
 //                  scaling by a power of two.  The bound is |q| |de| + |dq| |e| with the norms of the roundings made.
+#include <algorithm>
+
 #include "stx_rank.h"
 
 namespace stx {
@@ -33,6 +39,12 @@ constexpr int kSadThreads = 512;
 constexpr int kListCap = 128;          // undecided pairs a wavefront collects before it recomputes them
 constexpr float kUnit = 5.9604645e-8f; // 2^-24
 
+struct FilterState {
+    unsigned long long n_pairs;        // undecided pairs found (a sweep may find up to 2^31 x 2^31), cleared by k_rank_prep
+    int32_t pad[30];                   // (the wavefronts that read the rest do not wait for those that count)
+    int32_t full;                      // there were too many, in this sweep or one before it in the call
+    int32_t skip;                      // `full` as it was before this sweep, the same for all of its wavefronts
+};
 struct FilterArgs {
     RankArgs a;
     int32_t q_first;                   // first query of this chunk (relations: 0)
@@ -51,9 +63,12 @@ struct FilterArgs {
                                        //     the tile's scale, largest norm, largest rounding, squared-norm term
     int32_t slice;                     // sweeps: candidates (mfma) or query groups (sad) per blockIdx.y
     int head;                          // side: q = t - r instead of h + r
-    unsigned long long *n_pairs;       // undecided pairs found, cleared by k_rank_prep (a sweep may find up to 2^31 x 2^31) ...
-    uint2 *pairs;                      // ... and the pairs: (candidate | table << z_shift, position in the query arrays)
-    int32_t pair_cap;
+    FilterState *st;
+    int32_t first;                     // the first sweep of the call, and its k_rank_prep
+    int32_t tables;                    // relations of a TransR launch, else 1
+    uint2 *pairs;                      // undecided pairs: (candidate | table << z_shift, position in the query arrays)
+    int32_t pair_cap;                  // places of the list
+    unsigned long long pair_limit;     // undecided pairs beyond which the sweep stops
     int z_shift;                       // 32: one table
 };
 
@@ -159,11 +174,21 @@ __device__ inline void pair_recheck(const FilterArgs &f, uint2 pr, bool in, int 
 
 // All undecided pairs of a sweep, many wavefronts in flight: bound by the latency and the bytes of the rows it reads.
 template <int DIST>
-__global__ __launch_bounds__(kThreads) void k_rank_pairs(FilterArgs f)
+__global__ __launch_bounds__(kThreads) void k_rank_pairs(FilterArgs f, RankIds ids)
 {
+    if (f.st->full) {                                      // what the chunk's sweeps counted is not used
+        const RankArgs &a = f.a;
+        for (int z = 0; z < f.tables; ++z) {
+            const int64_t q0 = a.grp_counts ? a.grp_offsets[ids.g[z]] : f.q_first;
+            const int64_t nq = a.grp_counts ? a.grp_counts[ids.g[z]] : min(a.nq - f.q_first, (int64_t)f.q_cap);
+            for (int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x; i < nq; i += (int64_t)gridDim.x * kThreads)
+                a.n_less[q0 + i] = a.n_equal[q0 + i] = 0;
+        }
+        return;
+    }
     __shared__ uint2 s_ties[4][72];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int n = (int)min(*f.n_pairs, (unsigned long long)f.pair_cap), step = (int)gridDim.x * 32;
+    const int n = (int)min(f.st->n_pairs, (unsigned long long)f.pair_cap), step = (int)gridDim.x * 32;
     int n_ties = 0;
     for (int i0 = ((int)blockIdx.x * 4 + wave) * 8; i0 < n; i0 += step) {
         const int i = i0 + (lane >> 3);
@@ -178,18 +203,26 @@ __global__ __launch_bounds__(kThreads) void k_rank_pairs(FilterArgs f)
 }
 
 // A wavefront's collected pairs move to the list of the sweep; when that is full they are treated here, one per lane.
+// false: the sweep has found too many, nothing it counts is used any more.
 template <int DIST>
-__device__ inline void flush_pairs(const FilterArgs &f, const uint2 *list, int cnt, int lane)
+__device__ inline bool flush_pairs(const FilterArgs &f, const uint2 *list, int cnt, int lane)
 {
-    int base = 0;                                          // first place, pair_cap: none left
-    if (lane == 0) base = (int)min(atomicAdd(f.n_pairs, (unsigned long long)cnt), (unsigned long long)f.pair_cap);
+    int base = 0;                                          // first place, pair_cap: none left, beyond: stop
+    if (lane == 0) {
+        const unsigned long long n = atomicAdd(&f.st->n_pairs, (unsigned long long)cnt);
+        base = n > f.pair_limit ? f.pair_cap + 1 : (int)min(n, (unsigned long long)f.pair_cap);
+    }
     base = __builtin_amdgcn_readfirstlane(base);
+    if (base > f.pair_cap) {
+        if (lane == 0) __hip_atomic_store(&f.st->full, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return false;
+    }
     for (int i = lane; i < cnt; i += 64) {
         if (i < f.pair_cap - base) f.pairs[base + i] = list[i];
         else pair_exact<DIST>(f, list[i]);
     }
+    return true;
 }
-
 __device__ inline float max_group8(float v)
 {
 #pragma unroll
@@ -281,7 +314,12 @@ __global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds id
 {
     constexpr bool SAD = DIST == STX_L1 || DIST == STX_TORUS_L1, TORUS = DIST == STX_TORUS_L1;
     RankArgs a = f.a;
-    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) *f.n_pairs = 0ull;
+    if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) {
+        const int32_t full = f.first ? 0 : f.st->full;
+        f.st->n_pairs = 0ull;
+        f.st->skip = full;
+        if (f.first) f.st->full = 0;
+    }
     rank_group(a, ids);
     __shared__ float s_y[32][65];
     __shared__ float s_t[32];
@@ -409,7 +447,7 @@ __global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds id
         }
         return;
     }
-    if (SAD) return;
+    if (SAD || (!f.first && f.st->full)) return;
     // ---- 32 candidates: tile number et of the segment -----------------------------------------------------
     const int et = (int)blockIdx.x - f.nqb;
     const int64_t e = (int64_t)f.e_first + (int64_t)et * 32 + u;
@@ -476,6 +514,7 @@ __global__ __launch_bounds__(kSadThreads) void k_rank_sad(FilterArgs f)
     extern __shared__ __align__(16) unsigned char s_arena[];
     const RankArgs &a = f.a;
     const int np = f.np;
+    const int32_t full = f.st->full;                       // (tested below: the load travels beside those of the staging)
     uint4 *s_e = reinterpret_cast<uint4 *>(s_arena);                           // [piece][candidate]
     uint2 *s_list = reinterpret_cast<uint2 *>(s_e + (size_t)np * NE);          // [wavefront][kListCap]
     uint64_t *s_mask = reinterpret_cast<uint64_t *>(s_list + NW * kListCap);   // [wavefront][16 C]
@@ -520,6 +559,7 @@ __global__ __launch_bounds__(kSadThreads) void k_rank_sad(FilterArgs f)
     uint2 *list = s_list + wave * kListCap;
     uint64_t *masks = s_mask + wave * kSadGroup * C;
     int cnt = 0;
+    if (full) return;                                      // (no barrier from here on)
     for (int64_t g = (int64_t)blockIdx.y * f.slice + wave; g < g_end; g += NW) {
         const STX_CONST_AS uint32_t *qp = (const STX_CONST_AS uint32_t *)(f.qt + g * np * (4 * kSadGroup));
         uint32_t acc[C][kSadGroup];
@@ -572,7 +612,7 @@ __global__ __launch_bounds__(kSadThreads) void k_rank_sad(FilterArgs f)
             if (m >> lane & 1) list[cnt + mask_rank(m)] = make_uint2((uint32_t)(e0 + (i % C) * 64 + lane), (uint32_t)(q0 + i / C));
             cnt += __builtin_popcountll(m);
             if (cnt > kListCap - 64) {
-                flush_pairs<DIST>(f, list, cnt, lane);
+                if (!flush_pairs<DIST>(f, list, cnt, lane)) return;
                 cnt = 0;
             }
         }
@@ -622,6 +662,7 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int nq = (int)min(a.nq - f.q_first, (int64_t)f.q_cap);
     if ((int)blockIdx.x * 4 * QF * 32 >= nq) return;
+    const int32_t skip = f.first ? 0 : f.st->skip;
     const int q_base = f.q_first + (int)(a.true_score - f.a.true_score);       // position of the chunk in the query arrays
     const uint32_t zbits = f.z_shift < 32 ? (uint32_t)z << f.z_shift : 0u;
     // Wavefronts with queries of their own: four, or two or one where the workgroup's queries are few; the others take
@@ -666,6 +707,7 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
 #pragma unroll
     for (int q = 0; q < QF; ++q) less[q] = 0;
     int cnt = 0, t = t0;
+    bool listing = true;                                   // until there are too many undecided pairs
     floatx16 acc[QF];
     float w[QF];
     auto begin_tile = [&](const float *ta) {
@@ -702,7 +744,7 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
             less[q] += 16 - __builtin_popcount(neg | near);
             und |= near << (16 * (1 - q));
         }
-        while (__any(und != 0)) {
+        while (__any(und != 0) && listing) {
             const int i = __builtin_clz(und | 1u);
             const int e = f.e_first + t * 32 + (i & 3) + 8 * ((i >> 2) & 3) + 4 * half, q = (qb + i / 16) * 32 + (lane & 31);
             const uint64_t m = __ballot(und != 0 && e < a.n_ent && q < nq);
@@ -710,13 +752,17 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
             if (m >> lane & 1) s_list[wave][cnt + mask_rank(m)] = make_uint2((uint32_t)e | zbits, (uint32_t)(q_base + q));
             cnt += __builtin_popcountll(m);
             if (cnt > kListCap - 64) {
-                flush_pairs<STX_L2>(f, s_list[wave], cnt, lane);
+                listing = flush_pairs<STX_L2>(f, s_list[wave], cnt, lane);
                 cnt = 0;
             }
         }
     };
 #pragma unroll
     for (int c = 0; c < NB - 1; ++c) fetch(c, c);
+    if (skip) {
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        return;
+    }
     for (int c0 = 0; c0 < chunks; c0 += CPT) {
 #pragma unroll
         for (int cc = 0; cc < CPT; ++cc) {
@@ -761,7 +807,7 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
     }
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // (loads into LDS still in flight must not outlive the workgroup)
     if (!works) return;
-    if (cnt) flush_pairs<STX_L2>(f, s_list[wave], cnt, lane);
+    if (cnt && listing) flush_pairs<STX_L2>(f, s_list[wave], cnt, lane);
 #pragma unroll
     for (int q = 0; q < QF; ++q) {
         const int n = less[q] + __shfl_xor(less[q], 32, 64);
@@ -874,7 +920,8 @@ static void go_sad(stx_ctx *c, FilterArgs &f, int64_t nq)
     hipLaunchKernelGGL((k_rank_sad<DIST, C>), dim3((unsigned)gx, (unsigned)slices), dim3(kSadThreads), lds, c->stream, f);
 }
 
-bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &ws, int nz, const RankIds &ids)
+bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &ws, int nz, const RankIds &ids,
+                   int64_t queries)
 {
     const int dist = c->cfg.dist, width = a.dim;
     const bool sad = sad_kind(dist) && nz == 0;
@@ -892,9 +939,11 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
         q_each += mfma_query_bytes(f.np / 2);
     }
     // the list of undecided pairs takes a third of the query scratch; about one pair in a thousand to three hundred is
-    // undecided, so one table's sweep covers at most 1,000 pairs per place (fixed point; 32 queries at least) or 300
-    // (matrix cores).  Beyond the list, and TransR's sweeps cover any number, pairs are treated inside the sweep.
-    f.pair_cap = (int32_t)(ws.q_bytes / 3 / sizeof(uint2));
+    // undecided in tables of ordinary values, so one table's sweep covers at most 1,000 pairs per place (fixed point; 32
+    // queries at least) or 300 (matrix cores).  Beyond the list, and TransR's sweeps cover any number of pairs, they are
+    // treated inside the sweep.
+    f.pair_cap = (int32_t)std::min(ws.q_bytes / 3 / sizeof(uint2), (size_t)1 << 30);
+    f.tables = tables;
     f.z_shift = 32;
     if (nz > 0) {
         f.z_shift = 26;
@@ -908,7 +957,7 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
     if (cap < 32 || (nz > 0 && cap < a.nq)) return false;
     f.q_cap = (int32_t)cap;
     char *q = ws.q;
-    f.n_pairs = (unsigned long long *)q;
+    f.st = (FilterState *)q;
     f.pairs = (uint2 *)(q + 256);
     q += 256 + (size_t)f.pair_cap * sizeof(uint2);
     q += -(uintptr_t)q & 255u;
@@ -937,15 +986,26 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
         f.ef = (uint4 *)ws.e;
         f.eaux = (float *)(ws.e + (size_t)tiles * tables * (f.np / 2) * 1024 + 32 * 1024);
     }
+    int64_t swept = 0;                                         // pairs of the sweep at hand
+    auto limit = [&](int64_t nq) {
+        swept = (nz > 0 ? queries : nq) * (sad ? a.n_ent : f.e_count);
+        f.pair_limit = (unsigned long long)f.pair_cap + (unsigned long long)swept / 256;
+    };
     auto pairs = [&] {
         ProfScope prof(c, "k_rank_pairs");
-        const dim3 grid(2048);                                 // eight workgroups per compute unit
-        if (dist == STX_L1) hipLaunchKernelGGL((k_rank_pairs<STX_L1>), grid, dim3(kThreads), 0, c->stream, f);
-        else if (dist == STX_TORUS_L1) hipLaunchKernelGGL((k_rank_pairs<STX_TORUS_L1>), grid, dim3(kThreads), 0, c->stream, f);
-        else hipLaunchKernelGGL((k_rank_pairs<STX_L2>), grid, dim3(kThreads), 0, c->stream, f);
+        // up to eight workgroups per compute unit, 32 pairs each at a time, for one pair in 256
+        const dim3 grid((unsigned)std::min(std::max(swept / 8192, (int64_t)64), (int64_t)2048));
+        if (dist == STX_L1) hipLaunchKernelGGL((k_rank_pairs<STX_L1>), grid, dim3(kThreads), 0, c->stream, f, ids);
+        else if (dist == STX_TORUS_L1) hipLaunchKernelGGL((k_rank_pairs<STX_TORUS_L1>), grid, dim3(kThreads), 0, c->stream, f, ids);
+        else hipLaunchKernelGGL((k_rank_pairs<STX_L2>), grid, dim3(kThreads), 0, c->stream, f, ids);
+    };
+    // (a call whose pairs all fit the list needs none)
+    auto behind = [&](int64_t q0, int64_t nq) {
+        if ((unsigned long long)swept > f.pair_limit || seg < a.n_ent) rank_plain_behind(c, a, side, q0, nq, tables, ids, &f.st->full);
     };
     auto prep = [&](int nqb, int neb) {
         f.nqb = nqb;
+        f.first = f.q_first == 0 && f.e_first == 0;
         const dim3 grid((unsigned)(nqb + neb), 1, (unsigned)tables);
         ProfScope prof(c, "k_rank_prep");
 #define STX_PREP(D)                                                                                           \
@@ -965,11 +1025,13 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
         const int nqb = (int)((nq + 31) / 32);
         f.q_first = (int32_t)q0;
         if (sad) {
+            limit(nq);
             prep(nqb, 0);
             const bool narrow = width <= 256;                  // two candidates per lane while their tile leaves LDS for two workgroups
             if (dist == STX_L1) { if (narrow) go_sad<STX_L1, 2>(c, f, nq); else go_sad<STX_L1, 1>(c, f, nq); }
             else { if (narrow) go_sad<STX_TORUS_L1, 2>(c, f, nq); else go_sad<STX_TORUS_L1, 1>(c, f, nq); }
             pairs();
+            behind(q0, nq);
             continue;
         }
         for (int64_t e0 = 0; e0 < a.n_ent; e0 += seg) {
@@ -978,6 +1040,7 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
             const bool packed = q0 > 0 && seg >= a.n_ent;      // a table of one segment stays packed for the later chunks
             // (packed and no queries cannot both hold: the first segment of a chunk always has queries to prepare)
             const int nb_q = e0 == 0 ? nqb : 0, nb_e = packed ? 0 : (f.e_count + 31) / 32;
+            limit(nq);
             prep(nb_q, nb_e);
             switch (f.np / 2) {
             case 1: go_mfma_q<2, 1, 1>(c, f, nq, tables, ids); break;
@@ -995,6 +1058,7 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
             }
             pairs();
         }
+        behind(q0, nq);
     }
     return true;
 }

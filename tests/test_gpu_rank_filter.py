@@ -114,6 +114,76 @@ def test_transr_zero_projections_tie(dist):
         assert np.allclose(ts[r == 2], k if dist == "l2_sq" else np.sqrt(k), rtol=1e-6)
 
 
+# More undecided pairs than the list of a sweep holds: the plain sweep does the chunk.  In the first chunk of queries or in
+# a later one, over one segment of candidates or several, with the queries before and after it decided as usual.
+@pytest.mark.parametrize("dist,n_ent,dim,nq,equal", [
+    ("l1", 15_000, 128, 59_071, 15_000), ("l1", 4_097, 128, 9_000, 3_000), ("torus_l1", 40_000, 36, 700, 40_000),
+    ("l2", 4_129, 128, 9_000, 4_000), ("l2_sq", 2_050, 260, 5_250, 2_050), ("l2", 60_001, 16, 4_000, 50_000),
+    ("l2", 500_000, 100, 33, 400_000)])
+def test_tables_of_equal_rows(dist, n_ent, dim, nq, equal):
+    n_rel = 5
+    rng = np.random.default_rng(equal)
+    X = rng.uniform(0, 1, (n_ent + n_rel, dim)).astype(np.float32)
+    X[:equal] = X[n_ent - 1]
+    X[n_ent:] = X[n_ent]
+    h, t = (rng.integers(0, n_ent, nq).astype(np.int32) for _ in range(2))
+    if nq > 4_000 and equal < n_ent:                      # the first queries decide against the equal rows
+        h[:2_000] = rng.integers(equal, n_ent - 1, 2_000)
+        t[:2_000] = rng.integers(equal, n_ent - 1, 2_000)
+    r = rng.integers(0, n_rel, nq).astype(np.int32)
+    cfg = B.make_config("toruse" if dist.startswith("torus") else "transe", dist, n_ent, n_rel, dim, 8, 1)
+    ctx, p = B.Context(cfg, G.DEV), B.Params(G.dev_f32(X))
+    hd, rd, td = G.dev_i32(h), G.dev_i32(r), G.dev_i32(t)
+    parts = [(hd[i:i + 128].clone(), rd[i:i + 128].clone(), td[i:i + 128].clone()) for i in range(0, nq, 128)]
+    for side in (B.STX_TAIL, B.STX_HEAD):
+        got = _rank(ctx, p, hd, rd, td, side)
+        if 128.0 * n_ent * dim < FILTER_STEPS:
+            want = [torch.cat(x) for x in zip(*(_rank(ctx, p, *q, side) for q in parts))]
+        else:
+            want = [torch.from_numpy(x).to(G.DEV) for x in _by_ranges(cfg, X, h, r, t, side, n_ent, n_rel, dim, dist)]
+        for g, w in zip(got, want):
+            assert torch.equal(g, w)
+    if nq < 4_000 or 128.0 * n_ent * dim >= FILTER_STEPS:
+        return
+    # and at the plain sweep's pace (pair by pair, such a table took tens of times as long)
+    def seconds(f):
+        torch.cuda.synchronize()
+        a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+        a.record()
+        f()
+        b.record()
+        torch.cuda.synchronize()
+        return a.elapsed_time(b)
+    one = min(seconds(lambda: _rank(ctx, p, hd, rd, td, B.STX_TAIL)) for _ in range(3))
+    many = min(seconds(lambda: [_rank(ctx, p, *q, B.STX_TAIL) for q in parts]) for _ in range(3))
+    assert one < 2 * many, (one, many)
+
+
+def test_transr_relations_of_equal_rows():
+    # relations 1, 4, 7, ... map all entities to one point; they share launches with others that do not
+    n_ent, dim, k, n_rel, nq = 6_000, 64, 32, 40, 30_000
+    rng = np.random.default_rng(6)
+    M = rng.uniform(-1, 1, (n_rel, k, dim)).astype(np.float32)
+    M[1::3] = 0.0
+    R = rng.uniform(-1, 1, (n_rel, k)).astype(np.float32)
+    p = B.Params(G.dev_f32(rng.uniform(-1, 1, (n_ent, dim))), G.dev_f32(R), proj=G.dev_f32(M))
+    h, t = (rng.integers(0, n_ent, nq).astype(np.int32) for _ in range(2))
+    r = np.where(rng.random(nq) < 0.3, 1, rng.integers(0, n_rel, nq)).astype(np.int32)   # relation 1 has a launch of its own
+    ctx = B.Context(B.make_config("transr", "l2", n_ent, n_rel, dim, 8, 1, rel_dim=k, flags=B.STX_FLAG_BF16_PROJ), G.DEV)
+    work = torch.empty(B.stx_rank_work_bytes(ctx, nq) + 256, dtype=torch.uint8, device=G.DEV)
+    hd, rd, td = G.dev_i32(h), G.dev_i32(r), G.dev_i32(t)
+    for side in (B.STX_TAIL, B.STX_HEAD):
+        ts, less, equal = (x.cpu().numpy() for x in _rank(ctx, p, hd, rd, td, side, work))
+        flat = r % 3 == 1
+        assert not less[flat].any() and np.all(equal[flat] == n_ent)
+        for rel in (0, 2, 39):                            # the others as they come out in calls of their own
+            i = np.nonzero(r == rel)[0]
+            one = [x.cpu().numpy() for x in _rank(ctx, p, hd[i].clone(), rd[i].clone(), td[i].clone(), side, work)]
+            for a, b in zip((ts[i], less[i], equal[i]), one):
+                assert np.array_equal(a, b)
+            assert equal[i].max() <= 3
+
+
 # More undecided pairs in one sweep than an int32 counts (every candidate ties): a chunk of fixed-point queries is
 # never smaller than 32, and a TransR relation is swept in one piece.
 def test_more_undecided_pairs_than_an_int32_counts():
