@@ -36,6 +36,7 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kSadGroup = 16;          // queries per group of k_rank_sad: one accumulator each
 constexpr int kSadThreads = 512;
+constexpr int kNoQuery = -(1 << 30);   // threshold of the places past the last query
 constexpr int kListCap = 128;          // undecided pairs a wavefront collects before it recomputes them
 constexpr float kUnit = 5.9604645e-8f; // 2^-24
 
@@ -104,6 +105,26 @@ __device__ inline PairRows pair_rows(const FilterArgs &f, uint2 pr)
 // One term's difference as k_rank forms it (the factor +-1 is exact).
 __device__ inline float pair_diff(float sg, float qv, float ev) { return sg * (qv - ev); }
 
+// Counts of the active lanes' pairs.  A query that decides nothing brings many at once, and 400,000 additions to one
+// counter, one by one, take 5 ms: the pairs of one query are added together.  ALL: whatever queries the lanes hold,
+// else only where all hold the same one (the usual mixture costs less in single additions).
+template <bool ALL>
+__device__ inline void pair_count(const FilterArgs &f, int64_t q, bool less, bool equal)
+{
+    for (;;) {
+        const bool mine = (uint32_t)q == (uint32_t)__builtin_amdgcn_readfirstlane((int)q);
+        if (!ALL && __ballot(!mine) != 0ull) break;
+        const int nl = __builtin_popcountll(__ballot(mine && less)), ne = __builtin_popcountll(__ballot(mine && equal));
+        if (mask_rank(__ballot(true)) == 0) {
+            if (nl) atomicAdd(&f.a.n_less[q], nl);
+            if (ne) atomicAdd(&f.a.n_equal[q], ne);
+        }
+        if (mine) return;
+    }
+    if (less) atomicAdd(&f.a.n_less[q], 1);
+    if (equal) atomicAdd(&f.a.n_equal[q], 1);
+}
+
 // The index-order sum of one pair per lane.
 template <int DIST>
 __device__ inline void pair_exact(const FilterArgs &f, uint2 pr)
@@ -128,8 +149,7 @@ __device__ inline void pair_exact(const FilterArgs &f, uint2 pr)
                 acc = rank_step<DIST>(acc, pair_diff(sg, vq[u].w, ve[u].w));
             }
     }
-    if (acc < p.st) atomicAdd(&f.a.n_less[p.q], 1);
-    if (acc == p.st) atomicAdd(&f.a.n_equal[p.q], 1);
+    pair_count<true>(f, p.q, acc < p.st, acc == p.st);
 }
 
 // Eight lanes per pair: a sum in another order, which decides all but ties and near-ties; these go to `ties`.
@@ -163,10 +183,8 @@ __device__ inline void pair_recheck(const FilterArgs &f, uint2 pr, bool in, int 
     // index-order one by at most (dim + 2) 2^-24.
     const float wd = ((float)dim * 1.126f + 16.f) * kUnit * s;
     const bool less = !self && s + wd < p.st, tie = !self && !less && !(s - wd > p.st);
-    if ((lane & 7) == 0 && in) {
-        if (less) atomicAdd(&f.a.n_less[p.q], 1);
-        if (self && p.st == p.st) atomicAdd(&f.a.n_equal[p.q], 1);   // the very sum k_rank_prep formed
-    }
+    const bool one = (lane & 7) == 0 && in;
+    pair_count<false>(f, p.q, one && less, one && self && p.st == p.st);   // (the true entity: the very sum k_rank_prep formed)
     const uint64_t m = __ballot(tie && in && (lane & 7) == 0);
     if (m >> lane & 1) ties[n_ties + mask_rank(m)] = pr;
     n_ties += __builtin_popcountll(m);
@@ -279,14 +297,17 @@ __device__ inline uint32_t fixed16(float v, float sc, bool upper_q, float &res)
 }
 
 // ---- scale of the L1 kind ---------------------------------------------------------------------------------
-// The largest element among up to 128 queries' points and true entities sets the range of the fixed-point numbers.
-// (Elements beyond it are clamped; what that loses is part of their row's bound.)  One workgroup.
+// Up to 128 queries' points and true entities are looked at.  The largest element sets the range of the fixed-point numbers
+// (elements beyond it are clamped; what that loses is part of their row's bound), but where few rows lie far outside the
+// others' range, leaving those undecided costs less than the coarser steps of all: of the rows' largest elements the one
+// is taken at which the share of rows beyond it, and of pairs that its steps leave undecided (about one in 2,000 where
+// it is the median), add up to the least.  One workgroup.
 template <bool HEAD>
 __global__ __launch_bounds__(1024) void k_rank_scale(RankArgs a, float *scale)
 {
-    __shared__ float s_mx[16];
+    __shared__ float s_mx[128], s_med, s_best[2][2];
     const int u = (int)threadIdx.x >> 3, l8 = (int)threadIdx.x & 7;
-    const int64_t q = a.nq <= 128 ? min((int64_t)u, a.nq - 1) : (int64_t)u * (a.nq / 128);
+    const int64_t q = a.nq <= 128 ? u % a.nq : (int64_t)u * (a.nq / 128);
     const RankRows rw = rank_rows<HEAD>(a, q);
     float mx = 0.f;
     for (int j = l8 * 4; j < a.dim; j += 32) {
@@ -295,14 +316,35 @@ __global__ __launch_bounds__(1024) void k_rank_scale(RankArgs a, float *scale)
         mx = fmaxf(fmaxf(fmaxf(mx, fabsf(q4.x)), fmaxf(fabsf(q4.y), fabsf(q4.z))), fabsf(q4.w));
         mx = fmaxf(fmaxf(fmaxf(mx, fabsf(ve.x)), fmaxf(fabsf(ve.y), fabsf(ve.z))), fabsf(ve.w));
     }
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) mx = fmaxf(mx, __shfl_xor(mx, m, 64));
-    if ((threadIdx.x & 63) == 0) s_mx[threadIdx.x >> 6] = mx;
+    mx = max_group8(mx);
+    if (l8 == 0) s_mx[u] = mx;
     __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int i = 1; i < 16; ++i) mx = fmaxf(mx, s_mx[i]);
-        *scale = (mx > 1e-12f && mx < 1e12f) ? 32767.f / mx : 1.f;
+    const int me = (int)threadIdx.x;
+    int above = 0, before = 0;
+    if (me < 128) {
+        mx = s_mx[me];
+#pragma unroll 16
+        for (int i = 0; i < 128; ++i) {
+            const float o = s_mx[i];
+            above += o > mx;
+            before += o < mx || (o == mx && i < me);
+        }
+        if (before == 64) s_med = mx;
     }
+    __syncthreads();
+    if (me < 128) {
+        const float med = s_med > 1e-12f ? s_med : mx;
+        const bool usable = mx > 1e-12f && mx < 1e12f;
+        float cost = usable ? (float)above * (1.f / 128.f) + 5e-4f * (mx / med) : __builtin_inff(), best = usable ? mx : 32767.f;
+#pragma unroll
+        for (int m = 32; m >= 1; m >>= 1) {
+            const float oc = __shfl_xor(cost, m, 64), ob = __shfl_xor(best, m, 64);
+            if (oc < cost) { cost = oc; best = ob; }
+        }
+        if ((me & 63) == 0) { s_best[me >> 6][0] = cost; s_best[me >> 6][1] = best; }
+    }
+    __syncthreads();
+    if (me == 0) *scale = 32767.f / (s_best[1][0] < s_best[0][0] ? s_best[1][1] : s_best[0][1]);   // none usable: 1
 }
 
 // ---- preparation ------------------------------------------------------------------------------------------
@@ -396,7 +438,7 @@ __global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds id
             }
             res = group_sum<8>(res);
             if (l8 == 0) {
-                int2 thr = make_int2(-(1 << 30), -(1 << 30));  // past the last query: nothing is below, nothing undecided
+                int2 thr = make_int2(kNoQuery, kNoQuery);  // past the last query: nothing is below, nothing undecided
                 if (ql < nq) {
                     // the index-order sum is within (dim + 8) 2^-24 of the sum of its terms' exact values
                     const double t = (double)st * (double)sc, rel = 1.02 * (dim + 8) * (double)kUnit;
@@ -538,21 +580,30 @@ __global__ __launch_bounds__(kSadThreads) void k_rank_sad(FilterArgs f)
         atomicAdd(&s_res[c], res);
     }
     __syncthreads();
-    // the largest rounding of the wavefront's candidates, in whole units
+    // The largest rounding of the tile's candidates, in whole units.  Candidates with far larger ones (clamped rows, infinities,
+    // NaN) do not count: they are left undecided one by one instead of widening the bound for all.  (Elements inside the
+    // range are off by half a unit each; four times the smallest: the torus kind's unwrapped rows are all off by more.)
+    uint64_t valid[C], out[C];
+    float least = __builtin_inff();
+#pragma unroll
+    for (int c = 0; c < C; ++c) least = fminf(least, s_res[c * 64 + lane]);
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) least = fminf(least, __shfl_xor(least, m, 64));
+    const float far = fminf(fmaxf(0.55f * 8.f * (float)np + 1.f, 4.f * least), 1e8f);
     float res = 0.f;
-    uint64_t valid[C];
-    bool finite = true;
+    bool any_out = false;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
         const float r = s_res[c * 64 + lane];
-        finite = finite && r < 1e8f;
-        res = fmaxf(res, r);
-        valid[c] = __ballot(e0 + c * 64 + lane < a.n_ent);
+        const uint64_t in = __ballot(e0 + c * 64 + lane < a.n_ent);
+        out[c] = __ballot(!(r <= far)) & in;
+        valid[c] = in & ~out[c];
+        any_out = any_out || out[c] != 0ull;
+        if (r <= far) res = fmaxf(res, r);
     }
 #pragma unroll
     for (int m = 32; m >= 1; m >>= 1) res = fmaxf(res, __shfl_xor(res, m, 64));
-    int er = __builtin_amdgcn_readfirstlane((int)ceilf(res * 1.001f) + 1);
-    if (!__all(finite)) er = 1 << 29;
+    const int er = __builtin_amdgcn_readfirstlane((int)ceilf(res * 1.001f) + 1);
 
     const int64_t ngroups = ((int64_t)min(a.nq - f.q_first, (int64_t)f.q_cap) + kSadGroup - 1) / kSadGroup;
     const int64_t g_end = min((int64_t)(blockIdx.y + 1) * f.slice, ngroups);
@@ -602,6 +653,15 @@ __global__ __launch_bounds__(kSadThreads) void k_rank_sad(FilterArgs f)
                 }
             }
             lessv = lane == q ? n : lessv;
+        }
+        if (any_out) {
+#pragma unroll 1
+            for (int i = 0; i < kSadGroup * C; ++i) {
+                const uint64_t o = C == 2 && (i & 1) ? out[C - 1] : out[0];
+                if (!o || thr[i / C].y == kNoQuery) continue;
+                masks[i] = o | (dirty >> i & 1u ? masks[i] : 0ull);
+                dirty |= 1u << i;
+            }
         }
         const int64_t q0 = f.q_first + g * kSadGroup;
         if (lane < kSadGroup && lessv) atomicAdd(&a.n_less[q0 + lane], lessv);
@@ -989,7 +1049,8 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
     int64_t swept = 0;                                         // pairs of the sweep at hand
     auto limit = [&](int64_t nq) {
         swept = (nz > 0 ? queries : nq) * (sad ? a.n_ent : f.e_count);
-        f.pair_limit = (unsigned long long)f.pair_cap + (unsigned long long)swept / 256;
+        // (inside the sweep a pair costs 42 times what it costs the plain one at d = 128, L1; 13 to 23 times with the L2 kinds)
+        f.pair_limit = (unsigned long long)f.pair_cap + (unsigned long long)swept / (sad ? 256 : 128);
     };
     auto pairs = [&] {
         ProfScope prof(c, "k_rank_pairs");
