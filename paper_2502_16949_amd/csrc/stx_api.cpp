@@ -247,7 +247,6 @@ stx_status stx_create(const stx_config *cfg, void *workspace, size_t workspace_b
     c->ahead.inc = nullptr;
     c->sorted_inc = nullptr;
     c->sampled_inc = nullptr;
-    c->fwd_serial = 0;
     c->sorted_keys = nullptr;
     c->prof_ev = nullptr;
     c->prof_tag = nullptr;

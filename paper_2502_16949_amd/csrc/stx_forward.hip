@@ -37,23 +37,18 @@ __global__ __launch_bounds__(kThreads) void k_finish_loss(const float *__restric
     finish_loss_body(partials, n, scale, loss);
 }
 
-// general_flag (may be null): the kernel runs only if *general_flag == serial, i.e. if the fast kernel before it met
-// a positive whose negatives it does not cover; it then redoes the whole batch (the same bits where both apply).
-template <int LPR, int ITERS, int DIST, bool FROM_Y, bool PACKED>
-__global__ __launch_bounds__(kThreads, ITERS == 1 ? 8 : 1) void k_forward_stacked(ForwardArgs a, const int32_t *general_flag,
-                                                                                 int32_t serial)
+template <int LPR, int ITERS, int DIST>
+__global__ __launch_bounds__(kThreads, ITERS == 1 ? 8 : 1) void k_forward_y(ForwardArgs a)
 {
-    if (general_flag && *general_flag != serial) return;
-    forward_stacked_body<LPR, ITERS, DIST, FROM_Y, PACKED>((int)blockIdx.x, a);
+    forward_y_body<LPR, ITERS, DIST>((int)blockIdx.x, a);
 }
 
 // (rows of one float4 per lane: 64 registers, every workgroup of a large batch resident at once; wider rows hold
 // four rows of ITERS float4 per lane)
-template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE>
-__global__ __launch_bounds__(kThreads, ITERS == 1 ? (NB == 1 || (PACKED && !MORE) ? 8 : PACKED ? 6 : 5) : ITERS == 2 ? (NB > 1 ? 3 : 4) : 2) void k_forward_fast(ForwardArgs a, int32_t *general_flag,
-                                                                                                 int32_t serial)
+template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK>
+__global__ __launch_bounds__(kThreads, ITERS == 1 ? (NB == 1 || (PACKED && !MORE && !CHECK) ? 8 : PACKED && !(MORE && CHECK) ? 6 : 5) : ITERS == 2 ? (NB > 1 ? 3 : 4) : 2) void k_forward_stacked(ForwardArgs a)
 {
-    forward_fast_body<LPR, ITERS, DIST, PACKED, NB, MORE>((int)blockIdx.x, a, general_flag, serial);
+    forward_body<LPR, ITERS, DIST, PACKED, NB, MORE, CHECK>((int)blockIdx.x, a);
 }
 
 // TransR in stx_train_step: the first kernel of the next batch's build (which also counts the rows per relation)
@@ -62,7 +57,7 @@ template <int LPR, int ITERS, int DIST>
 __global__ __launch_bounds__(kThreads) void k_forward_y_emit(ForwardArgs a, EmitAhead ea)
 {
     if ((int)blockIdx.x < ea.ntiles) emit_body<kSortItems, true, true, true>((int)blockIdx.x, ea.ntiles, ea.args);
-    else forward_stacked_body<LPR, ITERS, DIST, true, false>((int)blockIdx.x - ea.ntiles, a);
+    else forward_y_body<LPR, ITERS, DIST>((int)blockIdx.x - ea.ntiles, a);
 }
 
 __global__ void k_zero_loss(float *loss) { loss[0] = 0.f; }
@@ -157,65 +152,38 @@ static void forward_go(stx_ctx *c, const stx_incidence *inc, const stx_params *p
     EmitAhead ea{};
     if (from_y && c->ahead.armed && !c->ahead.emit_done && c->ahead.args.rc.cur) ea = take_emit_ahead(c);
     const dim3 grid_e(grid.x + (unsigned)ea.ntiles);
-    // The kernel that fetches the positive's rows once (forward_fast_body) covers negatives that keep the relation and
-    // one entity of their positive; when the batch was not drawn by the library's sampler in this build, the general
-    // kernel is enqueued behind it and runs only if the fast one met another kind of negative.
-    const bool fast = !from_y;
+    // Negatives that the library's sampler drew in this build need no check of their kind.
     const bool sampled = c->sampled_inc == inc;
-    int32_t *flag = c->ctrl + CTRL_GENERAL;
-    const int32_t serial = fast ? ++c->fwd_serial : 0;
-#define STX_FWD(D, Y, P)                                                                                        \
-    hipLaunchKernelGGL((k_forward_stacked<LPR, ITERS, D, Y, P>), grid, dim3(kThreads), 0, c->stream, fa,        \
-                       fast ? flag : nullptr, serial)
-#define STX_FAST(D, P)                                                                                          \
+#define STX_ROWS2(D, P, NB, MORE)                                                                               \
     do {                                                                                                        \
-        if (inc->k <= 1)                                                                                        \
-            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, true), false>), grid, dim3(kThreads), 0, \
-                               c->stream, fa, flag, serial);                                                    \
-        else if (inc->k <= 4)                                                                                   \
-            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, false), (ITERS > 2)>), grid, dim3(kThreads), 0, \
-                               c->stream, fa, flag, serial);                                                    \
+        if (sampled)                                                                                            \
+            hipLaunchKernelGGL((k_forward_stacked<LPR, ITERS, D, P, NB, MORE, false>), grid, dim3(kThreads), 0, c->stream, fa); \
         else                                                                                                    \
-            hipLaunchKernelGGL((k_forward_fast<LPR, ITERS, D, P, fast_batch(ITERS, false), true>), grid, dim3(kThreads), 0, \
-                               c->stream, fa, flag, serial);                                                    \
+            hipLaunchKernelGGL((k_forward_stacked<LPR, ITERS, D, P, NB, MORE, true>), grid, dim3(kThreads), 0, c->stream, fa); \
     } while (0)
-#define STX_FWD2(D)                                                                                             \
+#define STX_ROWS(D, P)                                                                                          \
     do {                                                                                                        \
-        if (from_y && ea.ntiles)                                                                                \
-            hipLaunchKernelGGL((k_forward_y_emit<LPR, ITERS, D>), grid_e, dim3(kThreads), 0, c->stream, fa, ea); \
-        else if (from_y) STX_FWD(D, true, false);                                                               \
-        else {                                                                                                  \
-            if (fast) {                                                                                         \
-                ProfScope prof(c, "k_forward_stacked");                                                         \
-                STX_FAST(D, is_sign_kind(D));                                                                   \
-            }                                                                                                   \
-            if (!fast || !sampled) {                                                                            \
-                ProfScope prof(c, fast ? "k_forward_general" : "k_forward_stacked");                            \
-                STX_FWD(D, false, is_sign_kind(D));                                                             \
-            }                                                                                                   \
-        }                                                                                                       \
+        if (inc->k <= 1) STX_ROWS2(D, P, fast_batch(ITERS, true), false);                                       \
+        else if (inc->k <= 4) STX_ROWS2(D, P, fast_batch(ITERS, false), (ITERS > 2));                           \
+        else STX_ROWS2(D, P, fast_batch(ITERS, false), true);                                                   \
     } while (0)
-    if (from_y) {
-        ProfScope prof(c, "k_forward_stacked");
-        switch (c->cfg.dist) {
-        case STX_L1: STX_FWD2(STX_L1); break;
-        case STX_L2: STX_FWD2(STX_L2); break;
-        case STX_TORUS_L1: STX_FWD2(STX_TORUS_L1); break;
-        case STX_L2_SQ: STX_FWD2(STX_L2_SQ); break;
-        default: STX_FWD2(STX_TORUS_L2); break;
-        }
-    } else {
-        switch (c->cfg.dist) {
-        case STX_L1: STX_FWD2(STX_L1); break;
-        case STX_L2: STX_FWD2(STX_L2); break;
-        case STX_TORUS_L1: STX_FWD2(STX_TORUS_L1); break;
-        case STX_L2_SQ: STX_FWD2(STX_L2_SQ); break;
-        default: STX_FWD2(STX_TORUS_L2); break;
-        }
+#define STX_FWD(D)                                                                                              \
+    do {                                                                                                        \
+        ProfScope prof(c, "k_forward_stacked");                                                                 \
+        if (!from_y) STX_ROWS(D, is_sign_kind(D));                                                              \
+        else if (ea.ntiles) hipLaunchKernelGGL((k_forward_y_emit<LPR, ITERS, D>), grid_e, dim3(kThreads), 0, c->stream, fa, ea); \
+        else hipLaunchKernelGGL((k_forward_y<LPR, ITERS, D>), grid, dim3(kThreads), 0, c->stream, fa);          \
+    } while (0)
+    switch (c->cfg.dist) {
+    case STX_L1: STX_FWD(STX_L1); break;
+    case STX_L2: STX_FWD(STX_L2); break;
+    case STX_TORUS_L1: STX_FWD(STX_TORUS_L1); break;
+    case STX_L2_SQ: STX_FWD(STX_L2_SQ); break;
+    default: STX_FWD(STX_TORUS_L2); break;
     }
-#undef STX_FAST
-#undef STX_FWD2
 #undef STX_FWD
+#undef STX_ROWS
+#undef STX_ROWS2
     if (c->defer_finish) { c->fin_n = (int)grid.x; c->fin_scale = scale; c->fin_loss = loss; }
     else launch_finish_loss(c, (int)grid.x, scale, loss);
 }

@@ -84,11 +84,12 @@ __device__ inline void finish_loss_body(const float *__restrict__ partials, int 
 // (3 + k table rows instead of 3 + 3k), so a wavefront pays two dependent memory round trips.  Further negatives
 // follow NB at a time, their ids requested a batch ahead, so each batch costs one more.
 // x is formed by the same two roundings in the same order as a full gather would: the bits are those of
-// forward_stacked_body.  A group that finds another kind of negative (a caller's own) stores `serial` in
-// *general_flag: the caller then runs the general kernel, which redoes the batch.
+// forward_any_rows.
 // MORE: the batch may have more than NB negatives per positive (the loop costs registers).
-template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE>
-__device__ inline void forward_fast_body(const int block, const ForwardArgs &a, int32_t *general_flag, int32_t serial)
+// CHECK: the negatives may be a caller's own.  false is returned, by all lanes of the group, when one of another kind
+// turns up: what was written until then is to be written again (forward_any_rows).
+template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK>
+__device__ inline bool forward_fast_rows(const int32_t i, const int lig, const ForwardArgs &a, float &hinge_sum)
 {
     constexpr int NI = (3 + 3 * NB + LPR - 1) / LPR;       // column ids per lane
     const int32_t *__restrict__ colidx = a.colidx;
@@ -96,107 +97,93 @@ __device__ inline void forward_fast_body(const int block, const ForwardArgs &a, 
     const int32_t b = a.b, k = a.k;
     const int dim = a.dim, d4 = dim / 4, gstride = a.gstride;
     float *__restrict__ scores = a.scores;
-    constexpr int GROUPS = kThreads / LPR;
-    __shared__ float s_loss[GROUPS];
-    const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
-    const int32_t i = block * GROUPS + grp;
-    float hinge_sum = 0.f;
-    if (i < b) {
-        const int32_t row0 = b + i * k;
-        int32_t mine[NI];                                  // id j of (positive, negatives of the batch) in lane j % LPR
+    const int32_t row0 = b + i * k;
+    int32_t mine[NI];                                  // id j of (positive, negatives of the batch) in lane j % LPR
 #pragma unroll
-        for (int u = 0; u < NI; ++u) {
-            const int j = lig + u * LPR;
-            mine[u] = 0;
-            if (j < 3 + 3 * min(k, NB)) mine[u] = colidx[j < 3 ? 3 * (int64_t)i + j : 3 * (int64_t)row0 + (j - 3)];
-        }
-        auto id = [&](int j) { return __shfl(mine[j / LPR], j % LPR, LPR); };
-        const int32_t c0 = id(0), c1 = id(1), c2 = id(2);
-        const float wr = a.rel_weight ? a.rel_weight[c1 - a.n_ent] : 1.0f;
-        // (lanes past the row's width hold zeros and take part in the reductions only)
-        RowVec<ITERS> hr, pr, pt, xp;
-        load_vec<LPR, ITERS>(X + (int64_t)c0 * dim, d4, lig, hr);
-        load_vec<LPR, ITERS>(X + (int64_t)c1 * dim, d4, lig, pr);
-        load_vec<LPR, ITERS>(X + (int64_t)c2 * dim, d4, lig, pt);
-        uint8_t *recs = reinterpret_cast<uint8_t *>(a.G);
-        float *gcoef = PACKED ? reinterpret_cast<float *>(recs + packed_coef_offset((int64_t)b * (1 + k), gstride)) : nullptr;
-        bool shared = true;
-        int n_active = 0;
-        float npos = 0.f, dpos = 0.f;
-        for (int q0 = 0; q0 == 0 || (MORE && q0 < k); q0 += NB) {
-            int32_t ce[NB];
-            unsigned tail_mask = 0;
-#pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                const int32_t nh = id(3 + 3 * q), nr = id(4 + 3 * q), nt = id(5 + 3 * q);
-                const bool ts = nh == c0;
-                ce[q] = ts ? nt : nh;
-                tail_mask |= ts ? 1u << q : 0u;
-                if (q0 + q < k) shared = shared && nr == c1 && (ts || nt == c2);
-            }
-            RowVec<ITERS> e[NB];
-#pragma unroll
-            for (int q = 0; q < NB; ++q)
-                if (q0 + q < k) {
-                    // a row used once does not displace the others when the table is far larger than the caches
-                    if (a.stream_rows) load_vec_stream<LPR, ITERS>(X + (int64_t)ce[q] * dim, d4, lig, e[q]);
-                    else load_vec<LPR, ITERS>(X + (int64_t)ce[q] * dim, d4, lig, e[q]);
-                }
-            if (MORE && q0 + NB < k) {                     // the next batch's ids, in the places of this one's
-#pragma unroll
-                for (int u = 0; u < NI; ++u) {
-                    const int j = lig + u * LPR;
-                    if (j >= 3 && j < 3 + 3 * min(k - q0 - NB, NB)) mine[u] = colidx[3 * (int64_t)(row0 + q0 + NB) + (j - 3)];
-                }
-            }
-            if (q0 == 0) {
-#pragma unroll
-                for (int it = 0; it < ITERS; ++it) {
-                    hr.v[it] = add4(hr.v[it], pr.v[it]);
-                    xp.v[it] = sub4(hr.v[it], pt.v[it]);
-                }
-                npos = row_distance<LPR, ITERS, DIST>(xp);
-                dpos = wr * npos;
-                if (lig == 0) scores[i] = dpos;
-            }
-#pragma unroll
-            for (int q = 0; q < NB; ++q)
-                if (q0 + q < k) {
-                    RowVec<ITERS> x;
-#pragma unroll
-                    for (int it = 0; it < ITERS; ++it)
-                        x.v[it] = (tail_mask >> q & 1u) ? sub4(hr.v[it], e[q].v[it]) : sub4(add4(e[q].v[it], pr.v[it]), pt.v[it]);
-                    const float nneg = row_distance<LPR, ITERS, DIST>(x);
-                    const float dneg = wr * nneg;
-                    const float arg = (a.margin + dpos) - dneg;
-                    const bool active = arg > 0.f;
-                    const int32_t row = row0 + q0 + q;
-                    if (lig == 0) scores[row] = dneg;
-                    if (active) { hinge_sum += arg; ++n_active; }
-                    if (PACKED)
-                        write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, row, d4, lig, x, active ? -a.scale * wr : 0.f);
-                    else if (a.coefs) {
-                        if (lig == 0) a.coefs[row] = formed_coef<DIST>(active ? -a.scale * wr : 0.f, nneg);
-                    } else
-                        write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)row * dim, d4, lig, x, active ? -a.scale * wr : 0.f, nneg);
-                }
-        }
-        if (PACKED)
-            write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, i, d4, lig, xp, (float)n_active * a.scale * wr);
-        else if (a.coefs) {
-            if (lig == 0) a.coefs[i] = formed_coef<DIST>((float)n_active * a.scale * wr, npos);
-        } else
-            write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)i * dim, d4, lig, xp, (float)n_active * a.scale * wr, npos);
-        if (!shared && lig == 0 && general_flag) *general_flag = serial;
+    for (int u = 0; u < NI; ++u) {
+        const int j = lig + u * LPR;
+        mine[u] = 0;
+        if (j < 3 + 3 * min(k, NB)) mine[u] = colidx[j < 3 ? 3 * (int64_t)i + j : 3 * (int64_t)row0 + (j - 3)];
     }
-    if (lig == 0) s_loss[grp] = hinge_sum;
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float sum = 0.f;
+    auto id = [&](int j) { return __shfl(mine[j / LPR], j % LPR, LPR); };
+    const int32_t c0 = id(0), c1 = id(1), c2 = id(2);
+    const float wr = a.rel_weight ? a.rel_weight[c1 - a.n_ent] : 1.0f;
+    // (lanes past the row's width hold zeros and take part in the reductions only)
+    RowVec<ITERS> hr, pr, pt, xp;
+    load_vec<LPR, ITERS>(X + (int64_t)c0 * dim, d4, lig, hr);
+    load_vec<LPR, ITERS>(X + (int64_t)c1 * dim, d4, lig, pr);
+    load_vec<LPR, ITERS>(X + (int64_t)c2 * dim, d4, lig, pt);
+    uint8_t *recs = reinterpret_cast<uint8_t *>(a.G);
+    float *gcoef = PACKED ? reinterpret_cast<float *>(recs + packed_coef_offset((int64_t)b * (1 + k), gstride)) : nullptr;
+    bool shared = true;
+    int n_active = 0;
+    float npos = 0.f, dpos = 0.f;
+    for (int q0 = 0; q0 == 0 || (MORE && q0 < k); q0 += NB) {
+        int32_t ce[NB];
+        unsigned tail_mask = 0;
 #pragma unroll
-        for (int g = 0; g < GROUPS; ++g) sum += s_loss[g];
-        a.loss_partials[block] = sum;
+        for (int q = 0; q < NB; ++q) {
+            const int32_t nh = id(3 + 3 * q), nr = id(4 + 3 * q), nt = id(5 + 3 * q);
+            const bool ts = nh == c0;
+            ce[q] = ts ? nt : nh;
+            tail_mask |= ts ? 1u << q : 0u;
+            if (CHECK && q0 + q < k) shared = shared && nr == c1 && (ts || nt == c2);
+        }
+        if (CHECK && !shared) return false;
+        RowVec<ITERS> e[NB];
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+            if (q0 + q < k) {
+                // a row used once does not displace the others when the table is far larger than the caches
+                if (a.stream_rows) load_vec_stream<LPR, ITERS>(X + (int64_t)ce[q] * dim, d4, lig, e[q]);
+                else load_vec<LPR, ITERS>(X + (int64_t)ce[q] * dim, d4, lig, e[q]);
+            }
+        if (MORE && q0 + NB < k) {                     // the next batch's ids, in the places of this one's
+#pragma unroll
+            for (int u = 0; u < NI; ++u) {
+                const int j = lig + u * LPR;
+                if (j >= 3 && j < 3 + 3 * min(k - q0 - NB, NB)) mine[u] = colidx[3 * (int64_t)(row0 + q0 + NB) + (j - 3)];
+            }
+        }
+        if (q0 == 0) {
+#pragma unroll
+            for (int it = 0; it < ITERS; ++it) {
+                hr.v[it] = add4(hr.v[it], pr.v[it]);
+                xp.v[it] = sub4(hr.v[it], pt.v[it]);
+            }
+            npos = row_distance<LPR, ITERS, DIST>(xp);
+            dpos = wr * npos;
+            if (lig == 0) scores[i] = dpos;
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q)
+            if (q0 + q < k) {
+                RowVec<ITERS> x;
+#pragma unroll
+                for (int it = 0; it < ITERS; ++it)
+                    x.v[it] = (tail_mask >> q & 1u) ? sub4(hr.v[it], e[q].v[it]) : sub4(add4(e[q].v[it], pr.v[it]), pt.v[it]);
+                const float nneg = row_distance<LPR, ITERS, DIST>(x);
+                const float dneg = wr * nneg;
+                const float arg = (a.margin + dpos) - dneg;
+                const bool active = arg > 0.f;
+                const int32_t row = row0 + q0 + q;
+                if (lig == 0) scores[row] = dneg;
+                if (active) { hinge_sum += arg; ++n_active; }
+                if (PACKED)
+                    write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, row, d4, lig, x, active ? -a.scale * wr : 0.f);
+                else if (a.coefs) {
+                    if (lig == 0) a.coefs[row] = formed_coef<DIST>(active ? -a.scale * wr : 0.f, nneg);
+                } else
+                    write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)row * dim, d4, lig, x, active ? -a.scale * wr : 0.f, nneg);
+            }
     }
+    if (PACKED)
+        write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, i, d4, lig, xp, (float)n_active * a.scale * wr);
+    else if (a.coefs) {
+        if (lig == 0) a.coefs[i] = formed_coef<DIST>((float)n_active * a.scale * wr, npos);
+    } else
+        write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)i * dim, d4, lig, xp, (float)n_active * a.scale * wr, npos);
+    return true;
 }
 
 // One group per positive i: rows i and b + i*k + kk (kk < k).
@@ -206,11 +193,10 @@ __device__ inline void forward_fast_body(const int block, const ForwardArgs &a, 
 //                 written by one group only.
 // PACKED (L1 kinds, gathered rows only): dL/dx is written as records of gstride bytes at G (sign bytes), the
 // rows' coefficients behind the records of the batch.
-// `block` is the index of the workgroup among those of the forward pass (the launch may hold others).
 // K1: at most one negative per positive (the benchmarks' shape): no registers are kept for a batch of them, and
 // more wavefronts fit (same arithmetic in the same order, so the same bits).
-template <int LPR, int ITERS, int DIST, bool FROM_Y, bool PACKED, bool K1 = false>
-__device__ inline void forward_stacked_body(const int block, const ForwardArgs &a)
+template <int LPR, int ITERS, int DIST, bool FROM_Y, bool PACKED, bool K1>
+__device__ inline void forward_any_rows(const int64_t i, const int lig, const ForwardArgs &a, float &hinge_sum)
 {
     const int32_t *__restrict__ colidx = a.colidx;
     const float *__restrict__ X = a.X;
@@ -222,98 +208,118 @@ __device__ inline void forward_stacked_body(const int block, const ForwardArgs &
     float *gcoef = PACKED ? reinterpret_cast<float *>(reinterpret_cast<uint8_t *>(a.G) +
                                                       packed_coef_offset((int64_t)b * (1 + k), gstride))
                           : nullptr;
-    float *__restrict__ loss_partials = a.loss_partials;
     static_assert(!PACKED || (is_sign_kind(DIST) && !FROM_Y), "packed rows need an L1-kind distance");
-    constexpr int GROUPS = kThreads / LPR;
-    __shared__ float s_loss[GROUPS];
-    const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
-    const int64_t i = (int64_t)block * GROUPS + grp;
     const int d4 = dim / 4;
-    float hinge_sum = 0.f;
-    if (i < b) {   // uniform within the group; shuffles below stay inside the group
-        // Negatives are taken NB at a time so that the kernel pays two memory round trips per batch (all
-        // column ids, then all table rows) instead of two per row; the positive rides with the first batch.
-        constexpr int NB = K1 ? 1 : (ITERS <= 2 ? 4 : 2);
-        RowVec<ITERS> xp;
-        float dpos = 0.f, npos = 0.f;   // the positive's score and its norm (they differ by the relation's weight)
-        int n_active = 0;
-        int32_t cp[3] = {0, 0, 0};
-        if (!FROM_Y) { cp[0] = colidx[3 * i]; cp[1] = colidx[3 * i + 1]; cp[2] = colidx[3 * i + 2]; }
-        // Table 2, TransM row: a fixed weight per relation multiplies the norm (1 when there is none; the
-        // negatives of a positive keep its relation).  Multiplying by 1 changes no bit.
-        const float wr = (!FROM_Y && a.rel_weight) ? a.rel_weight[cp[1] - a.n_ent] : 1.0f;
-        for (int kk0 = 0; kk0 < k || kk0 == 0; kk0 += NB) {
-            const int nb = min(NB, k - kk0);
-            const int64_t row0 = (int64_t)b + i * k + kk0;
-            int32_t cn[NB][3];
-            RowVec<ITERS> xn[NB];
-            if (!FROM_Y) {
-#pragma unroll
-                for (int q = 0; q < NB; ++q) {
-                    const int64_t rr = q < nb ? row0 + q : i;   // past the end: re-read the positive's ids
-                    cn[q][0] = colidx[3 * rr]; cn[q][1] = colidx[3 * rr + 1]; cn[q][2] = colidx[3 * rr + 2];
-                }
-            }
-            if (kk0 == 0) {
-                if (FROM_Y) load_vec<LPR, ITERS>(G + i * dim, d4, lig, xp);
-                else gather_row<LPR, ITERS, true>(X, dim, d4, lig, cp[0], cp[1], cp[2], xp);
-            }
+    // Negatives are taken NB at a time so that the kernel pays two memory round trips per batch (all
+    // column ids, then all table rows) instead of two per row; the positive rides with the first batch.
+    constexpr int NB = K1 ? 1 : (ITERS <= 2 ? 4 : 2);
+    RowVec<ITERS> xp;
+    float dpos = 0.f, npos = 0.f;   // the positive's score and its norm (they differ by the relation's weight)
+    int n_active = 0;
+    int32_t cp[3] = {0, 0, 0};
+    if (!FROM_Y) { cp[0] = colidx[3 * i]; cp[1] = colidx[3 * i + 1]; cp[2] = colidx[3 * i + 2]; }
+    // Table 2, TransM row: a fixed weight per relation multiplies the norm (1 when there is none; the
+    // negatives of a positive keep its relation).  Multiplying by 1 changes no bit.
+    const float wr = (!FROM_Y && a.rel_weight) ? a.rel_weight[cp[1] - a.n_ent] : 1.0f;
+    for (int kk0 = 0; kk0 < k || kk0 == 0; kk0 += NB) {
+        const int nb = min(NB, k - kk0);
+        const int64_t row0 = (int64_t)b + i * k + kk0;
+        int32_t cn[NB][3];
+        RowVec<ITERS> xn[NB];
+        if (!FROM_Y) {
 #pragma unroll
             for (int q = 0; q < NB; ++q) {
-                if (q < nb) {
-                    if (FROM_Y) load_vec<LPR, ITERS>(G + (row0 + q) * dim, d4, lig, xn[q]);
-                    else gather_row<LPR, ITERS, true>(X, dim, d4, lig, cn[q][0], cn[q][1], cn[q][2], xn[q]);
-                }
-            }
-            if (kk0 == 0) {
-                npos = row_distance<LPR, ITERS, DIST>(xp);
-                dpos = wr * npos;
-                if (lig == 0) scores[i] = dpos;
-            }
-#pragma unroll
-            for (int q = 0; q < NB; ++q) {
-                if (q < nb) {
-                    const int64_t row = row0 + q;
-                    const float nneg = row_distance<LPR, ITERS, DIST>(xn[q]);
-                    const float dneg = wr * nneg;
-                    const float arg = (margin + dpos) - dneg;
-                    const bool active = arg > 0.f;
-                    if (lig == 0) scores[row] = dneg;
-                    if (active) { hinge_sum += arg; ++n_active; }
-                    if (PACKED)
-                        write_grad_row_packed<LPR, ITERS, DIST>(reinterpret_cast<uint8_t *>(G), gstride, gcoef, row, d4,
-                                                                lig, xn[q], active ? -scale * wr : 0.f);
-                    else if (!FROM_Y && a.coefs) {
-                        if (lig == 0) a.coefs[row] = formed_coef<DIST>(active ? -scale * wr : 0.f, nneg);
-                    } else
-                        write_grad_row<LPR, ITERS, DIST>(G + row * dim, d4, lig, xn[q], active ? -scale * wr : 0.f,
-                                                         nneg);
-                }
+                const int64_t rr = q < nb ? row0 + q : i;   // past the end: re-read the positive's ids
+                cn[q][0] = colidx[3 * rr]; cn[q][1] = colidx[3 * rr + 1]; cn[q][2] = colidx[3 * rr + 2];
             }
         }
-        if (PACKED)
-            write_grad_row_packed<LPR, ITERS, DIST>(reinterpret_cast<uint8_t *>(G), gstride, gcoef, i, d4, lig, xp,
-                                                    (float)n_active * scale * wr);
-        else if (!FROM_Y && a.coefs) {
-            if (lig == 0) a.coefs[i] = formed_coef<DIST>((float)n_active * scale * wr, npos);
-        } else
-            write_grad_row<LPR, ITERS, DIST>(G + i * dim, d4, lig, xp, (float)n_active * scale * wr, npos);
+        if (kk0 == 0) {
+            if (FROM_Y) load_vec<LPR, ITERS>(G + i * dim, d4, lig, xp);
+            else gather_row<LPR, ITERS, true>(X, dim, d4, lig, cp[0], cp[1], cp[2], xp);
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            if (q < nb) {
+                if (FROM_Y) load_vec<LPR, ITERS>(G + (row0 + q) * dim, d4, lig, xn[q]);
+                else gather_row<LPR, ITERS, true>(X, dim, d4, lig, cn[q][0], cn[q][1], cn[q][2], xn[q]);
+            }
+        }
+        if (kk0 == 0) {
+            npos = row_distance<LPR, ITERS, DIST>(xp);
+            dpos = wr * npos;
+            if (lig == 0) scores[i] = dpos;
+        }
+#pragma unroll
+        for (int q = 0; q < NB; ++q) {
+            if (q < nb) {
+                const int64_t row = row0 + q;
+                const float nneg = row_distance<LPR, ITERS, DIST>(xn[q]);
+                const float dneg = wr * nneg;
+                const float arg = (margin + dpos) - dneg;
+                const bool active = arg > 0.f;
+                if (lig == 0) scores[row] = dneg;
+                if (active) { hinge_sum += arg; ++n_active; }
+                if (PACKED)
+                    write_grad_row_packed<LPR, ITERS, DIST>(reinterpret_cast<uint8_t *>(G), gstride, gcoef, row, d4,
+                                                            lig, xn[q], active ? -scale * wr : 0.f);
+                else
+                    write_grad_row<LPR, ITERS, DIST>(G + row * dim, d4, lig, xn[q], active ? -scale * wr : 0.f,
+                                                     nneg);
+            }
+        }
     }
+    if (PACKED)
+        write_grad_row_packed<LPR, ITERS, DIST>(reinterpret_cast<uint8_t *>(G), gstride, gcoef, i, d4, lig, xp,
+                                                (float)n_active * scale * wr);
+    else
+        write_grad_row<LPR, ITERS, DIST>(G + i * dim, d4, lig, xp, (float)n_active * scale * wr, npos);
+}
+
+// Sum of the groups' hinge terms of workgroup `block` (of those of the forward pass; the launch may hold others).
+template <int GROUPS>
+__device__ inline void forward_loss(const int block, const int lig, const int grp, float hinge_sum, const ForwardArgs &a)
+{
+    __shared__ float s_loss[GROUPS];
     if (lig == 0) s_loss[grp] = hinge_sum;
     __syncthreads();
     if (threadIdx.x == 0) {
         float sum = 0.f;
 #pragma unroll
         for (int g = 0; g < GROUPS; ++g) sum += s_loss[g];
-        loss_partials[block] = sum;
+        a.loss_partials[block] = sum;
     }
 }
 
-}  // namespace stx
+// The distances over rows of y (TransR).
+template <int LPR, int ITERS, int DIST>
+__device__ inline void forward_y_body(const int block, const ForwardArgs &a)
+{
+    constexpr int GROUPS = kThreads / LPR;
+    const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
+    const int64_t i = (int64_t)block * GROUPS + grp;
+    float hinge_sum = 0.f;
+    if (i < a.b) forward_any_rows<LPR, ITERS, DIST, true, false, false>(i, lig, a, hinge_sum);   // (uniform within the group)
+    forward_loss<GROUPS>(block, lig, grp, hinge_sum, a);
+}
 
-namespace stx {
+// Gathered rows.  CHECK: a positive whose negatives are a caller's own, of a kind that forward_fast_rows does not cover,
+// takes three table rows for each, in the same kernel: in a launch of its own behind a fast one, whose groups had then
+// loaded and stored for nothing, such batches took 1.4 to 1.7 times as long.
+template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK>
+__device__ inline void forward_body(const int block, const ForwardArgs &a)
+{
+    constexpr int GROUPS = kThreads / LPR;
+    const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
+    const int64_t i = (int64_t)block * GROUPS + grp;
+    float hinge_sum = 0.f;
+    if (i < a.b && !forward_fast_rows<LPR, ITERS, DIST, PACKED, NB, MORE, CHECK>((int32_t)i, lig, a, hinge_sum) && CHECK) {
+        hinge_sum = 0.f;
+        forward_any_rows<LPR, ITERS, DIST, false, PACKED, NB == 1>(i, lig, a, hinge_sum);
+    }
+    forward_loss<GROUPS>(block, lig, grp, hinge_sum, a);
+}
 
-// Negatives that forward_fast_body holds at a time, for k of them per positive: as many rows in flight as the
+// Negatives that forward_fast_rows holds at a time, for k of them per positive: as many rows in flight as the
 // registers allow (rows of ITERS float4 per lane, the positive's three beside them).
 // (Eight at a time, in one batch for up to eight: 35.6 us for 9,999 positives x 5 at d = 200, four waves per SIMD and
 // spills, against 27.0 with four at a time and five waves.)
@@ -324,7 +330,7 @@ constexpr int fast_batch(int iters, bool k1) { return k1 ? 1 : iters <= 2 ? 4 : 
 template <int LPR, int ITERS, int DIST, bool PACKED, bool K1>
 __device__ inline void forward_step_body(const int block, const ForwardArgs &fa)
 {
-    forward_fast_body<LPR, ITERS, DIST, PACKED, fast_batch(ITERS, K1), !K1>(block, fa, nullptr, 0);
+    forward_body<LPR, ITERS, DIST, PACKED, fast_batch(ITERS, K1), !K1, false>(block, fa);
 }
 
 }  // namespace stx

@@ -30,7 +30,7 @@ constexpr int kProjRows = 64;           // TransR: entries of one relation per w
 constexpr int kProjRowsDm = 256;        // ... and per work item of the product that forms dL/dM_r
 
 // Slots of the control block at the start of the workspace (int32 each).
-enum { CTRL_BAD_INDEX = 0, CTRL_GENERAL = 1 /* see k_forward_fast */, CTRL_WORDS = 64 };
+enum { CTRL_BAD_INDEX = 0, CTRL_WORDS = 64 };
 
 struct Launch {            // how a row of `width` floats maps onto lanes
     int lpr;               // lanes per row: power of two in 8..64
@@ -237,7 +237,6 @@ struct stx_ctx {
     const stx_incidence *sorted_inc;   // incidence of the last build, whose sorted keys are still in keys[]
     const int32_t *sorted_keys;
     const stx_incidence *sampled_inc;  // incidence whose negatives the library's sampler drew inside its build, or null
-    int32_t fwd_serial;            // number of the last forward pass that used the fast kernel (never 0 once used)
     const stx_incidence *fwd_inc;  // incidence of the last stx_forward, null if none
     int64_t fwd_rows;
     stx::EmitAheadState ahead;
