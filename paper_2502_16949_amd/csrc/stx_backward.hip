@@ -224,8 +224,9 @@ __device__ inline void apply_update(float *__restrict__ row, int d4, int lig, co
 // first scatter pass of the next batch's sort comes along; 4 as 2, and that kernel counts the rows per relation;
 // 5 as 3, and TransR's dL/dM_r product comes along (its 128 registers still leave four workgroups on a CU, more
 // than such a batch gives this product).
-template <int LPR, int ITERS, bool PACKED, int CHUNK, bool FUSED, int RIDE, int SRC = SRC_STORED>
-__global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && FUSED && RIDE != 4) ? 8 : 1) void k_seg_reduce(const int32_t *__restrict__ packed,
+// THREADS: threads of a workgroup; with LPR it makes the number of chunks in a tile, and so the order of the sums.
+template <int LPR, int ITERS, bool PACKED, int CHUNK, bool FUSED, int RIDE, int SRC = SRC_STORED, int THREADS = kThreads>
+__global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && FUSED && RIDE != 4) ? 8 : 1) void k_seg_reduce(const int32_t *__restrict__ packed,
                                                          const int32_t *__restrict__ seg_id, int32_t e_begin,
                                                          int32_t e_end, const float *__restrict__ src_a,
                                                          const float *__restrict__ src_b, int32_t split,
@@ -239,7 +240,8 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
     constexpr bool DIFF = SRC >= SRC_DIFF, SEMI = SRC != SRC_STORED && !DIFF;
     // One block of LDS for whichever part a workgroup plays (the parts' own arrays would add up and cost the
     // launch wavefronts per CU): the product's arrays below, or those of a body that rides.
-    constexpr int GROUPS_ = kThreads / LPR, ROWF_ = ITERS * LPR * 4;
+    static_assert(THREADS == kThreads || RIDE == 0, "the bodies that ride have kThreads threads");
+    constexpr int GROUPS_ = THREADS / LPR, ROWF_ = ITERS * LPR * 4;
     constexpr int OWN_LDS = (GROUPS_ * 2 * ROWF_ + (FUSED ? GROUPS_ * ROWF_ : 4) + 3 * GROUPS_) * 4;
     constexpr int RIDE_LDS = RIDE == 0 ? 0
                              : (RIDE == 3 || RIDE == 5) ? kScatterLds
@@ -309,7 +311,7 @@ __global__ __launch_bounds__(kThreads, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && 
         if (fu.table) fu.table += 4 * c4;
         if (fu.table_b) fu.table_b += 4 * c4;
     }
-    constexpr int GROUPS = kThreads / LPR;
+    constexpr int GROUPS = THREADS / LPR;
     // rows in flight per lane: dense rows cost 4*ITERS registers each; packed rows are a byte and a float,
     // so a whole chunk is fetched at once and the kernel pays one memory latency per chunk
     constexpr int UNROLL = SRC != SRC_STORED ? 4 : PACKED ? (FUSED ? 4 : (CHUNK < 8 ? CHUNK : 8)) : (ITERS == 1 ? (FUSED ? 4 : 8) : (ITERS == 2 ? 4 : 2));
@@ -969,25 +971,29 @@ static void sgd_go(stx_ctx *c, const stx_incidence *inc, const SgdTables &T, con
                        T.table_b, T.width_b / 4, T.table_w, T.mode_w, grad_rows, w_rows, c->ld, lr, big_tables(c));
 }
 
-// Stored rows of a batch that stx_train_step would form (formed_rows): the tiles and slices of launch_seg_formed, so
-// that the sums have the same bits.
+// Stored rows of a batch that stx_train_step would form (formed_rows): the tiles of launch_seg_formed, so that the sums
+// have the same bits.  Its slices of 16 lanes too where rows are whole memory lines (393,216 positives at d = 1024: 1,605 us,
+// 1,631 in slices of 64 lanes); other rows' short slices would begin and end inside lines that two of them then fetch
+// (131,072 at d = 516: 383 us against 332), and go in slices of 64 lanes, sixteen groups all the same.
 static void seg_slices(stx_ctx *c, const stx_incidence *inc, const float *src, int width, float *out_rows, int ld_out,
                        const FusedArgs *fused)
 {
     constexpr int LPR = 16, CH = 16, TILE = kThreads / LPR * CH;
     const int32_t nnz = (int32_t)inc->nnz;
     const int d4 = width / 4, ntiles = (nnz + TILE - 1) / TILE;
-    const dim3 grid((unsigned)ntiles, (unsigned)((d4 + LPR - 1) / LPR));
+    const dim3 grid((unsigned)ntiles, (unsigned)((d4 + LPR - 1) / LPR)), wide((unsigned)ntiles, (unsigned)((d4 + 63) / 64));
     const FusedArgs fu = fused ? *fused : FusedArgs{};
     const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
+#define STX_SLICES_R(F, L, T, GRID)                                                                             \
+    hipLaunchKernelGGL((k_seg_reduce<L, 1, false, CH, F, 0, SRC_STORED, T>), GRID, dim3(T), 0, c->stream,       \
+                       inc->at_packed, inc->at_seg_id, 0, nnz, src, src, nnz, width, d4, out_rows, ld_out,      \
+                       c->partials, fu, sec, SegWriteRide{}, EmitAhead{}, ScatterAhead{}, DmRide{})
 #define STX_SLICES(F)                                                                                           \
     do {                                                                                                        \
         {                                                                                                       \
             ProfScope prof(c, "k_seg_reduce");                                                                  \
-            hipLaunchKernelGGL((k_seg_reduce<LPR, 1, false, CH, F, 0>), grid, dim3(kThreads), 0, c->stream,     \
-                               inc->at_packed, inc->at_seg_id, 0, nnz, src, src, nnz, width, d4, out_rows,      \
-                               ld_out, c->partials, fu, sec, SegWriteRide{}, EmitAhead{}, ScatterAhead{},       \
-                               DmRide{});                                                                       \
+            if (width % 32 == 0) STX_SLICES_R(F, LPR, kThreads, grid);                                          \
+            else STX_SLICES_R(F, 64, 64 * (kThreads / LPR), wide);                                              \
         }                                                                                                       \
         ProfScope prof(c, "k_seg_fixup");                                                                       \
         hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, F, 0>), grid, dim3(kThreads), 0, c->stream, inc->at_packed, \
@@ -997,6 +1003,7 @@ static void seg_slices(stx_ctx *c, const stx_incidence *inc, const float *src, i
     if (fused) STX_SLICES(true);
     else STX_SLICES(false);
 #undef STX_SLICES
+#undef STX_SLICES_R
 }
 
 stx_status launch_seg_reduce(stx_ctx *c, const stx_incidence *inc, int64_t e_begin, int64_t e_end,

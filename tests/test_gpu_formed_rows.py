@@ -1,5 +1,5 @@
-"""Batches whose rows of dL/dx stx_train_step forms where they are summed (from 192 MiB of them on, narrow tables), with
-the same bits as the separate calls, which store them."""
+"""Batches whose rows of dL/dx stx_train_step forms where they are summed (from 192 MiB of them on, 384 below 256 floats a
+row; few columns), with the same bits as the separate calls, which store them."""
 import numpy as np
 import pytest
 import torch
@@ -10,17 +10,19 @@ from tests import gpu_util as G
 
 pytestmark = pytest.mark.gpu
 
-FORMED_BYTES = 192 << 20
+FORMED_BYTES = {True: 192 << 20, False: 384 << 20}       # dim >= 256
 CASES = [
     # model, dist, n_ent, n_rel, b, k, dim: rows of 16 slices of 16 float4, a ragged last slice, an odd last tile
     ("transe", "l2", 3000, 7, 24_667, 1, 1024),
     ("transe", "l2_sq", 900, 5, 10_001, 5, 852),
-    ("toruse", "torus_l2", 20_000, 300, 63_001, 3, 200),
+    ("toruse", "torus_l2", 20_000, 300, 130_001, 3, 200),
+    ("transe", "l2", 3000, 7, 401_000, 1, 128),
+    ("transe", "l2", 5_000, 11, 49_000, 1, 516),          # one float4 in the last slice
 ]
 
 
 def _setup(model, dist, n_ent, n_rel, b, k, dim):
-    assert b * (1 + k) * dim * 4 >= FORMED_BYTES
+    assert b * (1 + k) * dim * 4 >= FORMED_BYTES[dim >= 256] and dim >= 128
     wl = W.Workload("formed", 21, model, dist, n_ent, n_rel, b, dim, dim, b, k, 1.0, 0.01, 1, 1.1, 1.1)
     tabs = W.make_tables(wl)
     tabs["rel_weight"] = np.linspace(0.5, 1.5, n_rel).astype(np.float32)
