@@ -555,10 +555,10 @@ static stx_status run_backward(stx_ctx *ctx, const stx_incidence *inc, const stx
     float *rows = lr ? nullptr : g->rows;
     if (stacked(ctx)) {   // dL/dX = A^T G over all columns of X = [E;R] (Appendix G)
         const bool pk = packed_grad(ctx);
-        if (inc->n_rows > 0 && ctx->form_rows) {   // the rows of dL/dx were not stored: formed again here
-            float *out = lr ? formed_buffers(ctx, inc->n_rows).grads : g->rows;
+        if (inc->n_rows > 0 && ctx->form_rows) {   // stx_train_step: the rows of dL/dx were not stored, but are formed here
+            float *out = formed_buffers(ctx, inc->n_rows).grads;
             const stx_status s = launch_seg_formed(ctx, inc, p, out, ctx->ld);
-            if (s != STX_OK || !lr) return s;
+            if (s != STX_OK) return s;
             const SgdTables T{p->ent, dim, ctx->cfg.model == STX_TORUSE ? 1 : 0, ctx->cfg.n_ent + ctx->cfg.n_rel, nullptr,
                               dim, nullptr, 0};
             return launch_sgd_rows(ctx, inc, T, out, nullptr, *lr);
