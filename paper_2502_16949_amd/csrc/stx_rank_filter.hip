@@ -180,8 +180,9 @@ __device__ inline void pair_recheck(const FilterArgs &f, uint2 pr, bool in, int 
     }
     s = group_sum<8>(s);
     // The sum of the same rounded terms differs from this one by at most (dim / 8 + 6) 2^-24 of itself and from the
-    // index-order one by at most (dim + 2) 2^-24.
-    const float wd = ((float)dim * 1.126f + 16.f) * kUnit * s;
+    // index-order one by at most (dim + 2) 2^-24.  A step of the L2 kinds whose result is subnormal is off by up to 2^-150
+    // whatever its size: dim of them in either sum, and the roundings of this bound itself.
+    const float wd = ((float)dim * 1.126f + 16.f) * kUnit * s + (DIST == STX_L2 ? (float)(dim + 8) * 1.4012985e-45f : 0.f);
     const bool less = !self && s + wd < p.st, tie = !self && !less && !(s - wd > p.st);
     const bool one = (lane & 7) == 0 && in;
     pair_count<false>(f, p.q, one && less, one && self && p.st == p.st);   // (the true entity: the very sum k_rank_prep formed)

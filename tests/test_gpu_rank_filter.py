@@ -124,6 +124,32 @@ def test_transr_zero_projections_tie(dist):
         assert np.allclose(ts[r == 2], k if dist == "l2_sq" else np.sqrt(k), rtol=1e-6)
 
 
+# Sums in the subnormal range: there a step is off by up to half of 2^-149 whatever the sum.  Odd multiples of 2^-75 have
+# squares halfway between two subnormal numbers, which round to the even sum, so that rows of the same values in other orders
+# (of those and of any others, which make odd sums) have other sums.  A zero query point: the sums of the squares.
+@pytest.mark.parametrize("dist", ["l2", "l2_sq"])
+@pytest.mark.parametrize("largest", [3, 12, 60])
+def test_order_of_subnormal_sums(dist, largest):
+    n_ent, dim, nq, n_tiny = 4_129, 128, 1_300, 64
+    rng = np.random.default_rng(11)
+    X = rng.uniform(-1, 1, (n_ent + 1, dim)).astype(np.float32)
+    X[n_ent] = 0.0
+    row = np.concatenate([rng.integers(0, largest, dim // 2), rng.uniform(0, largest, dim // 2)]).astype(np.float32) * np.float32(2.0**-75)
+    X[:n_tiny] = [rng.permutation(row) for _ in range(n_tiny)]
+    X[100] = 0.0
+    h, t = (rng.integers(200, n_ent, nq).astype(np.int32) for _ in range(2))
+    h[:n_tiny], t[:n_tiny] = 100, np.arange(n_tiny)
+    hd, rd, td = G.dev_i32(h), G.dev_i32(np.zeros(nq)), G.dev_i32(t)
+    ctx = B.Context(B.make_config("transe", dist, n_ent, 1, dim, 8, 1), G.DEV)
+    p = B.Params(G.dev_f32(X))
+    got = _rank(ctx, p, hd, rd, td, B.STX_TAIL)
+    parts = [_rank(ctx, p, hd[i:i + 128].clone(), rd[i:i + 128].clone(), td[i:i + 128].clone(), B.STX_TAIL)
+             for i in range(0, nq, 128)]
+    for g, w in zip(got, zip(*parts)):
+        assert torch.equal(g, torch.cat(w))
+    assert (got[1][:n_tiny] > 1).any()                    # (their order is decided by those roundings)
+
+
 # More undecided pairs than the list of a sweep holds: the plain sweep does the chunk.  In the first chunk of queries or in
 # a later one, over one segment of candidates or several, with the queries before and after it decided as usual.
 @pytest.mark.parametrize("dist,n_ent,dim,nq,equal", [
