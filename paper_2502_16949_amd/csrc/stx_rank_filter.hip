@@ -697,15 +697,20 @@ struct MfmaShape {
 };
 
 // One kilobyte from global memory straight into LDS (16 bytes per lane, in lane order).  Completion is counted by
-// vmcnt like any load; the waits are placed by hand below.
+// vmcnt like any load; the waits are placed by hand below.  The compiler cannot be told that m0 is written (a reserved
+// register): it finds it as it left it.
 __device__ inline void load_lds_1k(const uint4 *g, uint32_t lds)
 {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
 }
 
 __device__ inline void load_lds_256(const float *g, uint32_t lds)             // ... 256 bytes, four per lane
 {
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off" : : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
 }
 
 template <int QF, int KS, int WPE>
