@@ -36,7 +36,7 @@ typedef enum {
     STX_ERR_NULL = 1,        /* a required pointer is null */
     STX_ERR_BAD_ARG = 2,     /* enum out of range, negative size, dim not a multiple of 4, ... */
     STX_ERR_INDEX_RANGE = 3, /* stx_check_indices: some triplet index was outside its table */
-    STX_ERR_WORKSPACE = 4,   /* workspace smaller than stx_workspace_bytes, or misaligned */
+    STX_ERR_WORKSPACE = 4,   /* workspace or work buffer too small, or misaligned */
     STX_ERR_STATE = 5,       /* call order violated (e.g. backward before forward) */
     STX_ERR_UNSUPPORTED = 6, /* valid request this build does not implement */
     STX_ERR_HIP = 7,         /* a HIP runtime call failed */
@@ -129,11 +129,14 @@ typedef struct {
 
 typedef struct stx_ctx stx_ctx;
 
-/* Bytes of device workspace a context with this configuration needs. */
+/* Bytes of device workspace for a context with this configuration.  TransE / TorusE with the distances L1, L2,
+ * squared L2 and torus-L1: the last part of it, up to 80 MiB, only makes large stx_rank calls faster. */
 stx_status stx_workspace_bytes(const stx_config *cfg, size_t *bytes /* host, out */);
 
-/* Create a context.  workspace: device memory, 256-byte aligned, at least stx_workspace_bytes, owned by
- * the caller and kept alive until stx_destroy.  stream: a hipStream_t (NULL = the default stream).
+/* Create a context.  workspace: device memory, 256-byte aligned, stx_workspace_bytes or more, owned by the caller
+ * and kept alive until stx_destroy.  (One that ends before the part for stx_rank is taken too: a program that
+ * only trains saves up to 80 MiB with it.  It has the size of the same configuration with the distance torus-L2.)
+ * stream: a hipStream_t (NULL = the default stream).
  * Enqueues one small kernel that clears the library's counters.                                       */
 stx_status stx_create(const stx_config *cfg, void *workspace, size_t workspace_bytes, void *stream,
                       stx_ctx **out /* host, out */);
@@ -286,9 +289,16 @@ stx_status stx_train_step(stx_ctx *ctx, const stx_batch *batch, stx_incidence *i
  * counted as in stx_build_incidence.  work: device scratch of stx_rank_work_bytes(nq) bytes, 256-byte
  * aligned, owned by the caller; TransE / TorusE / TransH need none (null is fine).  TransR groups the
  * queries by relation and builds one projected table per relation that occurs; it waits for the stream
- * once (to learn the group sizes) and launches a few kernels per relation.
- * Cost: nq * n_ent * dim steps of vector arithmetic (TransH about twice that; TransR rel_dim in place of
- * dim, plus n_ent * dim * rel_dim per relation that occurs).                                            */
+ * once (to learn the group sizes) and launches a few kernels per relation.  With the L2 kinds its work
+ * ends in scratch of the filter below, packed tables included; a buffer without it is taken too (it has the size
+ * of the same context with the distance L1) and the sweeps are plain then.
+ * Cost of a plain sweep: nq * n_ent * dim steps of vector arithmetic (TransH about twice that; TransR rel_dim
+ * in place of dim, plus n_ent * dim * rel_dim per relation that occurs), whatever the values.  L1, torus-L1, L2
+ * and squared L2 (TransE / TorusE: calls large enough to gain; TransR: the L2 kinds) order most candidates by a
+ * cheaper sum of known error, with the same results, two to five times as fast.  That sum leaves pairs undecided
+ * and they are summed exactly: one in some hundreds in ordinary tables, many more where many rows are equal
+ * or reach far outside the others' range.  Where there are too many the plain sweep is run as well: at most
+ * about twice its own time.                                                                              */
 enum { STX_TAIL = 0, STX_HEAD = 1 };
 stx_status stx_rank_work_bytes(const stx_ctx *ctx, int64_t nq, size_t *bytes /* host, out */);
 stx_status stx_rank(stx_ctx *ctx, const stx_params *p, const int32_t *h, const int32_t *r, const int32_t *t,

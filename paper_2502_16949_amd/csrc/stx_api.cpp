@@ -13,7 +13,7 @@ namespace {
 inline size_t align_up(size_t v, size_t a = 256) { return (v + a - 1) / a * a; }
 
 struct Layout {
-    size_t ctrl, keys[3], pay[2], cix[2], table, table1, super, tile_heads, loss_partials, partials, gbuf[4], total;
+    size_t ctrl, keys[3], pay[2], cix[2], table, table1, super, tile_heads, loss_partials, partials, gbuf[4], core, total;
     size_t tr_items, tr_dm_items, tr_fix_items, tr_counts, tr_m16, tr_m16t, tr_xt, tr_gyt;
     size_t colmap, rel_cnt;
     size_t rank_q, rank_e, rank_q_bytes, rank_e_bytes;
@@ -109,7 +109,8 @@ Layout make_layout(const stx_config *c)
         L.tr_gyt = take((items + 1) * kProjRows * c->rel_dim * 2);
         L.rel_cnt = take((size_t)2 * c->n_rel * 4);
     }
-    if (c->model == STX_TRANSE || c->model == STX_TORUSE) {
+    L.core = off;
+    if (c->model == STX_TRANSE || c->model == STX_TORUSE) {   // last, and optional: scratch of filtered sweeps
         size_t q = (size_t)(c->n_ent + c->n_rel) * c->dim * 16;          // in proportion to the table, 2 MB at least
         if (q < (size_t)2 << 20) q = (size_t)2 << 20;
         L.rank_q_bytes = rank_filter_q_bytes(c->dist, c->dim, 32) ? (q < kRankQBytes ? q : kRankQBytes) : 0;
@@ -179,7 +180,8 @@ stx_status stx_create(const stx_config *cfg, void *workspace, size_t workspace_b
     if (s != STX_OK) return s;
     if (!workspace) return STX_ERR_NULL;
     Layout L = make_layout(cfg);
-    if (workspace_bytes < L.total || ((uintptr_t)workspace & 255u)) return STX_ERR_WORKSPACE;
+    if (workspace_bytes < L.core || ((uintptr_t)workspace & 255u)) return STX_ERR_WORKSPACE;
+    if (workspace_bytes < L.total) L.rank_q_bytes = L.rank_e_bytes = 0;   // plain sweeps only
     stx_ctx *c = new (std::nothrow) stx_ctx();
     if (!c) return STX_ERR_BAD_ARG;
     c->cfg = *cfg;
@@ -505,10 +507,10 @@ stx_status stx_rank(stx_ctx *ctx, const stx_params *p, const int32_t *h, const i
     if (ctx->cfg.model == STX_TRANSR && (!p->rel || !p->proj)) return STX_ERR_NULL;
     if (nq == 0) return STX_OK;
     if (!h || !r || !t || !true_score || !n_less || !n_equal) return STX_ERR_NULL;
-    const size_t need = rank_work_bytes(ctx, nq);
+    const size_t need = rank_plain_work_bytes(ctx, nq);
     if (need > 0 && !work) return STX_ERR_NULL;
     if (need > 0 && (work_bytes < need || ((uintptr_t)work & 255u))) return STX_ERR_WORKSPACE;
-    return launch_rank(ctx, p, h, r, t, nq, side, true_score, n_less, n_equal, work);
+    return launch_rank(ctx, p, h, r, t, nq, side, true_score, n_less, n_equal, work, work_bytes);
 }
 
 // The forward pass; from_step: called by stx_train_step, whose own launches keep A and A^T paired.

@@ -373,8 +373,9 @@ stx_status launch_sgd_rows(stx_ctx *, const stx_incidence *, const SgdTables &, 
 stx_status launch_forward_from_y(stx_ctx *, const stx_incidence *, const stx_params *, float *scores, float *loss);
 // stx_rank.hip
 stx_status launch_rank(stx_ctx *, const stx_params *, const int32_t *h, const int32_t *r, const int32_t *t, int64_t nq,
-                       int side, float *true_score, int32_t *n_less, int32_t *n_equal, void *work);
-size_t rank_work_bytes(const stx_ctx *, int64_t nq);   // scratch launch_rank needs for nq queries (0 unless TransR)
+                       int side, float *true_score, int32_t *n_less, int32_t *n_equal, void *work, size_t work_bytes);
+size_t rank_work_bytes(const stx_ctx *, int64_t nq);         // scratch of launch_rank for nq queries (0 unless TransR) ...
+size_t rank_plain_work_bytes(const stx_ctx *, int64_t nq);   // ... and what it needs of that: plain sweeps below the whole
 // stx_semiring.hip
 stx_status launch_semiring(stx_ctx *, const stx_incidence *, const stx_params *, int kind, float *z_out);
 // work: 3 n_rows dim floats, used where out_rows shares memory with gz or the table; null: the library's fixed array

@@ -379,14 +379,14 @@ struct RankRWork {                      // partitions of the caller's work buffe
     float *table;                       // n_tables tables of (n_ent + 1) x rel_dim: P_r, then r
     int n_tables;
     RankScratch ws;                     // of the filtered sweeps (kinds that have one)
-    size_t total;
+    size_t plain_total, total;          // without and with that
 };
 constexpr int kRankBig = 1024;          // relations with more queries than this get a launch of their own
 static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
 {
     size_t off = 0;
     auto take = [&](size_t bytes) { size_t o = off; off = (off + bytes + 255) / 256 * 256; return (char *)base + o; };
-    RankRWork w;
+    RankRWork w{};
     w.counts = (int32_t *)take((size_t)cfg.n_rel * 4);
     w.cursor = (int32_t *)take((size_t)cfg.n_rel * 4);
     w.offsets = (int32_t *)take((size_t)(cfg.n_rel + 1) * 4);
@@ -402,6 +402,8 @@ static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
     w.n_tables = (int)(fit < 1 ? 1 : (fit > kRankTables ? kRankTables : fit));
     if (w.n_tables > cfg.n_rel) w.n_tables = (int)cfg.n_rel;
     w.table = (float *)take(table_bytes * w.n_tables);
+    w.plain_total = w.total = off;
+    if (cfg.dist != STX_L2 && cfg.dist != STX_L2_SQ) return w;                 // (no filtered sweep over projected tables)
     // one relation with all queries, or n_tables relations with up to kRankBig each
     const int64_t few = nq < kRankBig ? nq : kRankBig, many = ((few + 31) / 32 * 32) * w.n_tables;
     w.ws.q_bytes = rank_filter_q_bytes(cfg.dist, cfg.rel_dim, nq > many ? nq : many);
@@ -415,6 +417,10 @@ static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
 size_t rank_work_bytes(const stx_ctx *c, int64_t nq)
 {
     return c->cfg.model == STX_TRANSR ? rank_r_work(c->cfg, nq, nullptr).total : 0;
+}
+size_t rank_plain_work_bytes(const stx_ctx *c, int64_t nq)
+{
+    return c->cfg.model == STX_TRANSR ? rank_r_work(c->cfg, nq, nullptr).plain_total : 0;
 }
 
 __global__ __launch_bounds__(kThreads) void k_rr_clear(int32_t *counts, int32_t *cursor, int n_rel)
@@ -661,7 +667,8 @@ void rank_plain_behind(stx_ctx *c, const RankArgs &args, int side, int64_t q0, i
 }
 
 stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const int32_t *r, const int32_t *t,
-                       int64_t nq, int side, float *true_score, int32_t *n_less, int32_t *n_equal, void *work)
+                       int64_t nq, int side, float *true_score, int32_t *n_less, int32_t *n_equal, void *work,
+                       size_t work_bytes)
 {
     if (nq == 0) return STX_OK;
     const int32_t n_ent = (int32_t)c->cfg.n_ent, n_rel = (int32_t)c->cfg.n_rel;
@@ -725,7 +732,7 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
             hipLaunchKernelGGL(k_rr_project, pgrid, dim3(kThreads), 0, c->stream, p->ent, p->proj, p->rel, n_ent, dim, k,
                                w.table, ids, stride);
         }
-        if (!rank_filtered(c, a, side, w.ws, nz, ids, queries)) rank_sweep(c, a, sh, false, side, ids, nz, false);
+        if (work_bytes < w.total || !rank_filtered(c, a, side, w.ws, nz, ids, queries)) rank_sweep(c, a, sh, false, side, ids, nz, false);
     }
     if (c->cfg.dist == STX_L2) hipLaunchKernelGGL((k_rank_finish<STX_L2>), qgrid, dim3(kThreads), 0, c->stream, w.gts, nq);
     if (c->cfg.dist == STX_TORUS_L2)

@@ -240,6 +240,47 @@ def test_transr_relations_of_equal_rows():
             assert equal[i].max() <= 3
 
 
+# The scratch of the filtered sweeps is optional: without it the sweeps are plain, with the same results.
+def test_without_scratch_of_the_filter(monkeypatch):
+    n_ent, dim, nq, n_rel = 4_129, 128, 1_300, 3
+    rng = np.random.default_rng(3)
+    p = B.Params(G.dev_f32(rng.uniform(-1, 1, (n_ent + n_rel, dim))))
+    h, r, t = (G.dev_i32(rng.integers(0, n, nq)) for n in (n_ent, n_rel, n_ent))
+    cfg = B.make_config("transe", "l2", n_ent, n_rel, dim, 8, 1)
+    core = B.stx_workspace_bytes(B.make_config("transe", "torus_l2", n_ent, n_rel, dim, 8, 1))
+    assert core < B.stx_workspace_bytes(cfg)
+    full = B.Context(cfg, G.DEV)
+    monkeypatch.setattr(B, "stx_workspace_bytes", lambda c: core)
+    small = B.Context(cfg, G.DEV)
+    for a, b in zip(_rank(full, p, h, r, t, B.STX_HEAD), _rank(small, p, h, r, t, B.STX_HEAD)):
+        assert torch.equal(a, b)
+    monkeypatch.setattr(B, "stx_workspace_bytes", lambda c: core - 256)
+    with pytest.raises(B.StxError) as e:
+        B.Context(cfg, G.DEV)
+    assert e.value.status == B.STX_ERR_WORKSPACE
+
+
+def test_transr_without_scratch_of_the_filter():
+    n_ent, dim, k, nq, n_rel = 1_000, 64, 32, 3_000, 5
+    rng = np.random.default_rng(3)
+    p = B.Params(G.dev_f32(rng.uniform(-1, 1, (n_ent, dim))), G.dev_f32(rng.uniform(-1, 1, (n_rel, k))),
+                 proj=G.dev_f32(rng.uniform(-1, 1, (n_rel, k, dim))))
+    h, r, t = (G.dev_i32(rng.integers(0, n, nq)) for n in (n_ent, n_rel, n_ent))
+    ctx = {d: B.Context(B.make_config("transr", d, n_ent, n_rel, dim, 8, 1, rel_dim=k, flags=B.STX_FLAG_BF16_PROJ), G.DEV)
+           for d in ("l1", "l2")}
+    plain, full = (B.stx_rank_work_bytes(ctx[d], nq) for d in ("l1", "l2"))
+    assert plain < full
+    work = torch.empty(full + 512, dtype=torch.uint8, device=G.DEV)
+    work = work[-work.data_ptr() % 256:]
+    want = _rank(ctx["l2"], p, h, r, t, B.STX_TAIL, work[:full])
+    for size in (full - 256, plain):
+        for a, b in zip(_rank(ctx["l2"], p, h, r, t, B.STX_TAIL, work[:size]), want):
+            assert torch.equal(a, b)
+    with pytest.raises(B.StxError) as e:
+        _rank(ctx["l2"], p, h, r, t, B.STX_TAIL, work[:plain - 256])
+    assert e.value.status == B.STX_ERR_WORKSPACE
+
+
 # More undecided pairs in one sweep than an int32 counts (every candidate ties): a chunk of fixed-point queries is
 # never smaller than 32, and a TransR relation is swept in one piece.
 def test_more_undecided_pairs_than_an_int32_counts():
