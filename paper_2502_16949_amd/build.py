@@ -46,5 +46,13 @@ def build_lib(verbose: bool = False) -> str:
     return LIB
 
 
+def build_probe() -> str:
+    """The kernels by which the tests check single matrix-core instructions (tests/mfma_probe.hip)."""
+    src = os.path.join(ROOT, "tests", "mfma_probe.hip")
+    out = os.path.join(ROOT, "tests", "libmfma_probe.so")
+    _run(["hipcc", *FLAGS, src, "-o", out])
+    return out
+
+
 if __name__ == "__main__":
     print(build_lib(verbose=True))

@@ -471,15 +471,16 @@ __global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds id
             // In units scaled by sc (and, in the sweep, by the candidate tile's scale), with t = q.e - |e|^2/2 - tau and
             // tau = (|q|^2 - S_true)/2, a candidate is below the true entity when t > 0.  What is computed differs by
             //   the fp16 roundings        |q| |de| + |dq| (|e| + |de|)
-            //   the fp32 sums of the matrix cores: one instruction at most 2.5 * 2^-24 (|C| + sum |p|) (measured: 1.6),
-            //                             |C| up to |e|^2/2 + |tau| + |q| |e|
+            //   the fp32 sums of the matrix cores: one instruction at most 2^-24 (2.5 |C| + 10 sum |p|) (it cuts off what lies
+            //                             below 2^-24 of the largest of eight products; nine tenths of that measured, and
+            //                             tested), |C| up to |e|^2/2 + |tau| + |q| |e|, all the |p| up to |q| |e|
             //   the norms and tau         fp32 sums of |q|^2 and |e|^2 in chains of dim / 8, a few more roundings
             //   the index-order sums      (dim + 8) 2^-24 S_true / 2
             const float eps = 2.5f * kUnit * (float)(f.np / 2 + 2), kap = norm_slack(f.np);
             float4 par;
             const float qn = sqrtf(n2) * 1.0001f, dq = sqrtf(d2) * 1.002f;
             const float qq = n2 / sc;                          // sc |q|^2 in true units
-            par.x = dq * 1.001f + eps * qn;                    // times the tile's largest norm
+            par.x = dq * 1.001f + (eps + 5.f * kUnit) * qn;                    // times the tile's largest norm
             par.y = qn;                                        // times the tile's largest rounding
             par.z = 0.5f * (qq - st * sc);                     // tau
             par.w = kap * (qq + st * sc) + eps * fabsf(par.z) + 0.51f * (float)(dim + 8) * kUnit * (st * sc);
