@@ -159,6 +159,8 @@ def kernel_work(wl, kernel, rows, touched, fused=False, rides=False, segw=False)
         return rows * (3 * row + 12 + row), "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_seg_reduce_terms":  # semiring backward: the dL/dZ row, the entry's two other table rows and ids in
         return nnz * (3 * row + 16) + touched * row, "GB/s", "hbm", HBM_PEAK_GBS
+    if kernel == "k_forward_stacked_formed":   # the rows' coefficients in place of their dL/dx rows
+        return rows * (3 * row + 12 + 4 + 4), "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_seg_reduce_formed":  # x formed again: the entry's two other table rows and its record in, the
         return nnz * (2 * row + 20) + touched * 2 * row, "GB/s", "hbm", HBM_PEAK_GBS    # column's own row once
     if kernel == "k_scatter":
@@ -258,7 +260,8 @@ def bench_rank(args, wl, dev):
     for _ in range(args.warmup):
         step()
     torch.cuda.synchronize()
-    B.stx_profile_kernel(ctx, rank_kernel, 2 * args.steps * (wl.n_rel if transr else 1))
+    # (one launch a side, one per relation or group of them, or one per chunk of queries and segment of candidates)
+    B.stx_profile_kernel(ctx, rank_kernel, 2 * args.steps * max(wl.n_rel if transr else 1, 256))
     t0 = time.perf_counter()
     for _ in range(args.steps):
         step()
@@ -449,7 +452,8 @@ class Job:
                       and wl.n_ent + wl.n_rel <= 65536 and 3 * wl.rows_per_batch <= (1 << 19) and wl.dim <= 256)
         # the step forms the rows of dL/dx where they are summed (the library's rule for dense kinds, on a full batch)
         self.formed = (self.one_call and wl.model in ("transe", "toruse") and wl.dist not in ("l1", "torus_l1")
-                       and (wl.n_ent + wl.n_rel) * 256 <= 6 << 20 and wl.rows_per_batch * wl.dim * 4 >= 192 << 20)
+                       and (wl.n_ent + wl.n_rel) * 256 <= 6 << 20 and wl.dim >= 128
+                       and wl.rows_per_batch * wl.dim * 4 >= (192 if wl.dim >= 256 else 384) << 20)
         # the one-call step leaves the last kernel of the build to the launch of the transposed product (rows of
         # one float4 per lane; TransR when its work items come from the rows-per-relation counts)
         self.segw = not self.formed and self.one_call and (wl.model != "transr" or wl.n_rel <= 4096) and wl.dim <= 256
@@ -576,7 +580,7 @@ class Job:
         could move, the measured traffic where a profile has it, and the roof the figures are held against."""
         wl = self.wl
         u = touched * mean_rows / wl.rows_per_batch
-        formed = self.formed and kname == "k_seg_reduce"
+        formed = self.formed and kname in ("k_seg_reduce", "k_forward_stacked")
         w, unit, bound, peak = kernel_work(wl, kname + "_formed" if formed else kname, mean_rows, u, self.fused, self.rides,
                                            self.segw)
         ach = w / (us * 1e-6) / (1e9 if unit == "GB/s" else 1e12) if us > 0 else 0.0
@@ -590,7 +594,7 @@ class Job:
             e["achieved_min_bytes"] = round(bmin / (us * 1e-6) / 1e9, 1)
         if e["traffic"] and us > 0:
             e["achieved_traffic"] = round(e["traffic"] / (us * 1e-6) / 1e9, 1)
-        if formed:
+        if formed and kname == "k_seg_reduce":
             e["note"] = ("rows of dL/dx formed where they are summed: nearly all of these bytes come from the L2 caches, which "
                          "hold the 64-float slice of the table that is being read")
         if ach > peak and kname in ("k_forward_stacked", "k_fwd_scatter"):
