@@ -732,6 +732,9 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
             hipLaunchKernelGGL(k_rr_project, pgrid, dim3(kThreads), 0, c->stream, p->ent, p->proj, p->rel, n_ent, dim, k,
                                w.table, ids, stride);
         }
+        // (L2 kinds: always filtered.  At 131 sizes of 1,000 to 120,000 entities, 1 to 237 relations, widths of 32 to 256 and
+        // 1 to 20,000 queries a call took 0.11 to 1.01 times its time with plain sweeps: 84 us and 65 at 1,000 entities,
+        // k = 32, one query; 99 and 100 at 120,000; 20,000 queries of one relation at 14,500, k = 128: 1,927 and 342)
         if (work_bytes < w.total || !rank_filtered(c, a, side, w.ws, nz, ids, queries)) rank_sweep(c, a, sh, false, side, ids, nz, false);
     }
     if (c->cfg.dist == STX_L2) hipLaunchKernelGGL((k_rank_finish<STX_L2>), qgrid, dim3(kThreads), 0, c->stream, w.gts, nq);

@@ -8,6 +8,7 @@ import pytest
 import torch
 
 from paper_2502_16949_amd import binding as B
+from paper_2502_16949_amd.build import build_probe
 from tests import gpu_util as G
 
 pytestmark = pytest.mark.gpu
@@ -19,7 +20,8 @@ fmaf = np.frompyfunc(libm.fmaf, 3, 1)
 
 
 def _probe(name, a, b, c):
-    lib = C.CDLL(os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmfma_probe.so"))
+    so = os.path.join(os.path.dirname(os.path.abspath(__file__)), "libmfma_probe.so")
+    lib = C.CDLL(so if os.path.exists(so) else build_probe())
     a, b, c = (torch.from_numpy(x).to(G.DEV) for x in (a, b, c))
     d = torch.full_like(c, float("nan"))
     args = [C.c_void_p(x.data_ptr()) for x in (a, b, c, d)] + [C.c_int(len(c)), C.c_void_p(torch.cuda.current_stream().cuda_stream)]

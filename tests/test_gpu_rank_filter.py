@@ -22,6 +22,15 @@ def _rank(ctx, p, h, r, t, side, work=None):
     return ts, less, equal
 
 
+def _sweeps_filtered(ctx, *args):
+    """The counts, and how many filtered sweeps the call made."""
+    B.stx_profile_kernel(ctx, "k_rank_pairs", 256)
+    got = _rank(ctx, *args)
+    n = B.stx_profile_read(ctx)[1]
+    B.stx_profile_kernel(ctx, None, 0)
+    return got, n
+
+
 def _ms(f):
     a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
     torch.cuda.synchronize()
@@ -68,8 +77,11 @@ def test_filtered_counts_equal_the_plain_sweep(dist, n_ent, dim, nq, odd_rows):
     ctx, p = B.Context(cfg, G.DEV), B.Params(G.dev_f32(X))
     step = 128 if 128.0 * n_ent * dim < FILTER_STEPS else 0
     for side in (B.STX_TAIL, B.STX_HEAD):
-        got = [x.cpu().numpy() for x in _rank(ctx, p, hd, rd, td, side)]
+        got, sweeps = _sweeps_filtered(ctx, p, hd, rd, td, side)
+        assert sweeps > 0
+        got = [x.cpu().numpy() for x in got]
         if step:
+            assert _sweeps_filtered(ctx, p, hd[:step].clone(), rd[:step].clone(), td[:step].clone(), side)[1] == 0
             parts = [_rank(ctx, p, hd[i:i + step].clone(), rd[i:i + step].clone(), td[i:i + step].clone(), side)
                      for i in range(0, nq, step)]
             want = [torch.cat([x[k] for x in parts]).cpu().numpy() for k in range(3)]
@@ -170,6 +182,7 @@ def test_tables_of_equal_rows(dist, n_ent, dim, nq, equal):
     cfg = B.make_config("toruse" if dist.startswith("torus") else "transe", dist, n_ent, n_rel, dim, 8, 1)
     ctx, p = B.Context(cfg, G.DEV), B.Params(G.dev_f32(X))
     hd, rd, td = G.dev_i32(h), G.dev_i32(r), G.dev_i32(t)
+    assert _sweeps_filtered(ctx, p, hd, rd, td, B.STX_TAIL)[1] > 0
     parts = [(hd[i:i + 128].clone(), rd[i:i + 128].clone(), td[i:i + 128].clone()) for i in range(0, nq, 128)]
     for side in (B.STX_TAIL, B.STX_HEAD):
         got = _rank(ctx, p, hd, rd, td, side)
@@ -252,8 +265,8 @@ def test_without_scratch_of_the_filter(monkeypatch):
     full = B.Context(cfg, G.DEV)
     monkeypatch.setattr(B, "stx_workspace_bytes", lambda c: core)
     small = B.Context(cfg, G.DEV)
-    for a, b in zip(_rank(full, p, h, r, t, B.STX_HEAD), _rank(small, p, h, r, t, B.STX_HEAD)):
-        assert torch.equal(a, b)
+    (one, n_one), (two, n_two) = (_sweeps_filtered(c, p, h, r, t, B.STX_HEAD) for c in (full, small))
+    assert n_one > 0 and n_two == 0 and all(torch.equal(a, b) for a, b in zip(one, two))
     monkeypatch.setattr(B, "stx_workspace_bytes", lambda c: core - 256)
     with pytest.raises(B.StxError) as e:
         B.Context(cfg, G.DEV)
@@ -274,8 +287,8 @@ def test_transr_without_scratch_of_the_filter():
     work = work[-work.data_ptr() % 256:]
     want = _rank(ctx["l2"], p, h, r, t, B.STX_TAIL, work[:full])
     for size in (full - 256, plain):
-        for a, b in zip(_rank(ctx["l2"], p, h, r, t, B.STX_TAIL, work[:size]), want):
-            assert torch.equal(a, b)
+        got, n = _sweeps_filtered(ctx["l2"], p, h, r, t, B.STX_TAIL, work[:size])
+        assert n == 0 and all(torch.equal(a, b) for a, b in zip(got, want))
     with pytest.raises(B.StxError) as e:
         _rank(ctx["l2"], p, h, r, t, B.STX_TAIL, work[:plain - 256])
     assert e.value.status == B.STX_ERR_WORKSPACE
