@@ -439,7 +439,8 @@ inline bool formed_rows(const stx_ctx *c, int64_t n_rows)
     const int64_t cols = c->cfg.n_ent + c->cfg.n_rel, row = (int64_t)c->cfg.dim * 4;
     // (rows of fewer slices: the launches more and the update of its own take longer to repay.  14,951 entities, L2, a step
     // with stored and with formed rows at 202 MiB of them: d = 128 235 and 239 us, d = 256 231 and 222, d = 512 234 and 207;
-    // at 480 MiB: d = 68 769 and 882, d = 100 632 and 605, d = 128 550 and 474, d = 256 514 and 416)
+    // at 480 MiB: d = 68 769 and 882, d = 100 632 and 605, d = 128 550 and 474, d = 256 514 and 416; 22,000 entities, whose
+    // slices are 5.7 MiB: d = 512 508 and 397)
     const int64_t least = (int64_t)(c->cfg.dim >= 256 ? 192 : 384) << 20;
     return stacked && !packed_grad(c) && cols * 256 <= ((int64_t)6 << 20) && c->cfg.dim >= 128 && n_rows * row >= least &&
            // room in the buffer of those rows for what replaces them: coefficients, sorted records, gradient rows
