@@ -30,6 +30,8 @@
 // as extra workgroups of its launch, and one stage of the next batch's build rides in each launch; with TransR
 // the dL/dM_r product (stx_transr_dm_body.h) rides in the product's launch and the sums of its partial matrices
 // in the fix-up's.  All parts of a launch share one block of LDS.
+#include <type_traits>
+
 #include "stx_emit_body.h"
 #include "stx_forward_body.h"
 #include "stx_rowops.h"
@@ -145,31 +147,11 @@ struct SegSecond {
 // SRC_SEMIRING + kind: dL/dZ row and the rows of the entry's two other columns (semiring_term).  Storing the three
 // terms of every matrix row for the product to read took a launch and ten row transfers per matrix row where this takes
 // nine: 47 + 6 us at 65,536 rows of 128 floats (ComplEx) as two kernels and the fix-up.
-// SRC_DIFF + distance kind (formed_rows): x of the row, from the table rows of the entry's own column and the row's other
-// two, times the row's coefficient through the distance's derivative.  In 64-float slices, one after the other
-// (blockIdx.y), so that the slice of the table all workgroups read at a time stays in the L2 caches; columns and
-// coefficient come as one 16-byte record per sorted entry (k_seg_records).
-enum { SRC_STORED = 0, SRC_SEMIRING = 1, SRC_DIFF = 8 };
+enum { SRC_STORED = 0, SRC_SEMIRING = 1 };
 struct SrcArgs {
-    const int32_t *colidx;     // semiring: A's column ids, three per row
-    const float *X, *G;        // table and (semiring) per-row rows, d4 float4 each
-    const int4 *recs;          // formed rows: sorted records
+    const int32_t *colidx;     // A's column ids, three per row
+    const float *X, *G;        // table and per-row rows, d4 float4 each
 };
-
-// recs[e] = (column of sorted entry e, the other two columns of its row in row order, the row's coefficient).
-__global__ __launch_bounds__(kThreads) void k_seg_records(const int32_t *__restrict__ packed, const int32_t *__restrict__ colidx,
-                                                          const float *__restrict__ coefs, int32_t nnz, int32_t split,
-                                                          int4 *__restrict__ recs)
-{
-    const int32_t e = (int32_t)blockIdx.x * kThreads + threadIdx.x;
-    if (e >= nnz) return;
-    const int32_t m = packed[e];
-    const uint32_t row = (uint32_t)m >> 2;
-    const int32_t *cx = colidx + 3 * (int64_t)row;
-    const int32_t c0 = cx[0], c1 = cx[1], c2 = cx[2];
-    const bool tail = m & 1, rel = e >= split;
-    recs[e] = make_int4(tail ? c2 : rel ? c1 : c0, tail || rel ? c0 : c1, tail ? c1 : c2, __float_as_int(coefs[row]));
-}
 
 // table row <- x - lr * g, each product and difference rounded once, as in k_sgd_rows.
 template <int LPR, int ITERS>
@@ -214,6 +196,237 @@ __device__ inline void apply_update(float *__restrict__ row, int d4, int lig, co
     }
 }
 
+// Stitches the chunk-crossing runs of a tile of GROUPS chunks, each in chunk order and by a group of its own: the group in
+// whose chunk a run ends adds up its pieces, from the chunk in which the run began (or from the tile's first, for a run that
+// came in from an earlier workgroup).  One group walking all chunks took 250 cycles per chunk, 8,000 at 32 groups.
+// s_x, s_col_last (FUSED): table row and column of the run that leaves each chunk to the right.
+template <int LPR, int ITERS, int GROUPS, bool FUSED>
+__device__ inline void stitch_runs(const float (*s_part)[2][ITERS * LPR * 4], const int32_t *s_info, const int32_t *s_seg_last,
+                                   const float (*s_x)[FUSED ? ITERS * LPR * 4 : 4], const int32_t *s_col_last, float *my_part,
+                                   float *out_rows, int ld_out, int d4, int ld_tab, const FusedArgs &fu)
+{
+    const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
+    const int linfo = (int)(threadIdx.x & 63) < GROUPS ? s_info[threadIdx.x & 63] : 0, info = s_info[grp];
+    const uint64_t m_cont = __ballot((linfo & FIRST_CONT) != 0), m_last = __ballot((linfo & HAS_LAST) != 0);
+    // pieces of the run that reaches chunk g, oldest first; returns the chunk it began in, -1: an earlier workgroup's
+    auto run_sum = [&](int g, uint64_t before, Acc<ITERS> &cur) {
+        const uint64_t m = m_last & before;
+        const int s0 = m ? 63 - __clzll(m) : -1;
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it) cur.v[it] = ld4(&s_part[s0 < 0 ? 0 : s0][s0 < 0 ? 0 : 1][(lig + it * LPR) * 4]);
+        for (int h = s0 < 0 ? 1 : s0 + 1; h <= g; ++h) {
+            Acc<ITERS> p;
+#pragma unroll
+            for (int it = 0; it < ITERS; ++it) p.v[it] = ld4(&s_part[h][0][(lig + it * LPR) * 4]);
+            cur.add(p);
+        }
+        return s0;
+    };
+    if ((info & HAS_FIRST) && !(info & FIRST_CONT)) {      // a run ends inside this group's chunk
+        Acc<ITERS> cur;
+        const int s0 = run_sum(grp, (1ull << grp) - 1ull, cur);
+        if (s0 < 0) {
+            store_row<LPR, ITERS>(my_part, d4, lig, cur);
+        } else if constexpr (FUSED) {
+            Acc<ITERS> x;
+#pragma unroll
+            for (int it = 0; it < ITERS; ++it) x.v[it] = ld4(&s_x[s0][(lig + it * LPR) * 4]);
+            apply_update<LPR, ITERS>(fused_row(fu, s_col_last[s0], ld_tab), d4, lig, x, cur, fu.lr, fu.mode, fu.stream);
+        } else {
+            store_row<LPR, ITERS>(out_rows + (int64_t)s_seg_last[s0] * ld_out, d4, lig, cur);
+        }
+    }
+    // the run that goes on into the next tile (then the tile is full); taken by a group that seldom has another
+    if (grp == 0 && ((m_cont | m_last) >> (GROUPS - 1) & 1)) {
+        Acc<ITERS> cur;
+        const int s0 = run_sum(GROUPS - 1, (1ull << (GROUPS - 1) << 1) - 1ull, cur);
+        store_row<LPR, ITERS>(my_part + (s0 < 0 ? 0 : ld_out), d4, lig, cur);
+    }
+}
+
+struct alignas(64) FormedRecord {
+    uint32_t a[8], b[8], coef[8], flags[8];
+};
+// What 64 sorted entries (four chunks of 16) bring to the formed product: worked out once here, read by the wavefronts
+// that sum the 64 entries of each slice.
+struct alignas(64) FormedHead {
+    uint64_t heads;            // entries that head a segment
+    uint64_t events;           // positions at which a sum is closed (q: behind entry q - 1): chunk borders and heads ...
+    uint64_t to_lds, left;     // ... into LDS; as the run that entered its chunk from the left (else: that leaves it to the right)
+    int32_t seg, n_active;     // segment of the first entry; entries of active pairs
+    uint32_t info;             // the chunks' flags, a byte each
+    uint32_t last;             // the sum closed behind the last entry: 1 into LDS, 2 left
+    uint32_t pad[4];
+};
+// The entries of active pairs (of the others, whose coefficient is +0, nothing is added), in order, from the place of the
+// first of 64 on, eight to a record: the byte offsets of the table rows of the matrix row's columns other than the entry's
+// own, in row order; its coefficient; 1 tail entry | 2 a sum is closed before this entry | position << 2.  Up to a multiple
+// of eight: row 0.
+__global__ __launch_bounds__(kThreads) void k_seg_records(const int32_t *__restrict__ packed, const int32_t *__restrict__ seg_id,
+                                                          const int32_t *__restrict__ colidx, const float *__restrict__ coefs,
+                                                          int32_t nnz, int32_t split, uint32_t row_bytes,
+                                                          FormedRecord *__restrict__ recs, FormedHead *__restrict__ hds)
+{
+    const int lane = threadIdx.x & 63;
+    const int32_t e0 = ((int32_t)blockIdx.x * kThreads + (int32_t)threadIdx.x) & ~63;
+    if (e0 >= nnz) return;
+    const int n = min(64, nnz - e0);
+    uint4 rc = make_uint4(0u, 0u, 0u, 0u);
+    uint32_t m = 0u;
+    if (lane < n) {
+        m = (uint32_t)packed[e0 + lane];
+        const uint32_t row = m >> 2;
+        const int32_t *cx = colidx + 3 * (int64_t)row;
+        const uint32_t c0 = (uint32_t)cx[0] * row_bytes, c1 = (uint32_t)cx[1] * row_bytes, c2 = (uint32_t)cx[2] * row_bytes;
+        const bool tail = m & 1u, rel = e0 + lane >= split;
+        rc = make_uint4(tail || rel ? c0 : c1, tail ? c1 : c2, __float_as_uint(coefs[row]), 0u);
+    }
+    const bool right_head = e0 + n >= nnz || (packed[e0 + n] & 2);
+    const int32_t seg = seg_id[e0];
+    const uint64_t heads = __ballot((m & 2u) != 0), active = __ballot(rc.z != 0u);
+    const uint64_t events = (heads | 0x0001000100010001ull) & (n < 64 ? (1ull << n) - 1ull : ~0ull) & ~1ull;
+    auto from_left = [&](int q) {                          // (no head from the chunk's first entry to entry q - 1)
+        const int s = (q - 1) & ~15;
+        return e0 + s > 0 && (heads & ((1ull << (q - 1)) * 2ull - 1ull) >> s << s) == 0ull;
+    };
+    const bool fl = lane > 0 && from_left(max(lane, 1));
+    const uint64_t left = __ballot(fl), to_lds = __ballot(fl || ((lane & 15) == 0 && !(heads >> lane & 1ull)));
+    uint32_t info = 0u;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+        const int s = 16 * c, t = min(s + 16, n);
+        if (s >= n) break;
+        const bool first = e0 + s > 0 && !(heads >> s & 1ull), right = t == n ? !right_head : !(heads >> t & 1ull);
+        const bool inner = (heads >> s & 0xfffeull) != 0ull;
+        info |= (uint32_t)((first ? HAS_FIRST | (!inner && right ? FIRST_CONT : 0) : 0) | (right && (!first || inner) ? HAS_LAST : 0)) << (8 * c);
+    }
+    const int n_active = __builtin_popcountll(active);
+    const bool last_left = from_left(n);
+    if (lane == 0)
+        hds[e0 >> 6] = FormedHead{heads, events, to_lds, left, seg, n_active, info, (last_left || !right_head ? 1u : 0u) | (last_left ? 2u : 0u), {}};
+    const uint64_t upto = (1ull << lane) * 2ull - 1ull, before = active & (upto >> 1);
+    const uint64_t since = before ? ~((1ull << (63 - __builtin_clzll(before))) * 2ull - 1ull) : ~0ull;
+    const int rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(active >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)active, 0u));
+    rc.w = (m & 1u) | ((events & since & upto) ? 2u : 0u) | (uint32_t)lane << 2;
+    const bool on = active >> lane & 1ull;
+    if (!on) rc = make_uint4(0u, 0u, 0u, 0u);
+    const int place = on ? rank : n_active + lane - rank;
+    if (on || lane - rank < ((8 - n_active) & 7)) {
+        FormedRecord &rec = recs[(e0 + place) >> 3];
+        rec.a[place & 7] = rc.x; rec.b[place & 7] = rc.y; rec.coef[place & 7] = rc.z; rec.flags[place & 7] = rc.w;
+    }
+}
+
+// The transposed product over rows that are formed where they are summed (formed_rows): an active entry's term is
+// x = (h + r) - t, from the table row of its own column, which a run keeps in a register, and two others, times the row's
+// coefficient through the distance's derivative.  Work is cut as k_seg_reduce<16, 1, false, 16> cuts stored rows, and
+// the sums have its bits: tiles of 16 chunks of 16 sorted entries, in 64-float slices.  A wavefront takes four chunks of one
+// slice with one float per lane.  Everything but the arithmetic on floats is then the same for the whole wavefront: it
+// comes through scalar loads and runs on the scalar unit, and an active entry takes two 256-byte loads and four vector
+// instructions.  Bound by the L2 caches' rate for such rows (16 TB/s when every pair is active).  With 16 lanes of a float4
+// per entry, four entries side by side and their columns and flags broadcast by shuffles, the vector units were busy three
+// quarters of the time with everything but the sums: 393,216 positives at d = 1024 took 1,057 us a step (mean of 30
+// steps) and take 665 (1,109 while every pair is active, 530 when half of them are).
+// The slices are dealt to the eight dies, each of which keeps its own one or two in its L2 cache.
+template <int DIST>
+__global__ __launch_bounds__(kThreads, 8) void k_seg_formed(const FormedRecord *__restrict__ recs, const FormedHead *__restrict__ hds,
+                                                            const int32_t *__restrict__ touched_cols, int32_t nnz, int ntiles,
+                                                            int nslices, const float *__restrict__ X, uint32_t x_bytes, int dim,
+                                                            float *__restrict__ out_rows, int ld_out, float *__restrict__ partials)
+{
+    constexpr int CHUNKS = 16, CPW = CHUNKS / (kThreads / 64), LPR = 16;
+    __shared__ float s_part[CHUNKS][2][64];
+    __shared__ int32_t s_info[CHUNKS], s_seg_last[CHUNKS];
+    // workgroups are dealt to the dies in turn
+    const uint32_t total = (uint32_t)ntiles * (uint32_t)nslices, per = (total + 7u) / 8u;
+    const uint32_t work = (blockIdx.x & 7u) * per + (blockIdx.x >> 3);
+    if (work >= total) return;                             // (uniform)
+    const int slice = (int)(work / (uint32_t)ntiles), block = (int)(work - (uint32_t)slice * (uint32_t)ntiles);
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int col = slice * 64 + lane;
+    // (a row's offset is wavefront-uniform and stays in a scalar register, which a buffer load adds by itself)
+    const __amdgpu_buffer_rsrc_t xs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(X), 0, (int)x_bytes, 0x00027000);
+    const int lane_off = min(col, dim - 1) * 4;
+    auto row_at = [&](uint32_t off) {
+        return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(xs, lane_off, (int)off, 0));
+    };
+    const int e0 = (block * CHUNKS + wave * CPW) * 16;
+    if (e0 >= nnz) {
+        if (lane < CPW) s_info[wave * CPW + lane] = 0;
+    } else {
+        const STX_CONST_AS FormedHead *hd = (const STX_CONST_AS FormedHead *)(hds + (e0 >> 6));
+        const STX_CONST_AS FormedRecord *rp = (const STX_CONST_AS FormedRecord *)(recs + (e0 >> 3));
+        const STX_CONST_AS int32_t *tc = (const STX_CONST_AS int32_t *)touched_cols;
+        const uint64_t heads = hd->heads, to_lds = hd->to_lds, left = hd->left;
+        uint64_t waiting = hd->events;                     // events not yet reached
+        const int n_active = hd->n_active;
+        int32_t cur_seg = hd->seg;
+        if (lane < CPW) {
+            const uint64_t upto = (1ull << (16 * lane + 15)) * 2ull - 2ull;
+            s_info[wave * CPW + lane] = (int)(hd->info >> (8 * lane) & 0xffu);
+            s_seg_last[wave * CPW + lane] = cur_seg + __builtin_popcountll(heads & upto);   // (of the chunk's last entry)
+        }
+        // the rows of this run's column and of the next one's
+        const uint32_t row_bytes = (uint32_t)dim * 4u;
+        float own = row_at((uint32_t)tc[cur_seg] * row_bytes), next_own = 0.f, acc = 0.f;
+        if (heads & ~1ull) next_own = row_at((uint32_t)tc[cur_seg + 1] * row_bytes);
+        auto close = [&](int q, bool lds, bool slot0) {
+            if (lds) s_part[wave * CPW + ((q - 1) >> 4)][slot0 ? 0 : 1][lane] = acc;
+            else if (col < dim) __builtin_nontemporal_store(acc, out_rows + (int64_t)cur_seg * ld_out + col);
+            acc = 0.f;
+        };
+        auto close_until = [&](int p) {                    // the sums whose end lies at or before position p
+#pragma unroll 1
+            while (waiting & ((1ull << p) * 2ull - 1ull)) {
+                const int q = __builtin_ctzll(waiting);
+                waiting &= waiting - 1ull;
+                close(q, to_lds >> q & 1ull, left >> q & 1ull);
+                if (heads >> q & 1ull) {
+                    ++cur_seg;
+                    own = next_own;
+                    if (heads & ~((1ull << q) * 2ull - 1ull)) next_own = row_at((uint32_t)tc[cur_seg + 1] * row_bytes);
+                }
+            }
+        };
+        // NB entries at a time, all their rows in flight together
+        auto batch = [&](auto nb, int j, int cnt) {
+            constexpr int NB = decltype(nb)::value;
+            const STX_CONST_AS FormedRecord &rec = rp[j >> 3];
+            float va[NB], vb[NB];
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                va[u] = row_at(rec.a[u]);
+                vb[u] = row_at(rec.b[u]);
+            }
+            typedef uint32_t u16x __attribute__((ext_vector_type(16)));
+            u16x cf = *(const STX_CONST_AS u16x *)&rec.coef[0];
+            asm volatile("" : "+s"(cf));                   // (here, beside the rows' loads, and not one by one where they are used)
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                if (u < cnt) {
+                    const uint32_t fl = cf[8 + u];
+                    if (fl & 2u) close_until((int)(fl >> 2));
+                    // x rounded as the forward pass rounds it (a sum has the same bits either way round); then the derivative
+                    // times the coefficient, as write_grad_row would have stored it
+                    const float c = __uint_as_float(cf[u]);
+                    if (fl & 1u) acc -= dterm<DIST>((va[u] + vb[u]) - own, c);
+                    else acc += dterm<DIST>((own + va[u]) - vb[u], c);
+                }
+            }
+        };
+        int j = 0;
+        for (; j + 8 <= n_active; j += 8) batch(std::integral_constant<int, 8>{}, j, 8);
+        if (n_active - j > 4) batch(std::integral_constant<int, 8>{}, j, n_active - j);
+        else if (j < n_active) batch(std::integral_constant<int, 4>{}, j, n_active - j);
+        close_until(63);
+        close(min(64, nnz - e0), hd->last & 1u, hd->last & 2u);
+    }
+    __syncthreads();
+    const int c4 = slice * LPR;
+    stitch_runs<LPR, 1, CHUNKS, false>(s_part, s_info, s_seg_last, nullptr, nullptr, partials + (int64_t)block * 2 * ld_out + 4 * c4,
+                                       out_rows + 4 * c4, ld_out, min(LPR, dim / 4 - c4), dim, FusedArgs{});
+}
+
 // PACKED: the source rows are records of ld_src bytes at src_a (dim/4 sign bytes) with their coefficients in
 // src_b, as the forward pass of an L1-kind distance stores them; values and summation order are the same as with
 // dense rows, so both forms give the same bits.
@@ -237,7 +450,7 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
 {
     constexpr bool RAW = RIDE != 0;
     static_assert(SRC == SRC_STORED || (!RAW && !PACKED && ITERS == 1 && !FUSED), "formed rows: the plain product");
-    constexpr bool DIFF = SRC >= SRC_DIFF, SEMI = SRC != SRC_STORED && !DIFF;
+    constexpr bool SEMI = SRC != SRC_STORED;
     // One block of LDS for whichever part a workgroup plays (the parts' own arrays would add up and cost the
     // launch wavefronts per CU): the product's arrays below, or those of a body that rides.
     static_assert(THREADS == kThreads || RIDE == 0, "the bodies that ride have kThreads threads");
@@ -305,7 +518,7 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
         d4 = min(LPR, d4 - c4);
         if (PACKED) pk_off = c4;
         else if (SRC == SRC_STORED) { src_a += 4 * c4; src_b += 4 * c4; }
-        else { sr.X += 4 * c4; if (SEMI) sr.G += 4 * c4; }
+        else { sr.X += 4 * c4; sr.G += 4 * c4; }
         if (out_rows) out_rows += 4 * c4;
         partials += 4 * c4;
         if (fu.table) fu.table += 4 * c4;
@@ -355,14 +568,6 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
             if (ec1 < e_end) right_head = (packed[ec1] & 2) != 0;
         }
         int32_t o1 = 0, o2 = 0;                            // SRC: the other two columns of this lane's entry's row
-        int32_t own = 0;                                   // DIFF: its column and its row's coefficient
-        float cs = 0.f;
-        if constexpr (DIFF) {
-            if (lig < CHUNK && ec0 + lig < ec1) {
-                const int4 rc = sr.recs[ec0 + lig];
-                own = rc.x; o1 = rc.y; o2 = rc.z; cs = __int_as_float(rc.w);
-            }
-        }
         if constexpr (SEMI) {
             if (lig < CHUNK && ec0 + lig < ec1) {
                 const int32_t *cx = sr.colidx + 3 * (int64_t)((uint32_t)meta >> 2);
@@ -444,17 +649,6 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
                         sb[u][it] = j < d4 ? pb[it * LPR] : (uint8_t)0;
                     }
                     cf[u] = src_b[row];
-                } else if constexpr (DIFF) {
-                    const int src = (j0 + u) & (LPR - 1);
-                    const int32_t c1 = __shfl(o1, src, LPR), c2 = __shfl(o2, src, LPR);
-                    cf[u] = __shfl(cs, src, LPR);
-                    const int32_t c0 = __shfl(own, src, LPR);
-                    if ((mu[u] & 2) || j0 + u == 0)        // a run begins (or goes on) here: its column's own row
-                        load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c0 * (uint32_t)ld_tab, d4, lig, v[u]);
-                    if (__float_as_uint(cf[u])) {          // (+0, a row of inactive pairs, adds nothing)
-                        load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c1 * (uint32_t)ld_tab, d4, lig, va[u]);
-                        load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c2 * (uint32_t)ld_tab, d4, lig, vb[u]);
-                    }
                 } else if constexpr (SEMI) {
                     const int32_t c1 = __shfl(o1, (j0 + u) & (LPR - 1), LPR), c2 = __shfl(o2, (j0 + u) & (LPR - 1), LPR);
                     load_row_stream<LPR, ITERS>(sr.G + (uint64_t)row * (uint32_t)ld_tab, d4, lig, v[u]);
@@ -489,19 +683,6 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
                             acc.v[it].z = __builtin_fmaf(c, (float)((int)(b << 26) >> 30), acc.v[it].z);
                             acc.v[it].w = __builtin_fmaf(c, (float)((int)(b << 24) >> 30), acc.v[it].w);
                         }
-                    } else if constexpr (DIFF) {
-                        // x = (h + r) - t, rounded as the forward pass rounds it (a sum has the same bits either way
-                        // round); then the derivative times the coefficient, as write_grad_row would have stored it
-                        if ((mu[u] & 2) || jj == 0) xcur = v[u];
-                        if (__float_as_uint(cf[u])) {
-                            const bool tail = mu[u] & 1;
-                            const float4 x = tail ? sub4(add4(va[u].v[0], vb[u].v[0]), xcur.v[0])
-                                                  : sub4(add4(xcur.v[0], va[u].v[0]), vb[u].v[0]);
-                            const float c = cf[u];
-                            constexpr int DIST = DIFF ? SRC - SRC_DIFF : 0;
-                            const float4 g = make_float4(dterm<DIST>(x.x, c), dterm<DIST>(x.y, c), dterm<DIST>(x.z, c), dterm<DIST>(x.w, c));
-                            acc.v[0] = tail ? sub4(acc.v[0], g) : add4(acc.v[0], g);
-                        }
                     } else if constexpr (SEMI) {
                         Acc<ITERS> tm;
                         tm.v[0] = semiring_term<SRC - SRC_SEMIRING>(v[u].v[0], va[u].v[0], vb[u].v[0], (mu[u] & 1) != 0);
@@ -526,46 +707,8 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
     if (lig == 0) s_info[grp] = info;
     __syncthreads();
 
-    // Stitch the chunk-crossing runs, each in chunk order and by a group of its own: the group in whose chunk a run
-    // ends adds up its pieces, from the chunk in which the run began (or from the tile's first, for a run that came
-    // in from an earlier workgroup).  One group walking all chunks took 250 cycles per chunk, 8,000 at 32 groups.
-    const int linfo = (int)(threadIdx.x & 63) < GROUPS ? s_info[threadIdx.x & 63] : 0;
-    const uint64_t m_cont = __ballot((linfo & FIRST_CONT) != 0), m_last = __ballot((linfo & HAS_LAST) != 0);
-    float *my_part = partials + (int64_t)block * 2 * ld_out;
-    // pieces of the run that reaches chunk g, oldest first; returns the chunk it began in, -1: an earlier workgroup's
-    auto run_sum = [&](int g, uint64_t before, Acc<ITERS> &cur) {
-        const uint64_t m = m_last & before;
-        const int s0 = m ? 63 - __clzll(m) : -1;
-#pragma unroll
-        for (int it = 0; it < ITERS; ++it) cur.v[it] = ld4(&s_part[s0 < 0 ? 0 : s0][s0 < 0 ? 0 : 1][(lig + it * LPR) * 4]);
-        for (int h = s0 < 0 ? 1 : s0 + 1; h <= g; ++h) {
-            Acc<ITERS> p;
-#pragma unroll
-            for (int it = 0; it < ITERS; ++it) p.v[it] = ld4(&s_part[h][0][(lig + it * LPR) * 4]);
-            cur.add(p);
-        }
-        return s0;
-    };
-    if ((info & HAS_FIRST) && !(info & FIRST_CONT)) {      // a run ends inside this group's chunk
-        Acc<ITERS> cur;
-        const int s0 = run_sum(grp, (1ull << grp) - 1ull, cur);
-        if (s0 < 0) {
-            store_row<LPR, ITERS>(my_part, d4, lig, cur);
-        } else if constexpr (FUSED) {
-            Acc<ITERS> x;
-#pragma unroll
-            for (int it = 0; it < ITERS; ++it) x.v[it] = ld4(&s_x[s0][(lig + it * LPR) * 4]);
-            apply_update<LPR, ITERS>(fused_row(fu, s_col_last[s0], ld_tab), d4, lig, x, cur, fu.lr, fu.mode, fu.stream);
-        } else {
-            store_row<LPR, ITERS>(out_rows + (int64_t)s_seg_last[s0] * ld_out, d4, lig, cur);
-        }
-    }
-    // the run that goes on into the next tile (then the tile is full); taken by a group that seldom has another
-    if (grp == 0 && ((m_cont | m_last) >> (GROUPS - 1) & 1)) {
-        Acc<ITERS> cur;
-        const int s0 = run_sum(GROUPS - 1, (1ull << (GROUPS - 1) << 1) - 1ull, cur);
-        store_row<LPR, ITERS>(my_part + (s0 < 0 ? 0 : ld_out), d4, lig, cur);
-    }
+    stitch_runs<LPR, ITERS, GROUPS, FUSED>(s_part, s_info, s_seg_last, s_x, s_col_last, partials + (int64_t)block * 2 * ld_out,
+                                           out_rows, ld_out, d4, ld_tab, fu);
 }
 
 // RIDE: 1 the first scatter pass of the next batch's sort comes along, 2 its histogram pass of the second digit,
@@ -1039,7 +1182,7 @@ static void semiring_t_go(stx_ctx *c, const stx_incidence *inc, const float *X, 
     const int d4 = c->cfg.dim / 4;
     const FusedArgs fu{};
     const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
-    const SrcArgs sr{inc->a_colidx, X, gz, nullptr};
+    const SrcArgs sr{inc->a_colidx, X, gz};
 #define STX_SR_T(K, CH)                                                                                         \
     hipLaunchKernelGGL((k_seg_reduce<LPR, 1, false, CH, false, 0, SRC_SEMIRING + K>), grid, dim3(kThreads), 0,  \
                        c->stream, inc->at_packed, inc->at_seg_id, 0, nnz, nullptr, nullptr,                     \
@@ -1073,18 +1216,18 @@ stx_status launch_seg_formed(stx_ctx *c, const stx_incidence *inc, const stx_par
     {
         ProfScope prof(c, "k_seg_records");
         hipLaunchKernelGGL(k_seg_records, dim3((unsigned)((nnz + kThreads - 1) / kThreads)), dim3(kThreads), 0, c->stream,
-                           inc->at_packed, inc->a_colidx, fr.coefs, nnz, split, fr.recs);
+                           inc->at_packed, inc->at_seg_id, inc->a_colidx, fr.coefs, nnz, split, (uint32_t)c->cfg.dim * 4u,
+                           (FormedRecord *)fr.recs, (FormedHead *)fr.heads);
     }
-    const int d4 = c->cfg.dim / 4, ntiles = (nnz + TILE - 1) / TILE;
-    const dim3 grid((unsigned)ntiles, (unsigned)((d4 + LPR - 1) / LPR));
+    const int d4 = c->cfg.dim / 4, ntiles = (nnz + TILE - 1) / TILE, nslices = (d4 + LPR - 1) / LPR;
+    const dim3 grid((unsigned)ntiles, (unsigned)nslices);
     const FusedArgs fu{};
     const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
-    const SrcArgs sr{nullptr, p->ent, nullptr, fr.recs};
+    const uint32_t x_bytes = (uint32_t)(c->cfg.n_ent + c->cfg.n_rel) * (uint32_t)c->cfg.dim * 4u;   // (formed_rows: 96 MiB at most)
 #define STX_FORMED(D)                                                                                           \
-    hipLaunchKernelGGL((k_seg_reduce<LPR, 1, false, CH, false, 0, SRC_DIFF + D>), grid, dim3(kThreads), 0,      \
-                       c->stream, inc->at_packed, inc->at_seg_id, 0, nnz, nullptr, nullptr, split, 0, d4,       \
-                       out_rows, ld_out, c->partials, fu, sec, SegWriteRide{}, EmitAhead{}, ScatterAhead{},     \
-                       DmRide{}, sr)
+    hipLaunchKernelGGL((k_seg_formed<D>), dim3(((unsigned)ntiles * (unsigned)nslices + 7u) / 8u * 8u), dim3(kThreads), 0, \
+                       c->stream, (const FormedRecord *)fr.recs, (const FormedHead *)fr.heads, inc->at_touched_cols, nnz, ntiles, nslices, p->ent, x_bytes, \
+                       c->cfg.dim, out_rows, ld_out, c->partials)
     {
         ProfScope prof(c, "k_seg_reduce");
         if (c->cfg.dist == STX_L2) STX_FORMED(STX_L2);

@@ -9,6 +9,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#define STX_CONST_AS __attribute__((address_space(4)))      // uniform loads from here are scalar loads
+
 namespace stx {
 
 // Exclusive prefix sum of one value per thread across a 256-thread workgroup; *total (shared or
@@ -64,6 +66,12 @@ __device__ inline float4 ld4_stream(const float *p)
 {
     stx_f4 t = __builtin_nontemporal_load(reinterpret_cast<const stx_f4 *>(p));
     return make_float4(t.x, t.y, t.z, t.w);
+}
+__device__ inline uint4 ld_u4_stream(const uint4 *p)
+{
+    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
+    const u4 t = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(p));
+    return make_uint4(t.x, t.y, t.z, t.w);
 }
 __device__ inline void st4_stream(float *p, float4 v)
 {

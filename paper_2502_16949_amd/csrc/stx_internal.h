@@ -443,19 +443,21 @@ inline bool formed_rows(const stx_ctx *c, int64_t n_rows)
     // slices are 5.7 MiB: d = 512 508 and 397)
     const int64_t least = (int64_t)(c->cfg.dim >= 256 ? 192 : 384) << 20;
     return stacked && !packed_grad(c) && cols * 256 <= ((int64_t)6 << 20) && c->cfg.dim >= 128 && n_rows * row >= least &&
-           // room in the buffer of those rows for what replaces them: coefficients, sorted records, gradient rows
-           n_rows * (4 + 48) + (cols + 1) * row + 1024 <= c->rows_max * row;
+           // room in the buffer of those rows for what replaces them: coefficients, sorted records, their heads, gradient rows
+           n_rows * (4 + 48 + 3) + (cols + 1) * row + 4096 <= c->rows_max * row;
 }
 struct FormedRows {
     float *coefs;              // [n_rows]
-    int4 *recs;                // [3 n_rows], per sorted entry: its column, the row's other two columns, the coefficient
+    void *recs;                // 16 bytes for every sorted entry, see k_seg_records
+    void *heads;               // a FormedHead (64 bytes) for 64 of them
     float *grads;              // gradient rows of the touched columns, ld floats each (when the update follows at once)
 };
 inline FormedRows formed_buffers(const stx_ctx *c, int64_t n_rows)
 {
     char *b = (char *)c->gbuf[0];
-    const int64_t o1 = (n_rows * 4 + 255) / 256 * 256, o2 = o1 + (n_rows * 48 + 255) / 256 * 256;
-    return {(float *)b, (int4 *)(b + o1), (float *)(b + o2)};
+    const int64_t blocks = (3 * n_rows + 63) / 64;
+    const int64_t o1 = (n_rows * 4 + 255) / 256 * 256, o2 = o1 + blocks * 1024, o3 = o2 + (blocks * 64 + 255) / 256 * 256;
+    return {(float *)b, b + o1, b + o2, (float *)(b + o3)};
 }
 
 inline stx_status hip_ok(hipError_t e) { return e == hipSuccess ? STX_OK : STX_ERR_HIP; }

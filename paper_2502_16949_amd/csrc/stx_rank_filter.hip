@@ -32,7 +32,6 @@ namespace stx {
 
 typedef _Float16 half8 __attribute__((ext_vector_type(8)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
-#define STX_CONST_AS __attribute__((address_space(4)))      // uniform loads from here are scalar loads
 
 constexpr int kSadGroup = 16;          // queries per group of k_rank_sad: one accumulator each
 constexpr int kSadThreads = 512;
