@@ -30,6 +30,7 @@
 // as extra workgroups of its launch, and one stage of the next batch's build rides in each launch; with TransR
 // the dL/dM_r product (stx_transr_dm_body.h) rides in the product's launch and the sums of its partial matrices
 // in the fix-up's.  All parts of a launch share one block of LDS.
+#include <algorithm>
 #include <type_traits>
 
 #include "stx_emit_body.h"
@@ -764,15 +765,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
         out_rows = sec.out_rows; partials = sec.partials;
         fu.table_b = sec.fused_table; fu.mode = sec.fused_mode;
     }
-    const int ld_tab = d4 * 4;
-    if (gridDim.y > 1) {                                   // column slices, as in k_seg_reduce
-        const int c4 = (int)blockIdx.y * LPR;
-        d4 = min(LPR, d4 - c4);
-        if (out_rows) out_rows += 4 * c4;
-        partials += 4 * c4;
-        if (fu.table) fu.table += 4 * c4;
-        if (fu.table_b) fu.table_b += 4 * c4;
-    }
+    const int ld_tab = d4 * 4, d4_all = d4;
     constexpr int GROUPS = kThreads / LPR;
     constexpr int ROWF = ITERS * LPR * 4;
     constexpr int TILE = GROUPS * CHUNK;
@@ -798,44 +791,57 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
     const int32_t col = FUSED ? fu.touched_cols[seg] : 0;
     const int32_t j0 = (seg_ptr[seg] - e_begin) / TILE;         // tile in which the run began
     const int n = j - j0 + 1;                                   // partial rows: (j0, slot 1), (j0+1 .. j, slot 0)
-    Acc<ITERS> xrow;                                            // FUSED: the table row, fetched beside the partial rows
-    xrow.zero();
-    if (FUSED && grp == 0) {
-        if (fu.stream) load_row_stream<LPR, ITERS>(fused_row(fu, col, ld_tab), d4, lig, xrow);
-        else load_row<LPR, ITERS>(fused_row(fu, col, ld_tab), d4, lig, xrow);
-    }
-    const int per = (n + GROUPS - 1) / GROUPS;
-    const int lo = min(grp * per, n), hi = min(lo + per, n);
-    Acc<ITERS> acc;
-    acc.zero();
-    constexpr int FU = ITERS == 1 ? 8 : 2;
-    int q = lo;
-    for (; q + FU <= hi; q += FU) {   // FU partial rows in flight, added in tile order
-        Acc<ITERS> v[FU];
+    // Column slices of LPR ITERS float4, as in k_seg_reduce, dealt to the workgroups of blockIdx.y in turn: most tiles end no
+    // crossing run, so a workgroup for each of a wide row's slices mostly starts to find that out once more (16 slices of
+    // 9,216 tiles: 105 us as 16 workgroups a tile, 65 as four).  Launches with a ride hold whole rows.
+    for (int c4 = RIDE ? 0 : (int)blockIdx.y * ITERS * LPR; c4 < d4_all; c4 += (int)gridDim.y * ITERS * LPR) {
+        if (RIDE == 0) {
+            d4 = min(ITERS * LPR, d4_all - c4);
+            if (c4 != (int)blockIdx.y * ITERS * LPR) __syncthreads();   // the slice before this one has been read out of LDS
+        }
+        FusedArgs fs = fu;
+        if (fs.table) fs.table += 4 * c4;
+        if (fs.table_b) fs.table_b += 4 * c4;
+        Acc<ITERS> xrow;                                            // FUSED: the table row, fetched beside the partial rows
+        xrow.zero();
+        if (FUSED && grp == 0) {
+            if (fu.stream) load_row_stream<LPR, ITERS>(fused_row(fs, col, ld_tab), d4, lig, xrow);
+            else load_row<LPR, ITERS>(fused_row(fs, col, ld_tab), d4, lig, xrow);
+        }
+        const int per = (n + GROUPS - 1) / GROUPS;
+        const int lo = min(grp * per, n), hi = min(lo + per, n);
+        Acc<ITERS> acc;
+        acc.zero();
+        constexpr int FU = ITERS == 1 ? 8 : 2;
+        int q = lo;
+        for (; q + FU <= hi; q += FU) {   // FU partial rows in flight, added in tile order
+            Acc<ITERS> v[FU];
 #pragma unroll
-        for (int u = 0; u < FU; ++u)
-            load_row<LPR, ITERS>(partials + ((int64_t)(j0 + q + u) * 2 + (q + u == 0 ? 1 : 0)) * ld_out, d4, lig, v[u]);
+            for (int u = 0; u < FU; ++u)
+                load_row<LPR, ITERS>(partials + 4 * c4 + ((int64_t)(j0 + q + u) * 2 + (q + u == 0 ? 1 : 0)) * ld_out, d4, lig, v[u]);
 #pragma unroll
-        for (int u = 0; u < FU; ++u) acc.add(v[u]);
-    }
-    for (; q < hi; ++q) {
-        Acc<ITERS> v;
-        load_row<LPR, ITERS>(partials + ((int64_t)(j0 + q) * 2 + (q == 0 ? 1 : 0)) * ld_out, d4, lig, v);
-        acc.add(v);
-    }
-#pragma unroll
-    for (int it = 0; it < ITERS; ++it) st4(&s_sum[grp][(lig + it * LPR) * 4], acc.v[it]);
-    __syncthreads();
-    if (grp == 0) {
-        const int used = (n + per - 1) / per;                   // groups that had at least one row
-        for (int g = 1; g < used; ++g) {
+            for (int u = 0; u < FU; ++u) acc.add(v[u]);
+        }
+        for (; q < hi; ++q) {
             Acc<ITERS> v;
-#pragma unroll
-            for (int it = 0; it < ITERS; ++it) v.v[it] = ld4(&s_sum[g][(lig + it * LPR) * 4]);
+            load_row<LPR, ITERS>(partials + 4 * c4 + ((int64_t)(j0 + q) * 2 + (q == 0 ? 1 : 0)) * ld_out, d4, lig, v);
             acc.add(v);
         }
-        if constexpr (FUSED) apply_update<LPR, ITERS>(fused_row(fu, col, ld_tab), d4, lig, xrow, acc, fu.lr, fu.mode, fu.stream);
-        else store_row<LPR, ITERS>(out_rows + (int64_t)seg * ld_out, d4, lig, acc);
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it) st4(&s_sum[grp][(lig + it * LPR) * 4], acc.v[it]);
+        __syncthreads();
+        if (grp == 0) {
+            const int used = (n + per - 1) / per;                   // groups that had at least one row
+            for (int g = 1; g < used; ++g) {
+                Acc<ITERS> v;
+#pragma unroll
+                for (int it = 0; it < ITERS; ++it) v.v[it] = ld4(&s_sum[g][(lig + it * LPR) * 4]);
+                acc.add(v);
+            }
+            if constexpr (FUSED) apply_update<LPR, ITERS>(fused_row(fs, col, ld_tab), d4, lig, xrow, acc, fu.lr, fu.mode, fu.stream);
+            else store_row<LPR, ITERS>(out_rows + 4 * c4 + (int64_t)seg * ld_out, d4, lig, acc);
+        }
+        if (RIDE) break;
     }
 }
 
@@ -1139,8 +1145,8 @@ static void seg_slices(stx_ctx *c, const stx_incidence *inc, const float *src, i
             else STX_SLICES_R(F, 64, 64 * (kThreads / LPR), wide);                                              \
         }                                                                                                       \
         ProfScope prof(c, "k_seg_fixup");                                                                       \
-        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, F, 0>), grid, dim3(kThreads), 0, c->stream, inc->at_packed, \
-                           inc->at_seg_id, inc->at_seg_ptr, 0, nnz, d4, out_rows, ld_out, c->partials, fu, sec, \
+        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, F, 0>), dim3(grid.x, std::min(grid.y, 4u)), dim3(kThreads), 0, c->stream, \
+                           inc->at_packed, inc->at_seg_id, inc->at_seg_ptr, 0, nnz, d4, out_rows, ld_out, c->partials, fu, sec, \
                            ScatterAhead{}, HistAhead{}, DmRide{}, EmitAhead{});                                 \
     } while (0)
     if (fused) STX_SLICES(true);
@@ -1237,8 +1243,8 @@ stx_status launch_seg_formed(stx_ctx *c, const stx_incidence *inc, const stx_par
 #undef STX_FORMED
     if (ntiles > 1) {
         ProfScope prof(c, "k_seg_fixup");
-        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, false, 0>), grid, dim3(kThreads), 0, c->stream, inc->at_packed,
-                           inc->at_seg_id, inc->at_seg_ptr, 0, nnz, d4, out_rows, ld_out, c->partials, fu, sec,
+        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, false, 0>), dim3(grid.x, std::min(grid.y, 4u)), dim3(kThreads), 0, c->stream,
+                           inc->at_packed, inc->at_seg_id, inc->at_seg_ptr, 0, nnz, d4, out_rows, ld_out, c->partials, fu, sec,
                            ScatterAhead{}, HistAhead{}, DmRide{}, EmitAhead{});
     }
     return hip_ok(hipGetLastError());
