@@ -59,8 +59,10 @@ struct FilterArgs {
     uint4 *qf, *ef;                    // matrix cores: operand fragments [tile of 32 rows][step][lane]
     float4 *qpar;                      // ... [query]: bound factors and threshold, see k_rank_prep
     float *qscale;                     // ... [query]
+    float *qlow;                       // ... [query], wide rows: norm of the low bytes
     float *eaux;                       // ... [tile of 32][64]: half the candidates' squared norms, scaled; then, from 32 on,
-                                       //     the tile's scale, largest norm, largest rounding, squared-norm term
+                                       //     the tile's scale, largest norm, largest rounding, squared-norm term; wide rows:
+                                       //     largest norm of the low bytes
     int32_t slice;                     // sweeps: candidates (mfma) or query groups (sad) per blockIdx.y
     int head;                          // side: q = t - r instead of h + r
     FilterState *st;
@@ -105,14 +107,14 @@ __device__ inline PairRows pair_rows(const FilterArgs &f, uint2 pr)
 __device__ inline float pair_diff(float sg, float qv, float ev) { return sg * (qv - ev); }
 
 // Counts of the active lanes' pairs.  A query that decides nothing brings many at once, and 400,000 additions to one
-// counter, one by one, take 5 ms: the pairs of one query are added together.  ALL: whatever queries the lanes hold,
-// else only where all hold the same one (the usual mixture costs less in single additions).
-template <bool ALL>
+// counter, one by one, take 5 ms: the pairs of the first lane's query are added together, then those of the first lane that
+// is left, TRIES times; what is then left (the usual mixture of queries) costs less in single additions.
+template <int TRIES>
 __device__ inline void pair_count(const FilterArgs &f, int64_t q, bool less, bool equal)
 {
-    for (;;) {
+#pragma unroll 1
+    for (int i = 0; i < TRIES; ++i) {
         const bool mine = (uint32_t)q == (uint32_t)__builtin_amdgcn_readfirstlane((int)q);
-        if (!ALL && __ballot(!mine) != 0ull) break;
         const int nl = __builtin_popcountll(__ballot(mine && less)), ne = __builtin_popcountll(__ballot(mine && equal));
         if (mask_rank(__ballot(true)) == 0) {
             if (nl) atomicAdd(&f.a.n_less[q], nl);
@@ -148,46 +150,49 @@ __device__ inline void pair_exact(const FilterArgs &f, uint2 pr)
                 acc = rank_step<DIST>(acc, pair_diff(sg, vq[u].w, ve[u].w));
             }
     }
-    pair_count<true>(f, p.q, acc < p.st, acc == p.st);
+    pair_count<64>(f, p.q, acc < p.st, acc == p.st);
 }
 
-// Eight lanes per pair: a sum in another order, which decides all but ties and near-ties; these go to `ties`.
+// Eight lanes per pair, the same sum (1: below the true entity's, 2: equal, else 0): a lane adds the four terms it holds of 32 to what the lane before it hands on.  Every
+// lane goes through all eight turns and only one of them counts, which is five times the instructions of a sum in any
+// order; but such a sum has a bound of its own, a thousandth of the pairs stay within it at d = 1024, and walking
+// those one per lane behind the others took longer than all the rest: STX_PAIRS.
 template <int DIST>
-__device__ inline void pair_recheck(const FilterArgs &f, uint2 pr, bool in, int lane, uint2 *ties, int &n_ties)
+__device__ inline int pair_ordered(const FilterArgs &f, uint2 pr, int lane)
 {
     const PairRows p = pair_rows(f, pr);
     const float sg = f.head ? -1.f : 1.f;
     const int dim = f.a.dim;
-    const int32_t it = f.head ? f.a.h[p.q] : f.a.t[p.q];
-    const bool self = (int32_t)p.e == min(max(it, 0), f.a.n_ent - 1);
-    float s = 0.f;
-    for (int j0 = (lane & 7) * 4; j0 < dim; j0 += 128) {
+    float acc = 0.f;                                       // (of the lane whose turn is next)
+    for (int j0 = 0; j0 < dim; j0 += 128) {
         float4 vq[4], ve[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
-            const int j = min(j0 + 32 * u, dim - 4);
+            const int j = min(j0 + 32 * u + (lane & 7) * 4, dim - 4);
             vq[u] = ld4(p.pq + j); ve[u] = ld4(p.pe + j);
         }
 #pragma unroll
-        for (int u = 0; u < 4; ++u)
-            if (j0 + 32 * u < dim) {
-                s = rank_step<DIST>(s, pair_diff(sg, vq[u].x, ve[u].x));
-                s = rank_step<DIST>(s, pair_diff(sg, vq[u].y, ve[u].y));
-                s = rank_step<DIST>(s, pair_diff(sg, vq[u].z, ve[u].z));
-                s = rank_step<DIST>(s, pair_diff(sg, vq[u].w, ve[u].w));
+        for (int u = 0; u < 4; ++u) {
+            const int j = j0 + 32 * u;
+            if (j >= dim) break;
+            float y[4] = {pair_diff(sg, vq[u].x, ve[u].x), pair_diff(sg, vq[u].y, ve[u].y), pair_diff(sg, vq[u].z, ve[u].z), pair_diff(sg, vq[u].w, ve[u].w)};
+            if (j + (lane & 7) * 4 >= dim) y[0] = y[1] = y[2] = y[3] = 0.f;   // (adds nothing)
+            if (DIST != STX_L2) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) y[i] = rank_step<DIST>(0.f, y[i]);   // the term by itself
             }
+#pragma unroll
+            for (int turn = 0; turn < 8; ++turn) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc = DIST == STX_L2 ? __builtin_fmaf(y[i], y[i], acc) : acc + y[i];
+                // to the next lane (row_shr:1), from the last to the first (row_shl:7)
+                const int v = __float_as_int(acc);
+                acc = __int_as_float(turn < 7 ? __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false) : __builtin_amdgcn_update_dpp(v, v, 0x107, 0xf, 0xf, false));
+            }
+        }
     }
-    s = group_sum<8>(s);
-    // The sum of the same rounded terms differs from this one by at most (dim / 8 + 6) 2^-24 of itself and from the
-    // index-order one by at most (dim + 2) 2^-24.  A step of the L2 kinds whose result is subnormal is off by up to 2^-150
-    // whatever its size: dim of them in either sum, and the roundings of this bound itself.
-    const float wd = ((float)dim * 1.126f + 16.f) * kUnit * s + (DIST == STX_L2 ? (float)(dim + 8) * 1.4012985e-45f : 0.f);
-    const bool less = !self && s + wd < p.st, tie = !self && !less && !(s - wd > p.st);
-    const bool one = (lane & 7) == 0 && in;
-    pair_count<false>(f, p.q, one && less, one && self && p.st == p.st);   // (the true entity: the very sum k_rank_prep formed)
-    const uint64_t m = __ballot(tie && in && (lane & 7) == 0);
-    if (m >> lane & 1) ties[n_ties + mask_rank(m)] = pr;
-    n_ties += __builtin_popcountll(m);
+    acc = __shfl(acc, 0, 8);
+    return acc < p.st ? 1 : acc == p.st ? 2 : 0;
 }
 
 // All undecided pairs of a sweep, many wavefronts in flight: bound by the latency and the bytes of the rows it reads.
@@ -204,20 +209,20 @@ __global__ __launch_bounds__(kThreads) void k_rank_pairs(FilterArgs f, RankIds i
         }
         return;
     }
-    __shared__ uint2 s_ties[4][72];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int n = (int)min(f.st->n_pairs, (unsigned long long)f.pair_cap), step = (int)gridDim.x * 32;
-    int n_ties = 0;
-    for (int i0 = ((int)blockIdx.x * 4 + wave) * 8; i0 < n; i0 += step) {
-        const int i = i0 + (lane >> 3);
-        pair_recheck<DIST>(f, f.pairs[min(i, n - 1)], i < n, lane, s_ties[wave], n_ties);
-        if (n_ties >= 64) {
-            pair_exact<DIST>(f, s_ties[wave][lane]);
-            n_ties -= 64;
-            if (lane < n_ties) s_ties[wave][lane] = s_ties[wave][64 + lane];
+    for (int i0 = ((int)blockIdx.x * 4 + wave) * 8; i0 < n;) {
+        uint32_t q = 0u;                                   // eight turns' results, one a lane, are counted together
+        int res = 0;
+#pragma unroll 1
+        for (int u = 0; u < 8 && i0 < n; ++u, i0 += step) {
+            const int i = i0 + (lane >> 3);
+            const uint2 pr = f.pairs[min(i, n - 1)];
+            const int got = pair_ordered<DIST>(f, pr, lane);
+            if ((lane & 7) == u) { q = pr.y; res = i < n ? got : 0; }
         }
+        if (res) pair_count<4>(f, q, res == 1, res == 2);
     }
-    if (lane < n_ties) pair_exact<DIST>(f, s_ties[wave][lane]);
 }
 
 // A wavefront's collected pairs move to the list of the sweep; when that is full they are treated here, one per lane.
@@ -277,6 +282,37 @@ __device__ inline uint4 half_piece(const float (&v)[8], float sc, float &n2, flo
         d2 = __builtin_fmaf(d, d, d2);
     }
     return __builtin_bit_cast(uint4, h);
+}
+constexpr float kWideMax = 32639.f;    // largest 16-bit number whose high byte, the low one being signed, fits
+// The scale that brings `mx` there, as pow2_scale.
+__device__ inline float wide_scale(float mx, bool &ok)
+{
+    ok = mx == 0.f || (mx > 1e-12f && mx < 1e12f);
+    return ok && mx != 0.f ? kWideMax / mx : 1.f;
+}
+// Sixteen elements scaled and rounded to 16-bit fixed point, as high and (signed) low bytes; adds the squares of the scaled
+// values, of the roundings and of the low bytes.
+__device__ inline void wide_piece(const float *v, float sc, uint4 &hi, uint4 &lo, float &n2, float &d2, float &l2)
+{
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        h[w] = l[w] = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float x = v[4 * w + i] * sc;
+            const float k = fminf(fmaxf(rintf(x), -kWideMax), kWideMax);
+            const float d = x - k;
+            n2 = __builtin_fmaf(x, x, n2);
+            d2 = __builtin_fmaf(d, d, d2);
+            const int n = (int)k, b = (int)(int8_t)n;
+            l2 += (float)(b * b);
+            l[w] |= ((uint32_t)b & 0xffu) << (8 * i);
+            h[w] |= ((uint32_t)((n - b) >> 8) & 0xffu) << (8 * i);
+        }
+    }
+    hi = make_uint4(h[0], h[1], h[2], h[3]);
+    lo = make_uint4(l[0], l[1], l[2], l[3]);
 }
 // One element as 16-bit fixed point; adds the rounding made (in units of the last place).
 template <bool TORUS>
@@ -351,7 +387,7 @@ __global__ __launch_bounds__(1024) void k_rank_scale(RankArgs a, float *scale)
 // Blocks of 32 queries: the true entity's sum in index order (one lane per query walks the terms out of LDS), cleared
 // counters, and the packed query with its thresholds.  Matrix-core kinds: further blocks of 32 candidates each.
 // Eight threads per row.  Bound by the latency of its few dependent passes; the rows come from the caches.
-template <int DIST, bool HEAD>
+template <int DIST, bool HEAD, bool WIDE = false>
 __global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds ids)
 {
     constexpr bool SAD = DIST == STX_L1 || DIST == STX_TORUS_L1, TORUS = DIST == STX_TORUS_L1;
@@ -453,9 +489,51 @@ __global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds id
         }
         bool ok;
         mx = max_group8(mx);
-        const float sc = pow2_scale(mx, ok);
         float n2 = 0.f, d2 = 0.f;
         uint4 *dst = f.qf + ((int64_t)z * (f.q_cap / 32) + blockIdx.x) * (f.np / 2) * 64;
+        if constexpr (WIDE) {
+            const float sc = wide_scale(mx, ok);
+            float l2 = 0.f;
+            for (int p = l8; p < f.np / 2; p += 8) {           // sixteen elements a piece
+                float va[16], vr[16];
+                load8(rw.pa, p * 16, dim, *(float (*)[8])va);
+                load8(rw.pa, p * 16 + 8, dim, *(float (*)[8])(va + 8));
+                load8(rw.pr, p * 16, dim, *(float (*)[8])vr);
+                load8(rw.pr, p * 16 + 8, dim, *(float (*)[8])(vr + 8));
+#pragma unroll
+                for (int i = 0; i < 16; ++i) va[i] = HEAD ? va[i] - vr[i] : va[i] + vr[i];
+                uint4 hi, lo;
+                wide_piece(va, sc, hi, lo, n2, d2, l2);
+                dst[(p >> 1) * 128 + u + 32 * (p & 1)] = hi;
+                dst[(p >> 1) * 128 + 64 + u + 32 * (p & 1)] = lo;
+            }
+            n2 = group_sum<8>(n2);
+            d2 = group_sum<8>(d2);
+            l2 = group_sum<8>(l2);
+            if (l8 == 0) {
+                // As below, in units scaled by sc / 256 (and by the candidate tile's scale).  The sums of the matrix cores are
+                // exact here.  What is computed differs by
+                //   the fixed-point roundings |q| |de| + |dq| (|e| + |de|), and 2^-24 of either row where it is scaled
+                //   the low bytes' product    at most the product of their norms
+                //   a few fp32 roundings      of the sum, of |e|^2/2 and of tau
+                //   the norms and tau, the index-order sums: as below
+                const float eps = 4.f * kUnit, kap = norm_slack(f.np) + 4.f * kUnit;
+                const float qn = sqrtf(n2) * 1.0001f, dq = sqrtf(d2) * 1.002f + 1.01f * kUnit * qn, qq = n2 / sc, un = 1.f / 256.f;
+                float4 par;
+                par.x = (dq * 1.001f + 6.f * kUnit * qn) * un;
+                par.y = qn * un;
+                par.z = 0.5f * (qq - st * sc) * un;
+                par.w = (kap * (qq + st * sc) + 0.51f * (float)(dim + 8) * kUnit * (st * sc)) * un + eps * fabsf(par.z);
+                if (!ok || !(par.w < 1e30f)) par.w = __builtin_inff();
+                if (ql >= nq) par = make_float4(0.f, 0.f, 3e37f, 0.f);
+                const int64_t i = (int64_t)z * f.q_cap + ql;
+                f.qpar[i] = par;
+                f.qscale[i] = sc * un;
+                f.qlow[i] = sqrtf(l2) * 1.001f * un;
+            }
+            return;
+        }
+        const float sc = pow2_scale(mx, ok);
         for (int p = l8; p < f.np; p += 8) {
             float va[8], vr[8], q8[8];
             load8(rw.pa, p * 8, dim, va);
@@ -508,10 +586,22 @@ __global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds id
     __syncthreads();
     mx = fmaxf(fmaxf(s_r[0], s_r[1]), fmaxf(s_r[2], s_r[3]));
     bool ok;
-    const float sc = pow2_scale(mx, ok);
-    float n2 = 0.f, d2 = 0.f;
+    const float sc = WIDE ? wide_scale(mx, ok) : pow2_scale(mx, ok);
+    float n2 = 0.f, d2 = 0.f, l2 = 0.f;
     uint4 *dst = f.ef + ((int64_t)z * tiles + et) * (f.np / 2) * 64;
-    for (int p = l8; p < f.np; p += 8) {
+    if constexpr (WIDE) {
+        for (int p = l8; p < f.np / 2; p += 8) {
+            float v[16];
+            load8(pe, p * 16, dim, *(float (*)[8])v);
+            load8(pe, p * 16 + 8, dim, *(float (*)[8])(v + 8));
+            uint4 hi, lo;
+            wide_piece(v, sc, hi, lo, n2, d2, l2);
+            if (!in) hi = lo = make_uint4(0u, 0u, 0u, 0u);
+            dst[(p >> 1) * 128 + u + 32 * (p & 1)] = hi;
+            dst[(p >> 1) * 128 + 64 + u + 32 * (p & 1)] = lo;
+        }
+        l2 = group_sum<8>(l2);
+    } else for (int p = l8; p < f.np; p += 8) {
         float v[8];
         load8(pe, p * 8, dim, v);
         uint4 h = half_piece(v, sc, n2, d2);
@@ -523,23 +613,28 @@ __global__ __launch_bounds__(kThreads) void k_rank_prep(FilterArgs f, RankIds id
     if (l8 == 0) {
         s_t[u] = n2;
         s_y[0][u] = d2;
+        s_y[1][u] = l2;
         f.eaux[((int64_t)z * tiles + et) * 64 + u] = in ? 0.5f * n2 / sc : 3e37f;   // past the end: never below
     }
     __syncthreads();
     if (tid < 32) {
-        float m2 = s_t[tid], dd = s_y[0][tid];
+        float m2 = s_t[tid], dd = s_y[0][tid], ll = s_y[1][tid];
         bool fin = m2 < 1e30f && dd < 1e30f;                   // (false for NaN)
 #pragma unroll
         for (int m = 16; m >= 1; m >>= 1) {
             m2 = fmaxf(m2, __shfl_xor(m2, m, 32));
             dd = fmaxf(dd, __shfl_xor(dd, m, 32));
+            ll = fmaxf(ll, __shfl_xor(ll, m, 32));
         }
         fin = (__ballot(fin) & 0xffffffffull) == 0xffffffffull;
         if (tid == 0) {
-            const float kap = norm_slack(f.np) + 1.25f * kUnit * (float)(f.np / 2 + 2);
+            const float kap = norm_slack(f.np) + (WIDE ? 8.f * kUnit : 1.25f * kUnit * (float)(f.np / 2 + 2));
             float4 t = make_float4(sc, sqrtf(m2) * 1.0001f, sqrtf(dd) * 1.002f, kap * m2 / sc);
+            if (WIDE) t.z += 1.01f * kUnit * t.y;
             if (!fin || !ok) t.y = t.z = t.w = __builtin_inff();
-            st4(f.eaux + ((int64_t)z * tiles + et) * 64 + 32, t);
+            float *aux = f.eaux + ((int64_t)z * tiles + et) * 64;
+            st4(aux + 32, t);
+            aux[36] = sqrtf(ll) * 1.001f;
         }
     }
 }
@@ -882,6 +977,160 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
     }
 }
 
+// Wide rows.  Fp16 leaves one pair in a hundred undecided at d = 1024 (a rounding of 2^-12 a side against scores that differ
+// by a few per cent), and summing those took twice the sweep's time.  Here rows are 16-bit fixed point, as high and low
+// bytes: three byte products (v_mfma_i32_32x32x32_i8, exact, twice fp16's rate) leave out only the low bytes' own, and one
+// pair in a STX_WIDE_ONE_IN is undecided at the same bytes per row.
+// The queries' operands stay in registers, which d = 1024 would fill: every LDS read then waited for its use (5 times the
+// matrix cores' time).  So the steps of a row are dealt to KH wavefronts (even and odd ones), and each holds 128 registers
+// of them; a tile's halves are exchanged through LDS, behind the next chunk's barrier, and each decides half the candidates.
+template <int KS, int KH>
+__global__ __launch_bounds__(kThreads * KH, 2) void k_rank_wide(FilterArgs f, RankIds ids)
+{
+    typedef int intx4 __attribute__((ext_vector_type(4)));
+    typedef int intx16 __attribute__((ext_vector_type(16)));
+    constexpr int CK = KS % 16 == 0 ? 16 : 12, NB = 4, CPT = KS / CK, NW = 4 * KH, LW = CK / NW;   // as in k_rank_mfma
+    constexpr int S = KS / 2 / KH, SC = CK / 2 / KH;       // steps of 32 elements (two kilobytes) a wavefront takes of a tile, of a chunk
+    constexpr int NV = 16 / KH;                            // sums of a tile a lane decides
+    static_assert(CK % NW == 0 && KS % CK == 0 && CK / 2 % KH == 0, "whole chunks");
+    __shared__ __align__(1024) uint4 s_ring[NB][CK][64];
+    __shared__ __align__(256) float s_aux[NB][64];
+    __shared__ uint2 s_list[NW][kListCap];
+    __shared__ int s_half[KH > 1 ? NW : 1][KH > 1 ? NV : 1][64];
+    RankArgs a = f.a;
+    rank_group(a, ids);
+    const int lane = threadIdx.x & 63, half = lane >> 5, z = (int)blockIdx.z;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), kh = wave >> 2;
+    const int nq = (int)min(a.nq - f.q_first, (int64_t)f.q_cap);
+    if ((int)blockIdx.x * 128 >= nq) return;
+    const int32_t skip = f.first ? 0 : f.st->skip;
+    const int q_base = f.q_first + (int)(a.true_score - f.a.true_score);       // position of the chunk in the query arrays
+    const uint32_t zbits = f.z_shift < 32 ? (uint32_t)z << f.z_shift : 0u;
+    const int qb = (int)blockIdx.x * 4 + (wave & 3);                           // block of 32 queries
+    const bool works = qb * 32 < nq;                                           // (the others only fetch)
+    const int tiles = (f.e_count + 31) / 32;
+    const int t0 = (int)blockIdx.y * f.slice, t1 = min(t0 + f.slice, tiles);
+    const uint4 *src = f.ef + ((int64_t)z * tiles + t0) * KS * 64 + wave * LW * 64 + lane;
+    const int chunks = (t1 - t0) * CPT;
+    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&s_ring[0][0][0];
+    const uint32_t ring_aux = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&s_aux[0][0];
+    const float *aux = f.eaux + ((int64_t)z * tiles + t0) * 64 + lane;
+    auto fetch = [&](int c, int slot) {                                        // (past the end: the last chunk once more)
+        const int at = min(c, chunks - 1);
+        const uint4 *g = src + (int64_t)at * CK * 64;
+#pragma unroll
+        for (int i = 0; i < LW; ++i) load_lds_1k(g + i * 64, ring + (uint32_t)((slot * CK + wave * LW + i) * 1024));
+        load_lds_256(aux + (int64_t)(at / CPT) * 64, ring_aux + (uint32_t)(slot * 256));
+    };
+    intx4 qh[S], ql[S];
+    {
+        const int blk = works ? qb : 0;
+        const uint4 *qs = f.qf + ((int64_t)z * (f.q_cap / 32) + blk) * KS * 64 + lane;
+#pragma unroll
+        for (int i = 0; i < S; ++i) {
+            qh[i] = __builtin_bit_cast(intx4, qs[(KH * i + kh) * 128]);
+            ql[i] = __builtin_bit_cast(intx4, qs[(KH * i + kh) * 128 + 64]);
+        }
+    }
+    const int64_t qi0 = (int64_t)z * f.q_cap + (works ? qb : 0) * 32 + (lane & 31);
+    const float4 par = f.qpar[qi0];
+    const float p_s = f.qscale[qi0], p_l = f.qlow[qi0];
+    int less = 0, cnt = 0;
+    bool listing = true;                                   // until there are too many undecided pairs
+    float thr[NV], w = 0.f;                                // of the tile at hand: its sums are held against thr, give or take w
+    int mine[NV];
+    auto decide = [&](int t) {
+        uint32_t neg = 0, near = 0;                        // signs of t and of |t| - w
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const float v = (KH > 1 ? (float)mine[i] + (float)s_half[wave ^ 4][i][lane] : (float)mine[i]) - thr[i];
+            neg = __builtin_amdgcn_alignbit(neg, __float_as_uint(v), 31);
+            near = __builtin_amdgcn_alignbit(near, __float_as_uint(fabsf(v) - w), 31);
+        }
+        if (!(w < 1e37f)) near = (1u << NV) - 1u;          // no bound: nothing is decided
+        less += NV - __builtin_popcount(neg | near);
+        uint32_t und = near << (32 - NV);                  // the lane's undecided sums: bit 31 - i
+        while (__any(und != 0) && listing) {
+            const int b = __builtin_clz(und | 1u), i = b + kh * NV;
+            const int e = f.e_first + t * 32 + (i & 3) + 8 * ((i >> 2) & 3) + 4 * half, q = qb * 32 + (lane & 31);
+            const uint64_t m = __ballot(und != 0 && e < a.n_ent && q < nq);
+            und &= ~(0x80000000u >> b);
+            if (m >> lane & 1) s_list[wave][cnt + mask_rank(m)] = make_uint2((uint32_t)e | zbits, (uint32_t)(q_base + q));
+            cnt += __builtin_popcountll(m);
+            if (cnt > kListCap - 64) {
+                listing = flush_pairs<STX_L2>(f, s_list[wave], cnt, lane);
+                cnt = 0;
+            }
+        }
+    };
+#pragma unroll
+    for (int c = 0; c < NB - 1; ++c) fetch(c, c);
+    if (skip) {
+        asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
+        return;
+    }
+    intx16 hh, mid;
+    for (int c0 = 0; c0 < chunks; c0 += CPT) {
+        const int t = t0 + c0 / CPT;
+#pragma unroll
+        for (int cc = 0; cc < CPT; ++cc) {
+            const int c = c0 + cc;
+            // this wavefront's part of chunk c has landed when at most the later NB - 2 chunks' loads are outstanding
+            __builtin_amdgcn_sched_barrier(0);
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((NB - 2) * (LW + 1)) : "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            fetch(c + NB - 1, (c + NB - 1) % NB);          // over the chunk that every wavefront is done with
+            if (!works) continue;
+            const uint4 (*chunk)[64] = s_ring[c % NB];
+            if (cc == 0) {
+                if (KH > 1 && c0 > 0) decide(t - 1);       // the tile before: the other half's sums lie in LDS now
+                const float *ta = s_aux[c % NB];
+                const float4 et = ld4(ta + 32);
+                w = __builtin_fmaf(par.x, et.y, __builtin_fmaf(par.y, et.z, __builtin_fmaf(par.w, et.x, p_s * et.w)));
+                w = __builtin_fmaf(__builtin_fmaf(p_l, ta[36], w), 1.0001f, 1e-37f);   // (never zero: exact ties are undecided)
+                const float tau = par.z * et.x;
+#pragma unroll
+                for (int i = 0; i < NV; ++i) {
+                    const int j = i + kh * NV;
+                    thr[i] = __builtin_fmaf(ta[(j & 3) + 8 * (j >> 2) + 4 * half], p_s, tau);
+                }
+#pragma unroll
+                for (int i = 0; i < 16; ++i) hh[i] = mid[i] = 0;
+            }
+#pragma unroll
+            for (int k = 0; k < SC; ++k) {
+                const intx4 eh = __builtin_bit_cast(intx4, chunk[(KH * k + kh) * 2][lane]), el = __builtin_bit_cast(intx4, chunk[(KH * k + kh) * 2 + 1][lane]);
+                hh = __builtin_amdgcn_mfma_i32_32x32x32_i8(eh, qh[cc * SC + k], hh, 0, 0, 0);
+                mid = __builtin_amdgcn_mfma_i32_32x32x32_i8(el, qh[cc * SC + k], mid, 0, 0, 0);
+                mid = __builtin_amdgcn_mfma_i32_32x32x32_i8(eh, ql[cc * SC + k], mid, 0, 0, 0);
+            }
+        }
+        if (!works) continue;
+        // (at most 512 steps of up to 127 127 256 and twice 127 128: below 2^31)
+        if constexpr (KH > 1) {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const int lo = hh[i] * 256 + mid[i], up = hh[NV + i] * 256 + mid[NV + i];
+                mine[i] = kh ? up : lo;
+                s_half[wave][i][lane] = kh ? lo : up;
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < NV; ++i) mine[i] = hh[i] * 256 + mid[i];
+            decide(t);
+        }
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");   // (loads into LDS still in flight must not outlive the workgroup)
+    if (KH > 1) {
+        __syncthreads();
+        if (works && chunks > 0) decide(t1 - 1);
+    }
+    if (!works) return;
+    if (cnt && listing) flush_pairs<STX_L2>(f, s_list[wave], cnt, lane);
+    const int n = less + __shfl_xor(less, 32, 64), qi = qb * 32 + lane;
+    if (lane < 32 && qi < nq && n) atomicAdd(&a.n_less[f.q_first + qi], n);
+}
+
 // ---- host ---------------------------------------------------------------------------------------------------
 static bool sad_kind(int dist) { return dist == STX_L1 || dist == STX_TORUS_L1; }
 static bool mfma_kind(int dist) { return dist == STX_L2 || dist == STX_L2_SQ; }
@@ -894,7 +1143,8 @@ static int mfma_steps(int width)
         if (16 * s >= width) return s;
     return 64;
 }
-static size_t mfma_query_bytes(int ks) { return (size_t)ks * 32 + sizeof(float4) + sizeof(float); }
+static bool mfma_wide(int ks) { return ks >= 24; }
+static size_t mfma_query_bytes(int ks) { return (size_t)ks * 32 + sizeof(float4) + 2 * sizeof(float); }
 static size_t mfma_tile_bytes(int ks) { return (size_t)ks * 1024 + 256; }
 constexpr size_t kMfmaSlack = 32 * 1024 + 32 * 256;            // reads past the last tile
 
@@ -966,6 +1216,22 @@ static void go_mfma_q(stx_ctx *c, FilterArgs &f, int64_t nq, int nz, const RankI
 {
     if (nq <= 128) go_mfma<1, KS, WPE>(c, f, nq, nz, ids);
     else go_mfma<QF, KS, WPE>(c, f, nq, nz, ids);
+}
+template <int KS, int KH>
+static void go_wide(stx_ctx *c, FilterArgs &f, int64_t nq, int nz, const RankIds &ids)
+{
+    const unsigned gx = (unsigned)((nq + 127) / 128);
+    const int tiles = (f.e_count + 31) / 32;
+    const int64_t slots = 256 * 2 / KH, blocks = (int64_t)gx * nz;             // rounds as in go_mfma
+    int64_t rounds = (int64_t)tiles * KS * blocks / (slots * 256);
+    rounds = rounds < 1 ? 1 : rounds > 4 ? 4 : rounds;
+    int64_t slices = (slots * rounds + blocks - 1) / blocks;
+    int slice = (int)((tiles + slices - 1) / slices);
+    if (slice < 4) slice = 4;
+    slices = (tiles + slice - 1) / slice;
+    f.slice = slice;
+    ProfScope prof(c, "k_rank_wide");
+    hipLaunchKernelGGL((k_rank_wide<KS, KH>), dim3(gx, (unsigned)slices, (unsigned)nz), dim3(kThreads * KH), 0, c->stream, f, ids);
 }
 template <int DIST, int C>
 static void go_sad(stx_ctx *c, FilterArgs &f, int64_t nq)
@@ -1040,6 +1306,7 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
         f.qf = (uint4 *)q;
         f.qpar = (float4 *)(f.qf + (size_t)cap * tables * (f.np / 2) * 2);
         f.qscale = (float *)(f.qpar + (size_t)cap * tables);
+        f.qlow = f.qscale + (size_t)cap * tables;
     }
     int64_t seg = a.n_ent;                                     // candidates per segment (matrix cores)
     if (!sad) {
@@ -1075,12 +1342,13 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
         f.first = f.q_first == 0 && f.e_first == 0;
         const dim3 grid((unsigned)(nqb + neb), 1, (unsigned)tables);
         ProfScope prof(c, "k_rank_prep");
-#define STX_PREP(D)                                                                                           \
-    if (side) hipLaunchKernelGGL((k_rank_prep<D, true>), grid, dim3(kThreads), 0, c->stream, f, ids);         \
-    else hipLaunchKernelGGL((k_rank_prep<D, false>), grid, dim3(kThreads), 0, c->stream, f, ids);
-        if (dist == STX_L1) { STX_PREP(STX_L1) }
-        else if (dist == STX_TORUS_L1) { STX_PREP(STX_TORUS_L1) }
-        else { STX_PREP(STX_L2) }
+#define STX_PREP(D, W)                                                                                        \
+    if (side) hipLaunchKernelGGL((k_rank_prep<D, true, W>), grid, dim3(kThreads), 0, c->stream, f, ids);      \
+    else hipLaunchKernelGGL((k_rank_prep<D, false, W>), grid, dim3(kThreads), 0, c->stream, f, ids);
+        if (dist == STX_L1) { STX_PREP(STX_L1, false) }
+        else if (dist == STX_TORUS_L1) { STX_PREP(STX_TORUS_L1, false) }
+        else if (mfma_wide(f.np / 2)) { STX_PREP(STX_L2, true) }
+        else { STX_PREP(STX_L2, false) }
 #undef STX_PREP
     };
     if (sad && dist == STX_L1) {
@@ -1118,10 +1386,10 @@ bool rank_filtered(stx_ctx *c, const RankArgs &a, int side, const RankScratch &w
             case 8: go_mfma_q<2, 8, 2>(c, f, nq, tables, ids); break;
             case 12: go_mfma_q<2, 12, 2>(c, f, nq, tables, ids); break;
             case 16: go_mfma_q<2, 16, 2>(c, f, nq, tables, ids); break;
-            case 24: go_mfma_q<2, 24, 1>(c, f, nq, tables, ids); break;
-            case 32: go_mfma_q<2, 32, 1>(c, f, nq, tables, ids); break;
-            case 48: go_mfma<1, 48, 1>(c, f, nq, tables, ids); break;
-            default: go_mfma<1, 64, 1>(c, f, nq, tables, ids); break;
+            case 24: go_wide<24, 1>(c, f, nq, tables, ids); break;
+            case 32: go_wide<32, 1>(c, f, nq, tables, ids); break;
+            case 48: go_wide<48, 2>(c, f, nq, tables, ids); break;
+            default: go_wide<64, 2>(c, f, nq, tables, ids); break;
             }
             pairs();
         }
