@@ -864,6 +864,14 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
         if (qb + q > blk) { par = make_float4(0.f, 0.f, 3e37f, 0.f); p_s[q] = 1.f; }
         p_x[q] = par.x; p_y[q] = par.y; p_z[q] = par.z; p_w[q] = par.w;
     }
+    // (the operands arrive here: waited for where they are used, inside the loop, they would hold up the chunks ahead each
+    // time, whose loads the compiler does not count)
+#pragma unroll
+    for (int q = 0; q < QF; ++q)
+#pragma unroll
+        for (int k = 0; k < KS; ++k) asm volatile("" : "+v"(qf[q][k]));
+#pragma unroll
+    for (int q = 0; q < QF; ++q) asm volatile("" : "+v"(p_x[q]), "+v"(p_y[q]), "+v"(p_z[q]), "+v"(p_w[q]), "+v"(p_s[q]));
     int less[QF];
 #pragma unroll
     for (int q = 0; q < QF; ++q) less[q] = 0;
@@ -989,7 +997,7 @@ __global__ __launch_bounds__(kThreads * KH, 2) void k_rank_wide(FilterArgs f, Ra
 {
     typedef int intx4 __attribute__((ext_vector_type(4)));
     typedef int intx16 __attribute__((ext_vector_type(16)));
-    constexpr int CK = KS % 16 == 0 ? 16 : 12, NB = 4, CPT = KS / CK, NW = 4 * KH, LW = CK / NW;   // as in k_rank_mfma
+    constexpr int CK = KS / 2, NB = 4, CPT = KS / CK, NW = 4 * KH, LW = CK / NW;   // as in k_rank_mfma
     constexpr int S = KS / 2 / KH, SC = CK / 2 / KH;       // steps of 32 elements (two kilobytes) a wavefront takes of a tile, of a chunk
     constexpr int NV = 16 / KH;                            // sums of a tile a lane decides
     static_assert(CK % NW == 0 && KS % CK == 0 && CK / 2 % KH == 0, "whole chunks");
@@ -1032,9 +1040,14 @@ __global__ __launch_bounds__(kThreads * KH, 2) void k_rank_wide(FilterArgs f, Ra
             ql[i] = __builtin_bit_cast(intx4, qs[(KH * i + kh) * 128 + 64]);
         }
     }
+    // (they arrive here: waited for where they are used, inside the loop, they would hold up the chunks ahead each time,
+    // whose loads the compiler does not count)
+#pragma unroll
+    for (int i = 0; i < S; ++i) asm volatile("" : "+v"(qh[i]), "+v"(ql[i]));
     const int64_t qi0 = (int64_t)z * f.q_cap + (works ? qb : 0) * 32 + (lane & 31);
-    const float4 par = f.qpar[qi0];
-    const float p_s = f.qscale[qi0], p_l = f.qlow[qi0];
+    float4 par = f.qpar[qi0];
+    float p_s = f.qscale[qi0], p_l = f.qlow[qi0];
+    asm volatile("" : "+v"(par.x), "+v"(par.y), "+v"(par.z), "+v"(par.w), "+v"(p_s), "+v"(p_l));
     int less = 0, cnt = 0;
     bool listing = true;                                   // until there are too many undecided pairs
     float thr[NV], w = 0.f;                                // of the tile at hand: its sums are held against thr, give or take w
@@ -1097,8 +1110,12 @@ __global__ __launch_bounds__(kThreads * KH, 2) void k_rank_wide(FilterArgs f, Ra
 #pragma unroll
                 for (int i = 0; i < 16; ++i) hh[i] = mid[i] = 0;
             }
+            // (two LDS reads ahead of the three products that use them)
+            __builtin_amdgcn_sched_group_barrier(0x100, 4, 0);
 #pragma unroll
             for (int k = 0; k < SC; ++k) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 3, 0);
+                if (k + 2 < SC) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
                 const intx4 eh = __builtin_bit_cast(intx4, chunk[(KH * k + kh) * 2][lane]), el = __builtin_bit_cast(intx4, chunk[(KH * k + kh) * 2 + 1][lane]);
                 hh = __builtin_amdgcn_mfma_i32_32x32x32_i8(eh, qh[cc * SC + k], hh, 0, 0, 0);
                 mid = __builtin_amdgcn_mfma_i32_32x32x32_i8(el, qh[cc * SC + k], mid, 0, 0, 0);
