@@ -70,6 +70,43 @@ __device__ inline RankRows rank_rows(const RankArgs &a, int64_t qi)
             a.X + (int64_t)(HEAD ? ih : it) * a.dim, HEAD ? ih : it, bad};
 }
 
+// Counts of the active lanes' pairs.  A query that decides nothing brings many at once, and 400,000 additions to one
+// counter, one by one, take 5 ms: the pairs of the first lane's query are added together, then those of the first lane that
+// is left, TRIES times; what is then left (the usual mixture of queries) costs less in single additions.
+template <int TRIES>
+__device__ inline void rank_count(int32_t *n_less, int32_t *n_equal, uint32_t q, bool less, bool equal)
+{
+#pragma unroll 1
+    for (int i = 0; i < TRIES; ++i) {
+        const bool mine = q == (uint32_t)__builtin_amdgcn_readfirstlane((int)q);
+        const int nl = __builtin_popcountll(__ballot(mine && less)), ne = __builtin_popcountll(__ballot(mine && equal));
+        const uint64_t on = __ballot(true);
+        if (__builtin_amdgcn_mbcnt_hi((uint32_t)(on >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)on, 0u)) == 0) {
+            if (nl) atomicAdd(&n_less[q], nl);
+            if (ne) atomicAdd(&n_equal[q], ne);
+        }
+        if (mine) return;
+    }
+    if (less) atomicAdd(&n_less[q], 1);
+    if (equal) atomicAdd(&n_equal[q], 1);
+}
+
+// ---- stx_rank_transr.hip ------------------------------------------------------------------------------
+struct RrBlock {
+    int32_t rel, slot, first, count;   // up to 32 queries of a relation: their first grouped position; slot: number of the
+};                                     // relation among those that occur
+struct RankGroups {                    // queries grouped by relation
+    const int32_t *h, *t;              // clamped
+    float *score;
+    int32_t *less, *equal;
+    const RrBlock *blocks;             // [nq / 32 + relations]
+    const int32_t *occ;                // relations that occur, in order
+};
+// TransR's L2 kinds: true sums and counts of grouped queries (not the final square roots), given the queries per relation
+// on the host.  false: not for this kind or scratch, nothing launched.
+bool rank_transr(stx_ctx *, const stx_params *, int64_t nq, int side, const RankGroups &, void *work, size_t bytes, const int32_t *counts);
+size_t rank_transr_bytes(const stx_config &, int64_t nq);                         // 0: a kind without
+
 // ---- stx_rank_filter.hip ------------------------------------------------------------------------------
 // Scratch of a filtered sweep: packed queries with their thresholds; packed candidates (matrix-core kinds).  Sweeps
 // of more queries or candidates than fit go chunk by chunk.

@@ -378,8 +378,11 @@ struct RankRWork {                      // partitions of the caller's work buffe
     int32_t *gless, *gequal;
     float *table;                       // n_tables tables of (n_ent + 1) x rel_dim: P_r, then r
     int n_tables;
-    RankScratch ws;                     // of the filtered sweeps (kinds that have one)
-    size_t plain_total, total;          // without and with that
+    RrBlock *blocks;                    // of the sweep without projected tables (kinds that have one) ...
+    int32_t *occ;
+    void *rr;
+    size_t rr_bytes;
+    size_t plain_total, total;          // ... without and with that
 };
 constexpr int kRankBig = 1024;          // relations with more queries than this get a launch of their own
 static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
@@ -403,14 +406,11 @@ static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
     if (w.n_tables > cfg.n_rel) w.n_tables = (int)cfg.n_rel;
     w.table = (float *)take(table_bytes * w.n_tables);
     w.plain_total = w.total = off;
-    if (cfg.dist != STX_L2 && cfg.dist != STX_L2_SQ) return w;                 // (no filtered sweep over projected tables)
-    // one relation with all queries, or n_tables relations with up to kRankBig each
-    const int64_t few = nq < kRankBig ? nq : kRankBig, many = ((few + 31) / 32 * 32) * w.n_tables;
-    w.ws.q_bytes = rank_filter_q_bytes(cfg.dist, cfg.rel_dim, nq > many ? nq : many);
-    w.ws.e_bytes = rank_filter_e_bytes(cfg.dist, cfg.rel_dim, cfg.n_ent, w.n_tables);
-    w.ws.q = take(w.ws.q_bytes);
-    w.ws.e = take(w.ws.e_bytes);
-    w.ws.q32 = w.ws.q_bytes ? (float *)take((size_t)nq * cfg.rel_dim * 4) : nullptr;
+    w.rr_bytes = rank_transr_bytes(cfg, nq);
+    if (!w.rr_bytes) return w;
+    w.blocks = (RrBlock *)take((size_t)(nq / 32 + std::min((int64_t)cfg.n_rel, nq)) * sizeof(RrBlock));
+    w.occ = (int32_t *)take((size_t)cfg.n_rel * 4);
+    w.rr = take(w.rr_bytes);
     w.total = off;
     return w;
 }
@@ -454,18 +454,30 @@ __global__ __launch_bounds__(kThreads) void k_rr_hist(const int32_t *h, const in
     }
 }
 
-// offsets[i] = counts[0] + ... + counts[i-1], offsets[n_rel] = nq.  One workgroup.
-__global__ __launch_bounds__(kThreads) void k_rr_scan(const int32_t *counts, int32_t *offsets, int n_rel)
+// offsets[i] = counts[0] + ... + counts[i-1], offsets[n_rel] = nq; the relations that occur and their blocks of 32 queries.
+// One workgroup.
+__global__ __launch_bounds__(kThreads) void k_rr_scan(const int32_t *counts, int32_t *offsets, int n_rel, RrBlock *blocks, int32_t *occ)
 {
     __shared__ int32_t s_total;
-    int32_t base = 0;
+    int32_t base = 0, base_b = 0, base_o = 0;
     for (int i0 = 0; i0 < n_rel; i0 += kThreads) {
         const int i = i0 + (int)threadIdx.x;
         const int32_t v = i < n_rel ? counts[i] : 0;
-        const int32_t ex = block_exclusive_scan(v, &s_total);
-        if (i < n_rel) offsets[i] = base + ex;
+        const int32_t ex = base + block_exclusive_scan(v, &s_total);
+        if (i < n_rel) offsets[i] = ex;
         __syncthreads();
         base += s_total;
+        if (!blocks) continue;
+        __syncthreads();
+        const int32_t b = base_b + block_exclusive_scan((v + 31) / 32, &s_total);
+        __syncthreads();
+        base_b += s_total;
+        __syncthreads();
+        const int32_t o = base_o + block_exclusive_scan(v > 0 ? 1 : 0, &s_total);
+        __syncthreads();
+        base_o += s_total;
+        if (v > 0) occ[o] = i;
+        for (int j = 0; j * 32 < v; ++j) blocks[b + j] = RrBlock{i, o, ex + j * 32, min(32, v - j * 32)};
     }
     if (threadIdx.x == 0) offsets[n_rel] = base;
 }
@@ -692,10 +704,12 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
     // projected table and one sweep per relation that occurs
     const RankRWork w = rank_r_work(c->cfg, nq, work);
     const int dim = c->cfg.dim, k = c->cfg.rel_dim;
+    const bool with_rr = w.rr && work_bytes >= w.total;
     const dim3 rgrid((unsigned)((n_rel + kThreads - 1) / kThreads)), qgrid((unsigned)((nq + kThreads - 1) / kThreads));
     hipLaunchKernelGGL(k_rr_clear, rgrid, dim3(kThreads), 0, c->stream, w.counts, w.cursor, n_rel);
     hipLaunchKernelGGL(k_rr_hist, qgrid, dim3(kThreads), 0, c->stream, h, r, t, nq, n_ent, n_rel, w.counts, bad);
-    hipLaunchKernelGGL(k_rr_scan, dim3(1), dim3(kThreads), 0, c->stream, w.counts, w.offsets, n_rel);
+    hipLaunchKernelGGL(k_rr_scan, dim3(1), dim3(kThreads), 0, c->stream, w.counts, w.offsets, n_rel,
+                       with_rr ? w.blocks : nullptr, w.occ);
     hipLaunchKernelGGL(k_rr_scatter, qgrid, dim3(kThreads), 0, c->stream, h, r, t, nq, n_ent, n_rel, w.offsets, w.cursor,
                        w.perm, w.gh, w.gt);
     int32_t *counts = new (std::nothrow) int32_t[2 * (size_t)n_rel];   // and the order of the relations
@@ -709,7 +723,9 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
     // Relations that occur, most queries first: neighbours in that order have similar numbers, so those with few can
     // share launches whose shape suits all of them.  Relations with many queries get launches of their own.
     int32_t *order = counts + n_rel, n_occ = 0;
-    for (int32_t rr = 0; rr < n_rel; ++rr)
+    const RankGroups groups{w.gh, w.gt, w.gts, w.gless, w.gequal, w.blocks, w.occ};
+    const bool done = with_rr && rank_transr(c, p, nq, side, groups, w.rr, w.rr_bytes, counts);
+    for (int32_t rr = 0; !done && rr < n_rel; ++rr)
         if (counts[rr]) order[n_occ++] = rr;
     std::sort(order, order + n_occ, [&](int32_t x, int32_t y) { return counts[x] != counts[y] ? counts[x] > counts[y] : x < y; });
     for (int32_t i = 0; i < n_occ;) {
@@ -732,10 +748,7 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
             hipLaunchKernelGGL(k_rr_project, pgrid, dim3(kThreads), 0, c->stream, p->ent, p->proj, p->rel, n_ent, dim, k,
                                w.table, ids, stride);
         }
-        // (L2 kinds: always filtered.  At 131 sizes of 1,000 to 120,000 entities, 1 to 237 relations, widths of 32 to 256 and
-        // 1 to 20,000 queries a call took 0.11 to 1.01 times its time with plain sweeps: 84 us and 65 at 1,000 entities,
-        // k = 32, one query; 99 and 100 at 120,000; 20,000 queries of one relation at 14,500, k = 128: 1,927 and 342)
-        if (work_bytes < w.total || !rank_filtered(c, a, side, w.ws, nz, ids, queries)) rank_sweep(c, a, sh, false, side, ids, nz, false);
+        rank_sweep(c, a, sh, false, side, ids, nz, false);
     }
     if (c->cfg.dist == STX_L2) hipLaunchKernelGGL((k_rank_finish<STX_L2>), qgrid, dim3(kThreads), 0, c->stream, w.gts, nq);
     if (c->cfg.dist == STX_TORUS_L2)

@@ -106,26 +106,6 @@ __device__ inline PairRows pair_rows(const FilterArgs &f, uint2 pr)
 // One term's difference as k_rank forms it (the factor +-1 is exact).
 __device__ inline float pair_diff(float sg, float qv, float ev) { return sg * (qv - ev); }
 
-// Counts of the active lanes' pairs.  A query that decides nothing brings many at once, and 400,000 additions to one
-// counter, one by one, take 5 ms: the pairs of the first lane's query are added together, then those of the first lane that
-// is left, TRIES times; what is then left (the usual mixture of queries) costs less in single additions.
-template <int TRIES>
-__device__ inline void pair_count(const FilterArgs &f, int64_t q, bool less, bool equal)
-{
-#pragma unroll 1
-    for (int i = 0; i < TRIES; ++i) {
-        const bool mine = (uint32_t)q == (uint32_t)__builtin_amdgcn_readfirstlane((int)q);
-        const int nl = __builtin_popcountll(__ballot(mine && less)), ne = __builtin_popcountll(__ballot(mine && equal));
-        if (mask_rank(__ballot(true)) == 0) {
-            if (nl) atomicAdd(&f.a.n_less[q], nl);
-            if (ne) atomicAdd(&f.a.n_equal[q], ne);
-        }
-        if (mine) return;
-    }
-    if (less) atomicAdd(&f.a.n_less[q], 1);
-    if (equal) atomicAdd(&f.a.n_equal[q], 1);
-}
-
 // The index-order sum of one pair per lane.
 template <int DIST>
 __device__ inline void pair_exact(const FilterArgs &f, uint2 pr)
@@ -150,7 +130,7 @@ __device__ inline void pair_exact(const FilterArgs &f, uint2 pr)
                 acc = rank_step<DIST>(acc, pair_diff(sg, vq[u].w, ve[u].w));
             }
     }
-    pair_count<64>(f, p.q, acc < p.st, acc == p.st);
+    rank_count<64>(f.a.n_less, f.a.n_equal, (uint32_t)p.q, acc < p.st, acc == p.st);
 }
 
 // Eight lanes per pair, the same sum (1: below the true entity's, 2: equal, else 0): a lane adds the four terms it holds of 32 to what the lane before it hands on.  Every
@@ -221,7 +201,7 @@ __global__ __launch_bounds__(kThreads) void k_rank_pairs(FilterArgs f, RankIds i
             const int got = pair_ordered<DIST>(f, pr, lane);
             if ((lane & 7) == u) { q = pr.y; res = i < n ? got : 0; }
         }
-        if (res) pair_count<4>(f, q, res == 1, res == 2);
+        if (res) rank_count<4>(f.a.n_less, f.a.n_equal, q, res == 1, res == 2);
     }
 }
 
