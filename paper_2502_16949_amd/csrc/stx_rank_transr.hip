@@ -8,7 +8,7 @@
 // so the sweep can run over the entity table itself, packed once for all relations, with v = M^T q in the query's place,
 // if |M e|^2 is known for the relation and entity: a number each, formed on the fp16 matrix cores from operands split in two
 // (22 bits).  All of this has a bound on its distance from the sums that count; the pairs it leaves undecided (about one in
-// STX_RR_ONE_IN) are projected and summed exactly as written there, 128 pairs of one relation at a time.
+// STX_RR_ONE_IN) are projected and summed exactly as written there, 64 pairs of one relation at a time.
 //
 //   k_rr_pack    entity table and matrices as operands, 32 rows a tile
 //   k_rr_query   blocks of 32 queries of one relation: their points and true sums (exact), v, its operands and bounds
@@ -32,7 +32,7 @@ typedef int intx16 __attribute__((ext_vector_type(16)));
 
 constexpr float kUnit = 5.9604645e-8f; // 2^-24
 constexpr float kWideMax = 32639.f;    // see stx_rank_filter.hip
-constexpr int kPairBlock = 128;        // undecided pairs of one relation that are projected together
+constexpr int kPairBlock = 64;         // undecided pairs of one relation that are projected together
 constexpr int kAux = 64;               // floats that go with a tile of 32 entities: of the table, and of a relation
 
 struct RrState {
@@ -193,85 +193,81 @@ __global__ __launch_bounds__(kThreads) void k_rr_pack(RrArgs f, int etiles)
 }
 
 // ---- exact rows -----------------------------------------------------------------------------------------------
-// P = M_r e of the 128 entities s_id, all k outputs, in registers: acc[c][u][v][i] is output 128 c + wa + 32 v + (lane & 31)
-// of row we + 32 u + (i & 3) + 8 (i >> 2) + 4 (lane >> 5).  v_mfma_f32_32x32x2_f32 performs the fused multiply-adds of
-// an index-order loop, as in k_rr_project.  lds: 2 x 32 x 132 floats.
-constexpr int kRrLd = 132;
+// P = M_r e of the 64 entities s_id, all k outputs, in registers: acc[c][u][i] is output 128 c + 32 wave + (lane & 31) of row
+// 32 u + (i & 3) + 8 (i >> 2) + 4 (lane >> 5).  v_mfma_f32_32x32x2_f32 performs the fused multiply-adds of an index-order
+// loop, as in k_rr_project.  lds: kStageLds bytes.
+constexpr int kLdM = 132, kLdE = 68;
+constexpr int kStageLds = 32 * (kLdM + kLdE) * 4;
 template <int A>
-__device__ inline void rr_project(const RrArgs &f, int32_t rel, const int32_t *s_id, float *lds, floatx16 (&acc)[A][2][2])
+__device__ inline void rr_project(const RrArgs &f, int32_t rel, const int32_t *s_id, float *lds, floatx16 (&acc)[A][2])
 {
-    float (*s_m)[kRrLd] = reinterpret_cast<float (*)[kRrLd]>(lds), (*s_e)[kRrLd] = s_m + 32;
-    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l31 = lane & 31;
-    const int we = ((tid >> 6) & 1) * 64, wa = (tid >> 7) * 64;
-    const int sc = tid & 127, sj = (tid >> 7) * 4, dim = f.dim;
-    const float *pe = f.E + (int64_t)s_id[sc] * dim + sj;
+    float (*s_m)[kLdM] = reinterpret_cast<float (*)[kLdM]>(lds);
+    float (*s_e)[kLdE] = reinterpret_cast<float (*)[kLdE]>(lds + 32 * kLdM);
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l31 = lane & 31, wa = (tid >> 6) * 32;
+    const int cm = tid & 127, jm = (tid >> 7) * 4, ce = tid & 63, je = (tid >> 6) * 4, dim = f.dim;
+    const float *pe = f.E + (int64_t)s_id[ce] * dim + je;
 #pragma unroll
     for (int c = 0; c < A; ++c) {
-        const float *pm = f.M + ((int64_t)rel * f.k + min(128 * c + sc, f.k - 1)) * dim + sj;
+        const float *pm = f.M + ((int64_t)rel * f.k + min(128 * c + cm, f.k - 1)) * dim + jm;
 #pragma unroll
         for (int u = 0; u < 2; ++u)
 #pragma unroll
-            for (int v = 0; v < 2; ++v)
+            for (int i = 0; i < 16; ++i) acc[c][u][i] = 0.f;
+        float4 vm[4], ve[2];
 #pragma unroll
-                for (int i = 0; i < 16; ++i) acc[c][u][v][i] = 0.f;
-        float4 vm[4], ve[4];
+        for (int i = 0; i < 4; ++i) vm[i] = ld4(pm + 8 * i);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) { vm[i] = ld4(pm + 8 * i); ve[i] = ld4(pe + 8 * i); }
+        for (int i = 0; i < 2; ++i) ve[i] = ld4(pe + 16 * i);
         for (int j0 = 0; j0 < dim; j0 += 32) {
             __syncthreads();
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                const int jj = sj + 8 * i;
-                s_m[jj][sc] = vm[i].x; s_m[jj + 1][sc] = vm[i].y; s_m[jj + 2][sc] = vm[i].z; s_m[jj + 3][sc] = vm[i].w;
-                s_e[jj][sc] = ve[i].x; s_e[jj + 1][sc] = ve[i].y; s_e[jj + 2][sc] = ve[i].z; s_e[jj + 3][sc] = ve[i].w;
+                const int jj = jm + 8 * i;
+                s_m[jj][cm] = vm[i].x; s_m[jj + 1][cm] = vm[i].y; s_m[jj + 2][cm] = vm[i].z; s_m[jj + 3][cm] = vm[i].w;
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int jj = je + 16 * i;
+                s_e[jj][ce] = ve[i].x; s_e[jj + 1][ce] = ve[i].y; s_e[jj + 2][ce] = ve[i].z; s_e[jj + 3][ce] = ve[i].w;
             }
             __syncthreads();
             if (j0 + 32 < dim) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { vm[i] = ld4(pm + j0 + 32 + 8 * i); ve[i] = ld4(pe + j0 + 32 + 8 * i); }
+                for (int i = 0; i < 4; ++i) vm[i] = ld4(pm + j0 + 32 + 8 * i);
+#pragma unroll
+                for (int i = 0; i < 2; ++i) ve[i] = ld4(pe + j0 + 32 + 16 * i);
             }
             if (128 * c + wa >= f.k) continue;             // (uniform over the wavefront)
 #pragma unroll
             for (int jj = 0; jj < 32; jj += 2) {
-                float ev[2], mv[2];
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    ev[u] = s_e[jj + half][we + 32 * u + l31];
-                    mv[u] = s_m[jj + half][wa + 32 * u + l31];
-                }
+                const float mv = s_m[jj + half][wa + l31];
 #pragma unroll
                 for (int u = 0; u < 2; ++u)
-#pragma unroll
-                    for (int v = 0; v < 2; ++v) acc[c][u][v] = __builtin_amdgcn_mfma_f32_32x32x2f32(ev[u], mv[v], acc[c][u][v], 0, 0, 0);
+                    acc[c][u] = __builtin_amdgcn_mfma_f32_32x32x2f32(s_e[jj + half][32 * u + l31], mv, acc[c][u], 0, 0, 0);
             }
         }
     }
     __syncthreads();                                       // (the caller may write over lds)
 }
-// ... into LDS: s_p[output * ld + row], the first `rows` rows.
+// ... into LDS: s_p[output * kLdP + row].
+constexpr int kLdP = 65;
 template <int A>
-__device__ inline void rr_spread(const RrArgs &f, const floatx16 (&acc)[A][2][2], float *s_p, int ld, int rows)
+__device__ inline void rr_spread(const RrArgs &f, const floatx16 (&acc)[A][2], float *s_p)
 {
-    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, l31 = lane & 31;
-    const int we = ((tid >> 6) & 1) * 64, wa = (tid >> 7) * 64;
-    if (we < rows) {
+    const int tid = threadIdx.x, lane = tid & 63, half = lane >> 5, wa = (tid >> 6) * 32;
 #pragma unroll
-        for (int c = 0; c < A; ++c)
+    for (int c = 0; c < A; ++c) {
+        const int a = 128 * c + wa + (lane & 31);
+        if (a < f.k)
 #pragma unroll
-            for (int v = 0; v < 2; ++v) {
-                const int a = 128 * c + wa + 32 * v + l31;
-                if (a < f.k)
+            for (int u = 0; u < 2; ++u)
 #pragma unroll
-                    for (int u = 0; u < 2; ++u)
-#pragma unroll
-                        for (int i = 0; i < 16; ++i) s_p[a * ld + we + 32 * u + (i & 3) + 8 * (i >> 2) + 4 * half] = acc[c][u][v][i];
-            }
+                for (int i = 0; i < 16; ++i) s_p[a * kLdP + 32 * u + (i & 3) + 8 * (i >> 2) + 4 * half] = acc[c][u][i];
     }
     __syncthreads();
 }
-constexpr int kStageLds = 2 * 32 * kRrLd * 4;
-static size_t rr_exact_lds(int k) { return std::max((size_t)kStageLds, (size_t)k * 129 * 4); }
-static size_t rr_query_lds(int dim, int k) { return std::max((size_t)kStageLds, (size_t)k * 65 * 4) + (size_t)32 * (dim + 1) * 4; }
+static size_t rr_exact_lds(int k) { return std::max((size_t)kStageLds, (size_t)k * kLdP * 4); }
+static size_t rr_query_lds(int dim, int k) { return rr_exact_lds(k) + (size_t)32 * (dim + 1) * 4; }
 
 // ---- queries --------------------------------------------------------------------------------------------------
 // A block of 32 queries: rows 0 .. 31 are their own entities, 32 .. 63 the true ones.  Then v = M^T q and what its sums
@@ -290,8 +286,8 @@ template <int KS, int A, bool HEAD>
 __global__ __launch_bounds__(kThreads, 2) void k_rr_query(RrArgs f)
 {
     extern __shared__ __align__(16) unsigned char s_dyn[];
-    __shared__ int32_t s_id[128];
-    __shared__ float s_st[32], s_qq[32], s_sum[3][4];
+    __shared__ int32_t s_id[64];
+    __shared__ float s_st[32], s_sum[3][4];
     const int tid = threadIdx.x, dim = f.dim, k = f.k;
     if (blockIdx.x == 0 && tid == 0) {
         const int32_t full = f.first ? 0 : f.st->full;
@@ -300,18 +296,18 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_query(RrArgs f)
         if (f.first) f.st->full = 0;
     }
     const RrBlock blk = f.blocks[f.b0 + blockIdx.x];
-    if (tid < 128) {
+    if (tid < 64) {
         const int q = blk.first + min(tid & 31, blk.count - 1);
-        s_id[tid] = ((tid >> 5) == 1) != HEAD ? f.gt[q] : f.gh[q];             // own: head (tail side) or tail; true: the other
+        s_id[tid] = (tid >= 32) != HEAD ? f.gt[q] : f.gh[q];             // own: head (tail side) or tail; true: the other
     }
     __syncthreads();
     float *s_p = reinterpret_cast<float *>(s_dyn);
-    float *s_v = s_p + (2 * 32 * kRrLd > k * 65 ? 2 * 32 * kRrLd : k * 65);
-    constexpr int LD = 65;
+    float *s_v = s_p + (kStageLds / 4 > k * kLdP ? kStageLds / 4 : k * kLdP);
+    constexpr int LD = kLdP;
     {
-        floatx16 acc[A][2][2];
+        floatx16 acc[A][2];
         rr_project<A>(f, blk.rel, s_id, s_p, acc);
-        rr_spread<A>(f, acc, s_p, LD, 64);
+        rr_spread<A>(f, acc, s_p);
     }
     const float *rvec = f.R + (int64_t)blk.rel * k;
     for (int i = tid; i < 32 * k; i += kThreads) {
@@ -323,9 +319,15 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_query(RrArgs f)
     __syncthreads();
     if (tid < 32) {                                        // the true entity's sum, index order
         float acc = 0.f;
-        for (int a = 0; a < k; ++a) {
-            const float q = s_p[a * LD + tid], e = s_p[a * LD + 32 + tid];
-            acc = rank_step<STX_L2>(acc, HEAD ? e - q : q - e);
+        for (int a0 = 0; a0 < k; a0 += 32) {
+            float y[32];
+#pragma unroll
+            for (int a = 0; a < 32; ++a) {
+                const float q = s_p[(a0 + a) * LD + tid], e = s_p[(a0 + a) * LD + 32 + tid];
+                y[a] = HEAD ? e - q : q - e;
+            }
+#pragma unroll
+            for (int a = 0; a < 32; ++a) acc = rank_step<STX_L2>(acc, y[a]);
         }
         s_st[tid] = acc;
         if (tid < blk.count) {
@@ -334,29 +336,31 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_query(RrArgs f)
             f.gequal[blk.first + tid] = 0;
         }
     }
-    // v: a thread per column and group of queries, eight queries at a time
-    const int groups = dim <= 32 ? 8 : dim <= 64 ? 4 : dim <= 128 ? 2 : 1, each = 32 / groups;
-    const int j = tid % (256 / groups), g = tid / (256 / groups);
-    const float *pm = f.M + (int64_t)blk.rel * k * dim + min(j, dim - 1);
+    // v on the fp32 matrix cores too, 32 columns a wavefront: rows are queries; and M's norms
     float f2 = 0.f, g2 = 0.f, h2 = 0.f;
-    for (int q0 = 0; q0 < each; q0 += 4) {
-        float v[4] = {0.f, 0.f, 0.f, 0.f};
-        const float *pq = s_p + g * each + q0;
-#pragma unroll 8
-        for (int a = 0; a < k; ++a) {
-            const float m = pm[(int64_t)a * dim];
+    for (int j0 = (tid >> 6) * 32; j0 < dim; j0 += 128) {
+        const int lane = tid & 63, half = lane >> 5, j = j0 + (lane & 31);
+        const float *pm = f.M + ((int64_t)blk.rel * k + half) * dim + j;
+        floatx16 acc;
 #pragma unroll
-            for (int i = 0; i < 4; ++i) v[i] = __builtin_fmaf(m, pq[a * LD + i], v[i]);
-            if (q0 == 0 && g == 0 && j < dim) {
-                const float wg = m * (float)(dim - j + 1), wh = m * (float)(k - a + 1);
-                f2 = __builtin_fmaf(m, m, f2);
+        for (int i = 0; i < 16; ++i) acc[i] = 0.f;
+        const float wj = (float)(dim - j + 1);
+        for (int a0 = 0; a0 < k; a0 += 32) {
+            float m[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) m[i] = pm[(int64_t)(a0 + 2 * i) * dim];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int a = a0 + 2 * i + half;
+                acc = __builtin_amdgcn_mfma_f32_32x32x2f32(s_p[a * LD + (lane & 31)], m[i], acc, 0, 0, 0);
+                const float wg = m[i] * wj, wh = m[i] * (float)(k - a + 1);
+                f2 = __builtin_fmaf(m[i], m[i], f2);
                 g2 = __builtin_fmaf(wg, wg, g2);
                 h2 = __builtin_fmaf(wh, wh, h2);
             }
         }
-        if (j < dim)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s_v[(g * each + q0 + i) * (dim + 1) + j] = v[i];
+        for (int i = 0; i < 16; ++i) s_v[((i & 3) + 8 * (i >> 2) + 4 * half) * (dim + 1) + j] = acc[i];
     }
     f2 = group_sum<64>(f2);
     g2 = group_sum<64>(g2);
@@ -541,7 +545,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_sweep(RrArgs f, int slice)
     __shared__ __align__(1024) uint4 s_ring[NB][CK][64];
     __shared__ __align__(256) float s_aux[NB][TPC][kAux];
     __shared__ __align__(256) float s_nn[NB][4][TPC][kAux];
-    __shared__ uint2 s_list[4][kPairBlock];
+    __shared__ uint2 s_list[4][2 * kPairBlock];
     const int lane = threadIdx.x & 63, half = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int b = f.b0 + (int)blockIdx.x * 4 + wave;
@@ -591,13 +595,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_sweep(RrArgs f, int slice)
         if (lane == 0) {
             at = (int)min(atomicAdd(&f.st->n_blocks, 1u), (uint32_t)f.pair_blocks);
             if (at == f.pair_blocks) __hip_atomic_store(&f.st->full, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            else f.heads[at] = make_int2(rel, cnt);
+            else f.heads[at] = make_int2(rel, min(cnt, kPairBlock));
         }
         at = __builtin_amdgcn_readfirstlane(at);
         if (at == f.pair_blocks) listing = false;
-        else
-            for (int i = lane; i < cnt; i += 64) f.pairs[(int64_t)at * kPairBlock + i] = s_list[wave][i];
-        cnt = 0;
+        else if (lane < cnt) f.pairs[(int64_t)at * kPairBlock + lane] = s_list[wave][lane];
+        cnt -= kPairBlock;
+        if (lane < cnt) s_list[wave][lane] = s_list[wave][kPairBlock + lane];
     };
 #pragma unroll
     for (int c = 0; c < NB - 1; ++c) fetch(c, c);
@@ -659,13 +663,13 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_sweep(RrArgs f, int slice)
                 if (mine) s_list[wave][cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u))] =
                     make_uint2((uint32_t)e, (uint32_t)(first + q));
                 cnt += __builtin_popcountll(m);
-                if (cnt > kPairBlock - 64) flush();
+                if (cnt >= kPairBlock) flush();
             }
         }
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" : : : "memory");   // (loads into LDS still in flight must not outlive the workgroup)
     if (!works) return;
-    if (cnt && listing) flush();
+    if (cnt > 0 && listing) flush();
     const int n = less + __shfl_xor(less, 32, 64);
     if (lane < count && n) atomicAdd(&f.gless[first + lane], n);
 }
@@ -674,10 +678,10 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_sweep(RrArgs f, int slice)
 // A block of undecided pairs at a time: their entities are projected together, then a thread walks each pair's sum.  Bound by
 // the fp32 matrix cores.  Where the sweep stopped, what it counted is cleared instead, for k_rr_behind.
 template <int A>
-__global__ __launch_bounds__(kThreads, A == 1 ? 2 : 1) void k_rr_pairs(RrArgs f)
+__global__ __launch_bounds__(kThreads, A == 1 ? 4 : 2) void k_rr_pairs(RrArgs f)
 {
     extern __shared__ __align__(16) unsigned char s_dyn[];
-    __shared__ int32_t s_id[128];
+    __shared__ int32_t s_id[kPairBlock];
     const int tid = threadIdx.x, k = f.k;
     if (f.st->full) {
         for (int b = f.b0 + (int)blockIdx.x * 8 + (tid >> 5); b < f.b1; b += (int)gridDim.x * 8) {
@@ -687,17 +691,16 @@ __global__ __launch_bounds__(kThreads, A == 1 ? 2 : 1) void k_rr_pairs(RrArgs f)
         return;
     }
     float *s_p = reinterpret_cast<float *>(s_dyn);
-    constexpr int LD = 129;
     const int n = (int)min(f.st->n_blocks, (uint32_t)f.pair_blocks);
     for (int b = blockIdx.x; b < n; b += gridDim.x) {
         const int2 head = f.heads[b];
-        const uint2 pr = f.pairs[(int64_t)b * kPairBlock + min(tid & 127, head.y - 1)];
+        const uint2 pr = f.pairs[(int64_t)b * kPairBlock + min(tid & (kPairBlock - 1), head.y - 1)];
         __syncthreads();                                   // (the block before this one has been walked)
-        if (tid < 128) s_id[tid] = (int32_t)pr.x;
+        if (tid < kPairBlock) s_id[tid] = (int32_t)pr.x;
         __syncthreads();
-        floatx16 acc[A][2][2];
+        floatx16 acc[A][2];
         rr_project<A>(f, head.x, s_id, s_p, acc);
-        rr_spread<A>(f, acc, s_p, LD, 128);
+        rr_spread<A>(f, acc, s_p);
         if (tid < head.y) {
             const float *q = f.q32 + (int64_t)pr.y * k;
             const float st = f.gts[pr.y];
@@ -706,27 +709,27 @@ __global__ __launch_bounds__(kThreads, A == 1 ? 2 : 1) void k_rr_pairs(RrArgs f)
                 const float4 x = ld4(q + a), y = ld4(q + a + 4);
                 const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
 #pragma unroll
-                for (int i = 0; i < 8; ++i) s = rank_step<STX_L2>(s, v[i] - s_p[(a + i) * LD + tid]);
+                for (int i = 0; i < 8; ++i) s = rank_step<STX_L2>(s, v[i] - s_p[(a + i) * kLdP + tid]);
             }
             rank_count<4>(f.gless, f.gequal, pr.y, s < st, s == st);
         }
     }
 }
 
-// All pairs of the sweep's queries, where it stopped: 128 entities of a relation are projected at a time and every thread
+// All pairs of the sweep's queries, where it stopped: 64 entities of a relation are projected at a time and every thread
 // walks the sums of one against the relation's queries.
 template <int A>
-__global__ __launch_bounds__(kThreads, A == 1 ? 2 : 1) void k_rr_behind(RrArgs f)
+__global__ __launch_bounds__(kThreads, A == 1 ? 4 : 2) void k_rr_behind(RrArgs f)
 {
     if (!f.st->full) return;
     extern __shared__ __align__(16) unsigned char s_dyn[];
-    __shared__ int32_t s_id[128];
+    __shared__ int32_t s_id[64];
     float *s_p = reinterpret_cast<float *>(s_dyn);
-    constexpr int LD = 129;
-    const int tid = threadIdx.x, k = f.k, row = tid & 127;
-    const int part = __builtin_amdgcn_readfirstlane(tid >> 7);
-    const int e = (int)blockIdx.x * 128 + row;
-    if (tid < 128) s_id[tid] = min(e, f.n_ent - 1);
+    constexpr int LD = kLdP;
+    const int tid = threadIdx.x, k = f.k, row = tid & 63;
+    const int part = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int e = (int)blockIdx.x * 64 + row;
+    if (tid < 64) s_id[tid] = min(e, f.n_ent - 1);
     for (int b = f.b0 + (int)blockIdx.y; b < f.b1;) {      // (a relation's blocks follow one another; the first to see it takes them)
         const RrBlock blk = f.blocks[b];
         const int rel = __builtin_amdgcn_readfirstlane(blk.rel);
@@ -735,10 +738,10 @@ __global__ __launch_bounds__(kThreads, A == 1 ? 2 : 1) void k_rr_behind(RrArgs f
         while (e_b < f.b1 && f.blocks[e_b].rel == rel) ++e_b;
         const int q0 = __builtin_amdgcn_readfirstlane(blk.first), q1 = __builtin_amdgcn_readfirstlane(f.blocks[e_b - 1].first + f.blocks[e_b - 1].count);
         __syncthreads();
-        floatx16 acc[A][2][2];
+        floatx16 acc[A][2];
         rr_project<A>(f, rel, s_id, s_p, acc);
-        rr_spread<A>(f, acc, s_p, LD, 128);
-        for (int q = q0 + part * 4; q < q1; q += 8) {      // four queries a wavefront at a time, their points through scalar loads
+        rr_spread<A>(f, acc, s_p);
+        for (int q = q0 + part * 4; q < q1; q += 16) {      // four queries a wavefront at a time, their points through scalar loads
             float s[4] = {0.f, 0.f, 0.f, 0.f};
             const STX_CONST_AS float *qp[4];
 #pragma unroll
@@ -789,8 +792,8 @@ static RrPlan rr_plan(const stx_config &cfg, int64_t nq)
     // relations in batches of at most 96 MiB of operands and |M e|^2
     const int64_t slot_bytes = (int64_t)(cfg.rel_dim / 32) * (ks * 2048 + 4) + tiles * kAux * 4;
     p.slots = std::max((int64_t)1, std::min(occ, ((int64_t)96 << 20) / slot_bytes));
-    // undecided pairs: room for one in 128 of the pairs in half-filled blocks, 64 MiB at most
-    const int64_t blocks = (int64_t)((double)nq * (double)cfg.n_ent / (128. * 64.)) + p.max_blocks * 8 + 256;
+    // undecided pairs: room for one in 128 of the pairs and the blocks that wavefronts leave partly filled, 64 MiB at most
+    const int64_t blocks = (int64_t)((double)nq * (double)cfg.n_ent / (128. * kPairBlock)) + p.max_blocks * 16 + 256;
     p.pair_blocks = std::min(blocks, ((int64_t)64 << 20) / (kPairBlock * (int64_t)sizeof(uint2)));
     p.q32 = take((size_t)nq * cfg.rel_dim * 4);
     p.qf = take((size_t)p.max_blocks * ks * 1024);
@@ -866,12 +869,12 @@ static void rr_go(stx_ctx *c, RrArgs f, const RrPlan &p, int64_t nq, const int32
             }
             {
                 ProfScope prof(c, "k_rank_pairs");
-                const int64_t most = (int64_t)nb * 32 * f.n_ent / (kPairBlock * 64) + 64;
-                hipLaunchKernelGGL((k_rr_pairs<A>), dim3((unsigned)std::min(most, (int64_t)(A == 1 ? 512 : 256))), dim3(kThreads), lds_x, c->stream, f);
+                const int64_t most = (int64_t)nb * 32 * f.n_ent / (kPairBlock * 128) + 64;
+                hipLaunchKernelGGL((k_rr_pairs<A>), dim3((unsigned)std::min(most, (int64_t)(A == 1 ? 1024 : 512))), dim3(kThreads), lds_x, c->stream, f);
             }
             {
                 ProfScope prof(c, "k_rr_behind");
-                hipLaunchKernelGGL((k_rr_behind<A>), dim3((unsigned)((f.n_ent + 127) / 128), (unsigned)std::min(nb, 16)), dim3(kThreads), lds_x, c->stream, f);
+                hipLaunchKernelGGL((k_rr_behind<A>), dim3((unsigned)((f.n_ent + 63) / 64), (unsigned)std::min(nb, 16)), dim3(kThreads), lds_x, c->stream, f);
             }
             f.first = 0;
         }
