@@ -18,6 +18,7 @@ __device__ inline float rank_step(float acc, float y)
 }
 
 constexpr int kRankTables = 32;        // TransR: relations per launch
+constexpr int kRankBig = 1024;         // ... those with more queries than this get a launch of their own
 struct RankIds {                       // (an argument of its own: indexed inside the struct that kernels copy and narrow,
     int32_t g[kRankTables];            // it would put that copy in memory)
 };
@@ -100,11 +101,14 @@ struct RankGroups {                    // queries grouped by relation
     float *score;
     int32_t *less, *equal;
     const RrBlock *blocks;             // [nq / 32 + relations]
-    const int32_t *occ;                // relations that occur, in order
+    const int32_t *occ;                // relations that occur with at most `most` queries, in order; the blocks are theirs
+    int32_t most;
 };
 // TransR's L2 kinds: true sums and counts of grouped queries (not the final square roots), given the queries per relation
-// on the host.  false: not for this kind or scratch, nothing launched.
-bool rank_transr(stx_ctx *, const stx_params *, int64_t nq, int side, const RankGroups &, void *work, size_t bytes, const int32_t *counts);
+// on the host, of the relations with at most `most` of them.  tables: relations that a launch over projected tables would
+// take.  false: it would be slower than that, nothing launched.
+bool rank_transr(stx_ctx *, const stx_params *, int64_t nq, int side, const RankGroups &, int tables, void *work, size_t bytes, const int32_t *counts);
+int32_t rank_transr_most(const stx_config &);
 size_t rank_transr_bytes(const stx_config &, int64_t nq);                         // 0: a kind without
 
 // ---- stx_rank_filter.hip ------------------------------------------------------------------------------

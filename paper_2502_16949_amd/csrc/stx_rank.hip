@@ -370,7 +370,8 @@ __global__ __launch_bounds__(kThreads, 2) void k_rank_h(RankArgs a, RankIds)
 // grouped by relation (counting sort), and for every relation that occurs its projected table is built
 // (k_rr_project, a plain fp32 product with sums in index order) and swept by k_rank_true / k_rank.  Relations
 // with many queries get launches of their own; the many relations with few queries are taken several per
-// launch (blockIdx.z), each with its own table, so that their small sweeps fill the chip together.
+// launch (blockIdx.z), each with its own table, so that their small sweeps fill the chip together.  The L2 kinds sweep most
+// relations without a table (stx_rank_transr.hip).
 struct RankRWork {                      // partitions of the caller's work buffer
     int32_t *counts, *cursor, *offsets; // [n_rel], [n_rel], [n_rel + 1]
     int32_t *perm, *gh, *gt;            // [nq]: query at each grouped position, its clamped head and tail
@@ -378,13 +379,13 @@ struct RankRWork {                      // partitions of the caller's work buffe
     int32_t *gless, *gequal;
     float *table;                       // n_tables tables of (n_ent + 1) x rel_dim: P_r, then r
     int n_tables;
-    RrBlock *blocks;                    // of the sweep without projected tables (kinds that have one) ...
+    RankScratch ws;                     // of the filtered sweeps (kinds that have one), over projected tables ...
+    RrBlock *blocks;                    // ... and without them, in the same place
     int32_t *occ;
     void *rr;
     size_t rr_bytes;
-    size_t plain_total, total;          // ... without and with that
+    size_t plain_total, total;          // without and with these
 };
-constexpr int kRankBig = 1024;          // relations with more queries than this get a launch of their own
 static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
 {
     size_t off = 0;
@@ -407,10 +408,22 @@ static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
     w.table = (float *)take(table_bytes * w.n_tables);
     w.plain_total = w.total = off;
     w.rr_bytes = rank_transr_bytes(cfg, nq);
-    if (!w.rr_bytes) return w;
+    if (!w.rr_bytes) return w;                                                 // (no filtered sweep)
     w.blocks = (RrBlock *)take((size_t)(nq / 32 + std::min((int64_t)cfg.n_rel, nq)) * sizeof(RrBlock));
     w.occ = (int32_t *)take((size_t)cfg.n_rel * 4);
+    // (the relations swept without a table are done before the others)
+    const size_t both = off;
     w.rr = take(w.rr_bytes);
+    const size_t end = off;
+    off = both;
+    // one relation with all queries, or n_tables relations with up to kRankBig each
+    const int64_t few = nq < kRankBig ? nq : kRankBig, many = ((few + 31) / 32 * 32) * w.n_tables;
+    w.ws.q_bytes = rank_filter_q_bytes(cfg.dist, cfg.rel_dim, nq > many ? nq : many);
+    w.ws.e_bytes = rank_filter_e_bytes(cfg.dist, cfg.rel_dim, cfg.n_ent, w.n_tables);
+    w.ws.q = take(w.ws.q_bytes);
+    w.ws.e = take(w.ws.e_bytes);
+    w.ws.q32 = w.ws.q_bytes ? (float *)take((size_t)nq * cfg.rel_dim * 4) : nullptr;
+    off = std::max(off, end);
     w.total = off;
     return w;
 }
@@ -454,30 +467,37 @@ __global__ __launch_bounds__(kThreads) void k_rr_hist(const int32_t *h, const in
     }
 }
 
-// offsets[i] = counts[0] + ... + counts[i-1], offsets[n_rel] = nq; the relations that occur and their blocks of 32 queries.
-// One workgroup.
-__global__ __launch_bounds__(kThreads) void k_rr_scan(const int32_t *counts, int32_t *offsets, int n_rel, RrBlock *blocks, int32_t *occ)
+// offsets[i] = counts[0] + ... + counts[i-1], offsets[n_rel] = nq; and blocks of 32 queries of the relations that occur with at
+// most `most` of them.  One workgroup.
+__global__ __launch_bounds__(kThreads) void k_rr_scan(const int32_t *counts, int32_t *offsets, int n_rel, int32_t most,
+                                                      RrBlock *blocks, int32_t *occ)
 {
     __shared__ int32_t s_total;
     int32_t base = 0, base_b = 0, base_o = 0;
     for (int i0 = 0; i0 < n_rel; i0 += kThreads) {
         const int i = i0 + (int)threadIdx.x;
-        const int32_t v = i < n_rel ? counts[i] : 0;
+        int32_t v = i < n_rel ? counts[i] : 0;
         const int32_t ex = base + block_exclusive_scan(v, &s_total);
         if (i < n_rel) offsets[i] = ex;
         __syncthreads();
         base += s_total;
         if (!blocks) continue;
-        __syncthreads();
-        const int32_t b = base_b + block_exclusive_scan((v + 31) / 32, &s_total);
+        if (v > most) v = 0;
+        const int32_t nb = (v + 31) / 32;
+        const int32_t b = base_b + block_exclusive_scan(nb, &s_total);
         __syncthreads();
         base_b += s_total;
-        __syncthreads();
         const int32_t o = base_o + block_exclusive_scan(v > 0 ? 1 : 0, &s_total);
         __syncthreads();
         base_o += s_total;
         if (v > 0) occ[o] = i;
-        for (int j = 0; j * 32 < v; ++j) blocks[b + j] = RrBlock{i, o, ex + j * 32, min(32, v - j * 32)};
+        for (int j = 0; j < min(nb, 4); ++j) blocks[b + j] = RrBlock{i, o, ex + j * 32, min(32, v - j * 32)};
+        // the blocks of relations with many: a wavefront together
+        for (uint64_t m = __ballot(nb > 4); m; m &= m - 1ull) {
+            const int l = __builtin_ctzll(m);
+            const int32_t lv = __shfl(v, l, 64), lb = __shfl(b, l, 64), lo = __shfl(o, l, 64), lx = __shfl(ex, l, 64), li = __shfl(i, l, 64);
+            for (int j = 4 + (int)(threadIdx.x & 63); j * 32 < lv; j += 64) blocks[lb + j] = RrBlock{li, lo, lx + j * 32, min(32, lv - j * 32)};
+        }
     }
     if (threadIdx.x == 0) offsets[n_rel] = base;
 }
@@ -704,12 +724,13 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
     // projected table and one sweep per relation that occurs
     const RankRWork w = rank_r_work(c->cfg, nq, work);
     const int dim = c->cfg.dim, k = c->cfg.rel_dim;
-    const bool with_rr = w.rr && work_bytes >= w.total;
+    const bool filtered = w.rr_bytes && work_bytes >= w.total;
+    const int32_t most = filtered ? rank_transr_most(c->cfg) : 0;              // queries of a relation that needs no table
     const dim3 rgrid((unsigned)((n_rel + kThreads - 1) / kThreads)), qgrid((unsigned)((nq + kThreads - 1) / kThreads));
     hipLaunchKernelGGL(k_rr_clear, rgrid, dim3(kThreads), 0, c->stream, w.counts, w.cursor, n_rel);
     hipLaunchKernelGGL(k_rr_hist, qgrid, dim3(kThreads), 0, c->stream, h, r, t, nq, n_ent, n_rel, w.counts, bad);
-    hipLaunchKernelGGL(k_rr_scan, dim3(1), dim3(kThreads), 0, c->stream, w.counts, w.offsets, n_rel,
-                       with_rr ? w.blocks : nullptr, w.occ);
+    hipLaunchKernelGGL(k_rr_scan, dim3(1), dim3(kThreads), 0, c->stream, w.counts, w.offsets, n_rel, most,
+                       most > 0 ? w.blocks : nullptr, w.occ);
     hipLaunchKernelGGL(k_rr_scatter, qgrid, dim3(kThreads), 0, c->stream, h, r, t, nq, n_ent, n_rel, w.offsets, w.cursor,
                        w.perm, w.gh, w.gt);
     int32_t *counts = new (std::nothrow) int32_t[2 * (size_t)n_rel];   // and the order of the relations
@@ -723,10 +744,10 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
     // Relations that occur, most queries first: neighbours in that order have similar numbers, so those with few can
     // share launches whose shape suits all of them.  Relations with many queries get launches of their own.
     int32_t *order = counts + n_rel, n_occ = 0;
-    const RankGroups groups{w.gh, w.gt, w.gts, w.gless, w.gequal, w.blocks, w.occ};
-    const bool done = with_rr && rank_transr(c, p, nq, side, groups, w.rr, w.rr_bytes, counts);
-    for (int32_t rr = 0; !done && rr < n_rel; ++rr)
-        if (counts[rr]) order[n_occ++] = rr;
+    const RankGroups groups{w.gh, w.gt, w.gts, w.gless, w.gequal, w.blocks, w.occ, most};
+    const bool done = most > 0 && rank_transr(c, p, nq, side, groups, w.n_tables, w.rr, w.rr_bytes, counts);
+    for (int32_t rr = 0; rr < n_rel; ++rr)
+        if (counts[rr] > (done ? most : 0)) order[n_occ++] = rr;
     std::sort(order, order + n_occ, [&](int32_t x, int32_t y) { return counts[x] != counts[y] ? counts[x] > counts[y] : x < y; });
     for (int32_t i = 0; i < n_occ;) {
         const int64_t max_n = counts[order[i]];
@@ -748,7 +769,9 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
             hipLaunchKernelGGL(k_rr_project, pgrid, dim3(kThreads), 0, c->stream, p->ent, p->proj, p->rel, n_ent, dim, k,
                                w.table, ids, stride);
         }
-        rank_sweep(c, a, sh, false, side, ids, nz, false);
+        // (L2 kinds: a projected table's sweep is always filtered.  At 131 sizes of 1,000 to 120,000 entities, 1 to 237 relations,
+        // widths of 32 to 256 and 1 to 20,000 queries a call took 0.11 to 1.01 times its time with plain sweeps)
+        if (!filtered || !rank_filtered(c, a, side, w.ws, nz, ids, queries)) rank_sweep(c, a, sh, false, side, ids, nz, false);
     }
     if (c->cfg.dist == STX_L2) hipLaunchKernelGGL((k_rank_finish<STX_L2>), qgrid, dim3(kThreads), 0, c->stream, w.gts, nq);
     if (c->cfg.dist == STX_TORUS_L2)

@@ -4,9 +4,8 @@
 // The counts of stx_rank are defined by the fp32 sums of k_rank (index order, every step rounded as written there),
 // so they must come out as if every candidate had been summed that way.  A sum S' with a bound |S' - S| <= W on its
 // distance from the exact-order sum S decides the candidate whenever |S' - S_true| > W; with W about a thousandth of
-// the spread of the scores, one candidate in about a thousand is left, and those are recomputed: first as a tree sum
-// in fp32, whose own bound leaves only ties and near-ties, then, for these, in index order.  So the result is that of
-// the exhaustive fp32 sweep, bit for bit.  Wherever a bound is not finite (values out of range, infinities, NaN) the
+// the spread of the scores, one candidate in about a thousand is left, and those are recomputed in index order.  So the
+// result is that of the exhaustive fp32 sweep, bit for bit.  Wherever a bound is not finite (values out of range, infinities, NaN) the
 // candidate counts as undecided.
 //
 // Undecided pairs go to a list that k_rank_pairs works through; when it is full they are summed inside the sweep, one per
@@ -17,13 +16,14 @@
 //
 // The plain sweep's rate is that of the vector ALU (two fp32 operations per element, five for the torus kind):
 // 59,071 queries x 15,000 entities at d = 128 (L1) took 3.85 ms a side and take 1.95; 256 x 4,000,000 (torus-L1) 10.2
-// and 4.2; 4,096 x 14,951 at d = 1024 (L2) 2.7 and 0.83.
+// and 4.2; 4,096 x 14,951 at d = 1024 (L2) 2.7 and 0.41.
 //
 //   L1, torus-L1   k_rank_sad: rows as 16-bit fixed point, two elements per vector operation (v_sad_u16 sums two
 //                  absolute differences; the torus kind wraps the difference by a 32-bit subtraction first).  The
 //                  bound is the sum of the roundings actually made in each row.
 //   L2, squared L2 k_rank_mfma: S = |q|^2 + |e|^2 - 2 q.e with q.e on the matrix cores, rows rounded to fp16 after
 //                  scaling by a power of two.  The bound is |q| |de| + |dq| |e| with the norms of the roundings made.
+//                  Rows of more than 256 floats: k_rank_wide, the same with 16-bit fixed point in two bytes.
 #include <algorithm>
 
 #include "stx_rank.h"
@@ -136,7 +136,7 @@ __device__ inline void pair_exact(const FilterArgs &f, uint2 pr)
 // Eight lanes per pair, the same sum (1: below the true entity's, 2: equal, else 0): a lane adds the four terms it holds of 32 to what the lane before it hands on.  Every
 // lane goes through all eight turns and only one of them counts, which is five times the instructions of a sum in any
 // order; but such a sum has a bound of its own, a thousandth of the pairs stay within it at d = 1024, and walking
-// those one per lane behind the others took longer than all the rest: STX_PAIRS.
+// those one per lane behind the others took longer than all the rest (4,096 x 14,951 at d = 1024: 290 us a side, now 125).
 template <int DIST>
 __device__ inline int pair_ordered(const FilterArgs &f, uint2 pr, int lane)
 {
@@ -968,7 +968,7 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
 // Wide rows.  Fp16 leaves one pair in a hundred undecided at d = 1024 (a rounding of 2^-12 a side against scores that differ
 // by a few per cent), and summing those took twice the sweep's time.  Here rows are 16-bit fixed point, as high and low
 // bytes: three byte products (v_mfma_i32_32x32x32_i8, exact, twice fp16's rate) leave out only the low bytes' own, and one
-// pair in a STX_WIDE_ONE_IN is undecided at the same bytes per row.
+// pair in 400 is undecided at the same bytes per row, most of them for the index-order sum's own rounding.
 // The queries' operands stay in registers, which d = 1024 would fill: every LDS read then waited for its use (5 times the
 // matrix cores' time).  So the steps of a row are dealt to KH wavefronts (even and odd ones), and each holds 128 registers
 // of them; a tile's halves are exchanged through LDS, behind the next chunk's barrier, and each decides half the candidates.

@@ -7,8 +7,9 @@
 //     |q - M e|^2 = |q|^2 - 2 (M^T q).e + |M e|^2,
 // so the sweep can run over the entity table itself, packed once for all relations, with v = M^T q in the query's place,
 // if |M e|^2 is known for the relation and entity: a number each, formed on the fp16 matrix cores from operands split in two
-// (22 bits).  All of this has a bound on its distance from the sums that count; the pairs it leaves undecided (about one in
-// STX_RR_ONE_IN) are projected and summed exactly as written there, 64 pairs of one relation at a time.
+// (22 bits).  All of this has a bound on its distance from the sums that count, most of it those sums' own rounding; the pairs
+// it leaves undecided (about one in 500 at d = k = 128) are projected and summed exactly as written there, 64 pairs of one
+// relation at a time.
 //
 //   k_rr_pack    entity table and matrices as operands, 32 rows a tile
 //   k_rr_query   blocks of 32 queries of one relation: their points and true sums (exact), v, its operands and bounds
@@ -17,7 +18,8 @@
 //   k_rr_pairs   undecided pairs, exactly
 //   k_rr_behind  all pairs exactly, where a sweep found too many of them; returns at once otherwise
 //
-// 20,466 queries of 237 relations x 14,500 entities, d = k = 128, both sides: 5,330 us with projected tables, STX_RR_NOW.
+// 20,466 queries of 237 relations x 14,500 entities, d = k = 128, both sides: 5,330 us with projected tables, 1,690 now, of
+// which a side's norms take 274, sweep 250, pairs 220, queries 57.  Relations with many queries keep a table (rank_transr_most).
 #include <algorithm>
 #include <new>
 
@@ -793,7 +795,7 @@ static RrPlan rr_plan(const stx_config &cfg, int64_t nq)
     const int64_t slot_bytes = (int64_t)(cfg.rel_dim / 32) * (ks * 2048 + 4) + tiles * kAux * 4;
     p.slots = std::max((int64_t)1, std::min(occ, ((int64_t)96 << 20) / slot_bytes));
     // undecided pairs: room for one in 128 of the pairs and the blocks that wavefronts leave partly filled, 64 MiB at most
-    const int64_t blocks = (int64_t)((double)nq * (double)cfg.n_ent / (128. * kPairBlock)) + p.max_blocks * 16 + 256;
+    const int64_t blocks = (int64_t)((double)nq * (double)cfg.n_ent / (128. * kPairBlock)) + p.max_blocks * 2 + 5120;
     p.pair_blocks = std::min(blocks, ((int64_t)64 << 20) / (kPairBlock * (int64_t)sizeof(uint2)));
     p.q32 = take((size_t)nq * cfg.rel_dim * 4);
     p.qf = take((size_t)p.max_blocks * ks * 1024);
@@ -816,7 +818,7 @@ size_t rank_transr_bytes(const stx_config &cfg, int64_t nq)
 }
 
 template <int KS, int A>
-static void rr_go(stx_ctx *c, RrArgs f, const RrPlan &p, int64_t nq, const int32_t *counts, int32_t n_rel)
+static void rr_go(stx_ctx *c, RrArgs f, const RrPlan &p, const int32_t *counts, int32_t n_rel, int32_t most)
 {
     const int tiles = (f.n_ent + 31) / 32, kt = f.k / 32;
     const size_t lds_q = rr_query_lds(f.dim, f.k), lds_x = rr_exact_lds(f.k);
@@ -836,7 +838,7 @@ static void rr_go(stx_ctx *c, RrArgs f, const RrPlan &p, int64_t nq, const int32
         f.slot0 = slot;
         const int32_t b_begin = block;
         for (; r < n_rel && slot - f.slot0 < p.slots; ++r)
-            if (counts[r]) { ++slot; block += (counts[r] + 31) / 32; }
+            if (counts[r] && counts[r] <= most) { ++slot; block += (counts[r] + 31) / 32; }
         if (slot == f.slot0) break;
         f.slots = slot - f.slot0;
         const int etiles = f.first ? tiles : 0;
@@ -860,9 +862,10 @@ static void rr_go(stx_ctx *c, RrArgs f, const RrPlan &p, int64_t nq, const int32
                                    c->stream, f, slice);
             }
             {
-                // two rounds of the workgroups that fit the chip, eight tiles each at least
+                // Two rounds of the workgroups that fit the chip; 32 tiles each at least, as a wavefront's last pairs take a block of
+                // their own (50 queries x 200,000 at d = 256 in slices of eight: 3,128 blocks for 20,000 pairs)
                 const int64_t gx = (nb + 3) / 4, want = std::max((int64_t)1, (1024 + gx - 1) / gx);
-                const int slice = (int)std::max((int64_t)8, (tiles + want - 1) / want);
+                const int slice = (int)std::max((int64_t)32, (tiles + want - 1) / want);
                 ProfScope prof(c, "k_rr_sweep");
                 hipLaunchKernelGGL((k_rr_sweep<KS>), dim3((unsigned)gx, (unsigned)((tiles + slice - 1) / slice)), dim3(kThreads), 0,
                                    c->stream, f, slice);
@@ -881,11 +884,35 @@ static void rr_go(stx_ctx *c, RrArgs f, const RrPlan &p, int64_t nq, const int32
     }
 }
 
-bool rank_transr(stx_ctx *c, const stx_params *p, int64_t nq, int side, const RankGroups &g, void *work, size_t bytes, const int32_t *counts)
+// The rule between this and projected tables, in us as measured at 50 sizes (1,000 to 200,000 entities, widths of 32 to 256,
+// 1 to 1,350 relations, 1 to 59,071 queries): what a relation costs as a table, projected and packed, or as |M e|^2; what a
+// query costs more without a table (more pairs are undecided, and they are dearer); launches and dependent passes.
+// One relation, 20,000 queries x 14,500 entities, d = k = 128: 697 us with a table, 1,043 without; 237 relations: 5,222 and
+// 1,674; 4 queries of 4 relations x 9,028 at 96 x 256: 239 and 308, at 133,311 entities: 579 and 353.
+static double rr_table_us(const stx_config &c) { return (double)c.n_ent * c.rel_dim * (2. * c.dim / 90e6 + 10. / 5e6); }
+static double rr_norms_us(const stx_config &c) { return (double)c.n_ent * c.rel_dim * 16. * rr_steps(c.dim) * 6. / 500e6; }
+static double rr_query_us(const stx_config &c) { return 0.0008 + 0.4 * (double)c.n_ent / 500. * c.dim * c.rel_dim * 2. / 65e6; }
+constexpr double kRrLaunchUs = 28.;    // of a set of launches over projected tables
+int32_t rank_transr_most(const stx_config &c)
 {
-    if (c->cfg.dist != STX_L2 && c->cfg.dist != STX_L2_SQ) return false;
+    const double most = (kRrLaunchUs + rr_table_us(c) - rr_norms_us(c)) / rr_query_us(c);
+    return (int32_t)std::max(0., std::min(most, 2e9));
+}
+
+bool rank_transr(stx_ctx *c, const stx_params *p, int64_t nq, int side, const RankGroups &g, int tables, void *work, size_t bytes, const int32_t *counts)
+{
     const RrPlan pl = rr_plan(c->cfg, nq);
-    if (bytes < pl.total) return false;
+    double rels = 0., queries = 0., big = 0.;
+    for (int64_t r = 0; r < c->cfg.n_rel; ++r)
+        if (counts[r] && counts[r] <= g.most) {
+            rels += 1.;
+            queries += counts[r];
+            big += counts[r] > kRankBig ? 1. : 0.;         // (launches of its own)
+        }
+    const double with_tables = (big + ceil((rels - big) / tables)) * kRrLaunchUs + rels * rr_table_us(c->cfg);
+    const double without = 55. + 0.0008 * c->cfg.dim * c->cfg.rel_dim + (double)c->cfg.n_ent * c->cfg.dim * 10. / 4e6 +
+                           rels * rr_norms_us(c->cfg) + queries * rr_query_us(c->cfg);
+    if (bytes < pl.total || without >= with_tables) return false;
     char *w = (char *)work;
     RrArgs f{};
     f.E = p->ent; f.M = p->proj; f.R = p->rel;
@@ -900,7 +927,7 @@ bool rank_transr(stx_ctx *c, const stx_params *p, int64_t nq, int side, const Ra
     f.st = (RrState *)(w + pl.state);
     const bool two = c->cfg.rel_dim > 128;
 #define STX_RR(KS)                                                                                              \
-    case KS: if (two) rr_go<KS, 2>(c, f, pl, nq, counts, (int32_t)c->cfg.n_rel); else rr_go<KS, 1>(c, f, pl, nq, counts, (int32_t)c->cfg.n_rel); break
+    case KS: if (two) rr_go<KS, 2>(c, f, pl, counts, (int32_t)c->cfg.n_rel, g.most); else rr_go<KS, 1>(c, f, pl, counts, (int32_t)c->cfg.n_rel, g.most); break
     switch (rr_steps(c->cfg.dim)) {
         STX_RR(2);
         STX_RR(4);
