@@ -574,10 +574,10 @@ static stx_status run_backward(stx_ctx *ctx, const stx_incidence *inc, const stx
     }
     const SegFusedHost fh{p->ent, p->rel, (int32_t)ctx->cfg.n_ent, lr ? *lr : 0.f, 0};
     if (ctx->cfg.model == STX_TRANSH) {
-        // entity columns: signed sums of gx; relation columns: sums of gy (-> d_r) and of gw (-> w_r)
+        // entity columns: signed sums of gx; relation columns: sums of gy (-> d_r) and of gw (-> w_r), one row per positive
         // (both products in the same pair of launches)
         const SegSecondHost second{(int32_t)ent_end, (int32_t)inc->nnz, ctx->gbuf[2], lr ? nullptr : g->w_rows, p->w,
-                                   (ctx->cfg.flags & STX_FLAG_RENORM_W) ? 2 : 0};
+                                   (ctx->cfg.flags & STX_FLAG_RENORM_W) ? 2 : 0, inc->b};
         return launch_seg_reduce(ctx, inc, 0, inc->nnz, ctx->gbuf[0], ctx->gbuf[1], ent_end, dim, dim, rows, ctx->ld,
                                  false, lr ? &fh : nullptr, &second);
     }

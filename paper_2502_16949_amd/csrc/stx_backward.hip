@@ -142,6 +142,7 @@ struct SegSecond {
     float *out_rows, *partials;
     float *fused_table;        // FUSED: its columns all lie at or above n_split and update this table ...
     int fused_mode;            // ... in this mode
+    int32_t n_pos;             // > 0: in the relation columns, of both products, only rows below this are stored (and not zero)
 };
 
 // Entries whose source row is not stored but formed where it is summed (template parameter SRC of k_seg_reduce).
@@ -439,7 +440,9 @@ __global__ __launch_bounds__(kThreads, 8) void k_seg_formed(const FormedRecord *
 // 5 as 3, and TransR's dL/dM_r product comes along (its 128 registers still leave four workgroups on a CU, more
 // than such a batch gives this product).
 // THREADS: threads of a workgroup; with LPR it makes the number of chunks in a tile, and so the order of the sums.
-template <int LPR, int ITERS, bool PACKED, int CHUNK, bool FUSED, int RIDE, int SRC = SRC_STORED, int THREADS = kThreads>
+// SUMS: relation columns are summed from rows of positives alone (SegSecond::n_pos); a kernel of its own, as the test for it
+// costs the others 2 per cent.
+template <int LPR, int ITERS, bool PACKED, int CHUNK, bool FUSED, int RIDE, int SRC = SRC_STORED, int THREADS = kThreads, bool SUMS = false>
 __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && FUSED && RIDE != 4) ? 8 : 1) void k_seg_reduce(const int32_t *__restrict__ packed,
                                                          const int32_t *__restrict__ seg_id, int32_t e_begin,
                                                          int32_t e_end, const float *__restrict__ src_a,
@@ -503,9 +506,11 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
         }
         block -= sca.ntiles;
     }
+    int32_t sums_from = split;                             // SUMS: entries from here on
     if (block >= sec.first_block) {   // uniform in the workgroup
         block -= sec.first_block;
         e_begin = sec.e_begin; e_end = sec.e_end;
+        sums_from = e_begin;
         src_a = src_b = sec.src; split = sec.e_end;
         out_rows = sec.out_rows; partials = sec.partials;
         fu.table_b = sec.fused_table; fu.mode = sec.fused_mode;
@@ -656,6 +661,8 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
                     load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c1 * (uint32_t)ld_tab, d4, lig, va[u]);
                     if (SRC != SRC_SEMIRING + SR_ROTATE)
                         load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c2 * (uint32_t)ld_tab, d4, lig, vb[u]);
+                } else if (SUMS && ec0 + j0 + u >= sums_from && (int32_t)row >= sec.n_pos) {
+                    v[u].zero();
                 } else {   // entries before `split` read src_a, the rest src_b (entity vs relation columns)
                     load_row<LPR, ITERS>((ec0 + j0 + u < split ? src_a : src_b) + (uint64_t)row * (uint32_t)ld_src, d4, lig, v[u]);
                 }
@@ -977,11 +984,11 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
     const bool small = (e_end - e_begin) <= (1 << 20);
     const int tile = GROUPS * (small ? CH_SHORT : CH_LONG);
     const int ntiles1 = (e_end - e_begin + tile - 1) / tile;
-    SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
+    SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0};
     int ntiles = ntiles1;
     if (second && second->e_end > second->e_begin) {
         sec = SegSecond{ntiles1, second->e_begin, second->e_end, second->src, second->out_rows,
-                        c->partials + (int64_t)ntiles1 * 2 * ld_out, second->fused_table, second->fused_mode};
+                        c->partials + (int64_t)ntiles1 * 2 * ld_out, second->fused_table, second->fused_mode, second->n_pos};
         ntiles += (second->e_end - second->e_begin + tile - 1) / tile;
     }
     const FusedArgs fu = fused ? *fused : FusedArgs{nullptr, nullptr, 0, nullptr, nullptr, 0.f, 0, 0};
@@ -1035,17 +1042,19 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
               f_blocks = f_scat.ntiles + f_hist.ntiles + f_dm.blocks + f_emit.ntiles;
     // Wide rows (more than one float4 per lane) run as column slices of the one-float4 kernels: more rows in
     // flight per lane and ITERS times the workgroups.  The unit-length rescale needs whole rows.
+    const bool sums = sec.n_pos > 0 && !packed_src;        // (TransH)
     const bool whole_rows = fused && (fu.mode == 2 || sec.fused_mode == 2);
     if (ITERS > 1 && !whole_rows) {
         const dim3 grid((unsigned)ntiles, (unsigned)ITERS);
+#define STX_SLICED_R(P, CH, F, S)                                                                               \
+    hipLaunchKernelGGL((k_seg_reduce<LPR, 1, P, CH, F, 0, SRC_STORED, kThreads, S>), grid, dim3(kThreads), 0, c->stream, \
+                       inc->at_packed, inc->at_seg_id, e_begin, e_end, src_a, src_b, split, ld_src, width / 4,  \
+                       out_rows, ld_out, c->partials, fu, sec, no_segw, r_emit, r_scat, r_dm)
 #define STX_SLICED(P, CH, F)                                                                                    \
     do {                                                                                                        \
         {                                                                                                       \
             ProfScope prof(c, "k_seg_reduce");                                                                  \
-            hipLaunchKernelGGL((k_seg_reduce<LPR, 1, P, CH, F, 0>), grid, dim3(kThreads), 0, c->stream,         \
-                               inc->at_packed, inc->at_seg_id, e_begin, e_end, src_a, src_b, split, ld_src,     \
-                               width / 4, out_rows, ld_out, c->partials, fu, sec, no_segw, r_emit,    \
-                               r_scat, r_dm);                                                                   \
+            if (sums) STX_SLICED_R(P, CH, F, !P); else STX_SLICED_R(P, CH, F, false);                           \
         }                                                                                                       \
         if (ntiles > 1) {                                                                                       \
             ProfScope prof(c, "k_seg_fixup");                                                                   \
@@ -1059,13 +1068,20 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
         else            { if (small) STX_SLICED2(false, CH_SHORT); else STX_SLICED2(false, CH_LONG); }
 #undef STX_SLICED2
 #undef STX_SLICED
+#undef STX_SLICED_R
         return;
     }
 #define STX_SEG_R(P, CH, F, R)                                                                                  \
-    hipLaunchKernelGGL((k_seg_reduce<LPR, ITERS, P, CH, F, (F && ITERS == 1 && !(R == 5 && (P || LPR > 32))) ? R : 0>), \
+    do { if (sums && R != 5) STX_SEG_RS(P, CH, F, R, !P && R != 5); else STX_SEG_RS(P, CH, F, R, false); } while (0)
+#define STX_SEG_RS(P, CH, F, R, S)                                                                              \
+    hipLaunchKernelGGL((k_seg_reduce<LPR, ITERS, P, CH, F, (F && ITERS == 1 && !(R == 5 && (P || LPR > 32))) ? R : 0, SRC_STORED, kThreads, S>), \
                        dim3(ntiles + segw_blocks + r_blocks), dim3(kThreads), 0, c->stream, segw.args.pay,      \
                        segw.args.keys, e_begin, e_end, src_a, src_b, split, ld_src, width / 4,        \
                        out_rows, ld_out, c->partials, fu, sec, segw, r_emit, r_scat, r_dm)
+#define STX_SEG_0(P, CH, F, S)                                                                                  \
+    hipLaunchKernelGGL((k_seg_reduce<LPR, ITERS, P, CH, F, 0, SRC_STORED, kThreads, S>), dim3(ntiles), dim3(kThreads), 0, \
+                       c->stream, inc->at_packed, inc->at_seg_id, e_begin, e_end, src_a, src_b, split, ld_src,  \
+                       width / 4, out_rows, ld_out, c->partials, fu, sec, no_segw, r_emit, r_scat, r_dm)
 #define STX_SEG_F(CH, F, R)                                                                                     \
     hipLaunchKernelGGL((k_seg_fixup<LPR, ITERS, CH, F, (F && ITERS == 1 && !(R == 3 && LPR > 32)) ? R : 0>), dim3(ntiles + f_blocks), \
                        dim3(kThreads), 0, c->stream, inc->at_packed, inc->at_seg_id, inc->at_seg_ptr, e_begin,  \
@@ -1079,11 +1095,8 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
             else if (F && ITERS == 1 && raw_now && r_emit.ntiles && r_emit.args.rc.cur) STX_SEG_R(P, CH, F, 4); \
             else if (F && ITERS == 1 && raw_now && r_emit.ntiles) STX_SEG_R(P, CH, F, 2);                       \
             else if (F && ITERS == 1 && raw_now) STX_SEG_R(P, CH, F, 1);                                        \
-            else                                                                                                \
-                hipLaunchKernelGGL((k_seg_reduce<LPR, ITERS, P, CH, F, 0>), dim3(ntiles), dim3(kThreads), 0,    \
-                                   c->stream, inc->at_packed, inc->at_seg_id, e_begin, e_end, src_a, src_b,     \
-                                   split, ld_src, width / 4, out_rows, ld_out, c->partials, fu, sec,  \
-                                   no_segw, r_emit, r_scat, r_dm);                                              \
+            else if (sums) STX_SEG_0(P, CH, F, !P);                                                             \
+            else STX_SEG_0(P, CH, F, false);                                                                    \
         }                                                                                                       \
         if (ntiles > 1) {                                                                                       \
             ProfScope prof(c, "k_seg_fixup");                                                                   \
@@ -1101,6 +1114,8 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
 #undef STX_SEG2
 #undef STX_SEG
 #undef STX_SEG_F
+#undef STX_SEG_0
+#undef STX_SEG_RS
 #undef STX_SEG_R
 }
 
@@ -1132,7 +1147,7 @@ static void seg_slices(stx_ctx *c, const stx_incidence *inc, const float *src, i
     const int d4 = width / 4, ntiles = (nnz + TILE - 1) / TILE;
     const dim3 grid((unsigned)ntiles, (unsigned)((d4 + LPR - 1) / LPR)), wide((unsigned)ntiles, (unsigned)((d4 + 63) / 64));
     const FusedArgs fu = fused ? *fused : FusedArgs{};
-    const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
+    const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0};
 #define STX_SLICES_R(F, L, T, GRID)                                                                             \
     hipLaunchKernelGGL((k_seg_reduce<L, 1, false, CH, F, 0, SRC_STORED, T>), GRID, dim3(T), 0, c->stream,       \
                        inc->at_packed, inc->at_seg_id, 0, nnz, src, src, nnz, width, d4, out_rows, ld_out,      \
@@ -1187,7 +1202,7 @@ static void semiring_t_go(stx_ctx *c, const stx_incidence *inc, const float *X, 
     const dim3 grid((unsigned)ntiles, (unsigned)ITERS);    // wide rows: column slices of one float4 per lane
     const int d4 = c->cfg.dim / 4;
     const FusedArgs fu{};
-    const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
+    const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0};
     const SrcArgs sr{inc->a_colidx, X, gz};
 #define STX_SR_T(K, CH)                                                                                         \
     hipLaunchKernelGGL((k_seg_reduce<LPR, 1, false, CH, false, 0, SRC_SEMIRING + K>), grid, dim3(kThreads), 0,  \
@@ -1228,7 +1243,7 @@ stx_status launch_seg_formed(stx_ctx *c, const stx_incidence *inc, const stx_par
     const int d4 = c->cfg.dim / 4, ntiles = (nnz + TILE - 1) / TILE, nslices = (d4 + LPR - 1) / LPR;
     const dim3 grid((unsigned)ntiles, (unsigned)nslices);
     const FusedArgs fu{};
-    const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0};
+    const SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0};
     const uint32_t x_bytes = (uint32_t)(c->cfg.n_ent + c->cfg.n_rel) * (uint32_t)c->cfg.dim * 4u;   // (formed_rows: 96 MiB at most)
 #define STX_FORMED(D)                                                                                           \
     hipLaunchKernelGGL((k_seg_formed<D>), dim3(((unsigned)ntiles * (unsigned)nslices + 7u) / 8u * 8u), dim3(kThreads), 0, \

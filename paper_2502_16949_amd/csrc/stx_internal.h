@@ -345,6 +345,7 @@ struct SegSecondHost {
     float *out_rows;
     float *fused_table;
     int fused_mode;
+    int32_t n_pos;             // relation columns (of both products): only the first n_pos rows are stored, the others are zero
 };
 struct SegFusedHost {
     float *table, *table_b;

@@ -443,7 +443,7 @@ __device__ inline uint32_t rr_lds_at(const void *p) { return (uint32_t)(uintptr_
 // rows of the product are outputs, columns (lanes) entities, so that the squares add up in the lane.  Three products of
 // split operands (the low ones' own is left out).  Bound by the matrix cores and the LDS reads that feed them.
 template <int KS, int EF>
-__global__ __launch_bounds__(kThreads, 2) void k_rr_norms(RrArgs f, int slice)
+__global__ __launch_bounds__(kThreads, KS == 16 ? 1 : 2) void k_rr_norms(RrArgs f, int slice)
 {
     constexpr int CK = 2 * KS, NB = 3, LW = CK / 4;        // kilobytes of a chunk, chunks in LDS, a wavefront's loads
     __shared__ __align__(1024) uint4 s_ring[NB][CK][64];
@@ -539,7 +539,7 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_norms(RrArgs f, int slice)
 // four blocks of queries, and every wavefront fetches its own relation's numbers along.  A wavefront's undecided pairs are
 // of one relation and leave in blocks for k_rr_pairs.
 template <int KS>
-__global__ __launch_bounds__(kThreads, 2) void k_rr_sweep(RrArgs f, int slice)
+__global__ __launch_bounds__(kThreads, KS <= 4 ? 1 : 2) void k_rr_sweep(RrArgs f, int slice)
 {
     constexpr int TPC = KS >= 12 ? 1 : KS >= 6 ? 2 : 16 / KS, CK = TPC * KS, NB = 4, LW = CK / 4, LA = TPC > 4 ? TPC / 4 : 1;
     static_assert(CK % 4 == 0, "whole chunks");
