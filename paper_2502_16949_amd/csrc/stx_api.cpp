@@ -585,16 +585,18 @@ static stx_status run_backward(stx_ctx *ctx, const stx_incidence *inc, const stx
     // and relation columns sum gy (width rel_dim)
     stx_status s = launch_transr_backward(ctx, inc, p, g, lr);
     if (s != STX_OK) return s;
-    // (the first of these launches takes the dL/dM_r product along or launches it)
+    // (the first of these launches takes the dL/dM_r product along or launches it; the fused forward kernel left one row
+    // of dL/dy per positive)
+    const SegSecondHost sums{0, 0, nullptr, nullptr, nullptr, 0, ctx->tr_fused_inc == inc ? inc->b : 0};
     if (dim == ctx->cfg.rel_dim) {   // rows of equal width: one product over all columns, as for TransH
         s = launch_seg_reduce(ctx, inc, 0, inc->nnz, ctx->gbuf[1], ctx->gbuf[0], ent_end, dim, dim, rows, ctx->ld,
-                              false, lr ? &fh : nullptr);
+                              false, lr ? &fh : nullptr, &sums);
     } else {
         s = launch_seg_reduce(ctx, inc, 0, ent_end, ctx->gbuf[1], ctx->gbuf[1], ent_end, dim, dim, rows, ctx->ld, false,
                               lr ? &fh : nullptr);
         if (s != STX_OK) return s;
-        s = launch_seg_reduce(ctx, inc, ent_end, inc->nnz, ctx->gbuf[0], ctx->gbuf[0], inc->nnz, ctx->cfg.rel_dim,
-                              ctx->cfg.rel_dim, rows, ctx->ld, false, lr ? &fh : nullptr);
+        s = launch_seg_reduce(ctx, inc, ent_end, inc->nnz, ctx->gbuf[0], ctx->gbuf[0], ent_end, ctx->cfg.rel_dim,
+                              ctx->cfg.rel_dim, rows, ctx->ld, false, lr ? &fh : nullptr, &sums);
     }
     if (s != STX_OK) return s;
     return launch_transr_dm_late(ctx);   // (nothing left to do unless no launch above ran)

@@ -801,11 +801,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
     // Column slices of LPR ITERS float4, as in k_seg_reduce, dealt to the workgroups of blockIdx.y in turn: most tiles end no
     // crossing run, so a workgroup for each of a wide row's slices mostly starts to find that out once more (16 slices of
     // 9,216 tiles: 105 us as 16 workgroups a tile, 65 as four).  Launches with a ride hold whole rows.
-    for (int c4 = RIDE ? 0 : (int)blockIdx.y * ITERS * LPR; c4 < d4_all; c4 += (int)gridDim.y * ITERS * LPR) {
-        if (RIDE == 0) {
-            d4 = min(ITERS * LPR, d4_all - c4);
-            if (c4 != (int)blockIdx.y * ITERS * LPR) __syncthreads();   // the slice before this one has been read out of LDS
-        }
+    auto slice = [&](int c4) {
         FusedArgs fs = fu;
         if (fs.table) fs.table += 4 * c4;
         if (fs.table_b) fs.table_b += 4 * c4;
@@ -848,7 +844,15 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
             if constexpr (FUSED) apply_update<LPR, ITERS>(fused_row(fs, col, ld_tab), d4, lig, xrow, acc, fu.lr, fu.mode, fu.stream);
             else store_row<LPR, ITERS>(out_rows + 4 * c4 + (int64_t)seg * ld_out, d4, lig, acc);
         }
-        if (RIDE) break;
+    };
+    if constexpr (RIDE != 0) {
+        slice(0);
+    } else {
+        for (int c4 = (int)blockIdx.y * ITERS * LPR; c4 < d4_all; c4 += (int)gridDim.y * ITERS * LPR) {
+            d4 = min(ITERS * LPR, d4_all - c4);
+            if (c4 != (int)blockIdx.y * ITERS * LPR) __syncthreads();   // the slice before this one has been read out of LDS
+            slice(c4);
+        }
     }
 }
 
@@ -986,6 +990,7 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
     const int ntiles1 = (e_end - e_begin + tile - 1) / tile;
     SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0};
     int ntiles = ntiles1;
+    if (second) sec.n_pos = second->n_pos;
     if (second && second->e_end > second->e_begin) {
         sec = SegSecond{ntiles1, second->e_begin, second->e_end, second->src, second->out_rows,
                         c->partials + (int64_t)ntiles1 * 2 * ld_out, second->fused_table, second->fused_mode, second->n_pos};
@@ -1042,7 +1047,7 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
               f_blocks = f_scat.ntiles + f_hist.ntiles + f_dm.blocks + f_emit.ntiles;
     // Wide rows (more than one float4 per lane) run as column slices of the one-float4 kernels: more rows in
     // flight per lane and ITERS times the workgroups.  The unit-length rescale needs whole rows.
-    const bool sums = sec.n_pos > 0 && !packed_src;        // (TransH)
+    const bool sums = sec.n_pos > 0 && !packed_src;        // (TransH, TransR)
     const bool whole_rows = fused && (fu.mode == 2 || sec.fused_mode == 2);
     if (ITERS > 1 && !whole_rows) {
         const dim3 grid((unsigned)ntiles, (unsigned)ITERS);
@@ -1072,7 +1077,7 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
         return;
     }
 #define STX_SEG_R(P, CH, F, R)                                                                                  \
-    do { if (sums && R != 5) STX_SEG_RS(P, CH, F, R, !P && R != 5); else STX_SEG_RS(P, CH, F, R, false); } while (0)
+    do { if (sums) STX_SEG_RS(P, CH, F, R, !P); else STX_SEG_RS(P, CH, F, R, false); } while (0)
 #define STX_SEG_RS(P, CH, F, R, S)                                                                              \
     hipLaunchKernelGGL((k_seg_reduce<LPR, ITERS, P, CH, F, (F && ITERS == 1 && !(R == 5 && (P || LPR > 32))) ? R : 0, SRC_STORED, kThreads, S>), \
                        dim3(ntiles + segw_blocks + r_blocks), dim3(kThreads), 0, c->stream, segw.args.pay,      \

@@ -333,7 +333,7 @@ stx_status launch_read_sectors(stx_ctx *, const void *src, int64_t n_slots, int 
 // before `split` read src_a, the others src_b (both with ld_src floats per row, `width` of them used).
 // packed_src: src_a holds packed L1-kind sign records (see packed_stride), ld_src is the record size in bytes,
 // and src_b the rows' coefficients.
-// second: another product of the same row width over the entries [e_begin, e_end), all reading `src`, that
+// second (may be empty): another product of the same row width over the entries [e_begin, e_end), all reading `src`, that
 // runs in the same two launches (its workgroups follow the first product's).
 // fused: no gradient row is written; the table row of the column (rows of `width` floats; `table` for
 // columns below n_split, row column - n_split of `table_b` for the others) becomes row - lr * gradient

@@ -429,7 +429,7 @@ struct FusedArgs {
     const float *E, *Rv;
     const uint16_t *Mf, *Mg;     // operand-order copies of M_r: forward (rows a, reduction over j), GX (rows j, reduction over a)
     uint16_t *xt, *gyt;          // per item: the transposed 64-entry tiles of x and of dL/dy for the dM product
-    float *gy, *gx;              // rows x k: dL/dy;  rows x d: dL/dx
+    float *gy, *gx;              // rows x k: dL/dy, summed over every positive and its negatives;  rows x d: dL/dx
     float *scores, *loss_partials;
     int d, k;
     int32_t kneg;                // negatives per positive; 1 + kneg divides 64
@@ -612,7 +612,8 @@ __global__ __launch_bounds__(kThreads, 3) void k_transr_fused(FusedArgs p, EmitA
         if (tid == 0) p.loss_partials[block] = hs;
     }
     __syncthreads();
-    // ---- dL/dy: to memory in fp32, and as bfloat16 into the operand tile (the products over x are done with it)
+    // ---- dL/dy: as bfloat16 into the operand tile (the products over x are done with it), and to memory in fp32 as one sum
+    // over a positive and its negatives, in the positive's row: their entries in the relation's column add to one row
     {
         const int stride = k + kLdsPad, q4 = k >> 2, total = 64 * q4;
         for (int g = tid; g < total; g += kThreads) {
@@ -622,7 +623,15 @@ __global__ __launch_bounds__(kThreads, 3) void k_transr_fused(FusedArgs p, EmitA
                 const float4 y = *reinterpret_cast<const float4 *>(s_y + i * kYS + c4);
                 const float cs = s_cs[i];
                 gy = make_float4(dterm<DIST>(y.x, cs), dterm<DIST>(y.y, cs), dterm<DIST>(y.z, cs), dterm<DIST>(y.w, cs));
-                st4(p.gy + (int64_t)s_row[i] * k + c4, gy);
+                if (i < Pn) {
+                    float4 sum = gy;
+                    for (int ns = Pn + i * p.kneg; ns < Pn + (i + 1) * p.kneg; ++ns) {
+                        const float4 yn = *reinterpret_cast<const float4 *>(s_y + ns * kYS + c4);
+                        const float cn = s_cs[ns];
+                        sum = add4(sum, make_float4(dterm<DIST>(yn.x, cn), dterm<DIST>(yn.y, cn), dterm<DIST>(yn.z, cn), dterm<DIST>(yn.w, cn)));
+                    }
+                    st4(p.gy + (int64_t)s_row[i] * k + c4, sum);
+                }
             }
             *reinterpret_cast<uint2 *>(s_a + i * stride + c4) = make_uint2(pack2(gy.x, gy.y), pack2(gy.z, gy.w));
         }
