@@ -24,6 +24,7 @@ if ROOT not in sys.path:
 
 HBM_PEAK_GBS = 8000.0
 MFMA_BF16_PEAK_TFLOPS = 2500.0
+MFMA_I8_PEAK_TOPS = 2 * MFMA_BF16_PEAK_TFLOPS
 # kernels that run TransR products on the matrix cores, and how many products of 2*rows*d*k flops each runs
 TRANSR_PRODUCTS = {"k_transr_fused": 2, "k_transr_project": 1, "k_transr_gx": 1, "k_transr_dm": 1}
 
@@ -54,11 +55,11 @@ TRAFFIC_BYTES = {("toruse", "k_seg_reduce", True): 1133.94e6 + 623.18e6,
                  ("mid", "k_seg_reduce", "rides"): 28.04e6 + 17.01e6,
                  ("mid", "k_fwd_scatter", "rides"): 27.44e6 + 9.25e6,
                  ("mid", "k_seg_fixup", "rides"): 3.67e6 + 0.42e6,
-                 ("transh", "k_seg_reduce", "rides"): 142.54e6 + 14.81e6,
-                 ("transh", "k_fwdh_scatter", "rides"): 34.67e6 + 105.22e6,
-                 ("transh", "k_seg_fixup", "rides"): 4.06e6 + 0.48e6,
-                 ("transr", "k_transr_fused", "rides"): 40.20e6 + 52.83e6,
-                 ("transr", "k_seg_reduce", "rides"): 89.66e6 + 31.35e6,
+                 ("transh", "k_seg_reduce", "rides"): 110.08e6 + 14.79e6,
+                 ("transh", "k_fwdh_scatter", "rides"): 32.64e6 + 72.46e6,
+                 ("transh", "k_seg_fixup", "rides"): 4.08e6 + 0.48e6,
+                 ("transr", "k_transr_fused", "rides"): 40.19e6 + 44.59e6,
+                 ("transr", "k_seg_reduce", "rides"): 81.35e6 + 31.34e6,
                  ("transr", "k_seg_fixup", "rides"): 9.78e6 + 1.26e6}
 
 
@@ -136,19 +137,22 @@ def kernel_work(wl, kernel, rows, touched, fused=False, rides=False, segw=False)
     if kernel == "k_fwd_scatter":      # the same forward pass and one scatter pass of the sort in one launch
         return rows * (3 * row + 12 + grow + 4) + nnz * 16, "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_fwdh_scatter":     # TransH forward (below) and one scatter pass
-        return rows * (2 * row + 2 * row / (1 + wl.n_neg) + 12 + 3 * row + 4) + nnz * 16, "GB/s", "hbm", HBM_PEAK_GBS
+        return rows * (3 * row + 4 * row / (1 + wl.n_neg) + 12 + 4) + nnz * 16, "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_forward_stacked":   # TransR: y row in, dL/dy row out, score out
         return rows * (2 * 4 * wl.rel_dim + 4), "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_forward_transh":
-        # 2 entity rows per row, w_r and d_r once per positive, 12 B of ids in; gx, gy, gw rows + score out
-        return rows * (2 * row + 2 * row / (1 + wl.n_neg) + 12 + 3 * row + 4), "GB/s", "hbm", HBM_PEAK_GBS
+        # 2 entity rows and 12 B of ids per row, w_r and d_r per positive in; a gx row + score, and per positive the sums of
+        # gy and of gw out
+        return rows * (3 * row + 4 * row / (1 + wl.n_neg) + 12 + 4), "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_seg_reduce":
         # one source row + 4 B packed entry per sorted entry in, one row per column out, over all 3*rows entries
-        if wl.model == "transh":   # both products (all entries -> dE, d(d_r); relation entries -> dw_r) in one launch
+        if wl.model == "transh":   # both products (all entries -> dE, d(d_r); relation entries -> dw_r) in one launch; the
+            # relation columns read a row per positive
             out_rows = (touched + min(wl.n_rel, rows)) * row * (2 if fused else 1)   # fused: table row in, table row out
-            return nnz * (row + 4) + rows * (row + 4) + out_rows, "GB/s", "hbm", HBM_PEAK_GBS
-        if wl.model == "transr":   # one launch when dim == rel_dim
-            return nnz * (row + 4) + touched * row * (2 if fused else 1), "GB/s", "hbm", HBM_PEAK_GBS
+            return nnz * 4 + rows * (4 + 2 * row + 2 * row / (1 + wl.n_neg)) + out_rows, "GB/s", "hbm", HBM_PEAK_GBS
+        if wl.model == "transr":   # one launch when dim == rel_dim; behind k_transr_fused the relation columns read a row per positive
+            sums = wl.dim <= 128 and wl.rel_dim <= 128 and 64 % (1 + wl.n_neg) == 0
+            return nnz * 4 + rows * row * (2 + (1 / (1 + wl.n_neg) if sums else 1)) + touched * row * (2 if fused else 1), "GB/s", "hbm", HBM_PEAK_GBS
         if fused and wl.model in ("transe", "toruse"):
             # fused update: the table row is read and written where the gradient row would have been written
             return nnz * (grow + 4) + touched * 2 * row, "GB/s", "hbm", HBM_PEAK_GBS
@@ -161,8 +165,8 @@ def kernel_work(wl, kernel, rows, touched, fused=False, rides=False, segw=False)
         return nnz * (3 * row + 16) + touched * row, "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_forward_stacked_formed":   # the rows' coefficients in place of their dL/dx rows
         return rows * (3 * row + 12 + 4 + 4), "GB/s", "hbm", HBM_PEAK_GBS
-    if kernel == "k_seg_reduce_formed":  # x formed again: the entry's two other table rows and its record in, the
-        return nnz * (2 * row + 20) + touched * 2 * row, "GB/s", "hbm", HBM_PEAK_GBS    # column's own row once
+    if kernel == "k_seg_reduce_formed":  # table rows in and gradient rows out once, 16 B an entry (two more rows an active entry: L2)
+        return nnz * 16 + touched * 2 * row, "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_scatter":
         return nnz * 16, "GB/s", "hbm", HBM_PEAK_GBS      # key + payload in, key + payload out
     # TransR's three products: 2*d*k flop per row against ~2 KB of row traffic is ~20 flop per byte, far left of
@@ -170,8 +174,9 @@ def kernel_work(wl, kernel, rows, touched, fused=False, rides=False, segw=False)
     # fp32 rows, the fp32 rows written, the bf16 transposed tiles, and the bf16 copy of M_r once per relation.
     nrel = min(wl.n_rel, rows)
     if kernel == "k_transr_fused":     # forward product, distances, hinge and GX product on one staged tile:
-        # h and t rows and 12 B of ids in; dL/dy row, dL/dx row, both bf16 tiles and the score out; both copies of M_r
-        return (rows * (2 * row + 12 + 4 * wl.rel_dim + row + 2 * wl.dim + 2 * wl.rel_dim + 4)
+        # h and t rows and 12 B of ids in; dL/dx row, both bf16 tiles and the score, and per positive the sum of dL/dy out; both
+        # copies of M_r
+        return (rows * (2 * row + 12 + 4 * wl.rel_dim / (1 + wl.n_neg) + row + 2 * wl.dim + 2 * wl.rel_dim + 4)
                 + nrel * 4 * wl.dim * wl.rel_dim), "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_transr_project":   # h and t rows, 12 B of ids, y row out, x tile out
         return rows * (2 * row + 12 + 4 * wl.rel_dim + 2 * wl.dim) + nrel * 2 * wl.dim * wl.rel_dim, "GB/s", "hbm", HBM_PEAK_GBS
@@ -245,8 +250,10 @@ def bench_rank(args, wl, dev):
     params = B.Params(*(None if tabs.get(k) is None else torch.from_numpy(tabs[k]).to(dev) for k in ("ent", "rel", "w", "proj")))
     need = B.stx_rank_work_bytes(ctx, nq)
     work = torch.empty(need + 256, dtype=torch.uint8, device=dev) if need else None
-    # sweeps behind the filter run other kernels: fixed-point sums for the L1 kinds, the matrix cores for the L2 kinds
-    rank_kernel = ("k_rank_h" if transh else "k_rank_mfma" if wl.dist in ("l2", "l2_sq") else
+    # sweeps behind the filter run other kernels: fixed-point sums for the L1 kinds, the matrix cores for the L2 kinds (rows of
+    # more than 256 floats as bytes; TransR: |M_r e|^2, the largest of several kernels)
+    rank_kernel = ("k_rank_h" if transh else "k_rr_norms" if transr and wl.dist in ("l2", "l2_sq") else
+                   ("k_rank_wide" if wl.dim > 256 else "k_rank_mfma") if wl.dist in ("l2", "l2_sq") else
                    "k_rank_sad" if wl.dist in ("l1", "torus_l1") and not transr else "k_rank")
     hd, rd, td = (torch.from_numpy(a).to(dev) for a in (h, r, t))
     ts = torch.empty(2, nq, dtype=torch.float32, device=dev)
@@ -277,6 +284,14 @@ def bench_rank(args, wl, dev):
     if rank_kernel == "k_rank_mfma":
         per, peak, unit, bound = 2, MFMA_BF16_PEAK_TFLOPS, "TFLOP/s", "mfma"
         note = "a multiply and an add per query x candidate x element on the fp16 matrix cores (dense peak)"
+    elif rank_kernel == "k_rank_wide":
+        per, peak, unit, bound = 6, MFMA_I8_PEAK_TOPS, "Tops/s", "mfma"
+        note = "three byte products per query x candidate x element on the matrix cores (dense peak)"
+    elif rank_kernel == "k_rr_norms":
+        elems, per = float(len(np.unique(r))) * wl.n_ent * wl.dim * wl.rel_dim, 6
+        peak, unit, bound = MFMA_BF16_PEAK_TFLOPS, "TFLOP/s", "mfma"
+        note = ("three fp16 products per relation x entity x element of its matrix (dense peak); the few relations with so "
+                "many queries that they keep a projected table are counted, too")
     elif rank_kernel == "k_rank_sad":
         per, peak, unit, bound = (1 if wl.dist == "torus_l1" else 0.5), VALU_OPS_PEAK_T / 2, "Tops/s", "alu"
         note = ("one v_sad_u16 per two elements of a query x candidate" + (", after a subtraction" if per == 1 else "") +
@@ -595,8 +610,8 @@ class Job:
         if e["traffic"] and us > 0:
             e["achieved_traffic"] = round(e["traffic"] / (us * 1e-6) / 1e9, 1)
         if formed and kname == "k_seg_reduce":
-            e["note"] = ("rows of dL/dx formed where they are summed: nearly all of these bytes come from the L2 caches, which "
-                         "hold the 64-float slice of the table that is being read")
+            e["note"] = ("rows of dL/dx formed where they are summed, two table rows for every entry of an active pair, out of the L2 "
+                         "caches, whose rate bounds the kernel; the bytes here are those that memory has to move")
         if ach > peak and kname in ("k_forward_stacked", "k_fwd_scatter"):
             # the algorithmic figure counts three gathered table rows per matrix row; the kernel requests a positive's
             # rows once for all of its negatives and repeated rows come from the caches
