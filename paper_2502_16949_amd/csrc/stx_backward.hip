@@ -201,14 +201,15 @@ __device__ inline void apply_update(float *__restrict__ row, int d4, int lig, co
 // Stitches the chunk-crossing runs of a tile of GROUPS chunks, each in chunk order and by a group of its own: the group in
 // whose chunk a run ends adds up its pieces, from the chunk in which the run began (or from the tile's first, for a run that
 // came in from an earlier workgroup).  One group walking all chunks took 250 cycles per chunk, 8,000 at 32 groups.
-// s_x, s_col_last (FUSED): table row and column of the run that leaves each chunk to the right.
+// info: the flags of this group's chunk (read back from s_info they would cost every workgroup an LDS round trip: 0.1 us of a
+// step of 20).  s_x, s_col_last (FUSED): table row and column of the run that leaves each chunk to the right.
 template <int LPR, int ITERS, int GROUPS, bool FUSED>
-__device__ inline void stitch_runs(const float (*s_part)[2][ITERS * LPR * 4], const int32_t *s_info, const int32_t *s_seg_last,
+__device__ inline void stitch_runs(const int info, const float (*s_part)[2][ITERS * LPR * 4], const int32_t *s_info, const int32_t *s_seg_last,
                                    const float (*s_x)[FUSED ? ITERS * LPR * 4 : 4], const int32_t *s_col_last, float *my_part,
                                    float *out_rows, int ld_out, int d4, int ld_tab, const FusedArgs &fu)
 {
     const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
-    const int linfo = (int)(threadIdx.x & 63) < GROUPS ? s_info[threadIdx.x & 63] : 0, info = s_info[grp];
+    const int linfo = (int)(threadIdx.x & 63) < GROUPS ? s_info[threadIdx.x & 63] : 0;
     const uint64_t m_cont = __ballot((linfo & FIRST_CONT) != 0), m_last = __ballot((linfo & HAS_LAST) != 0);
     // pieces of the run that reaches chunk g, oldest first; returns the chunk it began in, -1: an earlier workgroup's
     auto run_sum = [&](int g, uint64_t before, Acc<ITERS> &cur) {
@@ -425,7 +426,7 @@ __global__ __launch_bounds__(kThreads, 8) void k_seg_formed(const FormedRecord *
     }
     __syncthreads();
     const int c4 = slice * LPR;
-    stitch_runs<LPR, 1, CHUNKS, false>(s_part, s_info, s_seg_last, nullptr, nullptr, partials + (int64_t)block * 2 * ld_out + 4 * c4,
+    stitch_runs<LPR, 1, CHUNKS, false>(s_info[threadIdx.x / LPR], s_part, s_info, s_seg_last, nullptr, nullptr, partials + (int64_t)block * 2 * ld_out + 4 * c4,
                                        out_rows + 4 * c4, ld_out, min(LPR, dim / 4 - c4), dim, FusedArgs{});
 }
 
@@ -715,7 +716,7 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
     if (lig == 0) s_info[grp] = info;
     __syncthreads();
 
-    stitch_runs<LPR, ITERS, GROUPS, FUSED>(s_part, s_info, s_seg_last, s_x, s_col_last, partials + (int64_t)block * 2 * ld_out,
+    stitch_runs<LPR, ITERS, GROUPS, FUSED>(info, s_part, s_info, s_seg_last, s_x, s_col_last, partials + (int64_t)block * 2 * ld_out,
                                            out_rows, ld_out, d4, ld_tab, fu);
 }
 
