@@ -201,15 +201,15 @@ __device__ inline void apply_update(float *__restrict__ row, int d4, int lig, co
 // Stitches the chunk-crossing runs of a tile of GROUPS chunks, each in chunk order and by a group of its own: the group in
 // whose chunk a run ends adds up its pieces, from the chunk in which the run began (or from the tile's first, for a run that
 // came in from an earlier workgroup).  One group walking all chunks took 250 cycles per chunk, 8,000 at 32 groups.
-// info: the flags of this group's chunk (read back from s_info they would cost every workgroup an LDS round trip: 0.1 us of a
-// step of 20).  s_x, s_col_last (FUSED): table row and column of the run that leaves each chunk to the right.
-template <int LPR, int ITERS, int GROUPS, bool FUSED>
-__device__ inline void stitch_runs(const int info, const float (*s_part)[2][ITERS * LPR * 4], const int32_t *s_info, const int32_t *s_seg_last,
+// s_x, s_col_last (FUSED): table row and column of the run that leaves each chunk to the right.
+// OWN: the group holds its chunk's flags (own_info); else they are read back from s_info, as the flags of the others are.
+template <int LPR, int ITERS, int GROUPS, bool FUSED, bool OWN>
+__device__ inline void stitch_runs(const int own_info, const float (*s_part)[2][ITERS * LPR * 4], const int32_t *s_info, const int32_t *s_seg_last,
                                    const float (*s_x)[FUSED ? ITERS * LPR * 4 : 4], const int32_t *s_col_last, float *my_part,
                                    float *out_rows, int ld_out, int d4, int ld_tab, const FusedArgs &fu)
 {
     const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
-    const int linfo = (int)(threadIdx.x & 63) < GROUPS ? s_info[threadIdx.x & 63] : 0;
+    const int linfo = (int)(threadIdx.x & 63) < GROUPS ? s_info[threadIdx.x & 63] : 0, info = OWN ? own_info : s_info[grp];
     const uint64_t m_cont = __ballot((linfo & FIRST_CONT) != 0), m_last = __ballot((linfo & HAS_LAST) != 0);
     // pieces of the run that reaches chunk g, oldest first; returns the chunk it began in, -1: an earlier workgroup's
     auto run_sum = [&](int g, uint64_t before, Acc<ITERS> &cur) {
@@ -426,7 +426,7 @@ __global__ __launch_bounds__(kThreads, 8) void k_seg_formed(const FormedRecord *
     }
     __syncthreads();
     const int c4 = slice * LPR;
-    stitch_runs<LPR, 1, CHUNKS, false>(s_info[threadIdx.x / LPR], s_part, s_info, s_seg_last, nullptr, nullptr, partials + (int64_t)block * 2 * ld_out + 4 * c4,
+    stitch_runs<LPR, 1, CHUNKS, false, false>(0, s_part, s_info, s_seg_last, nullptr, nullptr, partials + (int64_t)block * 2 * ld_out + 4 * c4,
                                        out_rows + 4 * c4, ld_out, min(LPR, dim / 4 - c4), dim, FusedArgs{});
 }
 
@@ -716,14 +716,18 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
     if (lig == 0) s_info[grp] = info;
     __syncthreads();
 
-    stitch_runs<LPR, ITERS, GROUPS, FUSED>(info, s_part, s_info, s_seg_last, s_x, s_col_last, partials + (int64_t)block * 2 * ld_out,
+    stitch_runs<LPR, ITERS, GROUPS, FUSED, true>(info, s_part, s_info, s_seg_last, s_x, s_col_last, partials + (int64_t)block * 2 * ld_out,
                                            out_rows, ld_out, d4, ld_tab, fu);
 }
 
 // RIDE: 1 the first scatter pass of the next batch's sort comes along, 2 its histogram pass of the second digit,
 // 3 as 2, and the sums of TransR's partial dL/dM_r matrices come along, 4 the first kernel of the next batch's
 // build when that sort is a large one (nothing after this launch reads the A arrays it overwrites).
-template <int LPR, int ITERS, int CHUNK, bool FUSED, int RIDE>
+// MANY: a workgroup takes column slices of LPR float4 in turn, from blockIdx.y on: most tiles end no crossing run, so a
+// workgroup for each of a wide row's slices mostly starts to find that out once more (16 slices of 9,216 tiles: 105 us as 16
+// workgroups a tile, 65 as four).  A kernel of its own: the loop costs the others registers (four float4 per lane: 102 and 132
+// with the update fused, four and three wavefronts per SIMD; 65 and 110 without, seven and four).
+template <int LPR, int ITERS, int CHUNK, bool FUSED, int RIDE, bool MANY = false>
 __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restrict__ packed,
                                                         const int32_t *__restrict__ seg_id,
                                                         const int32_t *__restrict__ seg_ptr, int32_t e_begin,
@@ -773,7 +777,17 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
         out_rows = sec.out_rows; partials = sec.partials;
         fu.table_b = sec.fused_table; fu.mode = sec.fused_mode;
     }
-    const int ld_tab = d4 * 4, d4_all = d4;
+    const int ld_tab = d4 * 4;
+    // (Launches with a ride hold whole rows, but a step of 1,024 positives at d = 32 takes 19.47 us without this test in them
+    // and 19.31 with it.)
+    if (RIDE != 0 && gridDim.y > 1) {
+        const int c4 = (int)blockIdx.y * LPR;
+        d4 = min(LPR, d4 - c4);
+        if (out_rows) out_rows += 4 * c4;
+        partials += 4 * c4;
+        if (fu.table) fu.table += 4 * c4;
+        if (fu.table_b) fu.table_b += 4 * c4;
+    }
     constexpr int GROUPS = kThreads / LPR;
     constexpr int ROWF = ITERS * LPR * 4;
     constexpr int TILE = GROUPS * CHUNK;
@@ -799,18 +813,12 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
     const int32_t col = FUSED ? fu.touched_cols[seg] : 0;
     const int32_t j0 = (seg_ptr[seg] - e_begin) / TILE;         // tile in which the run began
     const int n = j - j0 + 1;                                   // partial rows: (j0, slot 1), (j0+1 .. j, slot 0)
-    // Column slices of LPR ITERS float4, as in k_seg_reduce, dealt to the workgroups of blockIdx.y in turn: most tiles end no
-    // crossing run, so a workgroup for each of a wide row's slices mostly starts to find that out once more (16 slices of
-    // 9,216 tiles: 105 us as 16 workgroups a tile, 65 as four).  Launches with a ride hold whole rows.
-    auto slice = [&](int c4) {
-        FusedArgs fs = fu;
-        if (fs.table) fs.table += 4 * c4;
-        if (fs.table_b) fs.table_b += 4 * c4;
-        Acc<ITERS> xrow;                                            // FUSED: the table row, fetched beside the partial rows
+    auto sum_row = [&](const FusedArgs &fa, float *rows, const float *part, int width4) {
+        Acc<ITERS> xrow;                                        // FUSED: the table row, fetched beside the partial rows
         xrow.zero();
         if (FUSED && grp == 0) {
-            if (fu.stream) load_row_stream<LPR, ITERS>(fused_row(fs, col, ld_tab), d4, lig, xrow);
-            else load_row<LPR, ITERS>(fused_row(fs, col, ld_tab), d4, lig, xrow);
+            if (fa.stream) load_row_stream<LPR, ITERS>(fused_row(fa, col, ld_tab), width4, lig, xrow);
+            else load_row<LPR, ITERS>(fused_row(fa, col, ld_tab), width4, lig, xrow);
         }
         const int per = (n + GROUPS - 1) / GROUPS;
         const int lo = min(grp * per, n), hi = min(lo + per, n);
@@ -822,38 +830,49 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
             Acc<ITERS> v[FU];
 #pragma unroll
             for (int u = 0; u < FU; ++u)
-                load_row<LPR, ITERS>(partials + 4 * c4 + ((int64_t)(j0 + q + u) * 2 + (q + u == 0 ? 1 : 0)) * ld_out, d4, lig, v[u]);
+                load_row<LPR, ITERS>(part + ((int64_t)(j0 + q + u) * 2 + (q + u == 0 ? 1 : 0)) * ld_out, width4, lig, v[u]);
 #pragma unroll
             for (int u = 0; u < FU; ++u) acc.add(v[u]);
         }
         for (; q < hi; ++q) {
             Acc<ITERS> v;
-            load_row<LPR, ITERS>(partials + 4 * c4 + ((int64_t)(j0 + q) * 2 + (q == 0 ? 1 : 0)) * ld_out, d4, lig, v);
+            load_row<LPR, ITERS>(part + ((int64_t)(j0 + q) * 2 + (q == 0 ? 1 : 0)) * ld_out, width4, lig, v);
             acc.add(v);
         }
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) st4(&s_sum[grp][(lig + it * LPR) * 4], acc.v[it]);
         __syncthreads();
         if (grp == 0) {
-            const int used = (n + per - 1) / per;                   // groups that had at least one row
+            const int used = (n + per - 1) / per;               // groups that had at least one row
             for (int g = 1; g < used; ++g) {
                 Acc<ITERS> v;
 #pragma unroll
                 for (int it = 0; it < ITERS; ++it) v.v[it] = ld4(&s_sum[g][(lig + it * LPR) * 4]);
                 acc.add(v);
             }
-            if constexpr (FUSED) apply_update<LPR, ITERS>(fused_row(fs, col, ld_tab), d4, lig, xrow, acc, fu.lr, fu.mode, fu.stream);
-            else store_row<LPR, ITERS>(out_rows + 4 * c4 + (int64_t)seg * ld_out, d4, lig, acc);
+            if constexpr (FUSED) apply_update<LPR, ITERS>(fused_row(fa, col, ld_tab), width4, lig, xrow, acc, fa.lr, fa.mode, fa.stream);
+            else store_row<LPR, ITERS>(rows + (int64_t)seg * ld_out, width4, lig, acc);
         }
     };
-    if constexpr (RIDE != 0) {
-        slice(0);
-    } else {
-        for (int c4 = (int)blockIdx.y * ITERS * LPR; c4 < d4_all; c4 += (int)gridDim.y * ITERS * LPR) {
-            d4 = min(ITERS * LPR, d4_all - c4);
-            if (c4 != (int)blockIdx.y * ITERS * LPR) __syncthreads();   // the slice before this one has been read out of LDS
-            slice(c4);
+    if constexpr (MANY) {
+        static_assert(ITERS == 1 && RIDE == 0, "slices of one float4 per lane");
+        for (int c4 = (int)blockIdx.y * LPR; c4 < d4; c4 += (int)gridDim.y * LPR) {
+            FusedArgs fa = fu;
+            if (fa.table) fa.table += 4 * c4;
+            if (fa.table_b) fa.table_b += 4 * c4;
+            if (c4 != (int)blockIdx.y * LPR) __syncthreads();   // the slice before this one has been read out of LDS
+            sum_row(fa, out_rows + 4 * c4, partials + 4 * c4, min(LPR, d4 - c4));
         }
+    } else {
+        if (RIDE == 0 && gridDim.y > 1) {                       // column slices, as in k_seg_reduce
+            const int c4 = (int)blockIdx.y * LPR;
+            d4 = min(LPR, d4 - c4);
+            if (out_rows) out_rows += 4 * c4;
+            partials += 4 * c4;
+            if (fu.table) fu.table += 4 * c4;
+            if (fu.table_b) fu.table_b += 4 * c4;
+        }
+        sum_row(fu, out_rows, partials, d4);
     }
 }
 
@@ -1166,7 +1185,7 @@ static void seg_slices(stx_ctx *c, const stx_incidence *inc, const float *src, i
             else STX_SLICES_R(F, 64, 64 * (kThreads / LPR), wide);                                              \
         }                                                                                                       \
         ProfScope prof(c, "k_seg_fixup");                                                                       \
-        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, F, 0>), dim3(grid.x, std::min(grid.y, 4u)), dim3(kThreads), 0, c->stream, \
+        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, F, 0, true>), dim3(grid.x, std::min(grid.y, 4u)), dim3(kThreads), 0, c->stream, \
                            inc->at_packed, inc->at_seg_id, inc->at_seg_ptr, 0, nnz, d4, out_rows, ld_out, c->partials, fu, sec, \
                            ScatterAhead{}, HistAhead{}, DmRide{}, EmitAhead{});                                 \
     } while (0)
@@ -1264,7 +1283,7 @@ stx_status launch_seg_formed(stx_ctx *c, const stx_incidence *inc, const stx_par
 #undef STX_FORMED
     if (ntiles > 1) {
         ProfScope prof(c, "k_seg_fixup");
-        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, false, 0>), dim3(grid.x, std::min(grid.y, 4u)), dim3(kThreads), 0, c->stream,
+        hipLaunchKernelGGL((k_seg_fixup<LPR, 1, CH, false, 0, true>), dim3(grid.x, std::min(grid.y, 4u)), dim3(kThreads), 0, c->stream,
                            inc->at_packed, inc->at_seg_id, inc->at_seg_ptr, 0, nnz, d4, out_rows, ld_out, c->partials, fu, sec,
                            ScatterAhead{}, HistAhead{}, DmRide{}, EmitAhead{});
     }

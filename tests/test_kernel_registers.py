@@ -1,0 +1,57 @@
+"""Wavefronts per SIMD that the built kernels leave room for, from the metadata that the compiler puts beside them."""
+import re
+import struct
+
+import msgpack
+import pytest
+
+from paper_2502_16949_amd import binding as B
+
+MAGIC = b"__CLANG_OFFLOAD_BUNDLE__"
+
+
+def _notes(elf):
+    """(type, contents) of the notes of a 64-bit ELF file."""
+    shoff, = struct.unpack_from("<Q", elf, 40)
+    shentsize, shnum = struct.unpack_from("<HH", elf, 58)
+    for i in range(shnum):
+        kind, _, _, at, size = struct.unpack_from("<IQQQQ", elf, shoff + i * shentsize + 4)
+        end = at + size
+        while kind == 7 and at + 12 <= end:                # SHT_NOTE
+            namesz, descsz, what = struct.unpack_from("<III", elf, at)
+            desc = at + 12 + (namesz + 3) // 4 * 4
+            yield what, elf[desc:desc + descsz]
+            at = desc + (descsz + 3) // 4 * 4
+
+
+@pytest.fixture(scope="module")
+def registers():
+    """Mangled kernel name -> vector registers (of both kinds)."""
+    lib = open(B.LIB_PATH, "rb").read()
+    out = {}
+    for m in re.finditer(MAGIC, lib):
+        at = m.end()
+        n, = struct.unpack_from("<Q", lib, at)
+        at += 8
+        for _ in range(n):
+            off, size, idlen = struct.unpack_from("<QQQ", lib, at)
+            at += 24 + idlen
+            if lib[at - idlen:at].endswith(b"gfx950"):
+                for what, desc in _notes(lib[m.start() + off:m.start() + off + size]):
+                    if what == 32:                         # NT_AMDGPU_METADATA
+                        out.update((k[".name"], k[".vgpr_count"]) for k in msgpack.unpackb(desc)["amdhsa.kernels"])
+    assert len(out) > 100
+    return out
+
+
+def _waves(vgprs):
+    return min(8, 512 // ((vgprs + 7) // 8 * 8))
+
+
+# The fix-up of one row or one column slice per workgroup (the loop over slices is a kernel of its own): the registers of a
+# row's sum, two to eight partial rows in flight, and with the update fused the table row and its new values.
+@pytest.mark.parametrize("iters,fused,waves", [(1, 0, 8), (1, 1, 8), (2, 0, 8), (2, 1, 8), (3, 0, 8), (3, 1, 6), (4, 0, 7), (4, 1, 4)])
+def test_fixup_of_single_slices(registers, iters, fused, waves):
+    seen = [v for k, v in registers.items()
+            if re.search(r"k_seg_fixupILi\d+ELi%dELi\d+ELb%dELi0E(Lb0E)?E" % (iters, fused), k)]
+    assert seen and all(_waves(v) >= waves for v in seen), seen
