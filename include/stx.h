@@ -215,7 +215,8 @@ stx_status stx_forward(stx_ctx *ctx, const stx_incidence *inc, const stx_params 
 /* Backward (Appendix G): g->rows[s] = sum over the entries e of segment s of sign[e] * (dL/dx of row
  * row_idx[e]), summed without atomics in a fixed order (bitwise reproducible); TransH and TransR first
  * pass dL/dy back through their projection (Sec. 4.4, 4.5) and also fill w_rows / proj.
- * Needs the stx_forward of the same incidence immediately before it on this context.                  */
+ * Needs the stx_forward of the same incidence before it on this context, with no other forward pass, update
+ * or step between them; another incidence may be built meanwhile (the next batch's, say).             */
 stx_status stx_backward(stx_ctx *ctx, const stx_incidence *inc, const stx_params *p, stx_grads *g);
 
 /* SGD on the touched rows only: row <- row - lr * grad (product and difference rounded separately).
@@ -228,7 +229,7 @@ stx_status stx_sgd_step(stx_ctx *ctx, stx_params *p, const stx_incidence *inc, c
  * optimiser step as part of the training loop, Table 1; fusing it with Appendix G's transposed product is
  * this library's choice).  The update is applied where the transposed products (and TransR's product for
  * dL/dM_r) would store a gradient, so no gradient is written: g may be null and, if given, is left
- * untouched.  Needs the stx_forward of the same incidence immediately before it.                       */
+ * untouched.  Needs the stx_forward of the same incidence before it, as stx_backward does.              */
 stx_status stx_backward_sgd(stx_ctx *ctx, const stx_incidence *inc, stx_params *p, stx_grads *g, float lr);
 
 /* One training step in one call.  The batch's positives plus what stx_sample_negatives needs to draw its

@@ -267,7 +267,7 @@ stx_status launch_build(stx_ctx *c, const int32_t *h, const int32_t *r, const in
     c->cnt_inc = nullptr;
     c->cnt_ptr = nullptr;
     c->prep_inc = nullptr;
-    c->tr_fused_inc = nullptr;
+    if (c->tr_fused_inc == inc) c->tr_fused_inc = nullptr;   // (another incidence's forward pass stays as it was stored)
     // the first kernels may already have run, in launches of the previous step
     const EmitAheadState prev = c->ahead;
     clear_ahead(c);

@@ -798,6 +798,7 @@ stx_status launch_transr_project(stx_ctx *c, const stx_incidence *inc, const stx
             hipLaunchKernelGGL(k_transr_prepare<false>, dim3(prep_blocks(c, a)), dim3(kThreads), 0, c->stream, a);
     }
     c->prep_inc = nullptr;      // the copies of M_r are good for this forward pass only: the update changes M_r
+    c->tr_fused_inc = nullptr;
     ProfScope prof(c, "k_transr_project");
     if (c->cfg.dim <= 128 && c->cfg.rel_dim <= 128)
         hipLaunchKernelGGL((k_transr_rows<false, true>), dim3(row_items_max(c, inc->n_rows)), dim3(kThreads), 0,
