@@ -289,12 +289,15 @@ stx_status stx_train_step(stx_ctx *ctx, const stx_batch *batch, stx_incidence *i
  * h, r, t: [nq] device, in; the three outputs: [nq] device.  Out-of-range indices are clamped and
  * counted as in stx_build_incidence.  work: device scratch of stx_rank_work_bytes(nq) bytes, 256-byte
  * aligned, owned by the caller; TransE / TorusE / TransH need none (null is fine).  TransR groups the
- * queries by relation and builds one projected table per relation that occurs; it waits for the stream
- * once (to learn the group sizes) and launches a few kernels per relation.  With the L2 kinds its work
- * ends in scratch of the filter below, packed tables included; a buffer without it is taken too (it has the size
- * of the same context with the distance L1) and the sweeps are plain then.
+ * queries by relation, waits for the stream once (to learn the group sizes) and builds a projected table per
+ * relation that occurs, a few kernels each.  With the L2 kinds its work goes on after the tables with scratch for
+ * the filter below, over projected tables or, for the relations for which that is faster, over the entity table
+ * itself with a squared norm per relation and entity (about 6 n_ent * dim bytes for the entities' operands and up to
+ * 160 MiB of norms, matrices and undecided pairs; only where nq and the sizes let it pay).  A buffer that holds the scratch of one of
+ * the two gets that one; one that ends after the tables (it has the size of the same context with the distance L1)
+ * is taken too and the sweeps are plain then.
  * Cost of a plain sweep: nq * n_ent * dim steps of vector arithmetic (TransH about twice that; TransR rel_dim
- * in place of dim, plus n_ent * dim * rel_dim per relation that occurs), whatever the values.  L1, torus-L1, L2
+ * in place of dim, plus n_ent * dim * rel_dim per projected table), whatever the values.  L1, torus-L1, L2
  * and squared L2 (TransE / TorusE: calls large enough to gain; TransR: the L2 kinds) order most candidates by a
  * cheaper sum of known error, with the same results, two to five times as fast.  That sum leaves pairs undecided
  * and they are summed exactly: one in some hundreds in ordinary tables, many more where many rows are equal

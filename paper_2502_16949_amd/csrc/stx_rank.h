@@ -109,7 +109,7 @@ struct RankGroups {                    // queries grouped by relation
 // take.  false: it would be slower than that, nothing launched.
 bool rank_transr(stx_ctx *, const stx_params *, int64_t nq, int side, const RankGroups &, int tables, void *work, size_t bytes, const int32_t *counts);
 int32_t rank_transr_most(const stx_config &);
-size_t rank_transr_bytes(const stx_config &, int64_t nq);                         // 0: a kind without
+size_t rank_transr_bytes(const stx_config &, int64_t nq, int tables);             // 0: a call that never takes this way
 
 // ---- stx_rank_filter.hip ------------------------------------------------------------------------------
 // Scratch of a filtered sweep: packed queries with their thresholds; packed candidates (matrix-core kinds).  Sweeps

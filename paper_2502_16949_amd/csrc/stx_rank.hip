@@ -380,11 +380,12 @@ struct RankRWork {                      // partitions of the caller's work buffe
     float *table;                       // n_tables tables of (n_ent + 1) x rel_dim: P_r, then r
     int n_tables;
     RankScratch ws;                     // of the filtered sweeps (kinds that have one), over projected tables ...
-    RrBlock *blocks;                    // ... and without them, in the same place
+    RrBlock *blocks;                    // ... and without them, in the same place (they are done before the others)
     int32_t *occ;
     void *rr;
-    size_t rr_bytes;
-    size_t plain_total, total;          // without and with these
+    size_t rr_bytes;                    // 0: no relation of such a call is swept without a table
+    size_t plain_total, ws_total, rr_total;   // bytes without these, with `ws`, with `blocks`, `occ` and `rr`
+    size_t total() const { return std::max(ws_total, rr_total); }
 };
 static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
 {
@@ -406,16 +407,8 @@ static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
     w.n_tables = (int)(fit < 1 ? 1 : (fit > kRankTables ? kRankTables : fit));
     if (w.n_tables > cfg.n_rel) w.n_tables = (int)cfg.n_rel;
     w.table = (float *)take(table_bytes * w.n_tables);
-    w.plain_total = w.total = off;
-    w.rr_bytes = rank_transr_bytes(cfg, nq);
-    if (!w.rr_bytes) return w;                                                 // (no filtered sweep)
-    w.blocks = (RrBlock *)take((size_t)(nq / 32 + std::min((int64_t)cfg.n_rel, nq)) * sizeof(RrBlock));
-    w.occ = (int32_t *)take((size_t)cfg.n_rel * 4);
-    // (the relations swept without a table are done before the others)
-    const size_t both = off;
-    w.rr = take(w.rr_bytes);
-    const size_t end = off;
-    off = both;
+    w.plain_total = w.ws_total = w.rr_total = off;
+    if (cfg.dist != STX_L2 && cfg.dist != STX_L2_SQ) return w;                 // (no filtered sweep)
     // one relation with all queries, or n_tables relations with up to kRankBig each
     const int64_t few = nq < kRankBig ? nq : kRankBig, many = ((few + 31) / 32 * 32) * w.n_tables;
     w.ws.q_bytes = rank_filter_q_bytes(cfg.dist, cfg.rel_dim, nq > many ? nq : many);
@@ -423,13 +416,19 @@ static RankRWork rank_r_work(const stx_config &cfg, int64_t nq, void *base)
     w.ws.q = take(w.ws.q_bytes);
     w.ws.e = take(w.ws.e_bytes);
     w.ws.q32 = w.ws.q_bytes ? (float *)take((size_t)nq * cfg.rel_dim * 4) : nullptr;
-    off = std::max(off, end);
-    w.total = off;
+    w.ws_total = off;
+    w.rr_bytes = rank_transr_bytes(cfg, nq, w.n_tables);
+    if (!w.rr_bytes) return w;
+    off = w.plain_total;
+    w.blocks = (RrBlock *)take((size_t)(nq / 32 + std::min((int64_t)cfg.n_rel, nq)) * sizeof(RrBlock));
+    w.occ = (int32_t *)take((size_t)cfg.n_rel * 4);
+    w.rr = take(w.rr_bytes);
+    w.rr_total = off;
     return w;
 }
 size_t rank_work_bytes(const stx_ctx *c, int64_t nq)
 {
-    return c->cfg.model == STX_TRANSR ? rank_r_work(c->cfg, nq, nullptr).total : 0;
+    return c->cfg.model == STX_TRANSR ? rank_r_work(c->cfg, nq, nullptr).total() : 0;
 }
 size_t rank_plain_work_bytes(const stx_ctx *c, int64_t nq)
 {
@@ -724,8 +723,9 @@ stx_status launch_rank(stx_ctx *c, const stx_params *p, const int32_t *h, const 
     // projected table and one sweep per relation that occurs
     const RankRWork w = rank_r_work(c->cfg, nq, work);
     const int dim = c->cfg.dim, k = c->cfg.rel_dim;
-    const bool filtered = w.rr_bytes && work_bytes >= w.total;
-    const int32_t most = filtered ? rank_transr_most(c->cfg) : 0;              // queries of a relation that needs no table
+    // (a buffer that holds one of the two ways' scratch gets that one)
+    const bool filtered = w.ws.q_bytes && work_bytes >= w.ws_total;
+    const int32_t most = w.rr_bytes && work_bytes >= w.rr_total ? rank_transr_most(c->cfg) : 0;   // queries of a relation that needs no table
     const dim3 rgrid((unsigned)((n_rel + kThreads - 1) / kThreads)), qgrid((unsigned)((nq + kThreads - 1) / kThreads));
     hipLaunchKernelGGL(k_rr_clear, rgrid, dim3(kThreads), 0, c->stream, w.counts, w.cursor, n_rel);
     hipLaunchKernelGGL(k_rr_hist, qgrid, dim3(kThreads), 0, c->stream, h, r, t, nq, n_ent, n_rel, w.counts, bad);

@@ -38,7 +38,7 @@ constexpr int kPairBlock = 64;         // undecided pairs of one relation that a
 constexpr int kAux = 64;               // floats that go with a tile of 32 entities: of the table, and of a relation
 
 struct RrState {
-    uint32_t n_blocks;                 // pair blocks begun, cleared by k_rr_query and k_rr_behind
+    uint32_t n_blocks;                 // pair blocks begun, cleared by k_rr_query
     int32_t pad[31];
     int32_t full;                      // there were too many, in this sweep or one before it in the call
     int32_t skip;                      // `full` as it was before this sweep
@@ -812,11 +812,6 @@ static RrPlan rr_plan(const stx_config &cfg, int64_t nq)
     p.total = off;
     return p;
 }
-size_t rank_transr_bytes(const stx_config &cfg, int64_t nq)
-{
-    return cfg.dist == STX_L2 || cfg.dist == STX_L2_SQ ? rr_plan(cfg, nq).total : 0;
-}
-
 template <int KS, int A>
 static void rr_go(stx_ctx *c, RrArgs f, const RrPlan &p, const int32_t *counts, int32_t n_rel, int32_t most)
 {
@@ -892,11 +887,23 @@ static void rr_go(stx_ctx *c, RrArgs f, const RrPlan &p, const int32_t *counts, 
 static double rr_table_us(const stx_config &c) { return (double)c.n_ent * c.rel_dim * (2. * c.dim / 90e6 + 10. / 5e6); }
 static double rr_norms_us(const stx_config &c) { return (double)c.n_ent * c.rel_dim * 16. * rr_steps(c.dim) * 6. / 500e6; }
 static double rr_query_us(const stx_config &c) { return 0.0008 + 0.4 * (double)c.n_ent / 500. * c.dim * c.rel_dim * 2. / 65e6; }
+static double rr_fixed_us(const stx_config &c) { return 55. + 0.0008 * c.dim * c.rel_dim + (double)c.n_ent * c.dim * 10. / 4e6; }
 constexpr double kRrLaunchUs = 28.;    // of a set of launches over projected tables
 int32_t rank_transr_most(const stx_config &c)
 {
     const double most = (kRrLaunchUs + rr_table_us(c) - rr_norms_us(c)) / rr_query_us(c);
     return (int32_t)std::max(0., std::min(most, 2e9));
+}
+// No scratch where the rule cannot come out on this side, whatever the relations of the queries: as many of them as there
+// can be, one query each and the most launches.  (Such calls do not list blocks of queries either: k_rr_scan takes 2.3 us
+// without, 4.0 with it, of calls of 80.)
+size_t rank_transr_bytes(const stx_config &cfg, int64_t nq, int tables)
+{
+    if ((cfg.dist != STX_L2 && cfg.dist != STX_L2_SQ) || rank_transr_most(cfg) == 0) return 0;
+    const double rels = (double)std::min((int64_t)cfg.n_rel, nq), big = std::min(rels, floor((double)nq / (kRankBig + 1)));
+    const double gain = (big + ceil(rels / tables)) * kRrLaunchUs +
+                        std::max(0., rels * (rr_table_us(cfg) - rr_norms_us(cfg) - rr_query_us(cfg))) - rr_fixed_us(cfg);
+    return gain > 0. ? rr_plan(cfg, nq).total : 0;
 }
 
 bool rank_transr(stx_ctx *c, const stx_params *p, int64_t nq, int side, const RankGroups &g, int tables, void *work, size_t bytes, const int32_t *counts)
@@ -910,8 +917,7 @@ bool rank_transr(stx_ctx *c, const stx_params *p, int64_t nq, int side, const Ra
             big += counts[r] > kRankBig ? 1. : 0.;         // (launches of its own)
         }
     const double with_tables = (big + ceil((rels - big) / tables)) * kRrLaunchUs + rels * rr_table_us(c->cfg);
-    const double without = 55. + 0.0008 * c->cfg.dim * c->cfg.rel_dim + (double)c->cfg.n_ent * c->cfg.dim * 10. / 4e6 +
-                           rels * rr_norms_us(c->cfg) + queries * rr_query_us(c->cfg);
+    const double without = rr_fixed_us(c->cfg) + rels * rr_norms_us(c->cfg) + queries * rr_query_us(c->cfg);
     if (bytes < pl.total || without >= with_tables) return false;
     char *w = (char *)work;
     RrArgs f{};

@@ -11,7 +11,7 @@ pytestmark = pytest.mark.gpu
 
 CASES = [
     # dist, n_ent, n_rel, dim, rel_dim, nq: every compiled number of steps, one and two halves of the outputs, ragged tiles of
-    # entities, blocks of one query and of 32, several batches of relations (the last)
+    # entities, blocks of one query and of 32, several sweeps (the last)
     ("l2", 1_999, 300, 32, 32, 900),
     ("l2_sq", 3_001, 200, 64, 96, 700),
     ("l2", 2_113, 150, 96, 256, 301),
@@ -23,18 +23,19 @@ CASES = [
 ]
 
 
-def _run(ctx, p, ids, side, work):
+def _run(ctx, p, ids, side, work, kernel="k_rr_sweep"):
     nq = len(ids[0])
     ts = torch.empty(nq, dtype=torch.float32, device=G.DEV)
     less, equal = (torch.empty(nq, dtype=torch.int32, device=G.DEV) for _ in range(2))
-    B.stx_profile_kernel(ctx, "k_rr_sweep", 256)
+    B.stx_profile_kernel(ctx, kernel, 256)
     B.stx_rank(ctx, p, *ids, side, ts, less, equal, work)
     n = B.stx_profile_read(ctx)[1]
     B.stx_profile_kernel(ctx, None, 0)
     return (ts, less, equal), n
 
 
-def _compare(dist, n_ent, n_rel, dim, k, nq, E, R, M, ids, sides=(B.STX_TAIL, B.STX_HEAD)):
+def _compare(dist, n_ent, n_rel, dim, k, nq, E, R, M, ids, sides=(B.STX_TAIL, B.STX_HEAD), launches=()):
+    """launches: (kernel, least number of them) of the call with all its scratch."""
     ctx = {d: B.Context(B.make_config("transr", d, n_ent, n_rel, dim, 8, 1, rel_dim=k, flags=B.STX_FLAG_BF16_PROJ), G.DEV)
            for d in ("l1", dist)}
     p = B.Params(G.dev_f32(E), G.dev_f32(R), proj=G.dev_f32(M))
@@ -48,6 +49,10 @@ def _compare(dist, n_ent, n_rel, dim, k, nq, E, R, M, ids, sides=(B.STX_TAIL, B.
         assert none == 0 and n > 0
         for a, b, what in zip(got, want, ("score", "less", "equal")):
             assert torch.equal(a.view(torch.int32), b.view(torch.int32)), (what, side)
+        for kernel, least in launches:
+            again, n = _run(ctx[dist], p, ids, side, work[:full], kernel)
+            assert n >= least, (kernel, n)
+            assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(again, want)), (kernel, side)
 
 
 def _inputs(seed, n_ent, n_rel, dim, k, nq):
@@ -95,3 +100,65 @@ def test_indices_out_of_range_are_counted():
     E, R, M, ids = _inputs(5, n_ent, n_rel, dim, k, nq)
     ids[0][3], ids[1][4], ids[2][5] = -1, n_rel, n_ent + 7
     _compare(dist, n_ent, n_rel, dim, k, nq, E, R, M, ids)
+
+
+# More relations than a batch of them holds operands for: 206 at these sizes, of 300 or so that occur.
+def _batches_case():
+    dist, n_ent, n_rel, dim, k, nq = case = ("l2", 60_001, 400, 64, 32, 1_000)
+    E, R, M, ids = _inputs(6, n_ent, n_rel, dim, k, nq)
+    r = np.random.default_rng(7).permutation(np.r_[np.arange(300), np.random.default_rng(8).integers(0, 300, nq - 300)])
+    ids[1] = G.dev_i32(r + 50)
+    return case, E, R, M, ids
+
+
+def test_several_batches_of_relations():
+    case, E, R, M, ids = _batches_case()
+    _compare(*case, E, R, M, ids, launches=[("k_rr_pack", 2), ("k_rr_norms", 2)])
+
+
+# ... the first of which leaves more pairs undecided than there are places: its matrices are zero.
+def test_a_batch_of_relations_behind_one_that_stopped():
+    case, E, R, M, ids = _batches_case()
+    M[50:250], R[50:250] = 0.0, 0.0
+    _compare(*case, E, R, M, ids, launches=[("k_rr_pack", 2)])
+
+
+# One relation with more queries than pay without a table (7,410 at these sizes), and many that have few: both ways in one
+# call, the second's scratch over the first's.
+def test_both_ways_in_one_call():
+    dist, n_ent, n_rel, dim, k, nq = case = ("l2", 2_049, 61, 256, 256, 10_500)
+    E, R, M, ids = _inputs(9, n_ent, n_rel, dim, k, nq)
+    rng = np.random.default_rng(10)
+    r = rng.permutation(np.r_[np.full(9_000, 17), rng.choice([x for x in range(n_rel) if x != 17], nq - 9_000)])
+    ids[1] = G.dev_i32(r)
+    _compare(*case, E, R, M, ids, launches=[("k_rr_sweep", 1), ("k_rank_mfma", 1)])
+
+
+# A buffer that holds the scratch of one way alone: that way runs.  (The first two relations' tables take less than the
+# entities' operands, the others' tables more.)
+@pytest.mark.parametrize("case,share,kernel", [(("l2", 60_000, 2, 256, 256, 300), 0.8, "k_rank_mfma"),
+                                               (("l2_sq", 9_000, 200, 64, 64, 1_000), 0.8, "k_rr_sweep")])
+def test_scratch_of_one_way(case, share, kernel):
+    dist, n_ent, n_rel, dim, k, nq = case
+    E, R, M, ids = _inputs(11, n_ent, n_rel, dim, k, nq)
+    cfg = lambda d: B.make_config("transr", d, n_ent, n_rel, dim, 8, 1, rel_dim=k, flags=B.STX_FLAG_BF16_PROJ)
+    ctx, p = B.Context(cfg(dist), G.DEV), B.Params(G.dev_f32(E), G.dev_f32(R), proj=G.dev_f32(M))
+    plain, full = B.stx_rank_work_bytes(B.Context(cfg("l1"), G.DEV), nq), B.stx_rank_work_bytes(ctx, nq)
+    some = plain + int(share * (full - plain)) // 256 * 256
+    work = torch.empty(full + 256, dtype=torch.uint8, device=G.DEV)
+    work = work[-work.data_ptr() % 256:]
+    want, none = _run(ctx, p, ids, B.STX_TAIL, work[:plain], kernel)
+    work.random_(0, 255)
+    got, n = _run(ctx, p, ids, B.STX_TAIL, work[:some], kernel)
+    assert none == 0 and n > 0
+    assert all(torch.equal(a.view(torch.int32), b.view(torch.int32)) for a, b in zip(got, want))
+    other = {"k_rank_mfma": "k_rr_sweep", "k_rr_sweep": "k_rank_mfma"}[kernel]
+    assert _run(ctx, p, ids, B.STX_TAIL, work[:some], other)[1] == 0
+
+
+# Calls that cannot gain by it keep no scratch for the sweep without tables.
+def test_no_scratch_for_few_queries():
+    cfg = lambda dist, n_rel: B.make_config("transr", dist, 9_951, n_rel, 64, 8, 1, rel_dim=64, flags=B.STX_FLAG_BF16_PROJ)
+    more = {n_rel: B.stx_rank_work_bytes(B.Context(cfg("l2", n_rel), G.DEV), 3) - B.stx_rank_work_bytes(B.Context(cfg("l1", n_rel), G.DEV), 3)
+            for n_rel in (32, 1_000)}
+    assert more[32] == more[1_000]                         # (the tables' filter: 32 tables at most)
