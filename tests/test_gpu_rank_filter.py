@@ -49,6 +49,8 @@ CASES = [
     ("l2", 60_001, 16, 4_000), ("l2", 30_000, 44, 600), ("l2", 4_129, 128, 1_300), ("l2", 9_000, 196, 385),
     ("l2_sq", 2_050, 260, 1_250), ("l2", 1_300, 700, 800), ("l2", 1_100, 1024, 700),
     ("l2", 500_000, 100, 33), ("l1", 200_000, 60, 5),     # few queries, several segments of candidates
+    # L2 kinds above 256 floats: the counts of steps that are not above, ragged; several segments
+    ("l2", 4_001, 388, 700), ("l2_sq", 2_050, 512, 1_250), ("l2", 2_050, 768, 900), ("l2", 40_001, 500, 200),
 ]
 
 
@@ -90,6 +92,24 @@ def test_filtered_counts_equal_the_plain_sweep(dist, n_ent, dim, nq, odd_rows):
         for g, w in zip(got, want):
             assert np.array_equal(g, w, equal_nan=True)
     assert B.stx_check_indices(ctx) == 0
+
+
+# Which kernel sweeps: bytes above 256 floats, fp16 up to there; launches: one per chunk of queries and segment of candidates.
+@pytest.mark.parametrize("n_ent,dim,nq,segments", [(8_193, 256, 700, 1), (8_193, 260, 700, 1), (4_001, 388, 700, 1), (4_001, 512, 700, 1),
+                                                   (4_001, 516, 700, 1), (4_001, 1024, 700, 1), (40_001, 500, 200, 2)])
+def test_kernel_of_wide_rows(n_ent, dim, nq, segments):
+    rng = np.random.default_rng(dim)
+    ctx = B.Context(B.make_config("transe", "l2", n_ent, 3, dim, 8, 1), G.DEV)
+    p = B.Params(G.dev_f32(rng.uniform(-1, 1, (n_ent + 3, dim))))
+    h, r, t = (G.dev_i32(rng.integers(0, n, nq)) for n in (n_ent, 3, n_ent))
+    seen = {}
+    for kernel in ("k_rank_wide", "k_rank_mfma"):
+        B.stx_profile_kernel(ctx, kernel, 64)
+        _rank(ctx, p, h, r, t, B.STX_TAIL)
+        seen[kernel] = B.stx_profile_read(ctx)[1]
+    B.stx_profile_kernel(ctx, None, 0)
+    wide, other = ("k_rank_wide", "k_rank_mfma") if dim > 256 else ("k_rank_mfma", "k_rank_wide")
+    assert seen[wide] >= segments and (segments > 1) == (seen[wide] > 1) and seen[other] == 0, seen
 
 
 # Zero query points against whole tiles (32 candidates) of zero rows: every sum is exactly zero and so is every rounding.

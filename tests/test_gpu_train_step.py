@@ -30,6 +30,11 @@ CASES = [
     ("transh", "l2", 1000, 20, 1024, 1, 128, 128, B.STX_FLAG_RENORM_W),
     ("transh", "l1", 400, 9, 777, 3, 64, 64, 0),
     ("transh", "l2", 200, 5, 200, 1, 1024, 1024, 0),
+    # whole rows of two, three and four float4 per lane, relation columns out of one row per positive
+    ("transh", "l2", 200, 5, 700, 2, 512, 512, B.STX_FLAG_RENORM_W),
+    ("transh", "l2", 200, 5, 600, 3, 700, 700, B.STX_FLAG_RENORM_W),
+    ("transh", "l1", 200, 5, 500, 5, 1024, 1024, B.STX_FLAG_RENORM_W),
+    ("transh", "l2", 200, 5, 600, 5, 700, 700, 0),                # ... and in column slices
     ("transr", "l2", 1000, 20, 1024, 1, 128, 128, B.STX_FLAG_BF16_PROJ),
     ("transr", "l1", 300, 40, 500, 2, 64, 32, B.STX_FLAG_BF16_PROJ),
 ]

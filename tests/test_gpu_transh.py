@@ -79,6 +79,13 @@ CASES = [
     ("l2", 200, 5, 200, 1, 1024, 0.0),
     ("torus_l2", 300, 6, 400, 2, 64, 1.1),
     ("l2_sq", 400, 9, 777, 3, 128, 1.1),
+    # negatives come four at a time, two above 512 floats: a positive's sums of gy and gw go on across such batches
+    ("l2", 300, 5, 250, 9, 128, 0.0),
+    ("l2", 300, 6, 200, 8, 64, 1.1),
+    ("l1", 200, 6, 150, 5, 64, 1.1),
+    ("l2", 150, 4, 120, 3, 768, 0.0),
+    ("l2_sq", 150, 4, 160, 5, 1024, 1.1),
+    ("l2", 200, 5, 300, 2, 512, 1.1),                     # two float4 per lane
 ]
 
 
