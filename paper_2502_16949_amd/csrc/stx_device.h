@@ -67,12 +67,6 @@ __device__ inline float4 ld4_stream(const float *p)
     stx_f4 t = __builtin_nontemporal_load(reinterpret_cast<const stx_f4 *>(p));
     return make_float4(t.x, t.y, t.z, t.w);
 }
-__device__ inline uint4 ld_u4_stream(const uint4 *p)
-{
-    typedef uint32_t u4 __attribute__((ext_vector_type(4)));
-    const u4 t = __builtin_nontemporal_load(reinterpret_cast<const u4 *>(p));
-    return make_uint4(t.x, t.y, t.z, t.w);
-}
 __device__ inline void st4_stream(float *p, float4 v)
 {
     stx_f4 t = {v.x, v.y, v.z, v.w};

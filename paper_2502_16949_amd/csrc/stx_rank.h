@@ -133,4 +133,58 @@ bool rank_filtered(stx_ctx *, const RankArgs &, int side, const RankScratch &, i
 // are cleared, done on the GPU only where *gate is not zero by then.
 void rank_plain_behind(stx_ctx *, const RankArgs &, int side, int64_t q0, int64_t nq, int nz, const RankIds &, const int32_t *gate);
 
+// ---- what the filtered sweeps share -------------------------------------------------------------------------------
+constexpr float kUnit = 5.9604645e-8f; // 2^-24
+constexpr float kWideMax = 32639.f;    // largest 16-bit number whose high byte, the low one being signed, fits
+
+// Elements j .. j + 7 of a row, zeros past its end.
+__device__ inline void load8(const float *p, int j, int dim, float (&v)[8])
+{
+    const float4 x = j < dim ? ld4(p + j) : make_float4(0.f, 0.f, 0.f, 0.f);
+    const float4 y = j + 4 < dim ? ld4(p + j + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
+    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
+}
+// Sixteen elements scaled and rounded to 16-bit fixed point, as high and (signed) low bytes; adds the squares of the scaled
+// values, of the roundings and of the low bytes.
+__device__ inline void wide_piece(const float *v, float sc, uint4 &hi, uint4 &lo, float &n2, float &d2, float &l2)
+{
+    uint32_t h[4], l[4];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        h[w] = l[w] = 0u;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float x = v[4 * w + i] * sc;
+            const float k = fminf(fmaxf(rintf(x), -kWideMax), kWideMax);
+            const float d = x - k;
+            n2 = __builtin_fmaf(x, x, n2);
+            d2 = __builtin_fmaf(d, d, d2);
+            const int n = (int)k, b = (int)(int8_t)n;
+            l2 += (float)(b * b);
+            l[w] |= ((uint32_t)b & 0xffu) << (8 * i);
+            h[w] |= ((uint32_t)((n - b) >> 8) & 0xffu) << (8 * i);
+        }
+    }
+    hi = make_uint4(h[0], h[1], h[2], h[3]);
+    lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
+// One kilobyte from global memory straight into LDS (16 bytes per lane, in lane order).  Completion is counted by
+// vmcnt like any load; the waits are placed by hand where they are used.  The compiler cannot be told that m0 is written (a reserved
+// register): it finds it as it left it.
+__device__ inline void load_lds_1k(const uint4 *g, uint32_t lds)
+{
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+}
+
+__device__ inline void load_lds_256(const float *g, uint32_t lds)             // ... 256 bytes, four per lane
+{
+    uint32_t m0;
+    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, off\n\ts_mov_b32 m0, %0"
+                 : "=&s"(m0) : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
+}
+__device__ inline uint32_t lds_at(const void *p) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p; }
+
 }  // namespace stx

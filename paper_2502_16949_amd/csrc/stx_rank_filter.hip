@@ -37,7 +37,6 @@ constexpr int kSadGroup = 16;          // queries per group of k_rank_sad: one a
 constexpr int kSadThreads = 512;
 constexpr int kNoQuery = -(1 << 30);   // threshold of the places past the last query
 constexpr int kListCap = 128;          // undecided pairs a wavefront collects before it recomputes them
-constexpr float kUnit = 5.9604645e-8f; // 2^-24
 
 struct FilterState {
     unsigned long long n_pairs;        // undecided pairs found (a sweep may find up to 2^31 x 2^31), cleared by k_rank_prep
@@ -242,13 +241,6 @@ __device__ inline float pow2_scale(float mx, bool &ok)
 }
 // Relative error of half a squared norm formed by eight lanes, and of the few roundings around it.
 __device__ inline float norm_slack(int np) { return 0.5f * kUnit * (float)(np + 24); }
-// Eight elements of a row, zeros past its end.
-__device__ inline void load8(const float *p, int j, int dim, float (&v)[8])
-{
-    const float4 x = j < dim ? ld4(p + j) : make_float4(0.f, 0.f, 0.f, 0.f);
-    const float4 y = j + 4 < dim ? ld4(p + j + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
-}
 // Eight elements scaled and rounded to fp16; adds the squares of the scaled values and of the roundings.
 __device__ inline uint4 half_piece(const float (&v)[8], float sc, float &n2, float &d2)
 {
@@ -263,36 +255,11 @@ __device__ inline uint4 half_piece(const float (&v)[8], float sc, float &n2, flo
     }
     return __builtin_bit_cast(uint4, h);
 }
-constexpr float kWideMax = 32639.f;    // largest 16-bit number whose high byte, the low one being signed, fits
-// The scale that brings `mx` there, as pow2_scale.
+// The scale that brings `mx` to kWideMax, as pow2_scale.
 __device__ inline float wide_scale(float mx, bool &ok)
 {
     ok = mx == 0.f || (mx > 1e-12f && mx < 1e12f);
     return ok && mx != 0.f ? kWideMax / mx : 1.f;
-}
-// Sixteen elements scaled and rounded to 16-bit fixed point, as high and (signed) low bytes; adds the squares of the scaled
-// values, of the roundings and of the low bytes.
-__device__ inline void wide_piece(const float *v, float sc, uint4 &hi, uint4 &lo, float &n2, float &d2, float &l2)
-{
-    uint32_t h[4], l[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        h[w] = l[w] = 0u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float x = v[4 * w + i] * sc;
-            const float k = fminf(fmaxf(rintf(x), -kWideMax), kWideMax);
-            const float d = x - k;
-            n2 = __builtin_fmaf(x, x, n2);
-            d2 = __builtin_fmaf(d, d, d2);
-            const int n = (int)k, b = (int)(int8_t)n;
-            l2 += (float)(b * b);
-            l[w] |= ((uint32_t)b & 0xffu) << (8 * i);
-            h[w] |= ((uint32_t)((n - b) >> 8) & 0xffu) << (8 * i);
-        }
-    }
-    hi = make_uint4(h[0], h[1], h[2], h[3]);
-    lo = make_uint4(l[0], l[1], l[2], l[3]);
 }
 // One element as 16-bit fixed point; adds the rounding made (in units of the last place).
 template <bool TORUS>
@@ -760,40 +727,17 @@ __global__ __launch_bounds__(kSadThreads) void k_rank_sad(FilterArgs f)
 // A wavefront keeps QF blocks of 32 queries (all KS steps of their rows) in registers; its workgroup's four wavefronts
 // share a stream of candidates, 32 to a tile, in operand order: a step of a tile is one contiguous kilobyte.  The
 // stream goes to LDS by direct loads, a chunk of CK kilobytes at a time, each wavefront fetching a quarter, NB - 1
-// chunks ahead (one barrier per chunk): with every wavefront reading the stream into its own registers, eight steps
-// ahead, the same 4,096 x 14,951 sweep at d = 1024 waited for memory most of the time (540 us).
+// chunks ahead (one barrier per chunk): with every wavefront reading the stream into its own registers the sweep waited
+// for memory most of the time.  Rows of at most 256 floats; 3,000 queries x 100,951 at d = 128 take 210 us.
 // v_mfma_f32_32x32x16_f16: rows are candidates, columns (lanes) queries; the accumulator starts at
 // -(|e|^2/2 + tau), so its sign is the decision.
-template <int KS>
-struct MfmaShape {
-    // kilobytes per chunk, chunks in LDS (64 KB at most: two workgroups per compute unit)
-    static constexpr int CK = KS <= 16 ? (32 % KS == 0 ? 32 : 24) : (KS % 16 == 0 ? 16 : 12);
-    static constexpr int NB = KS <= 16 ? 2 : 4;
-};
-
-// One kilobyte from global memory straight into LDS (16 bytes per lane, in lane order).  Completion is counted by
-// vmcnt like any load; the waits are placed by hand below.  The compiler cannot be told that m0 is written (a reserved
-// register): it finds it as it left it.
-__device__ inline void load_lds_1k(const uint4 *g, uint32_t lds)
-{
-    uint32_t m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0) : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
-}
-
-__device__ inline void load_lds_256(const float *g, uint32_t lds)             // ... 256 bytes, four per lane
-{
-    uint32_t m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, off\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0) : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
-}
-
 template <int QF, int KS, int WPE>
 __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankIds ids)
 {
-    constexpr int CK = MfmaShape<KS>::CK, NB = MfmaShape<KS>::NB, LW = CK / 4;
-    constexpr int TPC = KS <= CK ? CK / KS : 1, CPT = KS <= CK ? 1 : KS / CK;   // tiles per chunk / chunks per tile
-    constexpr int LA = TPC > 4 ? TPC / 4 : 1;                                   // auxiliary loads per wavefront and chunk
+    constexpr int CK = 32 % KS == 0 ? 32 : 24, NB = 2;     // kilobytes per chunk, chunks in LDS (64 KB at most: two workgroups per compute unit)
+    constexpr int LW = CK / 4, TPC = CK / KS;              // kilobytes a wavefront fetches, tiles per chunk
+    static_assert(CK % KS == 0, "whole tiles");
+    constexpr int LA = TPC > 4 ? TPC / 4 : 1;              // auxiliary loads per wavefront and chunk
     __shared__ __align__(1024) uint4 s_ring[NB][CK][64];
     __shared__ __align__(256) float s_aux[NB][TPC][64];
     __shared__ uint2 s_list[4][kListCap];
@@ -807,23 +751,23 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
     const int q_base = f.q_first + (int)(a.true_score - f.a.true_score);       // position of the chunk in the query arrays
     const uint32_t zbits = f.z_shift < 32 ? (uint32_t)z << f.z_shift : 0u;
     // Wavefronts with queries of their own: four, or two or one where the workgroup's queries are few; the others take
-    // the same queries and every second or fourth tile of a chunk (of one tile: nothing, they only fetch).
+    // the same queries and every second or fourth tile of a chunk.
     const int left = (nq - (int)blockIdx.x * 128 * QF + 32 * QF - 1) / (32 * QF), wq = left > 2 ? 4 : left > 1 ? 2 : 1;
     const int parts = 4 / wq, part = wave / wq;
     const int qb = ((int)blockIdx.x * 4 + wave % wq) * QF;                     // first block of 32 queries
-    const bool works = qb * 32 < nq && (TPC > 1 || part == 0);
+    const bool works = qb * 32 < nq;
     const int tiles = (f.e_count + 31) / 32;
     const int t0 = (int)blockIdx.y * f.slice, t1 = min(t0 + f.slice, tiles);
     const uint4 *src = f.ef + ((int64_t)z * tiles + t0) * KS * 64 + wave * LW * 64 + lane;
     const int chunks = ((t1 - t0) * KS + CK - 1) / CK;
-    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&s_ring[0][0][0];
-    const uint32_t ring_aux = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&s_aux[0][0][0];
+    const uint32_t ring = lds_at(&s_ring[0][0][0]);
+    const uint32_t ring_aux = lds_at(&s_aux[0][0][0]);
     const float *aux = f.eaux + ((int64_t)z * tiles + t0) * 64 + lane;
     auto fetch = [&](int c, int slot) {                                        // (past the end: the last chunk once more)
         const uint4 *g = src + (int64_t)min(c, chunks - 1) * CK * 64;
 #pragma unroll
         for (int i = 0; i < LW; ++i) load_lds_1k(g + i * 64, ring + (uint32_t)((slot * CK + wave * LW + i) * 1024));
-        const float *ga = aux + (int64_t)(CPT > 1 ? min(c, chunks - 1) / CPT : min(c, chunks - 1) * TPC) * 64;
+        const float *ga = aux + (int64_t)min(c, chunks - 1) * TPC * 64;
 #pragma unroll
         for (int i = 0; i < LA; ++i) {                                         // (fewer tiles than wavefronts: some fetch the same)
             const int tile = (wave + 4 * i) % TPC;
@@ -912,46 +856,27 @@ __global__ __launch_bounds__(kThreads, WPE) void k_rank_mfma(FilterArgs f, RankI
         asm volatile("s_waitcnt vmcnt(0)" : : : "memory");
         return;
     }
-    for (int c0 = 0; c0 < chunks; c0 += CPT) {
-#pragma unroll
-        for (int cc = 0; cc < CPT; ++cc) {
-            const int c = c0 + cc;
-            // this wavefront's quarter of chunk c has landed when at most the later NB - 2 chunks' loads are outstanding
-            __builtin_amdgcn_sched_barrier(0);
-            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((NB - 2) * (LW + LA)) : "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            fetch(c + NB - 1, (c + NB - 1) % NB);          // over the chunk that every wavefront is done with
-            if (!works) continue;
-            const uint4 (*chunk)[64] = s_ring[c % NB];
-            if (CPT > 1) {
-                if (cc == 0) begin_tile(s_aux[c % NB][0]);
-#pragma unroll
-                for (int k = 0; k < CK; ++k) {
-                    const half8 e8 = __builtin_bit_cast(half8, chunk[k][lane]);
-#pragma unroll
-                    for (int q = 0; q < QF; ++q)
-                        acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(e8, qf[q][cc * CK + k], acc[q], 0, 0, 0);
-                }
-            } else {
+    for (int c = 0; c < chunks; ++c) {
+        // this wavefront's quarter of chunk c has landed when at most the later NB - 2 chunks' loads are outstanding
+        __builtin_amdgcn_sched_barrier(0);
+        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" : : "n"((NB - 2) * (LW + LA)) : "memory");
+        __builtin_amdgcn_sched_barrier(0);
+        fetch(c + NB - 1, (c + NB - 1) % NB);              // over the chunk that every wavefront is done with
+        if (!works) continue;
+        const uint4 (*chunk)[64] = s_ring[c % NB];
 #pragma unroll 1
-                for (int tt = part; tt < TPC; tt += parts) {
-                    t = t0 + c * TPC + tt;
-                    if (t >= t1) break;
-                    begin_tile(s_aux[c % NB][tt]);
+        for (int tt = part; tt < TPC; tt += parts) {
+            t = t0 + c * TPC + tt;
+            if (t >= t1) break;
+            begin_tile(s_aux[c % NB][tt]);
 #pragma unroll
-                    for (int k = 0; k < KS; ++k) {
-                        const half8 e8 = __builtin_bit_cast(half8, chunk[tt * KS + k][lane]);
+            for (int k = 0; k < KS; ++k) {
+                const half8 e8 = __builtin_bit_cast(half8, chunk[tt * KS + k][lane]);
 #pragma unroll
-                        for (int q = 0; q < QF; ++q)
-                            acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(e8, qf[q][k], acc[q], 0, 0, 0);
-                    }
-                    end_tile();
-                }
+                for (int q = 0; q < QF; ++q)
+                    acc[q] = __builtin_amdgcn_mfma_f32_32x32x16_f16(e8, qf[q][k], acc[q], 0, 0, 0);
             }
-        }
-        if (CPT > 1 && works) {
             end_tile();
-            ++t;
         }
     }
     asm volatile("s_waitcnt vmcnt(0)" : : : "memory");     // (loads into LDS still in flight must not outlive the workgroup)
@@ -1000,8 +925,8 @@ __global__ __launch_bounds__(kThreads * KH, 2) void k_rank_wide(FilterArgs f, Ra
     const int t0 = (int)blockIdx.y * f.slice, t1 = min(t0 + f.slice, tiles);
     const uint4 *src = f.ef + ((int64_t)z * tiles + t0) * KS * 64 + wave * LW * 64 + lane;
     const int chunks = (t1 - t0) * CPT;
-    const uint32_t ring = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&s_ring[0][0][0];
-    const uint32_t ring_aux = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void *)&s_aux[0][0];
+    const uint32_t ring = lds_at(&s_ring[0][0][0]);
+    const uint32_t ring_aux = lds_at(&s_aux[0][0]);
     const float *aux = f.eaux + ((int64_t)z * tiles + t0) * 64 + lane;
     auto fetch = [&](int c, int slot) {                                        // (past the end: the last chunk once more)
         const int at = min(c, chunks - 1);

@@ -32,8 +32,6 @@ typedef float floatx16 __attribute__((ext_vector_type(16)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef int intx16 __attribute__((ext_vector_type(16)));
 
-constexpr float kUnit = 5.9604645e-8f; // 2^-24
-constexpr float kWideMax = 32639.f;    // see stx_rank_filter.hip
 constexpr int kPairBlock = 64;         // undecided pairs of one relation that are projected together
 constexpr int kAux = 64;               // floats that go with a tile of 32 entities: of the table, and of a relation
 
@@ -70,35 +68,6 @@ struct RrArgs {
 };
 
 // ---- operands -------------------------------------------------------------------------------------------------
-__device__ inline void rr_load(const float *p, int j, int dim, float (&v)[8])
-{
-    const bool in = j < dim;                               // (rows are whole pieces)
-    const float4 x = in ? ld4(p + j) : make_float4(0.f, 0.f, 0.f, 0.f), y = in ? ld4(p + j + 4) : make_float4(0.f, 0.f, 0.f, 0.f);
-    v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w; v[4] = y.x; v[5] = y.y; v[6] = y.z; v[7] = y.w;
-}
-// A row's elements j .. j + 15, scaled, as 16-bit fixed point in high and (signed) low bytes; adds the squares of the scaled
-// values, of the roundings and of the low bytes.
-__device__ inline void rr_bytes(const float (&a)[8], const float (&b)[8], float sc, uint4 &hi, uint4 &lo, float &n2, float &d2, float &l2)
-{
-    uint32_t h[4], l[4];
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-        h[w] = l[w] = 0u;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float x = (w < 2 ? a[4 * (w & 1) + i] : b[4 * (w & 1) + i]) * sc;
-            const float r = fminf(fmaxf(rintf(x), -kWideMax), kWideMax), d = x - r;
-            n2 = __builtin_fmaf(x, x, n2);
-            d2 = __builtin_fmaf(d, d, d2);
-            const int n = (int)r, s = (int)(int8_t)n;
-            l2 += (float)(s * s);
-            l[w] |= ((uint32_t)s & 0xffu) << (8 * i);
-            h[w] |= ((uint32_t)((n - s) >> 8) & 0xffu) << (8 * i);
-        }
-    }
-    hi = make_uint4(h[0], h[1], h[2], h[3]);
-    lo = make_uint4(l[0], l[1], l[2], l[3]);
-}
 // Eight elements as fp16 and the fp16 of what that leaves: 22 bits.
 __device__ inline void rr_split(const float (&v)[8], float sc, uint4 &hi, uint4 &lo)
 {
@@ -151,7 +120,7 @@ __global__ __launch_bounds__(kThreads) void k_rr_pack(RrArgs f, int etiles)
     for (int q = l8; q < 2 * KS; q += 8) {
         float v[8];
         uint4 hi, lo;
-        rr_load(p, q * 8, dim, v);
+        load8(p, q * 8, dim, v);
         rr_split(v, ok ? sp : 0.f, hi, lo);
         if (!in) hi = lo = make_uint4(0u, 0u, 0u, 0u);
         ds[(q >> 1) * 128 + u + 32 * (q & 1)] = hi;
@@ -165,11 +134,11 @@ __global__ __launch_bounds__(kThreads) void k_rr_pack(RrArgs f, int etiles)
     float n2 = 0.f, d2 = 0.f, l2 = 0.f;
     uint4 *dw = f.ew + (int64_t)tile * KS * 64;
     for (int q = l8; q < KS; q += 8) {                     // sixteen elements
-        float a[8], b[8];
+        float v[16];
         uint4 hi, lo;
-        rr_load(p, q * 16, dim, a);
-        rr_load(p, q * 16 + 8, dim, b);
-        rr_bytes(a, b, ok ? sw : 0.f, hi, lo, n2, d2, l2);
+        load8(p, q * 16, dim, *(float (*)[8])v);
+        load8(p, q * 16 + 8, dim, *(float (*)[8])(v + 8));
+        wide_piece(v, ok ? sw : 0.f, hi, lo, n2, d2, l2);
         if (!in) hi = lo = make_uint4(0u, 0u, 0u, 0u);
         dw[(q >> 1) * 128 + u + 32 * (q & 1)] = hi;
         dw[(q >> 1) * 128 + 64 + u + 32 * (q & 1)] = lo;
@@ -385,14 +354,11 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_query(RrArgs f)
     float n2 = 0.f, d2 = 0.f, l2 = 0.f;
     uint4 *dst = f.qf + (int64_t)(f.b0 + blockIdx.x) * KS * 64;
     for (int p = l8; p < KS; p += 8) {
-        float a[8], b[8];
+        float x[16];
         uint4 hi, lo;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            a[i] = p * 16 + i < dim ? v[p * 16 + i] : 0.f;
-            b[i] = p * 16 + 8 + i < dim ? v[p * 16 + 8 + i] : 0.f;
-        }
-        rr_bytes(a, b, ok ? sc : 0.f, hi, lo, n2, d2, l2);
+        for (int i = 0; i < 16; ++i) x[i] = p * 16 + i < dim ? v[p * 16 + i] : 0.f;
+        wide_piece(x, ok ? sc : 0.f, hi, lo, n2, d2, l2);
         dst[(p >> 1) * 128 + u + 32 * (p & 1)] = hi;
         dst[(p >> 1) * 128 + 64 + u + 32 * (p & 1)] = lo;
     }
@@ -422,21 +388,6 @@ __global__ __launch_bounds__(kThreads, 2) void k_rr_query(RrArgs f)
     par[0] = p0;
     par[1] = p1;
 }
-
-// ---- direct loads into LDS (as in stx_rank_filter.hip) --------------------------------------------------------
-__device__ inline void rr_lds_1k(const void *g, uint32_t lds)
-{
-    uint32_t m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0) : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
-}
-__device__ inline void rr_lds_256(const void *g, uint32_t lds)
-{
-    uint32_t m0;
-    asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dword %1, off\n\ts_mov_b32 m0, %0"
-                 : "=&s"(m0) : "v"(g), "s"(__builtin_amdgcn_readfirstlane(lds)) : "memory");
-}
-__device__ inline uint32_t rr_lds_at(const void *p) { return (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) void *)p; }
 
 // ---- |M e|^2 --------------------------------------------------------------------------------------------------
 // A wavefront keeps EF tiles of 32 entities in registers and its workgroup streams matrices past them, 32 outputs a chunk:
@@ -474,11 +425,11 @@ __global__ __launch_bounds__(kThreads, KS == 16 ? 1 : 2) void k_rr_norms(RrArgs 
         for (int i = 0; i < KS; ++i) asm volatile("" : "+v"(eh[q][i]), "+v"(el[q][i]));
     }
     const uint4 *src = f.ms + (int64_t)s0 * kt * KS * 128 + wave * LW * 64 + lane;
-    const uint32_t ring = rr_lds_at(&s_ring[0][0][0]);
+    const uint32_t ring = lds_at(&s_ring[0][0][0]);
     auto fetch = [&](int c, int slot) {                    // (past the end: the last chunk once more)
         const uint4 *g = src + (int64_t)min(c, chunks - 1) * CK * 64;
 #pragma unroll
-        for (int i = 0; i < LW; ++i) rr_lds_1k(g + i * 64, ring + (uint32_t)((slot * CK + wave * LW + i) * 1024));
+        for (int i = 0; i < LW; ++i) load_lds_1k(g + i * 64, ring + (uint32_t)((slot * CK + wave * LW + i) * 1024));
     };
 #pragma unroll
     for (int c = 0; c < NB - 1; ++c) fetch(c, c);
@@ -575,20 +526,20 @@ __global__ __launch_bounds__(kThreads, KS <= 4 ? 1 : 2) void k_rr_sweep(RrArgs f
     const int first = __builtin_amdgcn_readfirstlane(blk.first), count = __builtin_amdgcn_readfirstlane(blk.count);
     const uint4 *src = f.ew + (int64_t)t0 * KS * 64 + wave * LW * 64 + lane;
     const float *aux = f.eaux + (int64_t)t0 * kAux + lane, *nn = f.nn + ((int64_t)slot * tiles + t0) * kAux + lane;
-    const uint32_t ring = rr_lds_at(&s_ring[0][0][0]), ring_aux = rr_lds_at(&s_aux[0][0][0]), ring_nn = rr_lds_at(&s_nn[0][0][0][0]);
+    const uint32_t ring = lds_at(&s_ring[0][0][0]), ring_aux = lds_at(&s_aux[0][0][0]), ring_nn = lds_at(&s_nn[0][0][0][0]);
     const int last = t1 - t0 - 1;
     auto fetch = [&](int c, int at) {                      // (past the end: the last chunk or tile once more)
         const uint4 *g = src + (int64_t)min(c, chunks - 1) * CK * 64;
 #pragma unroll
-        for (int i = 0; i < LW; ++i) rr_lds_1k(g + i * 64, ring + (uint32_t)((at * CK + wave * LW + i) * 1024));
+        for (int i = 0; i < LW; ++i) load_lds_1k(g + i * 64, ring + (uint32_t)((at * CK + wave * LW + i) * 1024));
 #pragma unroll
         for (int i = 0; i < LA; ++i) {
             const int tile = (wave + 4 * i) % TPC;
-            rr_lds_256(aux + (int64_t)min(c * TPC + tile, last) * kAux, ring_aux + (uint32_t)((at * TPC + tile) * kAux * 4));
+            load_lds_256(aux + (int64_t)min(c * TPC + tile, last) * kAux, ring_aux + (uint32_t)((at * TPC + tile) * kAux * 4));
         }
 #pragma unroll
         for (int i = 0; i < TPC; ++i)
-            rr_lds_256(nn + (int64_t)min(c * TPC + i, last) * kAux, ring_nn + (uint32_t)(((at * 4 + wave) * TPC + i) * kAux * 4));
+            load_lds_256(nn + (int64_t)min(c * TPC + i, last) * kAux, ring_nn + (uint32_t)(((at * 4 + wave) * TPC + i) * kAux * 4));
     };
     int less = 0, cnt = 0;
     bool listing = true;                                   // until there are too many undecided pairs
