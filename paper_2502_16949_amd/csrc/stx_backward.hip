@@ -328,8 +328,9 @@ __global__ __launch_bounds__(kThreads) void k_seg_records(const int32_t *__restr
 // comes through scalar loads and runs on the scalar unit, and an active entry takes two 256-byte loads and four vector
 // instructions.  Bound by the L2 caches' rate for such rows (16 TB/s when every pair is active).  With 16 lanes of a float4
 // per entry, four entries side by side and their columns and flags broadcast by shuffles, the vector units were busy three
-// quarters of the time with everything but the sums: 393,216 positives at d = 1024 took 1,057 us a step (mean of 30
-// steps) and take 665 (1,109 while every pair is active, 530 when half of them are).
+// quarters of the time with everything but the sums.  This kernel at 393,216 positives, d = 1024, from a fresh table on: 1,197
+// us before and 1,112 now while every pair is active; 1,054 and 615 as the mean of the first 30 steps; 926 and 412 in the
+// 120th.
 // The slices are dealt to the eight dies, each of which keeps its own one or two in its L2 cache.
 template <int DIST>
 __global__ __launch_bounds__(kThreads, 8) void k_seg_formed(const FormedRecord *__restrict__ recs, const FormedHead *__restrict__ hds,
@@ -779,8 +780,8 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
     }
     const int ld_tab = d4 * 4;
     // (Launches with a ride hold whole rows, but a step of 1,024 positives at d = 32 takes 19.47 us without this test in them
-    // and 19.31 with it.)
-    if (RIDE != 0 && gridDim.y > 1) {
+    // and 19.31 with it; of 262,144 x 5 at d = 128, ride 4, 569.5 without and 570.6 with it.)
+    if (RIDE != 0 && RIDE != 4 && gridDim.y > 1) {
         const int c4 = (int)blockIdx.y * LPR;
         d4 = min(LPR, d4 - c4);
         if (out_rows) out_rows += 4 * c4;
