@@ -438,10 +438,13 @@ inline bool formed_rows(const stx_ctx *c, int64_t n_rows)
 {
     const bool stacked = c->cfg.model == STX_TRANSE || c->cfg.model == STX_TORUSE;
     const int64_t cols = c->cfg.n_ent + c->cfg.n_rel, row = (int64_t)c->cfg.dim * 4;
-    // (rows of fewer slices: the launches more and the update of its own take longer to repay.  14,951 entities, L2, a step
-    // with stored and with formed rows at 202 MiB of them: d = 128 235 and 239 us, d = 256 231 and 222, d = 512 234 and 207;
-    // at 480 MiB: d = 68 769 and 882, d = 100 632 and 605, d = 128 550 and 474, d = 256 514 and 416; 22,000 entities, whose
-    // slices are 5.7 MiB: d = 512 508 and 397)
+    // (Rows of fewer slices: the launches more and the update of its own take longer to repay.  14,951 entities, L2, us a step
+    // with stored rows, with formed ones while every pair is active, and with formed ones once half of them are: d = 128 at
+    // 202 MiB of rows 233, 231 and 189, at 300 MiB 328, 308 and 246, at 384 MiB 435, 377 and 297; d = 256 at 128 MiB 136, 161
+    // and 136, at 202 MiB 235, 215 and 175; d = 512 at 128 MiB 157, 150 and 127, at 202 MiB 227, 194 and 157; d = 1024 at
+    // 128 MiB 156, 160 and 139, at 202 MiB 220, 205 and 172.  So the lines lie where rows are formed faster whatever the share
+    // of active pairs, at d = 128 well behind that point.  d = 100 at 480 MiB 629, 555 and 436; 40,000 entities, whose slices
+    // are 10 MiB, d = 512 at 480 MiB 544, 397 and 310: both outside the lines.)
     const int64_t least = (int64_t)(c->cfg.dim >= 256 ? 192 : 384) << 20;
     return stacked && !packed_grad(c) && cols * 256 <= ((int64_t)6 << 20) && c->cfg.dim >= 128 && n_rows * row >= least &&
            // room in the buffer of those rows for what replaces them: coefficients, sorted records, their heads, gradient rows

@@ -1082,10 +1082,14 @@ size_t rank_filter_q_bytes(int dist, int width, int64_t queries)
     return b > (size_t)4 << 20 ? b : (size_t)4 << 20;
 }
 // Both sides as measured at 230 sizes over rows of 16 to 1,000 floats, tables of 1,000 to 1,500,000 entities and 1 to
-// 59,071 queries, in us a side; the rule took the slower filter at none of them.  The plain sweep: a serial walk of the row by the kernel of the true sums, then its steps, padded to
+// 59,071 queries, in us a side; the rule took the slower filter at none of them.  Rows above 256 floats were measured with
+// fp16 operands; k_rank_wide takes about half of that, so the rule still takes no slower filter there, but leaves calls of
+// few queries and long tables plain that would gain (128 queries x 150,001 at d = 400: 460 plain, 290 filtered).
+// The plain sweep: a serial walk of the row by the kernel of the true sums, then its steps, padded to
 // 128 queries and 32 floats.  The filter: launches and dependent passes for every chunk of queries that its scratch
 // holds, a little per query, then its steps; the matrix-core kinds also pack the table, which few queries do not repay
-// once it is past the caches (128 queries x 700,000 at d = 544: 2,290 plain, 2,790 filtered), and a small table gives
+// once it is past the caches (128 queries x 700,000 at d = 544: 2,010 plain, 2,245 filtered; 20 x 300,001 at d = 400: 680
+// and 465), and a small table gives
 // the fixed-point sweep too few candidates to share a query's load (8,000 x 1,000 at d = 256, L1: 177 plain, 597
 // filtered; 59,071 x 15,000 at d = 128: 3,850 and 1,950).
 bool rank_filter_pays(int dist, int64_t queries, int64_t n_ent, int width, size_t q_bytes)
