@@ -73,8 +73,8 @@ Layout make_layout(const stx_config *c)
     for (int i = 0; i < 3; ++i) L.keys[i] = take((size_t)L.nnz_max * 4);
     for (int i = 0; i < 2; ++i) L.pay[i] = take((size_t)L.nnz_max * 4);
     for (int i = 0; i < 2; ++i) L.cix[i] = take((size_t)L.nnz_max * 4);
-    L.table = take((size_t)256 * L.ntiles_max * 4);
-    L.table1 = take((size_t)256 * L.ntiles_max * 4);
+    L.table = take((size_t)256 * L.ntiles_max * 2);
+    L.table1 = take((size_t)256 * L.ntiles_max * 2);
     L.super = take((size_t)256 * (L.ntiles_max / kSuperTile + 1) * 4);
     L.tile_heads = take((size_t)(L.ntiles_max + 1) * 4);
     L.loss_partials = take((size_t)(L.fwd_blocks_max + 1) * 4);
@@ -201,8 +201,8 @@ stx_status stx_create(const stx_config *cfg, void *workspace, size_t workspace_b
     c->ctrl = (int32_t *)(base + L.ctrl);
     for (int i = 0; i < 3; ++i) c->keys[i] = (int32_t *)(base + L.keys[i]);
     for (int i = 0; i < 2; ++i) c->pay[i] = (int32_t *)(base + L.pay[i]);
-    c->table = (int32_t *)(base + L.table);
-    c->table1 = (int32_t *)(base + L.table1);
+    c->table = (uint16_t *)(base + L.table);
+    c->table1 = (uint16_t *)(base + L.table1);
     for (int i = 0; i < 2; ++i) c->cix[i] = (int32_t *)(base + L.cix[i]);
     c->cix_cur = 0;
     c->super = (int32_t *)(base + L.super);

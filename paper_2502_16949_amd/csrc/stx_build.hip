@@ -68,7 +68,7 @@ __global__ __launch_bounds__(kThreads) void k_emit(EmitArgs a)
 
 template <int ITEMS>
 __global__ __launch_bounds__(kThreads) void k_hist(const int32_t *__restrict__ keys, int32_t nnz, int shift,
-                                                   int radix, int32_t *__restrict__ table)
+                                                   int radix, uint16_t *__restrict__ table)
 {
     hist_body<ITEMS>((int)blockIdx.x, keys, nnz, shift, radix, table);
 }
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kThreads) void k_hist(const int32_t *__restrict__ k
 // With many tiles the scatter workgroups cannot each read the whole table.  This kernel adds the tile
 // histograms up in groups of kSuperTile tiles: super[g][digit] = sum over the tiles of group g.  A
 // scatter workgroup then needs its group's earlier tiles plus one row per group.
-__global__ __launch_bounds__(kThreads) void k_super_sums(const int32_t *__restrict__ table, int radix, int ntiles,
+__global__ __launch_bounds__(kThreads) void k_super_sums(const uint16_t *__restrict__ table, int radix, int ntiles,
                                                          int32_t *__restrict__ super)
 {
     const int tid = threadIdx.x, t0 = blockIdx.x * kSuperTile, t1 = min(t0 + kSuperTile, ntiles);

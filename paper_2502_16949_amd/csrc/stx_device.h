@@ -13,23 +13,44 @@
 
 namespace stx {
 
+// Wavefront-uniform values (kernel arguments) that are to be in scalar registers here.  Argument loads return in no order, so
+// each wait is for all of them; side by side they cost one.
+template <class... T>
+__device__ __forceinline__ void together(const T... v) { (..., [](const T x) { asm volatile("" ::"s"(x)); }(v)); }
+#define STX_TOGETHER(...) stx::together(__VA_ARGS__)
+
+// Inclusive prefix sum of one value per lane across a wavefront, by data-parallel moves between lanes (all lanes active).
+__device__ inline int32_t wave_inclusive_scan(int32_t v)
+{
+    v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);   // from 1, 2, 4 and 8 lanes below in a row of 16
+    v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+    v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);   // the last lane of rows 0 and 2 into rows 1 and 3 ...
+    v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);   // ... and lane 31 into rows 2 and 3
+    return v;
+}
+
 // Exclusive prefix sum of one value per thread across a 256-thread workgroup; *total (shared or
-// register, may be null) receives the sum.  All 256 threads must call it.
+// register, may be null) receives the sum.  All 256 threads must call it.  Two barriers; with every doubling of the
+// distance a round through LDS, as it was, sixteen: 1.0 us of a scatter pass's 9.1.
 __device__ inline int32_t block_exclusive_scan(int32_t v, int32_t *total)
 {
-    __shared__ int32_t s_scan[256];
-    const int tid = threadIdx.x;
-    __syncthreads();   // protect s_scan against a previous use
-    s_scan[tid] = v;
+    __shared__ int32_t s_wave[4];
+    const int w = threadIdx.x >> 6;
+    const int32_t incl = wave_inclusive_scan(v);
+    __syncthreads();   // protect s_wave against a previous use
+    if ((threadIdx.x & 63) == 63) s_wave[w] = incl;
     __syncthreads();
-    for (int off = 1; off < 256; off <<= 1) {
-        int32_t a = tid >= off ? s_scan[tid - off] : 0;
-        __syncthreads();
-        s_scan[tid] += a;
-        __syncthreads();
+    int32_t before = 0, sum = 0;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int32_t t = s_wave[u];
+        before += u < w ? t : 0;
+        sum += t;
     }
-    if (total) *total = s_scan[255];
-    return s_scan[tid] - v;
+    if (total) *total = sum;
+    return before + incl - v;
 }
 
 // The lanes of the wavefront (among those with `valid`) whose digit equals this lane's: one ballot per bit of the

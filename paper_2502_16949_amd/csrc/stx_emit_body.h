@@ -31,7 +31,7 @@ __device__ inline void emit_body(const int block, const int nblocks, const EmitA
     float *__restrict__ vals = a.vals;
     int32_t *__restrict__ keys = a.keys;
     const int radix = a.radix;
-    int32_t *__restrict__ table = a.table;
+    uint16_t *__restrict__ table = a.table;
     int32_t *__restrict__ ctrl = a.ctrl;
     const ColMap &map = a.map;
     const RelCnt &rc = a.rc;
@@ -112,7 +112,7 @@ __device__ inline void emit_body(const int block, const int nblocks, const EmitA
         }
     }
     __syncthreads();
-    if (tid < radix) table[block * radix + tid] = s_hist[tid];
+    if (tid < radix) table[block * radix + tid] = (uint16_t)s_hist[tid];
     if (MAP) {
         for (int w = tid; w < map.words; w += kThreads) {
             const uint32_t v = s_map[w];

@@ -88,7 +88,8 @@ struct EmitArgs {
     float *vals;
     int32_t *keys;
     int radix, ntiles;
-    int32_t *table, *ctrl;
+    uint16_t *table;               // [tile][digit], as everywhere: a tile's counts fit 16 bits
+    int32_t *ctrl;
     ColMap map;
     RelCnt rc;
     int32_t *colidx2;              // a second copy of colidx, kept by the context (see stx_ctx::cix), or null
@@ -100,7 +101,8 @@ struct ScatterArgs {
     int32_t *keys_out, *pay_out;
     int32_t nnz;
     int shift, bits, ntiles;
-    const int32_t *table, *super;
+    const uint16_t *table;
+    const int32_t *super;
 };
 
 // Arguments of a histogram pass of the sort (a later digit).
@@ -108,7 +110,7 @@ struct HistArgs {
     const int32_t *keys;
     int32_t nnz;
     int shift, radix;
-    int32_t *table;
+    uint16_t *table;
     int ntiles;
 };
 
@@ -194,8 +196,8 @@ struct stx_ctx {
     int32_t *ctrl;
     int32_t *keys[3];              // [0], [1]: ping-pong of the sort; [2]: the unsorted keys of the batch being built
     int32_t *pay[2];
-    int32_t *table;                // [256 * ntiles_max] tile histograms of the first digit (written by k_emit)
-    int32_t *table1;               // ... and of the later digits: a next batch's first kernel may run beside them
+    uint16_t *table;               // [256 * ntiles_max] tile histograms of the first digit (written by k_emit)
+    uint16_t *table1;              // ... and of the later digits: a next batch's first kernel may run beside them
     int32_t *cix[2];               // copies of A's column ids that the forward pass of stx_train_step reads: the
     int cix_cur;                   // next batch's first kernel may overwrite the caller's arrays meanwhile
     int32_t *super;                // [256 * (ntiles_max / kSuperTile + 1)] group sums of the tile histograms

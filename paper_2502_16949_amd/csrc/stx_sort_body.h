@@ -11,7 +11,7 @@ namespace stx {
 // Tile histograms of the digit at `shift` for the later passes.
 template <int ITEMS>
 __device__ inline void hist_body(const int block, const int32_t *__restrict__ keys, int32_t nnz, int shift,
-                                 int radix, int32_t *__restrict__ table)
+                                 int radix, uint16_t *__restrict__ table)
 {
     __shared__ int32_t s_hist[256];
     const int tid = threadIdx.x;
@@ -22,7 +22,7 @@ __device__ inline void hist_body(const int block, const int32_t *__restrict__ ke
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
         const int32_t e = base + it * kThreads + tid;
-        kv[it] = e < nnz ? keys[e] : 0;
+        kv[it] = keys[min(e, nnz - 1)];
     }
     // The lanes of a wavefront that hold the same digit are found by a ballot per bit, and one of them adds their
     // number: power-law keys put many lanes on one counter, and LDS serialises atomics on one address.
@@ -36,7 +36,7 @@ __device__ inline void hist_body(const int block, const int32_t *__restrict__ ke
         if (valid && ((m >> lane) >> 1) == 0) atomicAdd(&s_hist[dgt], (int32_t)__popcll(m));   // highest lane of its class
     }
     __syncthreads();
-    if (tid < radix) table[block * radix + tid] = s_hist[tid];
+    if (tid < radix) table[block * radix + tid] = (uint16_t)s_hist[tid];
 }
 
 // Stable scatter of one tile by the digit at `shift`.  Element order inside a tile is
@@ -58,7 +58,7 @@ __device__ inline void scatter_body(const int block, const ScatterArgs &a, unsig
     int32_t *__restrict__ pay_out = a.pay_out;
     const int32_t nnz = a.nnz;
     const int shift = a.shift, bits = a.bits, ntiles = a.ntiles;
-    const int32_t *__restrict__ table = a.table;
+    const uint16_t *__restrict__ table = a.table;
     const int32_t *__restrict__ super = a.super;
     int32_t *s_goff, (*s_hist)[256], *s_tot, *s_bel;
     if constexpr (ARENA) {
@@ -80,16 +80,13 @@ __device__ inline void scatter_body(const int block, const ScatterArgs &a, unsig
 #pragma unroll
         for (int it = 0; it < ITEMS; ++it) {             // all loads at once, so that they are in flight together
             const int32_t e = wave_base + it * 64 + lane;
-            const bool valid = e < nnz;
-            key[it] = valid ? keys_in[e] : 0;
-            pay[it] = FIRST ? e : (valid ? pay_in[e] : 0);
+            const int32_t f = min(e, nnz - 1);           // (past the end: the last one again, without a branch)
+            key[it] = keys_in[f];
+            pay[it] = FIRST ? e : pay_in[f];
         }
     };
-    // Large sorts: the tile's keys are requested before the offsets are derived from the histogram tables (a dozen
-    // dependent round trips with the two-level table), so that the two waits overlap.  The small sorts share
-    // launches with kernels that are capped at 64 registers and keep the order that needs fewer of them.
-    constexpr bool EARLY = ITEMS > kSortItems && !ARENA;
-    if constexpr (EARLY) load_items();
+    // The tile's keys are requested before the offsets are derived from the histogram tables, so that the two waits overlap.
+    load_items();
     if (TWO_LEVEL) {
         int32_t below = 0, total = 0;
         if (tid < radix) {
@@ -117,39 +114,59 @@ __device__ inline void scatter_body(const int block, const ScatterArgs &a, unsig
         int32_t base = block_exclusive_scan(total, nullptr);
         s_goff[tid] = base + below;
     } else {
-        // All 256 threads share the table: a thread owns four neighbouring digits (one 16-byte load per
-        // tile row) and every `parts`-th tile; up to SCAN loads are in flight per thread (few enough registers
-        // that this body does not lower the occupancy of the kernels it shares launches with).
+        // All 256 threads share the table: a thread owns eight neighbouring digits (one 16-byte load per tile row: a tile's
+        // counts fit 16 bits) and every `parts`-th tile, eight loads in flight.  Two counts a word are added at a time, for as
+        // many rows as cannot carry from one into the other.  (With counts of 32 bits the scan of 192 rows was 3.9 us of a
+        // scatter pass's 9.1.)
         const int me = block;
         int32_t below = 0, total = 0;
-        if (radix >= 4) {
-            const int r4 = radix >> 2, parts = kThreads / r4, d4 = tid % r4, q = tid / r4;
-            int4 tot = make_int4(0, 0, 0, 0), bel = make_int4(0, 0, 0, 0);
-            constexpr int SCAN = 8;
-            for (int t0 = q; t0 < ntiles; t0 += SCAN * parts) {
-                int4 v[SCAN];
+        if (radix >= 8) {
+            // (rows added two counts a word before they are taken apart: the tables of most batches of small tiles in one go,
+            // as the sums of 32 bits that would wait meanwhile are registers that lower the occupancy of the launches this
+            // body shares with others)
+            constexpr int SCAN = 8, TILE = kThreads * ITEMS, ROWS = 65535 / TILE / SCAN * SCAN;
+            static_assert(ROWS >= SCAN, "no carry between the two counts of a word");
+            const int r8 = radix >> 3, sh = 31 - __clz(r8), parts = kThreads >> sh, d8 = tid & (r8 - 1), q = tid >> sh;
+            for (int t1 = 0; t1 < ntiles; t1 += ROWS * parts) {
+                uint4 s4 = make_uint4(0u, 0u, 0u, 0u), b4 = s4;
+                for (int t0 = t1 + q; t0 < min(ntiles, t1 + ROWS * parts); t0 += SCAN * parts) {
+                    uint4 v[SCAN];
 #pragma unroll
-                for (int u = 0; u < SCAN; ++u) {
-                    const int t = t0 + u * parts;
-                    v[u] = t < ntiles ? *reinterpret_cast<const int4 *>(table + t * radix + 4 * d4)
-                                      : make_int4(0, 0, 0, 0);
+                    for (int u = 0; u < SCAN; ++u)         // (a row past the last one: the last one again, not added)
+                        v[u] = *reinterpret_cast<const uint4 *>(table + min(t0 + u * parts, ntiles - 1) * radix + 8 * d8);
+#pragma unroll
+                    for (int u = 0; u < SCAN; ++u) {
+                        const int t = t0 + u * parts;
+                        if (t < ntiles) { s4.x += v[u].x; s4.y += v[u].y; s4.z += v[u].z; s4.w += v[u].w; }
+                        if (t < me) { b4.x += v[u].x; b4.y += v[u].y; b4.z += v[u].z; b4.w += v[u].w; }
+                    }
                 }
+                int32_t tot[8] = {(int32_t)(s4.x & 0xffffu), (int32_t)(s4.x >> 16), (int32_t)(s4.y & 0xffffu), (int32_t)(s4.y >> 16),
+                                  (int32_t)(s4.z & 0xffffu), (int32_t)(s4.z >> 16), (int32_t)(s4.w & 0xffffu), (int32_t)(s4.w >> 16)};
+                int32_t bel[8] = {(int32_t)(b4.x & 0xffffu), (int32_t)(b4.x >> 16), (int32_t)(b4.y & 0xffffu), (int32_t)(b4.y >> 16),
+                                  (int32_t)(b4.z & 0xffffu), (int32_t)(b4.z >> 16), (int32_t)(b4.w & 0xffffu), (int32_t)(b4.w >> 16)};
+                for (int m = r8; m < 64; m <<= 1) {        // the parts that share a wavefront
 #pragma unroll
-                for (int u = 0; u < SCAN; ++u) {
-                    const int t = t0 + u * parts;
-                    tot.x += v[u].x; tot.y += v[u].y; tot.z += v[u].z; tot.w += v[u].w;
-                    if (t < me) { bel.x += v[u].x; bel.y += v[u].y; bel.z += v[u].z; bel.w += v[u].w; }
+                    for (int u = 0; u < 8; ++u) { tot[u] += __shfl_xor(tot[u], m, 64); bel[u] += __shfl_xor(bel[u], m, 64); }
+                }
+                if (lane < r8) {
+                    int32_t *pt = &s_tot[w * radix + 8 * d8], *pb = &s_bel[w * radix + 8 * d8];
+#pragma unroll
+                    for (int u = 0; u < 8; ++u) {
+                        pt[u] = t1 == 0 ? tot[u] : pt[u] + tot[u];
+                        pb[u] = t1 == 0 ? bel[u] : pb[u] + bel[u];
+                    }
                 }
             }
-            *reinterpret_cast<int4 *>(&s_tot[q * radix + 4 * d4]) = tot;
-            *reinterpret_cast<int4 *>(&s_bel[q * radix + 4 * d4]) = bel;
             __syncthreads();
-            if (tid < radix)
-                for (int qq = 0; qq < parts; ++qq) {
-                    total += s_tot[qq * radix + tid];
-                    below += s_bel[qq * radix + tid];
+            if (tid < radix) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    total += s_tot[u * radix + tid];
+                    below += s_bel[u * radix + tid];
                 }
-        } else if (tid < radix) {   // two bins only
+            }
+        } else if (tid < radix) {   // two or four bins only
             for (int t = 0; t < ntiles; ++t) {
                 const int32_t v = table[t * radix + tid];
                 total += v;
@@ -161,7 +178,6 @@ __device__ inline void scatter_body(const int block, const ScatterArgs &a, unsig
     }
     __syncthreads();
 
-    if constexpr (!EARLY) load_items();
 #pragma unroll
     for (int it = 0; it < ITEMS; ++it) {
         int32_t e = wave_base + it * 64 + lane;

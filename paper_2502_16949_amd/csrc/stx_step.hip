@@ -27,6 +27,7 @@ __global__ __launch_bounds__(kThreads) void k_fwd_scatter(ForwardArgs fa, Scatte
 {
     __shared__ __align__(16) unsigned char s_arena[kRideLds];   // one block of LDS for the sort's bodies
     int block = (int)blockIdx.x;
+    STX_TOGETHER(sa.ntiles, ea.ntiles, fa.colidx, fa.X, fa.b, fa.k, fa.dim, fa.scores, fa.G, fa.gstride, fa.rel_weight);
     if (block < sa.ntiles) { scatter_body<FIRST, false, kSortItems, true>(block, sa, s_arena); return; }
     block -= sa.ntiles;
     if constexpr (!FIRST) {
@@ -41,6 +42,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_fwdh_scatter(TranshArgs ta, Sca
 {
     __shared__ __align__(16) unsigned char s_arena[kRideLds];
     int block = (int)blockIdx.x;
+    STX_TOGETHER(sa.ntiles, ea.ntiles, ta.colidx, ta.E, ta.D, ta.W, ta.n_ent, ta.b, ta.k, ta.dim, ta.scores, ta.GX, ta.GY, ta.GW);
     if (block < sa.ntiles) { scatter_body<FIRST, false, kSortItems, true>(block, sa, s_arena); return; }
     block -= sa.ntiles;
     if constexpr (!FIRST) {
@@ -51,7 +53,7 @@ __global__ __launch_bounds__(kThreads, 4) void k_fwdh_scatter(TranshArgs ta, Sca
 }
 
 __global__ __launch_bounds__(kThreads) void k_hist_finish(const int32_t *__restrict__ keys, int32_t nnz, int shift,
-                                                          int radix, int32_t *__restrict__ table,
+                                                          int radix, uint16_t *__restrict__ table,
                                                           const float *__restrict__ partials, int n_partials,
                                                           float scale, float *__restrict__ loss)
 {
@@ -64,7 +66,7 @@ __global__ __launch_bounds__(kThreads) void k_hist_finish(const int32_t *__restr
 // pass after it.  The first kernel of the next batch's build can come along (ea.ntiles > 0).
 template <int LPR, int ITERS, int DIST, bool PACKED>
 __global__ __launch_bounds__(kThreads) void k_fwd_hist(ForwardArgs fa, const int32_t *__restrict__ keys, int32_t nnz,
-                                                       int shift, int radix, int32_t *__restrict__ table, int ntiles,
+                                                       int shift, int radix, uint16_t *__restrict__ table, int ntiles,
                                                        EmitAhead ea)
 {
     __shared__ __align__(16) unsigned char s_arena[emit_lds(true, false)];
@@ -77,7 +79,7 @@ __global__ __launch_bounds__(kThreads) void k_fwd_hist(ForwardArgs fa, const int
 
 template <int LPR, int ITERS, int DIST>
 __global__ __launch_bounds__(kThreads) void k_fwdh_hist(TranshArgs ta, const int32_t *__restrict__ keys, int32_t nnz,
-                                                        int shift, int radix, int32_t *__restrict__ table, int ntiles,
+                                                        int shift, int radix, uint16_t *__restrict__ table, int ntiles,
                                                         EmitAhead ea)
 {
     __shared__ __align__(16) unsigned char s_arena[emit_lds(true, false)];
