@@ -57,6 +57,22 @@ struct SegWriteRide {
     float *fin_loss;
 };
 
+// A value of lane j of each group of LPR lanes, in all lanes of the group.  Groups of whole wavefronts read it into scalar
+// registers: what follows from it is then the wavefront's own.
+template <int LPR>
+__device__ inline int32_t of_lane(int32_t v, int j)
+{
+    if constexpr (LPR == 64) return __builtin_amdgcn_readlane(v, j);
+    else return __shfl(v, j & (LPR - 1), LPR);
+}
+// The index of a thread's group in the workgroup.
+template <int LPR>
+__device__ inline int group_index()
+{
+    const int g = (int)threadIdx.x / LPR;
+    return LPR == 64 ? __builtin_amdgcn_readfirstlane(g) : g;
+}
+
 enum { HAS_FIRST = 1, FIRST_CONT = 2, HAS_LAST = 4 };
 
 template <int ITERS>
@@ -76,23 +92,15 @@ struct Acc {
     }
 };
 
-template <int LPR, int ITERS>
+// STREAM: a row of a table far larger than the caches, read once and rewritten: fetched past them.  (Lanes past the row's width
+// load its last float4 again, see load_vec.)
+template <int LPR, int ITERS, bool STREAM = false>
 __device__ inline void load_row(const float *__restrict__ p, int d4, int lig, Acc<ITERS> &a)
 {
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
-        int j = lig + it * LPR;
-        a.v[it] = j < d4 ? ld4(p + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-}
-// ... of a table far larger than the caches, read once and rewritten: fetched past them
-template <int LPR, int ITERS>
-__device__ inline void load_row_stream(const float *__restrict__ p, int d4, int lig, Acc<ITERS> &a)
-{
-#pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-        int j = lig + it * LPR;
-        a.v[it] = j < d4 ? ld4_stream(p + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const int j = min(lig + it * LPR, d4 - 1);
+        a.v[it] = STREAM ? ld4_stream(p + 4 * j) : ld4(p + 4 * j);
     }
 }
 template <int LPR, int ITERS>
@@ -155,8 +163,8 @@ struct SrcArgs {
     const float *X, *G;        // table and per-row rows, d4 float4 each
 };
 
-// table row <- x - lr * g, each product and difference rounded once, as in k_sgd_rows.
-template <int LPR, int ITERS>
+// table row <- x - lr * g, each product and difference rounded once, as in k_sgd_rows.  UNIT: mode 2 may be asked for.
+template <int LPR, int ITERS, bool UNIT = true>
 __device__ inline void apply_update(float *__restrict__ row, int d4, int lig, const Acc<ITERS> &x, const Acc<ITERS> &g,
                                     float lr, int mode, int stream)
 {
@@ -175,10 +183,10 @@ __device__ inline void apply_update(float *__restrict__ row, int d4, int lig, co
                 if (nv >= 1.0f) nv = 0.0f;
             }
             ov[q] = nv;
-            ss += nv * nv;
+            ss += lig + it * LPR < d4 ? nv * nv : 0.f;
         }
     }
-    if (mode == 2) {   // all lanes of the group are here together
+    if (UNIT && mode == 2) {   // all lanes of the group are here together
         ss = group_sum<LPR>(ss);
         if (ss > 0.f) {
             const float inv = 1.0f / sqrtf(ss);
@@ -445,7 +453,7 @@ __global__ __launch_bounds__(kThreads, 8) void k_seg_formed(const FormedRecord *
 // SUMS: relation columns are summed from rows of positives alone (SegSecond::n_pos); a kernel of its own, as the test for it
 // costs the others 2 per cent.
 template <int LPR, int ITERS, bool PACKED, int CHUNK, bool FUSED, int RIDE, int SRC = SRC_STORED, int THREADS = kThreads, bool SUMS = false>
-__global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && FUSED && RIDE != 4) ? 8 : 1) void k_seg_reduce(const int32_t *__restrict__ packed,
+__global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && FUSED && RIDE != 4 && !SUMS) ? (PACKED ? 8 : 7) : 1) void k_seg_reduce(const int32_t *__restrict__ packed,
                                                          const int32_t *__restrict__ seg_id, int32_t e_begin,
                                                          int32_t e_end, const float *__restrict__ src_a,
                                                          const float *__restrict__ src_b, int32_t split,
@@ -470,6 +478,14 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
     static_assert(kFinishLds <= OWN_LDS || RIDE == 0 || kFinishLds <= RIDE_LDS, "the loss sum fits the block");
     __shared__ __align__(16) unsigned char s_arena[ARENA_LDS];
     int block = (int)blockIdx.x;
+    // The arguments that say which part a workgroup plays, and those the product begins with, in one wait: loaded where they
+    // are first used, one behind the other, they were 0.8 us of every workgroup of the product.
+    if constexpr (RAW) STX_TOGETHER(sw.ntiles, sw.fin_n);
+    if constexpr (RIDE == 2 || RIDE == 4) STX_TOGETHER(ea.ntiles);
+    if constexpr (RIDE == 3 || RIDE == 5) STX_TOGETHER(sca.ntiles);
+    if constexpr (RIDE == 5) STX_TOGETHER(dm.blocks);
+    STX_TOGETHER(sec.first_block, gridDim.y, packed, seg_id, e_begin, e_end, src_a, src_b, split, ld_src, d4, partials, ld_out);
+    if constexpr (FUSED) STX_TOGETHER(fu.table, fu.table_b, fu.n_split, fu.lr, fu.mode, fu.stream);
     if constexpr (RAW) {
         static_assert(FUSED, "the segment of an entry is not known here");
         static_assert(kSegWriteLds <= ARENA_LDS && kFinishLds <= ARENA_LDS, "riders fit the block of LDS");
@@ -547,9 +563,8 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
     int32_t *s_small = reinterpret_cast<int32_t *>(s_arena + (GROUPS * 2 * ROWF + (FUSED ? GROUPS * ROWF : 4)) * 4);
     int32_t *s_info = s_small, *s_seg_last = s_small + GROUPS, *s_col_last = s_small + 2 * GROUPS;
 
-    const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
+    const int lig = threadIdx.x % LPR, grp = group_index<LPR>();
     const int pk_sh = PACKED ? 31 - __clz(ld_src) : 0;
-    const uint8_t *pk_lane = reinterpret_cast<const uint8_t *>(src_a) + pk_off + lig;
     const int32_t tile0 = e_begin + block * TILE;
     const int32_t ec0 = tile0 + grp * CHUNK;
     const int32_t ec1 = min(ec0 + CHUNK, e_end);
@@ -585,11 +600,24 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
                 o2 = (meta & 1) ? c1 : c2;
             }
         }
+        const bool skip = SUMS && ec0 + lig >= sums_from && (meta >> 2) >= sec.n_pos;   // (no source row is stored)
+        const int32_t my_row = skip ? sec.n_pos - 1 : meta >> 2;   // (... for loads without a branch: the last one that is)
+        // (groups of whole wavefronts: each lane fetches its own entry's; the others a batch's at a time, as a shuffle for each
+        // entry would keep the LDS units busier than those loads keep the caches)
+        constexpr bool LANE_COEF = PACKED && LPR == 64;
+        float my_coef = 0.f;
+        if (LANE_COEF) my_coef = src_b[my_row];
         Acc<ITERS> xcur;                                   // FUSED: table row of the run that is being summed
-        int32_t colcur = 0;
+        int at = 0;                                        // ... and the entry of the chunk it begins with
         xcur.zero();
-        const int32_t meta0 = __shfl(meta, 0, LPR);
-        const bool first_open = (ec0 > e_begin) && !(meta0 & 2);
+        // entries of the chunk that head a segment, and tail entries
+        const int gsh = (int)(threadIdx.x & 63) & ~(LPR - 1);
+        const uint64_t b_head = __ballot((meta & 2) != 0), b_tail = __ballot((meta & 1) != 0);
+        using Bits = std::conditional_t<(CHUNK > 32), uint64_t, uint32_t>;
+        const Bits heads = (Bits)(b_head >> gsh), tails = (Bits)(b_tail >> gsh);
+        // SUMS: ... and those whose source row is stored
+        const Bits stored = SUMS ? (Bits)(__ballot(!skip) >> gsh) : 0;
+        const bool first_open = (ec0 > e_begin) && !(heads & 1u);
         const bool right_open = (ec1 < e_end) && !right_head;
         int32_t cur_seg = RAW ? 0 : seg_id[ec0];
         int nflush = 0;
@@ -601,7 +629,7 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
             const bool open_right = last_run && right_open;
             if (!open_left && !open_right) {
                 if constexpr (FUSED)
-                    apply_update<LPR, ITERS>(fused_row(fu, colcur, ld_tab), d4, lig, xcur, acc, fu.lr, fu.mode, fu.stream);
+                    apply_update<LPR, ITERS, SUMS>(fused_row(fu, of_lane<LPR>(colv, at), ld_tab), d4, lig, xcur, acc, fu.lr, fu.mode, fu.stream);
                 else
                     store_row_stream<LPR, ITERS>(out_rows + (int64_t)cur_seg * ld_out, d4, lig, acc);
             } else {
@@ -617,74 +645,72 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
                     if constexpr (FUSED) {   // the run began in this chunk: its table row is already here
 #pragma unroll
                         for (int it = 0; it < ITERS; ++it) st4(&s_x[grp][(lig + it * LPR) * 4], xcur.v[it]);
-                        if (lig == 0) s_col_last[grp] = colcur;
+                        if (lig == (at & (LPR - 1))) s_col_last[grp] = colv;
                     }
                 }
             }
             ++nflush;
         };
 
+        auto walk = [&](auto stream) {
+        constexpr bool STREAM = decltype(stream)::value;
         for (int j0 = 0; j0 < n; j0 += UNROLL) {
             Acc<ITERS> v[VROWS];
             Acc<ITERS> va[SRC != SRC_STORED ? UNROLL : 1], vb[SRC != SRC_STORED ? UNROLL : 1];
             Acc<ITERS> xr[FUSED ? UNROLL : 1];
-            int32_t mu[UNROLL], cu[UNROLL];
+            const Bits hb = heads >> j0, tb = tails >> j0;
             uint8_t sb[UNROLL][ITERS];
             float cf[UNROLL];
-            // every lane learns the batch's entries first (shuffles back to back, one wait), then all row
-            // loads go out unconditionally: entries past the end of the chunk carry meta 0, i.e. row 0
+            // all loads of the batch go out together: entries past the end of the chunk carry meta 0, i.e. row 0
+            if constexpr (FUSED) {   // a run begins here: its table row comes along with its first source row
+                int32_t cu[UNROLL];
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) mu[u] = __shfl(meta, (j0 + u) & (LPR - 1), LPR);
-            if constexpr (FUSED) {
+                for (int u = 0; u < UNROLL; ++u) cu[u] = of_lane<LPR>(colv, j0 + u);
 #pragma unroll
-                for (int u = 0; u < UNROLL; ++u) cu[u] = __shfl(colv, (j0 + u) & (LPR - 1), LPR);
+                for (int u = 0; u < UNROLL; ++u)
+                    // (a row of a table beyond the caches is read once here and rewritten: past them)
+                    if (hb >> u & 1) load_row<LPR, ITERS, STREAM>(fused_row(fu, cu[u], ld_tab), d4, lig, xr[u]);
             }
+            if (!SUMS || (stored >> j0 & (((Bits)1 << UNROLL) - 1))) {
+                uint32_t row[UNROLL];
 #pragma unroll
-            for (int u = 0; u < UNROLL; ++u) {
-                const uint32_t row = (uint32_t)mu[u] >> 2;
-                if constexpr (FUSED) {   // a run begins here: its table row comes along with its first source row
-                    if (mu[u] & 2) {   // (a row of a table beyond the caches is read once here and rewritten: past them)
-                        if (fu.stream) load_row_stream<LPR, ITERS>(fused_row(fu, cu[u], ld_tab), d4, lig, xr[u]);
-                        else load_row<LPR, ITERS>(fused_row(fu, cu[u], ld_tab), d4, lig, xr[u]);
-                    }
-                }
-                if constexpr (PACKED) {
-                    // (records of 1 << pk_sh bytes: a shift and an add give the address)
-                    const uint8_t *pb = pk_lane + ((uint64_t)row << pk_sh);
+                for (int u = 0; u < UNROLL; ++u) row[u] = (uint32_t)of_lane<LPR>(my_row, j0 + u);
 #pragma unroll
-                    for (int it = 0; it < ITERS; ++it) {
-                        const int j = lig + it * LPR;
-                        sb[u][it] = j < d4 ? pb[it * LPR] : (uint8_t)0;
+                for (int u = 0; u < UNROLL; ++u) {
+                    if constexpr (PACKED) {
+                        // (records of 1 << pk_sh bytes: a shift and an add give the address)
+                        const uint8_t *pb = reinterpret_cast<const uint8_t *>(src_a) + pk_off + ((uint64_t)row[u] << pk_sh);
+#pragma unroll
+                        for (int it = 0; it < ITERS; ++it) sb[u][it] = pb[min(lig + it * LPR, d4 - 1)];
+                        if (!LANE_COEF) cf[u] = src_b[row[u]];
+                    } else if constexpr (SEMI) {
+                        const int32_t c1 = of_lane<LPR>(o1, j0 + u), c2 = of_lane<LPR>(o2, j0 + u);
+                        load_row<LPR, ITERS, true>(sr.G + (uint64_t)row[u] * (uint32_t)ld_tab, d4, lig, v[u]);
+                        load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c1 * (uint32_t)ld_tab, d4, lig, va[u]);
+                        if (SRC != SRC_SEMIRING + SR_ROTATE)
+                            load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c2 * (uint32_t)ld_tab, d4, lig, vb[u]);
+                    } else {   // entries before `split` read src_a, the rest src_b (entity vs relation columns)
+                        load_row<LPR, ITERS>((ec0 + j0 + u < split ? src_a : src_b) + (uint64_t)row[u] * (uint32_t)ld_src, d4, lig, v[u]);
                     }
-                    cf[u] = src_b[row];
-                } else if constexpr (SEMI) {
-                    const int32_t c1 = __shfl(o1, (j0 + u) & (LPR - 1), LPR), c2 = __shfl(o2, (j0 + u) & (LPR - 1), LPR);
-                    load_row_stream<LPR, ITERS>(sr.G + (uint64_t)row * (uint32_t)ld_tab, d4, lig, v[u]);
-                    load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c1 * (uint32_t)ld_tab, d4, lig, va[u]);
-                    if (SRC != SRC_SEMIRING + SR_ROTATE)
-                        load_row<LPR, ITERS>(sr.X + (uint64_t)(uint32_t)c2 * (uint32_t)ld_tab, d4, lig, vb[u]);
-                } else if (SUMS && ec0 + j0 + u >= sums_from && (int32_t)row >= sec.n_pos) {
-                    v[u].zero();
-                } else {   // entries before `split` read src_a, the rest src_b (entity vs relation columns)
-                    load_row<LPR, ITERS>((ec0 + j0 + u < split ? src_a : src_b) + (uint64_t)row * (uint32_t)ld_src, d4, lig, v[u]);
                 }
             }
 #pragma unroll
             for (int u = 0; u < UNROLL; ++u) {
                 const int jj = j0 + u;
                 if (jj < n) {
-                    if (mu[u] & 2) {
+                    if (hb >> u & 1) {
                         if (jj > 0) {
                             flush(false);
                             ++cur_seg;
                             acc.zero();
                         }
-                        if constexpr (FUSED) { xcur = xr[u]; colcur = cu[u]; }
+                        if constexpr (FUSED) { xcur = xr[u]; at = jj; }
                     }
                     if constexpr (PACKED) {
                         // the dense row the forward pass would have stored is +c, -c or 0 per element, and a tail
                         // entry subtracts it: one fused multiply-add per element with the element's sign
-                        const float c = (mu[u] & 1) ? -cf[u] : cf[u];
+                        const float m = LANE_COEF ? __int_as_float(of_lane<LPR>(__float_as_int(my_coef), jj)) : cf[u];
+                        const float c = (tb >> u & 1) ? -m : m;
 #pragma unroll
                         for (int it = 0; it < ITERS; ++it) {
                             const unsigned b = sb[u][it];   // (shift up, arithmetic shift down: sign-extends two bits)
@@ -695,22 +721,27 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && PACKED && F
                         }
                     } else if constexpr (SEMI) {
                         Acc<ITERS> tm;
-                        tm.v[0] = semiring_term<SRC - SRC_SEMIRING>(v[u].v[0], va[u].v[0], vb[u].v[0], (mu[u] & 1) != 0);
+                        tm.v[0] = semiring_term<SRC - SRC_SEMIRING>(v[u].v[0], va[u].v[0], vb[u].v[0], (tb >> u & 1) != 0);
                         acc.add(tm);
-                    } else {
-                        Acc<ITERS> &vu = v[u];
-                        if (mu[u] & 1) {
+                    } else if (!SUMS || (stored >> jj & 1)) {
+                        // (a sum or a difference, rounded once either way)
+                        const float sg = (tb >> u & 1) ? -1.0f : 1.0f;
 #pragma unroll
-                            for (int it = 0; it < ITERS; ++it) {
-                                acc.v[it].x -= vu.v[it].x; acc.v[it].y -= vu.v[it].y;
-                                acc.v[it].z -= vu.v[it].z; acc.v[it].w -= vu.v[it].w;
-                            }
-                        } else {
-                            acc.add(vu);
+                        for (int it = 0; it < ITERS; ++it) {
+                            acc.v[it].x = __builtin_fmaf(sg, v[u].v[it].x, acc.v[it].x); acc.v[it].y = __builtin_fmaf(sg, v[u].v[it].y, acc.v[it].y);
+                            acc.v[it].z = __builtin_fmaf(sg, v[u].v[it].z, acc.v[it].z); acc.v[it].w = __builtin_fmaf(sg, v[u].v[it].w, acc.v[it].w);
                         }
                     }
                 }
             }
+        }
+        };
+        // (the choice lies outside the loop: beside each load it made every head wait for all loads before it)
+        if constexpr (FUSED) {
+            if (fu.stream) walk(std::true_type{});
+            else walk(std::false_type{});
+        } else {
+            walk(std::false_type{});
         }
         flush(true);
     }
@@ -738,6 +769,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
                                                         EmitAhead ea)
 {
     int block = (int)blockIdx.x;
+    STX_TOGETHER(ha.ntiles, sa.ntiles, dm.blocks, sec.first_block, gridDim.x, gridDim.y, packed, seg_id, seg_ptr, e_begin, e_end, d4, ld_out, partials);
     if constexpr (RIDE == 4) {
         if (block < ea.ntiles) {      // uniform in the workgroup
             emit_body<kBigSortItems, false, true, false>(block, ea.ntiles, ea.args);
@@ -816,9 +848,8 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
     const int n = j - j0 + 1;                                   // partial rows: (j0, slot 1), (j0+1 .. j, slot 0)
     auto sum_row = [&](const FusedArgs &fa, float *rows, const float *part, int width4) {
         Acc<ITERS> xrow;                                        // FUSED: the table row, fetched beside the partial rows
-        xrow.zero();
         if (FUSED && grp == 0) {
-            if (fa.stream) load_row_stream<LPR, ITERS>(fused_row(fa, col, ld_tab), width4, lig, xrow);
+            if (fa.stream) load_row<LPR, ITERS, true>(fused_row(fa, col, ld_tab), width4, lig, xrow);
             else load_row<LPR, ITERS>(fused_row(fa, col, ld_tab), width4, lig, xrow);
         }
         const int per = (n + GROUPS - 1) / GROUPS;
@@ -826,8 +857,21 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
         Acc<ITERS> acc;
         acc.zero();
         constexpr int FU = ITERS == 1 ? 8 : 2;
+        // NB partial rows in flight, added in tile order (past the last one: it again, not added)
+        auto rows_at = [&](auto nb, int q) {
+            constexpr int NB = decltype(nb)::value;
+            Acc<ITERS> v[NB];
+#pragma unroll
+            for (int u = 0; u < NB; ++u) {
+                const int t = min(q + u, hi - 1);
+                load_row<LPR, ITERS>(part + ((int64_t)(j0 + t) * 2 + (t == 0 ? 1 : 0)) * ld_out, width4, lig, v[u]);
+            }
+#pragma unroll
+            for (int u = 0; u < NB; ++u)
+                if (q + u < hi) acc.add(v[u]);
+        };
         int q = lo;
-        for (; q + FU <= hi; q += FU) {   // FU partial rows in flight, added in tile order
+        for (; q + FU <= hi; q += FU) {
             Acc<ITERS> v[FU];
 #pragma unroll
             for (int u = 0; u < FU; ++u)
@@ -835,11 +879,9 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
 #pragma unroll
             for (int u = 0; u < FU; ++u) acc.add(v[u]);
         }
-        for (; q < hi; ++q) {
-            Acc<ITERS> v;
-            load_row<LPR, ITERS>(part + ((int64_t)(j0 + q) * 2 + (q == 0 ? 1 : 0)) * ld_out, width4, lig, v);
-            acc.add(v);
-        }
+        if (hi - q > 2) rows_at(std::integral_constant<int, FU>{}, q);
+        else if (hi - q == 2) rows_at(std::integral_constant<int, 2>{}, q);
+        else if (hi > q) rows_at(std::integral_constant<int, 1>{}, q);
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) st4(&s_sum[grp][(lig + it * LPR) * 4], acc.v[it]);
         __syncthreads();
@@ -904,7 +946,7 @@ __device__ inline void sgd_row(float *__restrict__ row, const float *__restrict_
                 if (nv >= 1.0f) nv = 0.0f;
             }
             xv[q] = nv;
-            ss += nv * nv;
+            ss += lig + it * LPR < d4 ? nv * nv : 0.f;
         }
     }
     if (mode == 2) {
@@ -936,6 +978,8 @@ __global__ __launch_bounds__(kThreads) void k_sgd_rows(const int32_t *__restrict
         // One table (TransE / TorusE): a group takes four consecutive segments per turn so that the four
         // column ids, then the eight rows (table + gradient), are in flight together.
         constexpr int UB = ITERS <= 2 ? 4 : 2;
+        auto walk = [&](auto past) {
+        constexpr bool STREAM = decltype(past)::value;
         for (int64_t s0 = ((int64_t)blockIdx.x * GROUPS + grp) * UB; s0 < U; s0 += (int64_t)gridDim.x * GROUPS * UB) {
             int32_t col[UB];
 #pragma unroll
@@ -943,14 +987,8 @@ __global__ __launch_bounds__(kThreads) void k_sgd_rows(const int32_t *__restrict
             Acc<ITERS> x[UB], g[UB];
 #pragma unroll
             for (int u = 0; u < UB; ++u) {
-                if (stream) load_row_stream<LPR, ITERS>(table_a + (int64_t)col[u] * d4_a * 4, d4_a, lig, x[u]);
-                else load_row<LPR, ITERS>(table_a + (int64_t)col[u] * d4_a * 4, d4_a, lig, x[u]);
-                const float *pg = grad_rows + min(s0 + u, (int64_t)U - 1) * ld;
-#pragma unroll
-                for (int it = 0; it < ITERS; ++it) {
-                    const int j = lig + it * LPR;
-                    g[u].v[it] = j < d4_a ? ld4_stream(pg + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
-                }
+                load_row<LPR, ITERS, STREAM>(table_a + (int64_t)col[u] * d4_a * 4, d4_a, lig, x[u]);
+                load_row<LPR, ITERS, true>(grad_rows + min(s0 + u, (int64_t)U - 1) * ld, d4_a, lig, g[u]);
             }
 #pragma unroll
             for (int u = 0; u < UB; ++u) {
@@ -975,13 +1013,16 @@ __global__ __launch_bounds__(kThreads) void k_sgd_rows(const int32_t *__restrict
                     for (int it = 0; it < ITERS; ++it) {
                         const int j = lig + it * LPR;
                         if (j < d4_a) {
-                            if (stream) st4_stream(pr + 4 * j, x[u].v[it]);
+                            if (STREAM) st4_stream(pr + 4 * j, x[u].v[it]);
                             else st4(pr + 4 * j, x[u].v[it]);
                         }
                     }
                 }
             }
         }
+        };
+        if (stream) walk(std::true_type{});
+        else walk(std::false_type{});
         return;
     }
     for (int64_t s = (int64_t)blockIdx.x * GROUPS + grp; s < U; s += (int64_t)gridDim.x * GROUPS) {

@@ -48,7 +48,8 @@ __global__ __launch_bounds__(kThreads, ITERS == 1 ? 8 : 1) void k_forward_y(Forw
 template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK>
 __global__ __launch_bounds__(kThreads, ITERS == 1 ? (NB == 1 || (PACKED && !MORE && !CHECK) ? 8 : PACKED && !(MORE && CHECK) ? 6 : 5) : ITERS == 2 ? (NB > 1 ? 3 : 4) : 2) void k_forward_stacked(ForwardArgs a)
 {
-    forward_body<LPR, ITERS, DIST, PACKED, NB, MORE, CHECK>((int)blockIdx.x, a);
+    if (a.stream_rows) forward_body<LPR, ITERS, DIST, PACKED, NB, MORE, CHECK, true>((int)blockIdx.x, a);
+    else forward_body<LPR, ITERS, DIST, PACKED, NB, MORE, CHECK, false>((int)blockIdx.x, a);
 }
 
 // TransR in stx_train_step: the first kernel of the next batch's build (which also counts the rows per relation)

@@ -88,7 +88,8 @@ __device__ inline void finish_loss_body(const float *__restrict__ partials, int 
 // MORE: the batch may have more than NB negatives per positive (the loop costs registers).
 // CHECK: the negatives may be a caller's own.  false is returned, by all lanes of the group, when one of another kind
 // turns up: what was written until then is to be written again (forward_any_rows).
-template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK>
+// STREAM: the table is far larger than the caches, and a row used once does not displace the others.
+template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK, bool STREAM>
 __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const ForwardArgs &a, float &hinge_sum)
 {
     constexpr int NI = (3 + 3 * NB + LPR - 1) / LPR;       // column ids per lane
@@ -133,11 +134,7 @@ __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const F
         RowVec<ITERS> e[NB];
 #pragma unroll
         for (int q = 0; q < NB; ++q)
-            if (q0 + q < k) {
-                // a row used once does not displace the others when the table is far larger than the caches
-                if (a.stream_rows) load_vec_stream<LPR, ITERS>(X + (int64_t)ce[q] * dim, d4, lig, e[q]);
-                else load_vec<LPR, ITERS>(X + (int64_t)ce[q] * dim, d4, lig, e[q]);
-            }
+            if (q0 + q < k) load_vec<LPR, ITERS, STREAM>(X + (int64_t)ce[q] * dim, d4, lig, e[q]);
         if (MORE && q0 + NB < k) {                     // the next batch's ids, in the places of this one's
 #pragma unroll
             for (int u = 0; u < NI; ++u) {
@@ -151,7 +148,7 @@ __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const F
                 hr.v[it] = add4(hr.v[it], pr.v[it]);
                 xp.v[it] = sub4(hr.v[it], pt.v[it]);
             }
-            npos = row_distance<LPR, ITERS, DIST>(xp);
+            npos = row_distance<LPR, ITERS, DIST>(xp, d4, lig);
             dpos = wr * npos;
             if (lig == 0) scores[i] = dpos;
         }
@@ -162,7 +159,7 @@ __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const F
 #pragma unroll
                 for (int it = 0; it < ITERS; ++it)
                     x.v[it] = (tail_mask >> q & 1u) ? sub4(hr.v[it], e[q].v[it]) : sub4(add4(e[q].v[it], pr.v[it]), pt.v[it]);
-                const float nneg = row_distance<LPR, ITERS, DIST>(x);
+                const float nneg = row_distance<LPR, ITERS, DIST>(x, d4, lig);
                 const float dneg = wr * nneg;
                 const float arg = (a.margin + dpos) - dneg;
                 const bool active = arg > 0.f;
@@ -245,7 +242,7 @@ __device__ inline void forward_any_rows(const int64_t i, const int lig, const Fo
             }
         }
         if (kk0 == 0) {
-            npos = row_distance<LPR, ITERS, DIST>(xp);
+            npos = row_distance<LPR, ITERS, DIST>(xp, d4, lig);
             dpos = wr * npos;
             if (lig == 0) scores[i] = dpos;
         }
@@ -253,7 +250,7 @@ __device__ inline void forward_any_rows(const int64_t i, const int lig, const Fo
         for (int q = 0; q < NB; ++q) {
             if (q < nb) {
                 const int64_t row = row0 + q;
-                const float nneg = row_distance<LPR, ITERS, DIST>(xn[q]);
+                const float nneg = row_distance<LPR, ITERS, DIST>(xn[q], d4, lig);
                 const float dneg = wr * nneg;
                 const float arg = (margin + dpos) - dneg;
                 const bool active = arg > 0.f;
@@ -305,14 +302,14 @@ __device__ inline void forward_y_body(const int block, const ForwardArgs &a)
 // Gathered rows.  CHECK: a positive whose negatives are a caller's own, of a kind that forward_fast_rows does not cover,
 // takes three table rows for each, in the same kernel: in a launch of its own behind a fast one, whose groups had then
 // loaded and stored for nothing, such batches took 1.4 to 1.7 times as long.
-template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK>
+template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK, bool STREAM>
 __device__ inline void forward_body(const int block, const ForwardArgs &a)
 {
     constexpr int GROUPS = kThreads / LPR;
     const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
     const int64_t i = (int64_t)block * GROUPS + grp;
     float hinge_sum = 0.f;
-    if (i < a.b && !forward_fast_rows<LPR, ITERS, DIST, PACKED, NB, MORE, CHECK>((int32_t)i, lig, a, hinge_sum) && CHECK) {
+    if (i < a.b && !forward_fast_rows<LPR, ITERS, DIST, PACKED, NB, MORE, CHECK, STREAM>((int32_t)i, lig, a, hinge_sum) && CHECK) {
         hinge_sum = 0.f;
         forward_any_rows<LPR, ITERS, DIST, false, PACKED, NB == 1>(i, lig, a, hinge_sum);
     }
@@ -330,7 +327,7 @@ constexpr int fast_batch(int iters, bool k1) { return k1 ? 1 : iters <= 2 ? 4 : 
 template <int LPR, int ITERS, int DIST, bool PACKED, bool K1>
 __device__ inline void forward_step_body(const int block, const ForwardArgs &fa)
 {
-    forward_body<LPR, ITERS, DIST, PACKED, fast_batch(ITERS, K1), !K1, false>(block, fa);
+    forward_body<LPR, ITERS, DIST, PACKED, fast_batch(ITERS, K1), !K1, false, false>(block, fa);
 }
 
 }  // namespace stx

@@ -15,23 +15,18 @@ struct RowVec {
 __device__ inline float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
 __device__ inline float4 sub4(float4 a, float4 b) { return make_float4(a.x - b.x, a.y - b.y, a.z - b.z, a.w - b.w); }
 
-template <int LPR, int ITERS>
+// (Lanes past the row's width load its last float4 again: what they hold takes part in no sum and is not stored.  A zero
+// put there instead is a second write to the load's registers: on a path that another load into them may still be on its way
+// on, the compiler waits for every load in flight before it.)
+// STREAM: non-temporal loads, for rows that are used once and should not displace others in the caches.  Chosen where code is
+// chosen: a run-time choice beside each load made such paths of the two.
+template <int LPR, int ITERS, bool STREAM = false>
 __device__ inline void load_vec(const float *__restrict__ p, int d4, int lig, RowVec<ITERS> &x)
 {
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
-        int j = lig + it * LPR;
-        x.v[it] = j < d4 ? ld4(p + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-}
-// the same with non-temporal loads: for rows that are used once and should not displace others in the caches
-template <int LPR, int ITERS>
-__device__ inline void load_vec_stream(const float *__restrict__ p, int d4, int lig, RowVec<ITERS> &x)
-{
-#pragma unroll
-    for (int it = 0; it < ITERS; ++it) {
-        int j = lig + it * LPR;
-        x.v[it] = j < d4 ? ld4_stream(p + 4 * j) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const int j = min(lig + it * LPR, d4 - 1);
+        x.v[it] = STREAM ? ld4_stream(p + 4 * j) : ld4(p + 4 * j);
     }
 }
 template <int LPR, int ITERS>
@@ -122,29 +117,34 @@ __device__ inline float coef_scale(float coef, float dist)
 }
 
 template <int LPR, int ITERS, int DIST>
-__device__ inline float row_distance(const RowVec<ITERS> &x)
+__device__ inline float row_distance(const RowVec<ITERS> &x, int d4, int lig)
 {
     float acc = 0.f;
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
-        acc += term<DIST>(x.v[it].x);
-        acc += term<DIST>(x.v[it].y);
-        acc += term<DIST>(x.v[it].z);
-        acc += term<DIST>(x.v[it].w);
+        float a = acc;
+        a += term<DIST>(x.v[it].x);
+        a += term<DIST>(x.v[it].y);
+        a += term<DIST>(x.v[it].z);
+        a += term<DIST>(x.v[it].w);
+        acc = lig + it * LPR < d4 ? a : acc;
     }
-    return finish<DIST>(group_sum<LPR>(acc));
+    // (a sum of non-negative terms; of two NaN in an addition the compiler's order of its operands decides whose sign stays)
+    return finish<DIST>(fabsf(group_sum<LPR>(acc)));
 }
 
 template <int LPR, int ITERS>
-__device__ inline float group_dot(const RowVec<ITERS> &a, const RowVec<ITERS> &b)
+__device__ inline float group_dot(const RowVec<ITERS> &a, const RowVec<ITERS> &b, int d4, int lig)
 {
     float acc = 0.f;
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
-        acc += a.v[it].x * b.v[it].x;
-        acc += a.v[it].y * b.v[it].y;
-        acc += a.v[it].z * b.v[it].z;
-        acc += a.v[it].w * b.v[it].w;
+        float s = acc;
+        s += a.v[it].x * b.v[it].x;
+        s += a.v[it].y * b.v[it].y;
+        s += a.v[it].z * b.v[it].z;
+        s += a.v[it].w * b.v[it].w;
+        acc = lig + it * LPR < d4 ? s : acc;
     }
     return group_sum<LPR>(acc);
 }

@@ -24,13 +24,13 @@ struct HRow {
 
     // h, t: the two entity rows as loaded; w, dr: the relation's normal and translation
     __device__ inline void project(const RowVec<ITERS> &h, const RowVec<ITERS> &t, const RowVec<ITERS> &w,
-                                   const RowVec<ITERS> &dr)
+                                   const RowVec<ITERS> &dr, int d4, int lig)
     {
 #pragma unroll
         for (int it = 0; it < ITERS; ++it)
             x.v[it] = make_float4(h.v[it].x - t.v[it].x, h.v[it].y - t.v[it].y, h.v[it].z - t.v[it].z,
                                   h.v[it].w - t.v[it].w);
-        s = group_dot<LPR, ITERS>(w, x);
+        s = group_dot<LPR, ITERS>(w, x, d4, lig);
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
             y.v[it].x = (x.v[it].x + dr.v[it].x) - s * w.v[it].x;
@@ -38,7 +38,7 @@ struct HRow {
             y.v[it].z = (x.v[it].z + dr.v[it].z) - s * w.v[it].z;
             y.v[it].w = (x.v[it].w + dr.v[it].w) - s * w.v[it].w;
         }
-        dist = row_distance<LPR, ITERS, DIST>(y);
+        dist = row_distance<LPR, ITERS, DIST>(y, d4, lig);
     }
 
     // gx of the row is stored; gy and gw are added to the positive's sums (ADD: else they begin them)
@@ -51,7 +51,7 @@ struct HRow {
         for (int it = 0; it < ITERS; ++it)
             gy.v[it] = make_float4(dterm<DIST>(y.v[it].x, cs), dterm<DIST>(y.v[it].y, cs),
                                    dterm<DIST>(y.v[it].z, cs), dterm<DIST>(y.v[it].w, cs));
-        const float a = group_dot<LPR, ITERS>(gy, w);
+        const float a = group_dot<LPR, ITERS>(gy, w, d4, lig);
 #pragma unroll
         for (int it = 0; it < ITERS; ++it) {
             gx.v[it] = make_float4(gy.v[it].x - a * w.v[it].x, gy.v[it].y - a * w.v[it].y,
@@ -116,7 +116,7 @@ __device__ inline void forward_transh_body(const int block, const TranshArgs &a)
                 }
             }
             if (kk0 == 0) {
-                pos.project(ph, pt, w, dr);
+                pos.project(ph, pt, w, dr, d4, lig);
                 if (lig == 0) a.scores[i] = pos.dist;
             }
 #pragma unroll
@@ -124,7 +124,7 @@ __device__ inline void forward_transh_body(const int block, const TranshArgs &a)
                 if (q < nb) {
                     const int64_t row = row0 + q;
                     HRow<LPR, ITERS, DIST> neg;
-                    neg.project(nh[q], nt[q], w, dr);
+                    neg.project(nh[q], nt[q], w, dr, d4, lig);
                     const float arg = (a.margin + pos.dist) - neg.dist;
                     const bool active = arg > 0.f;
                     if (lig == 0) a.scores[row] = neg.dist;
