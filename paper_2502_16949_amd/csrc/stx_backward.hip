@@ -276,10 +276,17 @@ struct alignas(64) FormedHead {
 __global__ __launch_bounds__(kThreads) void k_seg_records(const int32_t *__restrict__ packed, const int32_t *__restrict__ seg_id,
                                                           const int32_t *__restrict__ colidx, const float *__restrict__ coefs,
                                                           int32_t nnz, int32_t split, uint32_t row_bytes,
-                                                          FormedRecord *__restrict__ recs, FormedHead *__restrict__ hds)
+                                                          FormedRecord *__restrict__ recs, FormedHead *__restrict__ hds,
+                                                          SegWriteRide fin)
 {
+    // (the sum of the loss comes along as the first workgroup: 18 us at 98,304 partials as a launch of its own)
+    const int fins = fin.fin_n > 0 ? 1 : 0;
+    if ((int)blockIdx.x < fins) {                          // uniform in the workgroup
+        finish_loss_body(fin.fin_partials, fin.fin_n, fin.fin_scale, fin.fin_loss);
+        return;
+    }
     const int lane = threadIdx.x & 63;
-    const int32_t e0 = ((int32_t)blockIdx.x * kThreads + (int32_t)threadIdx.x) & ~63;
+    const int32_t e0 = (((int32_t)blockIdx.x - fins) * kThreads + (int32_t)threadIdx.x) & ~63;
     if (e0 >= nnz) return;
     const int n = min(64, nnz - e0);
     uint4 rc = make_uint4(0u, 0u, 0u, 0u);
@@ -287,10 +294,14 @@ __global__ __launch_bounds__(kThreads) void k_seg_records(const int32_t *__restr
     if (lane < n) {
         m = (uint32_t)packed[e0 + lane];
         const uint32_t row = m >> 2;
-        const int32_t *cx = colidx + 3 * (int64_t)row;
-        const uint32_t c0 = (uint32_t)cx[0] * row_bytes, c1 = (uint32_t)cx[1] * row_bytes, c2 = (uint32_t)cx[2] * row_bytes;
-        const bool tail = m & 1u, rel = e0 + lane >= split;
-        rc = make_uint4(tail || rel ? c0 : c1, tail ? c1 : c2, __float_as_uint(coefs[row]), 0u);
+        rc.z = __float_as_uint(coefs[row]);
+        if (rc.z != 0u) {                                  // (of the others nothing more is needed)
+            const int32_t *cx = colidx + 3 * (int64_t)row;
+            const uint32_t c0 = (uint32_t)cx[0] * row_bytes, c1 = (uint32_t)cx[1] * row_bytes, c2 = (uint32_t)cx[2] * row_bytes;
+            const bool tail = m & 1u, rel = e0 + lane >= split;
+            rc.x = tail || rel ? c0 : c1;
+            rc.y = tail ? c1 : c2;
+        }
     }
     const bool right_head = e0 + n >= nnz || (packed[e0 + n] & 2);
     const int32_t seg = seg_id[e0];
@@ -1303,9 +1314,12 @@ stx_status launch_seg_formed(stx_ctx *c, const stx_incidence *inc, const stx_par
     const FormedRows fr = formed_buffers(c, inc->n_rows);
     {
         ProfScope prof(c, "k_seg_records");
-        hipLaunchKernelGGL(k_seg_records, dim3((unsigned)((nnz + kThreads - 1) / kThreads)), dim3(kThreads), 0, c->stream,
+        SegWriteRide fin{};
+        fin.fin_partials = c->loss_partials; fin.fin_n = c->fin_n; fin.fin_scale = c->fin_scale; fin.fin_loss = c->fin_loss;
+        hipLaunchKernelGGL(k_seg_records, dim3((unsigned)((nnz + kThreads - 1) / kThreads + (c->fin_n > 0 ? 1 : 0))), dim3(kThreads), 0, c->stream,
                            inc->at_packed, inc->at_seg_id, inc->a_colidx, fr.coefs, nnz, split, (uint32_t)c->cfg.dim * 4u,
-                           (FormedRecord *)fr.recs, (FormedHead *)fr.heads);
+                           (FormedRecord *)fr.recs, (FormedHead *)fr.heads, fin);
+        c->fin_n = 0;
     }
     const int d4 = c->cfg.dim / 4, ntiles = (nnz + TILE - 1) / TILE, nslices = (d4 + LPR - 1) / LPR;
     const dim3 grid((unsigned)ntiles, (unsigned)nslices);

@@ -89,7 +89,8 @@ __device__ inline void finish_loss_body(const float *__restrict__ partials, int 
 // CHECK: the negatives may be a caller's own.  false is returned, by all lanes of the group, when one of another kind
 // turns up: what was written until then is to be written again (forward_any_rows).
 // STREAM: the table is far larger than the caches, and a row used once does not displace the others.
-template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK, bool STREAM>
+// SLICES: distances are summed as the sliced pass sums them (forward_slice_body).
+template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK, bool STREAM, bool SLICES>
 __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const ForwardArgs &a, float &hinge_sum)
 {
     constexpr int NI = (3 + 3 * NB + LPR - 1) / LPR;       // column ids per lane
@@ -148,7 +149,7 @@ __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const F
                 hr.v[it] = add4(hr.v[it], pr.v[it]);
                 xp.v[it] = sub4(hr.v[it], pt.v[it]);
             }
-            npos = row_distance<LPR, ITERS, DIST>(xp, d4, lig);
+            npos = row_distance<LPR, ITERS, DIST, SLICES>(xp, d4, lig);
             dpos = wr * npos;
             if (lig == 0) scores[i] = dpos;
         }
@@ -159,7 +160,7 @@ __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const F
 #pragma unroll
                 for (int it = 0; it < ITERS; ++it)
                     x.v[it] = (tail_mask >> q & 1u) ? sub4(hr.v[it], e[q].v[it]) : sub4(add4(e[q].v[it], pr.v[it]), pt.v[it]);
-                const float nneg = row_distance<LPR, ITERS, DIST>(x, d4, lig);
+                const float nneg = row_distance<LPR, ITERS, DIST, SLICES>(x, d4, lig);
                 const float dneg = wr * nneg;
                 const float arg = (a.margin + dpos) - dneg;
                 const bool active = arg > 0.f;
@@ -168,17 +169,13 @@ __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const F
                 if (active) { hinge_sum += arg; ++n_active; }
                 if (PACKED)
                     write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, row, d4, lig, x, active ? -a.scale * wr : 0.f);
-                else if (a.coefs) {
-                    if (lig == 0) a.coefs[row] = formed_coef<DIST>(active ? -a.scale * wr : 0.f, nneg);
-                } else
+                else
                     write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)row * dim, d4, lig, x, active ? -a.scale * wr : 0.f, nneg);
             }
     }
     if (PACKED)
         write_grad_row_packed<LPR, ITERS, DIST>(recs, gstride, gcoef, i, d4, lig, xp, (float)n_active * a.scale * wr);
-    else if (a.coefs) {
-        if (lig == 0) a.coefs[i] = formed_coef<DIST>((float)n_active * a.scale * wr, npos);
-    } else
+    else
         write_grad_row<LPR, ITERS, DIST>(a.G + (int64_t)i * dim, d4, lig, xp, (float)n_active * a.scale * wr, npos);
     return true;
 }
@@ -192,7 +189,7 @@ __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const F
 // rows' coefficients behind the records of the batch.
 // K1: at most one negative per positive (the benchmarks' shape): no registers are kept for a batch of them, and
 // more wavefronts fit (same arithmetic in the same order, so the same bits).
-template <int LPR, int ITERS, int DIST, bool FROM_Y, bool PACKED, bool K1>
+template <int LPR, int ITERS, int DIST, bool FROM_Y, bool PACKED, bool K1, bool SLICES = false>
 __device__ inline void forward_any_rows(const int64_t i, const int lig, const ForwardArgs &a, float &hinge_sum)
 {
     const int32_t *__restrict__ colidx = a.colidx;
@@ -242,7 +239,7 @@ __device__ inline void forward_any_rows(const int64_t i, const int lig, const Fo
             }
         }
         if (kk0 == 0) {
-            npos = row_distance<LPR, ITERS, DIST>(xp, d4, lig);
+            npos = row_distance<LPR, ITERS, DIST, SLICES>(xp, d4, lig);
             dpos = wr * npos;
             if (lig == 0) scores[i] = dpos;
         }
@@ -250,7 +247,7 @@ __device__ inline void forward_any_rows(const int64_t i, const int lig, const Fo
         for (int q = 0; q < NB; ++q) {
             if (q < nb) {
                 const int64_t row = row0 + q;
-                const float nneg = row_distance<LPR, ITERS, DIST>(xn[q], d4, lig);
+                const float nneg = row_distance<LPR, ITERS, DIST, SLICES>(xn[q], d4, lig);
                 const float dneg = wr * nneg;
                 const float arg = (margin + dpos) - dneg;
                 const bool active = arg > 0.f;
@@ -302,16 +299,16 @@ __device__ inline void forward_y_body(const int block, const ForwardArgs &a)
 // Gathered rows.  CHECK: a positive whose negatives are a caller's own, of a kind that forward_fast_rows does not cover,
 // takes three table rows for each, in the same kernel: in a launch of its own behind a fast one, whose groups had then
 // loaded and stored for nothing, such batches took 1.4 to 1.7 times as long.
-template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK, bool STREAM>
+template <int LPR, int ITERS, int DIST, bool PACKED, int NB, bool MORE, bool CHECK, bool STREAM, bool SLICES = false>
 __device__ inline void forward_body(const int block, const ForwardArgs &a)
 {
     constexpr int GROUPS = kThreads / LPR;
     const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
     const int64_t i = (int64_t)block * GROUPS + grp;
     float hinge_sum = 0.f;
-    if (i < a.b && !forward_fast_rows<LPR, ITERS, DIST, PACKED, NB, MORE, CHECK, STREAM>((int32_t)i, lig, a, hinge_sum) && CHECK) {
+    if (i < a.b && !forward_fast_rows<LPR, ITERS, DIST, PACKED, NB, MORE, CHECK, STREAM, SLICES>((int32_t)i, lig, a, hinge_sum) && CHECK) {
         hinge_sum = 0.f;
-        forward_any_rows<LPR, ITERS, DIST, false, PACKED, NB == 1>(i, lig, a, hinge_sum);
+        forward_any_rows<LPR, ITERS, DIST, false, PACKED, NB == 1, SLICES>(i, lig, a, hinge_sum);
     }
     forward_loss<GROUPS>(block, lig, grp, hinge_sum, a);
 }
@@ -328,6 +325,113 @@ template <int LPR, int ITERS, int DIST, bool PACKED, bool K1>
 __device__ inline void forward_step_body(const int block, const ForwardArgs &fa)
 {
     forward_body<LPR, ITERS, DIST, PACKED, fast_batch(ITERS, K1), !K1, false, false>(block, fa);
+}
+
+// The forward pass of a batch whose rows of dL/dx are formed where they are summed (formed_rows), first part: the share of one
+// 64-float slice of the columns in every row's distance.  Such a batch reads the table many times over, and whole rows of it
+// come from the last-level cache (8 TB/s for random rows of 64 MB); a slice of the whole table stays in a die's L2, which gives
+// 30 TB/s in float4 loads of 16 lanes a row (18 in single floats of 64 lanes).  Sixteen lanes per positive, PP positives side by
+// side in each group; sums[slice][row].  The second part (k_forward_combine) adds a row's shares in order.
+template <int DIST, int NB, bool MORE, int PP>
+__device__ inline void forward_slice_body(const int block, const int slice, const ForwardArgs &a)
+{
+    constexpr int LPR = 16, GROUPS = kThreads / LPR, SPAN = LPR / PP;   // SPAN: lanes that hold a positive's column ids
+    static_assert(3 + 3 * NB <= SPAN && (PP == 1 || !MORE), "a lane for each column id");
+    const int lig = threadIdx.x % LPR, grp = threadIdx.x / LPR;
+    const int32_t b = a.b, k = a.k;
+    const int dim = a.dim, c4 = slice * LPR, n4 = min(LPR, dim / 4 - c4);   // float4 of the slice
+    const float *__restrict__ X = a.X + 4 * c4;
+    const int32_t *__restrict__ colidx = a.colidx;
+    float *__restrict__ sums = a.sums + (int64_t)slice * b * (1 + k);
+    const int32_t i0 = (block * GROUPS + grp) * PP;
+    if (i0 >= b) return;
+    const int mp = min(lig / SPAN, PP - 1), mj = lig % SPAN;
+    const int32_t mi = min(i0 + mp, b - 1);                // (a positive past the last one: the last one again, not stored)
+    int32_t mine = 0;
+    if (mj < 3 + 3 * min(k, NB)) mine = colidx[mj < 3 ? 3 * (int64_t)mi + mj : 3 * ((int64_t)b + (int64_t)mi * k) + (mj - 3)];
+    auto id = [&](int p, int j) { return __shfl(mine, p * SPAN + j, LPR); };
+    RowVec<1> hr[PP], pr[PP], pt[PP];
+    int32_t c0[PP];
+#pragma unroll
+    for (int p = 0; p < PP; ++p) {
+        c0[p] = id(p, 0);
+        load_vec<LPR, 1>(X + (int64_t)c0[p] * dim, n4, lig, hr[p]);
+        load_vec<LPR, 1>(X + (int64_t)id(p, 1) * dim, n4, lig, pr[p]);
+        load_vec<LPR, 1>(X + (int64_t)id(p, 2) * dim, n4, lig, pt[p]);
+    }
+    for (int q0 = 0; q0 == 0 || (MORE && q0 < k); q0 += NB) {
+        RowVec<1> e[PP][NB];
+        unsigned tail_mask[PP];
+#pragma unroll
+        for (int p = 0; p < PP; ++p) {
+            tail_mask[p] = 0;
+#pragma unroll
+            for (int q = 0; q < NB; ++q) {
+                const int32_t nh = id(p, 3 + 3 * q), nt = id(p, 5 + 3 * q);
+                const bool ts = nh == c0[p];
+                tail_mask[p] |= ts ? 1u << q : 0u;
+                if (q0 + q < k) load_vec<LPR, 1>(X + (int64_t)(ts ? nt : nh) * dim, n4, lig, e[p][q]);
+            }
+        }
+        if (MORE && q0 + NB < k && mj >= 3 && mj < 3 + 3 * min(k - q0 - NB, NB))   // the next batch's ids
+            mine = colidx[3 * ((int64_t)b + (int64_t)mi * k + q0 + NB) + (mj - 3)];
+#pragma unroll
+        for (int p = 0; p < PP; ++p) {
+            if (q0 == 0) {
+                hr[p].v[0] = add4(hr[p].v[0], pr[p].v[0]);
+                const float s = sum16(lig < n4 ? sum_terms<DIST>(sub4(hr[p].v[0], pt[p].v[0])) : 0.f);
+                if (lig == 0 && i0 + p < b) sums[i0 + p] = s;
+            }
+#pragma unroll
+            for (int q = 0; q < NB; ++q)
+                if (q0 + q < k) {
+                    const float4 x = (tail_mask[p] >> q & 1u) ? sub4(hr[p].v[0], e[p][q].v[0]) : sub4(add4(e[p][q].v[0], pr[p].v[0]), pt[p].v[0]);
+                    const float s = sum16(lig < n4 ? sum_terms<DIST>(x) : 0.f);
+                    if (lig == 0 && i0 + p < b) sums[(int64_t)b + (int64_t)(i0 + p) * k + q0 + q] = s;
+                }
+        }
+    }
+}
+
+// ... second part: a thread per positive adds the shares of its rows, slice by slice, and does the rest of the forward step.
+// per: positives to a loss partial, as the kernel for whole rows has them.
+template <int DIST>
+__device__ inline void forward_combine_body(const int block, const int nslices, const int per, const ForwardArgs &a)
+{
+    __shared__ float s_hinge[kThreads];
+    const int32_t b = a.b, k = a.k, i = block * kThreads + (int)threadIdx.x;
+    const int64_t rows = (int64_t)b * (1 + k);
+    float hinge_sum = 0.f;
+    if (i < b) {
+        auto distance = [&](int64_t row) {
+            float sum = 0.f;
+#pragma unroll 8
+            for (int s = 0; s < nslices; ++s) sum += a.sums[s * rows + row];
+            return finish<DIST>(fabsf(sum));
+        };
+        const float wr = a.rel_weight ? a.rel_weight[a.colidx[3 * (int64_t)i + 1] - a.n_ent] : 1.0f;
+        const float npos = distance(i), dpos = wr * npos;
+        a.scores[i] = dpos;
+        int n_active = 0;
+        for (int q = 0; q < k; ++q) {
+            const int64_t row = (int64_t)b + (int64_t)i * k + q;
+            const float nneg = distance(row), dneg = wr * nneg;
+            const float arg = (a.margin + dpos) - dneg;
+            const bool active = arg > 0.f;
+            a.scores[row] = dneg;
+            if (active) { hinge_sum += arg; ++n_active; }
+            a.coefs[row] = formed_coef<DIST>(active ? -a.scale * wr : 0.f, nneg);
+        }
+        a.coefs[i] = formed_coef<DIST>((float)n_active * a.scale * wr, npos);
+    }
+    s_hinge[threadIdx.x] = hinge_sum;
+    __syncthreads();
+    const int at = (int)threadIdx.x * per;
+    if (at < kThreads && block * kThreads + at < b) {
+        float sum = 0.f;
+        for (int g = 0; g < per; ++g) sum += s_hinge[at + g];
+        a.loss_partials[(block * kThreads + at) / per] = sum;
+    }
 }
 
 }  // namespace stx

@@ -260,7 +260,9 @@ struct ForwardArgs {
     const float *rel_weight;   // fixed weight of every relation's distance, or null (gathered rows only)
     int32_t n_ent;
     int32_t stream_rows;       // the table is far larger than the caches: rows used once are fetched past them
-    float *coefs;              // dense kinds: only the rows' coefficients are stored, here (see formed_rows), or null
+    int32_t slice_sums;        // distances are summed as the sliced pass sums them (batches of its sizes)
+    // the sliced pass (see formed_rows): the rows' coefficients, and the slices' shares of their distances
+    float *coefs, *sums;
 };
 
 
@@ -457,13 +459,14 @@ struct FormedRows {
     void *recs;                // 16 bytes for every sorted entry, see k_seg_records
     void *heads;               // a FormedHead (64 bytes) for 64 of them
     float *grads;              // gradient rows of the touched columns, ld floats each (when the update follows at once)
+    float *sums;               // [slices of 64 floats][n_rows], until the records take their place (1 / 64 of the rows)
 };
 inline FormedRows formed_buffers(const stx_ctx *c, int64_t n_rows)
 {
     char *b = (char *)c->gbuf[0];
     const int64_t blocks = (3 * n_rows + 63) / 64;
     const int64_t o1 = (n_rows * 4 + 255) / 256 * 256, o2 = o1 + blocks * 1024, o3 = o2 + (blocks * 64 + 255) / 256 * 256;
-    return {(float *)b, b + o1, b + o2, (float *)(b + o3)};
+    return {(float *)b, b + o1, b + o2, (float *)(b + o3), (float *)(b + o1)};
 }
 
 inline stx_status hip_ok(hipError_t e) { return e == hipSuccess ? STX_OK : STX_ERR_HIP; }

@@ -2,6 +2,8 @@
 // a group, the `hrt` / `ht` gathers of SparseTransX Sec. 4.2, and the distance terms of Sec. 4.3 / 4.6.
 #pragma once
 
+#include <type_traits>
+
 #include "stx_device.h"
 #include "stx_internal.h"
 
@@ -116,9 +118,45 @@ __device__ inline float coef_scale(float coef, float dist)
     return coef;
 }
 
-template <int LPR, int ITERS, int DIST>
+// Sum over 16 neighbouring lanes (in all of them), by data-parallel moves: the bits of group_sum<16>.
+__device__ inline float sum16(float v)
+{
+    auto moved = [](float x, auto ctrl) {
+        return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(x), decltype(ctrl)::value, 0xf, 0xf, false));
+    };
+    v += moved(v, std::integral_constant<int, 0xb1>{});    // the neighbour, the other pair of four, the other four of eight,
+    v += moved(v, std::integral_constant<int, 0x4e>{});    // the other eight
+    v += moved(v, std::integral_constant<int, 0x141>{});
+    v += moved(v, std::integral_constant<int, 0x140>{});
+    return v;
+}
+
+// The terms of a lane's float4, summed in order.
+template <int DIST>
+__device__ inline float sum_terms(float4 y)
+{
+    float a = term<DIST>(y.x);
+    a += term<DIST>(y.y);
+    a += term<DIST>(y.z);
+    a += term<DIST>(y.w);
+    return a;
+}
+
+// SLICES: summed as the sliced forward pass sums (forward_slice_body): 64 floats at a time, these sums in order.
+template <int LPR, int ITERS, int DIST, bool SLICES = false>
 __device__ inline float row_distance(const RowVec<ITERS> &x, int d4, int lig)
 {
+    if constexpr (SLICES) {
+        static_assert(LPR >= 16, "slices of 16 lanes");
+        float sum = 0.f;
+#pragma unroll
+        for (int it = 0; it < ITERS; ++it) {
+            const float mine = sum16(lig + it * LPR < d4 ? sum_terms<DIST>(x.v[it]) : 0.f);
+#pragma unroll
+            for (int g = 0; g < LPR / 16; ++g) sum += __shfl(mine, 16 * g, LPR);
+        }
+        return finish<DIST>(fabsf(sum));
+    }
     float acc = 0.f;
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
