@@ -81,14 +81,16 @@ __global__ __launch_bounds__(kThreads) void k_super_sums(const uint16_t *__restr
 {
     const int tid = threadIdx.x, t0 = blockIdx.x * kSuperTile, t1 = min(t0 + kSuperTile, ntiles);
     if (tid >= radix) return;
-    int32_t a = 0;
-#pragma unroll 8
-    for (int t = t0; t < t1; ++t) a += table[t * radix + tid];
+    int32_t a = 0, v[kSuperTile];
+#pragma unroll
+    for (int u = 0; u < kSuperTile; ++u) v[u] = table[min(t0 + u, t1 - 1) * radix + tid];   // (all in flight together)
+#pragma unroll
+    for (int u = 0; u < kSuperTile; ++u) a += t0 + u < t1 ? v[u] : 0;
     super[blockIdx.x * radix + tid] = a;
 }
 
 template <bool FIRST, bool TWO_LEVEL, int ITEMS>
-__global__ __launch_bounds__(kThreads) void k_scatter(ScatterArgs a)
+__global__ __launch_bounds__(kThreads, 4) void k_scatter(ScatterArgs a)
 {
     scatter_body<FIRST, TWO_LEVEL, ITEMS>((int)blockIdx.x, a);
 }

@@ -23,7 +23,7 @@ constexpr int kRideLds = kScatterLds > emit_lds(true, false) ? kScatterLds : emi
 
 // (a later pass, FIRST false, can also take the first kernel of the next batch's build along: ea.ntiles > 0)
 template <int LPR, int ITERS, int DIST, bool PACKED, bool FIRST, bool K1>
-__global__ __launch_bounds__(kThreads) void k_fwd_scatter(ForwardArgs fa, ScatterArgs sa, EmitAhead ea)
+__global__ __launch_bounds__(kThreads, K1 ? 8 : 1) void k_fwd_scatter(ForwardArgs fa, ScatterArgs sa, EmitAhead ea)
 {
     __shared__ __align__(16) unsigned char s_arena[kRideLds];   // one block of LDS for the sort's bodies
     int block = (int)blockIdx.x;
