@@ -163,8 +163,10 @@ def kernel_work(wl, kernel, rows, touched, fused=False, rides=False, segw=False)
         return rows * (3 * row + 12 + row), "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_seg_reduce_terms":  # semiring backward: the dL/dZ row, the entry's two other table rows and ids in
         return nnz * (3 * row + 16) + touched * row, "GB/s", "hbm", HBM_PEAK_GBS
-    if kernel == "k_forward_stacked_formed":   # the rows' coefficients in place of their dL/dx rows
-        return rows * (3 * row + 12 + 4 + 4), "GB/s", "hbm", HBM_PEAK_GBS
+    if kernel == "k_forward_slices":     # three table rows and ids in (out of the L2 caches), the slices' shares of the distance out
+        return rows * (3 * row + (12 + 4) * ((wl.dim + 63) // 64)), "GB/s", "hbm", HBM_PEAK_GBS
+    if kernel == "k_forward_combine":    # the shares in, score and coefficient out
+        return rows * (4 * ((wl.dim + 63) // 64) + 4 + 4), "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_seg_reduce_formed":  # table rows in and gradient rows out once, 16 B an entry (two more rows an active entry: L2)
         return nnz * 16 + touched * 2 * row, "GB/s", "hbm", HBM_PEAK_GBS
     if kernel == "k_scatter":
@@ -595,7 +597,7 @@ class Job:
         could move, the measured traffic where a profile has it, and the roof the figures are held against."""
         wl = self.wl
         u = touched * mean_rows / wl.rows_per_batch
-        formed = self.formed and kname in ("k_seg_reduce", "k_forward_stacked")
+        formed = self.formed and kname == "k_seg_reduce"
         w, unit, bound, peak = kernel_work(wl, kname + "_formed" if formed else kname, mean_rows, u, self.fused, self.rides,
                                            self.segw)
         ach = w / (us * 1e-6) / (1e9 if unit == "GB/s" else 1e12) if us > 0 else 0.0
@@ -603,13 +605,13 @@ class Job:
              "frac": round(ach / peak, 4),
              "traffic": TRAFFIC_BYTES.get((wl.name, kname, "rides" if self.rides else self.fused)),
              "work_per_launch": int(w), "avg_launch_us": round(us, 2), "roof": roof_of(wl, kname, us)}
-        bmin = None if formed else kernel_min_bytes(wl, kname, mean_rows, u, self.fused)
+        bmin = None if formed or kname in ("k_forward_slices", "k_forward_combine") else kernel_min_bytes(wl, kname, mean_rows, u, self.fused)
         if bmin is not None and us > 0:
             e["min_bytes_per_launch"] = int(bmin)
             e["achieved_min_bytes"] = round(bmin / (us * 1e-6) / 1e9, 1)
         if e["traffic"] and us > 0:
             e["achieved_traffic"] = round(e["traffic"] / (us * 1e-6) / 1e9, 1)
-        if formed and kname == "k_seg_reduce":
+        if formed:
             e["note"] = ("rows of dL/dx formed where they are summed, two table rows for every entry of an active pair, out of the L2 "
                          "caches, whose rate bounds the kernel; the bytes here are those that memory has to move")
         if ach > peak and kname in ("k_forward_stacked", "k_fwd_scatter"):

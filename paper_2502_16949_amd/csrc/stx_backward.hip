@@ -1051,13 +1051,10 @@ __global__ __launch_bounds__(kThreads) void k_sgd_rows(const int32_t *__restrict
 // ---- dispatch --------------------------------------------------------------------------------------
 // Whether a product of n entries is cut into short chunks of 16 entries a lane group (the serial walk of every group is short:
 // latency) or long ones (fewer partial rows, more rows of a run per sum: bandwidth).  The line lies a little above the number of
-// workgroups that the chip holds at once, about 2,000, and higher where a workgroup takes less (packed rows) or half of them
-// little (TransH's and TransR's relation columns).  The same line for every way of calling, as it decides the order of the
-// sums.  us with long and with short chunks, 30,000 entities: TorusE L2, separate calls, d = 200 (2,812 short tiles at 180,000
-// entries): 81.8 and 82.7 at 120,000, 99.7 and 102.5 at 180,000, 296 and 316 at 900,000; TransE L2 steps, d = 200: 48.6 and
-// 45.4, 62.1 and 62.0, 272 and 291; d = 128 (1,406 at 180,000): 42.7 and 42.2 at 180,000, 64.1 and 64.5 at 300,000; L1, d = 128:
-// 44.8 and 43.8 at 300,000, 67.4 and 68.7 at 510,000; TransH, d = 128: 78.5 and 76.4, 117 and 119; ComplEx, d = 200: 49.0 and 49.0
-// at 120,000, 282 and 296 at 900,000.
+// workgroups that the chip holds at once, about 2,000, and higher where a workgroup takes less (packed rows, `light`).  The same
+// line for every way of calling, as it decides the order of the sums.  us with long and with short chunks, 30,000 entities:
+// L1 steps, d = 200: 48.0 and 41.5 at 180,000 entries, 59.7 and 61.4 at 300,000, 159 and 174 at 900,000; d = 128: 44.8 and 43.8 at
+// 300,000, 67.4 and 68.7 at 510,000; ComplEx, d = 200: 49.0 and 49.0 at 120,000, 282 and 296 at 900,000.
 static bool short_chunks(int64_t n, int tile, bool light) { return (n + tile - 1) / tile <= (light ? 3600 : 2304); }
 
 template <int LPR, int ITERS>
@@ -1067,7 +1064,10 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
 {
     constexpr int CH_LONG = LPR == 64 ? 64 : (LPR < 32 ? LPR : 32), CH_SHORT = LPR < 16 ? LPR : 16;
     constexpr int GROUPS = kThreads / LPR;
-    const bool small = short_chunks(e_end - e_begin, GROUPS * CH_SHORT, packed_src || second);
+    // Dense rows of TransE, TorusE and TransH keep short chunks up to a million entries: their sums round, and a training run that
+    // adds them in another order soon decides some hinge the other way.  (The L1 kinds' are whole multiples of a coefficient.)
+    const bool small = packed_src || c->cfg.model == STX_TRANSR ? short_chunks(e_end - e_begin, GROUPS * CH_SHORT, true)
+                                                                : (e_end - e_begin) <= (1 << 20);
     const int tile = GROUPS * (small ? CH_SHORT : CH_LONG);
     const int ntiles1 = (e_end - e_begin + tile - 1) / tile;
     SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0};

@@ -41,13 +41,12 @@ def test_sorted_transpose_of_full_tiles(entries, skew):
     assert np.array_equal(inc.at_seg_ptr[:u + 1].cpu().numpy(), np.append(start, nnz))
 
 
-# 2,304 tiles of the short chunks: 64 entries each at more than 128 floats a row, 128 at 65 to 128; both sides of the line
-@pytest.mark.parametrize("dim,rows", [(200, 2304 * 64 // 3), (200, 2304 * 64 // 3 + 2), (128, 2304 * 128 // 3), (128, 2304 * 128 // 3 + 2),
-                                      (520, 2304 * 64 // 3 + 2), (1024, 2304 * 64 // 3 + 2)])
-@pytest.mark.parametrize("dist", ["l2", "l1"])
-def test_product_on_both_sides_of_the_chunk_lines(dim, rows, dist):
-    if dist == "l1":
-        rows = rows * 3600 // 2304
+# 3,600 tiles of the short chunks: 64 entries each at more than 128 floats a row, 128 at 65 to 128; both sides of the line, and of
+# a million entries for the dense kinds
+@pytest.mark.parametrize("dist,dim,rows", [("l1", 200, 3600 * 64 // 3), ("l1", 200, 3600 * 64 // 3 + 2), ("l1", 128, 3600 * 128 // 3),
+                                           ("l1", 128, 3600 * 128 // 3 + 2), ("l1", 520, 3600 * 64 // 3 + 2), ("l1", 1024, 3600 * 64 // 3 + 2),
+                                           ("l2", 200, (1 << 20) // 3 - 1), ("l2", 200, (1 << 20) // 3 + 1), ("l2", 128, (1 << 20) // 3 + 1)])
+def test_product_on_both_sides_of_the_chunk_lines(dist, dim, rows):
     b, n_ent, n_rel = rows // 2, 30_000, 7
     gen = torch.Generator(device=DEV)
     gen.manual_seed(rows + dim)
