@@ -770,8 +770,10 @@ __global__ __launch_bounds__(THREADS, RIDE == 5 ? 4 : (ITERS == 1 && FUSED && RI
 // workgroup for each of a wide row's slices mostly starts to find that out once more (16 slices of 9,216 tiles: 105 us as 16
 // workgroups a tile, 65 as four).  A kernel of its own: the loop costs the others registers (four float4 per lane: 102 and 132
 // with the update fused, four and three wavefronts per SIMD; 65 and 110 without, seven and four).
+// Bound to eight wavefronts per SIMD, and without the wait for all arguments at the start, as most of its workgroups only look at
+// a few words and end: 260,000 positives and as many negatives, d = 200: 34.3 us, with seven 40.0.
 template <int LPR, int ITERS, int CHUNK, bool FUSED, int RIDE, bool MANY = false>
-__global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restrict__ packed,
+__global__ __launch_bounds__(kThreads, MANY && !FUSED ? 8 : 1) void k_seg_fixup(const int32_t *__restrict__ packed,
                                                         const int32_t *__restrict__ seg_id,
                                                         const int32_t *__restrict__ seg_ptr, int32_t e_begin,
                                                         int32_t e_end, int d4, float *__restrict__ out_rows,
@@ -780,7 +782,7 @@ __global__ __launch_bounds__(kThreads) void k_seg_fixup(const int32_t *__restric
                                                         EmitAhead ea)
 {
     int block = (int)blockIdx.x;
-    STX_TOGETHER(ha.ntiles, sa.ntiles, dm.blocks, sec.first_block, gridDim.x, gridDim.y, packed, seg_id, seg_ptr, e_begin, e_end, d4, ld_out, partials);
+    if constexpr (!MANY) STX_TOGETHER(ha.ntiles, sa.ntiles, dm.blocks, sec.first_block, gridDim.x, gridDim.y, packed, seg_id, seg_ptr, e_begin, e_end, d4, ld_out, partials);
     if constexpr (RIDE == 4) {
         if (block < ea.ntiles) {      // uniform in the workgroup
             emit_body<kBigSortItems, false, true, false>(block, ea.ntiles, ea.args);

@@ -25,8 +25,8 @@ def _notes(elf):
 
 
 @pytest.fixture(scope="module")
-def registers():
-    """Mangled kernel name -> vector registers (of both kinds)."""
+def kernels():
+    """Mangled kernel name -> what the compiler says about it."""
     lib = open(B.LIB_PATH, "rb").read()
     out = {}
     for m in re.finditer(MAGIC, lib):
@@ -39,9 +39,15 @@ def registers():
             if lib[at - idlen:at].endswith(b"gfx950"):
                 for what, desc in _notes(lib[m.start() + off:m.start() + off + size]):
                     if what == 32:                         # NT_AMDGPU_METADATA
-                        out.update((k[".name"], k[".vgpr_count"]) for k in msgpack.unpackb(desc)["amdhsa.kernels"])
+                        out.update((k[".name"], k) for k in msgpack.unpackb(desc)["amdhsa.kernels"])
     assert len(out) > 100
     return out
+
+
+@pytest.fixture(scope="module")
+def registers(kernels):
+    """Mangled kernel name -> vector registers (of both kinds)."""
+    return {name: k[".vgpr_count"] for name, k in kernels.items()}
 
 
 def _waves(vgprs):
@@ -55,3 +61,9 @@ def test_fixup_of_single_slices(registers, iters, fused, waves):
     seen = [v for k, v in registers.items()
             if re.search(r"k_seg_fixupILi\d+ELi%dELi\d+ELb%dELi0E(Lb0E)?E" % (iters, fused), k)]
     assert seen and all(_waves(v) >= waves for v in seen), seen
+
+
+# The fix-up whose workgroups take several column slices: 65 registers were a wavefront less, and 40.0 us in place of 34.3.
+def test_fixup_of_many_slices(registers):
+    seen = [v for k, v in registers.items() if re.search(r"k_seg_fixupILi16ELi1ELi16ELb[01]ELi0ELb1EE", k)]
+    assert len(seen) == 2 and all(_waves(v) >= 8 for v in seen), seen
