@@ -67,3 +67,9 @@ def test_fixup_of_single_slices(registers, iters, fused, waves):
 def test_fixup_of_many_slices(registers):
     seen = [v for k, v in registers.items() if re.search(r"k_seg_fixupILi16ELi1ELi16ELb[01]ELi0ELb1EE", k)]
     assert len(seen) == 2 and all(_waves(v) >= 8 for v in seen), seen
+
+
+# Distances over rows of y of one float4 per lane (all that a projection can be wide): nothing of them goes to memory.
+def test_distances_over_rows_of_y_do_not_spill(kernels):
+    seen = [k[".vgpr_spill_count"] for name, k in kernels.items() if re.search(r"k_forward_yILi\d+ELi1E", name)]
+    assert len(seen) == 20 and not any(seen), seen
