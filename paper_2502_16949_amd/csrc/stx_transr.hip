@@ -287,6 +287,8 @@ struct RowsArgs {
 // (DIFF), U float4 a thread and turn.  All loads of a turn are in flight together, with no branch between them: with a difference
 // formed where its row was known to be one of the item's, each waited for its own two loads, eight round trips one behind the
 // other.  k_transr_fused, 16,384 positives, d = k = 128: 25.0 -> 22.6 us; k_transr_rows, 925,000 rows, d = k = 64: 161 -> 140.
+// U is what a thread has to stage, width / 16, up to 8, as rows past the last are loaded all the same: k_transr_fused, 20,000
+// positives, d = k = 32: 14.9 us with eight, 14.0 with two; d = k = 64: 17.9 with eight, 17.5 with four.
 template <int U, bool DIFF>
 __device__ inline void stage_rows(uint16_t *s_a, const float *__restrict__ src, const int32_t *ra, const int32_t *rb, int width, int count)
 {
@@ -328,7 +330,7 @@ __device__ inline void stage_rows(uint16_t *s_a, const float *__restrict__ src, 
 // GX = true : GX[row] = gy . M_r              (out width d, reduction over k)
 // SMALL (both widths <= 128): all of the wavefront's M_r fragments are requested before the operand rows
 // are staged, so that their latency is hidden behind the gather instead of following it.
-template <bool GX, bool SMALL>
+template <bool GX, bool SMALL, int U = 8>
 __global__ __launch_bounds__(kThreads) void k_transr_rows(RowsArgs p, const float *__restrict__ gy,
                                                           float *__restrict__ out)
 {
@@ -367,7 +369,7 @@ __global__ __launch_bounds__(kThreads) void k_transr_rows(RowsArgs p, const floa
     // stage the tile: rows past `count` are zero
     const int stride = p.n_red + kLdsPad;
     if constexpr (GX) stage_rows<8, false>(s_a, gy, s_row, s_row, p.n_red, count);
-    else stage_rows<SMALL ? 4 : 8, true>(s_a, p.E, s_h, s_t, p.n_red, count);
+    else stage_rows<U, true>(s_a, p.E, s_h, s_t, p.n_red, count);
     __syncthreads();
 
     {   // the transposed tile, in operand order, for the dM product (reduction steps past `count` are never read)
@@ -465,7 +467,8 @@ struct FusedArgs {
 // The first workgroups of the launch may run the first kernel of the next batch's build (ea.ntiles > 0), which
 // overwrites the caller's A arrays: the launcher lets it ride only when p.colidx is the context's own copy of this
 // batch's column ids.
-template <int DIST>
+// U: float4 that a thread stages in one turn (stage_rows).
+template <int DIST, int U>
 __global__ __launch_bounds__(kThreads, 3) void k_transr_fused(FusedArgs p, EmitAhead ea)
 {
     constexpr int kW = 128;
@@ -515,7 +518,7 @@ __global__ __launch_bounds__(kThreads, 3) void k_transr_fused(FusedArgs p, EmitA
     }
     __syncthreads();
     // ---- x = E[h] - E[t] of the 64 slots as bfloat16 (slots past `count` are zero)
-    stage_rows<8, true>(s_a, p.E, s_h, s_t, d, count);
+    stage_rows<U, true>(s_a, p.E, s_h, s_t, d, count);
     __syncthreads();
     // ---- a tile of 64 slots, transposed into operand order for the dM product
     auto put_transposed = [&](uint16_t *tiles, int width) {
@@ -794,12 +797,13 @@ stx_status launch_transr_project(stx_ctx *c, const stx_incidence *inc, const stx
     c->prep_inc = nullptr;      // the copies of M_r are good for this forward pass only: the update changes M_r
     c->tr_fused_inc = nullptr;
     ProfScope prof(c, "k_transr_project");
-    if (c->cfg.dim <= 128 && c->cfg.rel_dim <= 128)
-        hipLaunchKernelGGL((k_transr_rows<false, true>), dim3(row_items_max(c, inc->n_rows)), dim3(kThreads), 0,
-                           c->stream, rows_args(c, inc, p, false), (const float *)nullptr, c->gbuf[0]);
-    else
-        hipLaunchKernelGGL((k_transr_rows<false, false>), dim3(row_items_max(c, inc->n_rows)), dim3(kThreads), 0,
-                           c->stream, rows_args(c, inc, p, false), (const float *)nullptr, c->gbuf[0]);
+#define STX_ROWS(SMALL, U)                                                                                      \
+    hipLaunchKernelGGL((k_transr_rows<false, SMALL, U>), dim3(row_items_max(c, inc->n_rows)), dim3(kThreads), 0, \
+                       c->stream, rows_args(c, inc, p, false), (const float *)nullptr, c->gbuf[0])
+    if (c->cfg.dim <= 128 && c->cfg.rel_dim <= 128) STX_ROWS(true, 4);
+    else if (c->cfg.dim <= 64) STX_ROWS(false, 4);
+    else STX_ROWS(false, 8);
+#undef STX_ROWS
     return hip_ok(hipGetLastError());
 }
 
@@ -842,13 +846,18 @@ stx_status launch_transr_fused(stx_ctx *c, const stx_incidence *inc, const stx_p
     const dim3 grid(items + (unsigned)ea.ntiles);
     {
         ProfScope prof(c, "k_transr_fused");
+#define STX_FUSED_U(D, U) hipLaunchKernelGGL((k_transr_fused<D, U>), grid, dim3(kThreads), 0, c->stream, a, ea)
+#define STX_FUSED(D)                                                                                            \
+    do { if (a.d <= 32) STX_FUSED_U(D, 2); else if (a.d <= 64) STX_FUSED_U(D, 4); else STX_FUSED_U(D, 8); } while (0)
         switch (c->cfg.dist) {
-        case STX_L1: hipLaunchKernelGGL(k_transr_fused<STX_L1>, grid, dim3(kThreads), 0, c->stream, a, ea); break;
-        case STX_L2: hipLaunchKernelGGL(k_transr_fused<STX_L2>, grid, dim3(kThreads), 0, c->stream, a, ea); break;
-        case STX_TORUS_L1: hipLaunchKernelGGL(k_transr_fused<STX_TORUS_L1>, grid, dim3(kThreads), 0, c->stream, a, ea); break;
-        case STX_L2_SQ: hipLaunchKernelGGL(k_transr_fused<STX_L2_SQ>, grid, dim3(kThreads), 0, c->stream, a, ea); break;
-        default: hipLaunchKernelGGL(k_transr_fused<STX_TORUS_L2>, grid, dim3(kThreads), 0, c->stream, a, ea); break;
+        case STX_L1: STX_FUSED(STX_L1); break;
+        case STX_L2: STX_FUSED(STX_L2); break;
+        case STX_TORUS_L1: STX_FUSED(STX_TORUS_L1); break;
+        case STX_L2_SQ: STX_FUSED(STX_L2_SQ); break;
+        default: STX_FUSED(STX_TORUS_L2); break;
         }
+#undef STX_FUSED
+#undef STX_FUSED_U
     }
     c->tr_fused_inc = inc;
     if (c->defer_finish) { c->fin_n = (int)items; c->fin_scale = scale; c->fin_loss = loss; return hip_ok(hipGetLastError()); }

@@ -73,3 +73,9 @@ def test_fixup_of_many_slices(registers):
 def test_distances_over_rows_of_y_do_not_spill(kernels):
     seen = [k[".vgpr_spill_count"] for name, k in kernels.items() if re.search(r"k_forward_yILi\d+ELi1E", name)]
     assert len(seen) == 20 and not any(seen), seen
+
+
+# TransR's fused forward kernel for operand rows of up to 64 floats, which stages as many float4 a thread as they have.
+def test_transr_fused_stages_narrow_rows(registers):
+    seen = [v for k, v in registers.items() if re.search(r"k_transr_fusedILi\dELi[24]EE", k)]
+    assert len(seen) == 10 and all(_waves(v) >= 4 for v in seen), seen
