@@ -547,6 +547,14 @@ stx_status stx_forward(stx_ctx *ctx, const stx_incidence *inc, const stx_params 
     return run_forward(ctx, inc, p, scores, loss, false);
 }
 
+// The L1 kinds' coefficients are whole multiples of one number, each at most k times it, when no weights of relations are on
+// them.  If that is a power of two, the sums of a batch whose chunks this decides (at most 2^20 entries) are exact.
+static bool exact_sums(const stx_ctx *ctx, const stx_incidence *inc, const stx_params *p)
+{
+    const int64_t pairs = (int64_t)inc->b * inc->k;
+    return !p->rel_weight && (ctx->cfg.reduce != STX_MEAN || (pairs & (pairs - 1)) == 0);
+}
+
 // The backward pass.  lr == nullptr: gradients go to g.  Otherwise the update is applied where a
 // gradient would be stored and g is not touched (it may be null).
 static stx_status run_backward(stx_ctx *ctx, const stx_incidence *inc, const stx_params *p, stx_grads *g,
@@ -570,7 +578,8 @@ static stx_status run_backward(stx_ctx *ctx, const stx_incidence *inc, const stx
                                                                   packed_coef_offset(inc->n_rows, packed_stride(dim)))
                                 : ctx->gbuf[0];
         return launch_seg_reduce(ctx, inc, 0, inc->nnz, ctx->gbuf[0], coefs, inc->nnz, pk ? packed_stride(dim) : dim, dim,
-                                 rows, ctx->ld, pk, lr ? &fh : nullptr);
+                                 rows, ctx->ld, !pk ? SegRows::dense : exact_sums(ctx, inc, p) ? SegRows::packed_exact : SegRows::packed,
+                                 lr ? &fh : nullptr);
     }
     const SegFusedHost fh{p->ent, p->rel, (int32_t)ctx->cfg.n_ent, lr ? *lr : 0.f, 0};
     if (ctx->cfg.model == STX_TRANSH) {
@@ -579,7 +588,7 @@ static stx_status run_backward(stx_ctx *ctx, const stx_incidence *inc, const stx
         const SegSecondHost second{(int32_t)ent_end, (int32_t)inc->nnz, ctx->gbuf[2], lr ? nullptr : g->w_rows, p->w,
                                    (ctx->cfg.flags & STX_FLAG_RENORM_W) ? 2 : 0, inc->b};
         return launch_seg_reduce(ctx, inc, 0, inc->nnz, ctx->gbuf[0], ctx->gbuf[1], ent_end, dim, dim, rows, ctx->ld,
-                                 false, lr ? &fh : nullptr, &second);
+                                 SegRows::dense, lr ? &fh : nullptr, &second);
     }
     // TransR: gx = M_r^T gy and dL/dM_r on the matrix cores, then entity columns sum gx (signed, width dim)
     // and relation columns sum gy (width rel_dim)
@@ -590,13 +599,13 @@ static stx_status run_backward(stx_ctx *ctx, const stx_incidence *inc, const stx
     const SegSecondHost sums{0, 0, nullptr, nullptr, nullptr, 0, ctx->tr_fused_inc == inc ? inc->b : 0};
     if (dim == ctx->cfg.rel_dim) {   // rows of equal width: one product over all columns, as for TransH
         s = launch_seg_reduce(ctx, inc, 0, inc->nnz, ctx->gbuf[1], ctx->gbuf[0], ent_end, dim, dim, rows, ctx->ld,
-                              false, lr ? &fh : nullptr, &sums);
+                              SegRows::dense, lr ? &fh : nullptr, &sums);
     } else {
-        s = launch_seg_reduce(ctx, inc, 0, ent_end, ctx->gbuf[1], ctx->gbuf[1], ent_end, dim, dim, rows, ctx->ld, false,
+        s = launch_seg_reduce(ctx, inc, 0, ent_end, ctx->gbuf[1], ctx->gbuf[1], ent_end, dim, dim, rows, ctx->ld, SegRows::dense,
                               lr ? &fh : nullptr);
         if (s != STX_OK) return s;
         s = launch_seg_reduce(ctx, inc, ent_end, inc->nnz, ctx->gbuf[0], ctx->gbuf[0], ent_end, ctx->cfg.rel_dim,
-                              ctx->cfg.rel_dim, rows, ctx->ld, false, lr ? &fh : nullptr, &sums);
+                              ctx->cfg.rel_dim, rows, ctx->ld, SegRows::dense, lr ? &fh : nullptr, &sums);
     }
     if (s != STX_OK) return s;
     return launch_transr_dm_late(ctx);   // (nothing left to do unless no launch above ran)

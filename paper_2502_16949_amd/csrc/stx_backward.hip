@@ -1051,25 +1051,29 @@ __global__ __launch_bounds__(kThreads) void k_sgd_rows(const int32_t *__restrict
 }
 
 // ---- dispatch --------------------------------------------------------------------------------------
-// Whether a product of n entries is cut into short chunks of 16 entries a lane group (the serial walk of every group is short:
-// latency) or long ones (fewer partial rows, more rows of a run per sum: bandwidth).  The line lies a little above the number of
-// workgroups that the chip holds at once, about 2,000, and higher where a workgroup takes less (packed rows, `light`).  The same
-// line for every way of calling, as it decides the order of the sums.  us with long and with short chunks, 30,000 entities:
-// L1 steps, d = 200: 48.0 and 41.5 at 180,000 entries, 59.7 and 61.4 at 300,000, 159 and 174 at 900,000; d = 128: 44.8 and 43.8 at
-// 300,000, 67.4 and 68.7 at 510,000; ComplEx, d = 200: 49.0 and 49.0 at 120,000, 282 and 296 at 900,000.
-static bool short_chunks(int64_t n, int tile, bool light) { return (n + tile - 1) / tile <= (light ? 3600 : 2304); }
+// A product is cut into short chunks of 16 entries a lane group (the serial walk of every group is short: latency) or long ones
+// (fewer partial rows, more rows of a run per sum: bandwidth; with fewer than 32 lanes a group there is one length).  The same
+// line for every way of calling, as it decides the order of the sums.
+//
+// Sums that round (dense rows; the L1 kinds' when a mean over a number of pairs that is no power of two, or weights of relations,
+// scale them) keep short chunks up to a million entries: a training run that adds in another order soon decides some hinge the
+// other way.  Long ones would give TransR's step at d = k = 128 one per cent from 420,000 entries on.
+// Exact sums have the same bits either way.  us of an L1 step with short and with long chunks, 30,000 entities: d = 128: 63.4 and
+// 64.2 at 300,000 entries, 78.1 and 76.1 at 420,000, 111.8 and 108.1 at 720,000; d = 200: 71.7 and 74.6 at 240,000, 82.2 and 82.2 at
+// 300,000, 104.1 and 98.9 at 420,000, 178 and 164 at 900,000; two slices a row, d = 512: 82.5 and 85.4 at 120,000, 103 and 98.5 at
+// 180,000; four, d = 1024: 85.9 and 89.2 at 60,000, 127 and 123 at 120,000.  (Products alone, without the last kernel of the build
+// in their launch, meet their line at half as many entries: d = 200: 14.2 and 16.5 at 120,000, 17.9 and 17.2 at 180,000.)
+static bool short_chunks(int64_t n, int slices, bool exact) { return exact ? n * slices <= 300000 : n <= (1 << 20); }
 
 template <int LPR, int ITERS>
 static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_t e_end, const float *src_a,
                    const float *src_b, int32_t split, int ld_src, int width, float *out_rows, int ld_out,
-                   bool packed_src, const FusedArgs *fused, const SegSecondHost *second)
+                   SegRows kind, const FusedArgs *fused, const SegSecondHost *second)
 {
+    const bool packed_src = kind != SegRows::dense;
     constexpr int CH_LONG = LPR == 64 ? 64 : (LPR < 32 ? LPR : 32), CH_SHORT = LPR < 16 ? LPR : 16;
     constexpr int GROUPS = kThreads / LPR;
-    // Dense rows of TransE, TorusE and TransH keep short chunks up to a million entries: their sums round, and a training run that
-    // adds them in another order soon decides some hinge the other way.  (The L1 kinds' are whole multiples of a coefficient.)
-    const bool small = packed_src || c->cfg.model == STX_TRANSR ? short_chunks(e_end - e_begin, GROUPS * CH_SHORT, true)
-                                                                : (e_end - e_begin) <= (1 << 20);
+    const bool small = short_chunks(e_end - e_begin, ITERS, kind == SegRows::packed_exact);
     const int tile = GROUPS * (small ? CH_SHORT : CH_LONG);
     const int ntiles1 = (e_end - e_begin + tile - 1) / tile;
     SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0};
@@ -1261,7 +1265,7 @@ static void seg_slices(stx_ctx *c, const stx_incidence *inc, const float *src, i
 
 stx_status launch_seg_reduce(stx_ctx *c, const stx_incidence *inc, int64_t e_begin, int64_t e_end,
                              const float *src_a, const float *src_b, int64_t split, int ld_src, int width,
-                             float *out_rows, int ld_out, bool packed_src, const SegFusedHost *fh,
+                             float *out_rows, int ld_out, SegRows kind, const SegFusedHost *fh,
                              const SegSecondHost *second)
 {
     if (e_end <= e_begin) return STX_OK;
@@ -1276,7 +1280,7 @@ stx_status launch_seg_reduce(stx_ctx *c, const stx_incidence *inc, int64_t e_beg
         return hip_ok(hipGetLastError());
     }
     STX_DISPATCH_ROW(L, seg_go, c, inc, (int32_t)e_begin, (int32_t)e_end, src_a, src_b, (int32_t)split, ld_src, width,
-                     out_rows, ld_out, packed_src, fused, second);
+                     out_rows, ld_out, kind, fused, second);
     return hip_ok(hipGetLastError());
 }
 
@@ -1286,7 +1290,7 @@ static void semiring_t_go(stx_ctx *c, const stx_incidence *inc, const float *X, 
     constexpr int CH_LONG = LPR == 64 ? 64 : (LPR < 32 ? LPR : 32), CH_SHORT = LPR < 16 ? LPR : 16;
     constexpr int GROUPS = kThreads / LPR;
     const int32_t nnz = (int32_t)inc->nnz;
-    const bool small = short_chunks(nnz, GROUPS * CH_SHORT, false);
+    const bool small = (nnz + GROUPS * CH_SHORT - 1) / (GROUPS * CH_SHORT) <= 2304;   // workgroups that the chip holds at once
     const int tile = GROUPS * (small ? CH_SHORT : CH_LONG), ntiles = (nnz + tile - 1) / tile;
     const dim3 grid((unsigned)ntiles, (unsigned)ITERS);    // wide rows: column slices of one float4 per lane
     const int d4 = c->cfg.dim / 4;

@@ -357,9 +357,11 @@ struct SegFusedHost {
     float lr;
     int mode;
 };
+// The source rows: dense, or the L1 kinds' records (see k_seg_reduce); packed_exact when no sum of them rounds, in any order.
+enum class SegRows { dense, packed, packed_exact };
 stx_status launch_seg_reduce(stx_ctx *, const stx_incidence *, int64_t e_begin, int64_t e_end, const float *src_a,
                              const float *src_b, int64_t split, int ld_src, int width, float *out_rows, int ld_out,
-                             bool packed_src = false, const SegFusedHost *fused = nullptr,
+                             SegRows kind = SegRows::dense, const SegFusedHost *fused = nullptr,
                              const SegSecondHost *second = nullptr);
 // TransE / TorusE with formed_rows: out_rows[segment] as launch_seg_reduce forms it, from the coefficients and the table
 stx_status launch_seg_formed(stx_ctx *, const stx_incidence *, const stx_params *, float *out_rows, int ld_out);

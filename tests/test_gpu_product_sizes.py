@@ -41,10 +41,10 @@ def test_sorted_transpose_of_full_tiles(entries, skew):
     assert np.array_equal(inc.at_seg_ptr[:u + 1].cpu().numpy(), np.append(start, nnz))
 
 
-# 3,600 tiles of the short chunks: 64 entries each at more than 128 floats a row, 128 at 65 to 128; both sides of the line, and of
-# a million entries for the dense kinds
-@pytest.mark.parametrize("dist,dim,rows", [("l1", 200, 3600 * 64 // 3), ("l1", 200, 3600 * 64 // 3 + 2), ("l1", 128, 3600 * 128 // 3),
-                                           ("l1", 128, 3600 * 128 // 3 + 2), ("l1", 520, 3600 * 64 // 3 + 2), ("l1", 1024, 3600 * 64 // 3 + 2),
+# 300,000 entries of the exact sums (of the L1 kinds), divided by the slices of 256 floats that a row has, and a million of the
+# others: both sides of the lines, and the lengths of a lane group's walk on either side at 32 and 64 lanes
+@pytest.mark.parametrize("dist,dim,rows", [("l1", 200, 100_000), ("l1", 200, 100_002), ("l1", 128, 100_000), ("l1", 128, 100_002),
+                                           ("l1", 520, 33_332), ("l1", 520, 33_334), ("l1", 1024, 25_000), ("l1", 1024, 25_002),
                                            ("l2", 200, (1 << 20) // 3 - 1), ("l2", 200, (1 << 20) // 3 + 1), ("l2", 128, (1 << 20) // 3 + 1)])
 def test_product_on_both_sides_of_the_chunk_lines(dist, dim, rows):
     b, n_ent, n_rel = rows // 2, 30_000, 7
@@ -80,3 +80,73 @@ def test_product_on_both_sides_of_the_chunk_lines(dist, dim, rows):
     # each term is off by its distance's and its own roundings, each sum by one rounding a level and entry of a chunk and of the
     # partial rows: 1e-5 of the terms' magnitudes, as everywhere
     assert torch.all((grads.rows[:u, :dim].double() - want[touched]).abs() <= 1e-5 * size[touched] + 1e-30)
+
+
+# Sums that round are added in one order up to a million entries, also where the exact ones change theirs (more than 300,000
+# entries) or once did (460,800 of 65 to 128 floats, 230,400 of more): a column that sorts first and has the same entries in a
+# batch on either side gets the same bits.  The mean's scale is halved by twice the pairs, exactly.
+@pytest.mark.parametrize("model,dist,dim,mean,weights,b_small,b_large", [
+    ("transe", "l1", 200, False, True, 38_000, 76_000), ("transe", "l1", 200, True, False, 29_000, 58_000),
+    ("toruse", "torus_l1", 128, False, True, 49_000, 98_000), ("toruse", "torus_l1", 128, True, False, 40_000, 80_000),
+    ("transe", "l1", 520, False, True, 24_000, 48_000), ("transe", "l2", 200, False, False, 38_000, 76_000),
+    ("transr", "l2", 128, False, False, 76_000, 77_000), ("transr", "l2", 256, False, False, 38_000, 39_000)])
+def test_sums_that_round_keep_their_order(model, dist, dim, mean, weights, b_small, b_large):
+    n_ent, n_rel, hot = 30_000, 7, 9_000
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(dim)
+    rand = lambda *shape: torch.rand(*shape, generator=gen, device=DEV) - 0.5
+    p = B.Params(rand(n_ent, dim), rand(n_rel, dim), proj=rand(n_rel, dim, dim)) if model == "transr" else \
+        B.Params(rand(n_ent + n_rel, dim), rel_weight=torch.rand(n_rel, generator=gen, device=DEV) + 0.3 if weights else None)
+    if model == "toruse":
+        p.ent.copy_(p.ent - torch.floor(p.ent))
+    ints = lambda lo, hi: torch.randint(lo, hi, (b_large,), generator=gen, device=DEV, dtype=torch.int32)
+    h, r, t, nh = ints(1, n_ent), ints(0, n_rel), ints(1, n_ent), ints(1, n_ent)
+    h[torch.randperm(b_small, generator=gen, device=DEV)[:hot]] = 0
+    got = []
+    for b in (b_small, b_large):
+        ctx = B.Context(B.make_config(model, dist, n_ent, n_rel, dim, b, 1, rel_dim=dim, margin=1000.0,   # every pair is active
+                                      reduce=B.STX_MEAN if mean else B.STX_SUM,
+                                      flags=B.STX_FLAG_BF16_PROJ if model == "transr" else 0), DEV)
+        inc, grads = B.Incidence(ctx), B.Grads(ctx)
+        scores, loss = torch.zeros(2 * b, device=DEV), torch.zeros(1, device=DEV)
+        B.stx_build_incidence(ctx, h[:b], r[:b], t[:b], nh[:b], t[:b], 1, inc)
+        B.stx_forward(ctx, inc, p, scores, loss)
+        B.stx_backward(ctx, inc, p, grads)
+        torch.cuda.synchronize()
+        assert int(inc.at_touched_cols[0]) == 0 and int(inc.at_seg_ptr[1]) == hot
+        got.append(grads.rows[0, :dim] * (b / b_small if mean else 1.0))
+    assert torch.equal(got[0].view(torch.int32), got[1].view(torch.int32))
+
+
+# TransR's rows of dL/dx and dL/dy, on both sides of a million entries: a batch's gradient is the sum of its halves', which lie on
+# the short side.
+@pytest.mark.parametrize("dim", [64, 128, 256])
+@pytest.mark.parametrize("b", [(1 << 20) // 6, (1 << 20) // 6 + 2])
+def test_transr_product_on_both_sides_of_a_million_entries(dim, b):
+    n_ent, n_rel = 5_000, 7
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(dim + b)
+    rand = lambda *shape: torch.rand(*shape, generator=gen, device=DEV) - 0.5
+    p = B.Params(rand(n_ent, dim), rand(n_rel, dim), proj=rand(n_rel, dim, dim))
+    h, r, t, nh = (torch.randint(0, hi, (b,), generator=gen, device=DEV, dtype=torch.int32) for hi in (n_ent, n_rel, n_ent, n_ent))
+    h[: b // 3] = 11
+
+    def gradient(part):
+        n = len(h[part])
+        ctx = B.Context(B.make_config("transr", "l2", n_ent, n_rel, dim, n, 1, rel_dim=dim, margin=1000.0, flags=B.STX_FLAG_BF16_PROJ), DEV)
+        inc, grads = B.Incidence(ctx), B.Grads(ctx)
+        scores, loss = torch.zeros(2 * n, device=DEV), torch.zeros(1, device=DEV)
+        B.stx_build_incidence(ctx, h[part], r[part], t[part], nh[part], t[part], 1, inc)
+        B.stx_forward(ctx, inc, p, scores, loss)
+        B.stx_backward(ctx, inc, p, grads)
+        torch.cuda.synchronize()
+        u = int(inc.n_touched.item())
+        out = torch.zeros(n_ent + n_rel, dim, dtype=torch.float64, device=DEV)
+        out[inc.at_touched_cols[:u].long()] = grads.rows[:u, :dim].double()
+        return out
+
+    got, want = gradient(slice(0, b)), gradient(slice(0, b // 2)) + gradient(slice(b // 2, b))
+    # the terms' magnitudes: |dL/dy| is one (L2, weight one), so |dL/dx| is at most the largest |M_r|, row by row
+    bound = torch.cat([p.proj.norm(dim=1).max().expand(n_ent), torch.ones(n_rel, device=DEV)]).double()[:, None]
+    count = torch.bincount(torch.cat([h, nh, t, t, r + n_ent, r + n_ent]).cpu().long(), minlength=n_ent + n_rel).to(DEV)
+    assert torch.all((got - want).abs() <= 1e-5 * bound * count[:, None])
