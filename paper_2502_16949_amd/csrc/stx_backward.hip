@@ -1290,7 +1290,11 @@ static void semiring_t_go(stx_ctx *c, const stx_incidence *inc, const float *X, 
     constexpr int CH_LONG = LPR == 64 ? 64 : (LPR < 32 ? LPR : 32), CH_SHORT = LPR < 16 ? LPR : 16;
     constexpr int GROUPS = kThreads / LPR;
     const int32_t nnz = (int32_t)inc->nnz;
-    const bool small = (nnz + GROUPS * CH_SHORT - 1) / (GROUPS * CH_SHORT) <= 2304;   // workgroups that the chip holds at once
+    // Short chunks (see short_chunks) up to where long ones are faster at every size measured; below, either is, by how full the
+    // last workgroups leave the chip.  ComplEx, us with short and with long ones at 162,000, 240,000, 330,000 and 390,000 entries:
+    // d = 128: 32.1 and 34.6, 45.3 and 44.1, 59.6 and 60.8, 67.2 and 64.0; d = 200: 53.5 and 55.7, 75.1 and 72.5, 101 and 103, 116
+    // and 108 (900,000: 254 and 239); two slices a row, d = 512: 114 and 116, 163 and 165, 219 and 221, 257 and 248.
+    const bool small = nnz <= 360000;
     const int tile = GROUPS * (small ? CH_SHORT : CH_LONG), ntiles = (nnz + tile - 1) / tile;
     const dim3 grid((unsigned)ntiles, (unsigned)ITERS);    // wide rows: column slices of one float4 per lane
     const int d4 = c->cfg.dim / 4;

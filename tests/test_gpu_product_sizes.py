@@ -118,6 +118,43 @@ def test_sums_that_round_keep_their_order(model, dist, dim, mean, weights, b_sma
     assert torch.equal(got[0].view(torch.int32), got[1].view(torch.int32))
 
 
+# The semiring gradient, whose line is 360,000 entries.
+@pytest.mark.parametrize("kind", [B.STX_DISTMULT, B.STX_COMPLEX, B.STX_ROTATE])
+@pytest.mark.parametrize("dim", [128, 200, 520])
+@pytest.mark.parametrize("b", [360_000 // 3, 360_000 // 3 + 1])
+def test_semiring_gradient_on_both_sides_of_its_line(kind, dim, b):
+    n_ent, n_rel = 9_000, 7
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(dim + b)
+    x = torch.rand(n_ent + n_rel, dim, generator=gen, device=DEV) - 0.5
+    h, r, t = (torch.randint(0, hi, (b,), generator=gen, device=DEV, dtype=torch.int32) for hi in (n_ent, n_rel, n_ent))
+    h[: b // 3] = 11
+    ctx = B.Context(B.make_config("transe", "l2", n_ent, n_rel, dim, b, 0), DEV)
+    inc, grads = B.Incidence(ctx), B.Grads(ctx)
+    none = torch.zeros(0, dtype=torch.int32, device=DEV)
+    B.stx_build_incidence(ctx, h, r, t, none, none, 0, inc)
+    gz, work = torch.rand(b, dim, generator=gen, device=DEV) - 0.5, torch.empty(3 * b * dim, device=DEV)
+    B.stx_spmm_semiring_t(ctx, inc, B.Params(x), kind, gz, work, grads)
+    torch.cuda.synchronize()
+    cols = [c.long() for c in (h, r + n_ent, t)]
+    leaves = [x.double()[c].requires_grad_() for c in cols]
+    if kind == B.STX_DISTMULT:
+        z = leaves[0] * leaves[1] * leaves[2]
+    else:
+        ch, cr, ct = (torch.view_as_complex(v.view(b, dim // 2, 2)) for v in leaves)
+        z = torch.view_as_real(ch * cr * ct.conj() if kind == B.STX_COMPLEX else ch * cr - ct).reshape(b, dim)
+    g = torch.autograd.grad(z, leaves, gz.double())
+    u = int(inc.n_touched.item())
+    touched = inc.at_touched_cols[:u].long()
+    want = torch.zeros(n_ent + n_rel, dim, dtype=torch.float64, device=DEV)
+    size = torch.zeros_like(want)
+    # (the roundings of a ComplEx term are of the products it is the sum of: at most twice their larger ones, gz and two factors of 1/2)
+    for c, v in zip(cols, g):
+        want.index_add_(0, c, v)
+        size.index_add_(0, c, v.abs() + 2.0 ** -3)
+    assert torch.all((grads.rows[:u, :dim].double() - want[touched]).abs() <= 1e-5 * size[touched])
+
+
 # TransR's rows of dL/dx and dL/dy, on both sides of a million entries: a batch's gradient is the sum of its halves', which lie on
 # the short side.
 @pytest.mark.parametrize("dim", [64, 128, 256])
