@@ -15,16 +15,36 @@ def _build(ctx, inc, h, r, t, nh, nt, k):
     torch.cuda.synchronize()
 
 
-# 1,024 entries a tile: 1 tile, the tables that are added up in one go (448 tiles), in two (449, 512), two levels (beyond, 4,096 a
-# tile), and a last tile of one entry
-@pytest.mark.parametrize("entries", [3, 1024 * 3, 448 * 1024, 449 * 1024, 511 * 1024 + 1, 512 * 1024, 512 * 1024 + 3, 33 * 4096 * 8])
-@pytest.mark.parametrize("skew", ["one column", "spread"])
-def test_sorted_transpose_of_full_tiles(entries, skew):
-    b, n_ent, n_rel = entries // 3, 70_000, 3
+# columns, entries, and what the sort does with them: bits of a digit, entries a tile, levels of its tables, and rounds of rows that a
+# workgroup adds two counts a word before it takes them apart (one level)
+SORTS = [(70_003, 3, 6, 1024, 1, 1), (70_003, 1024 * 3, 6, 1024, 1, 1), (70_003, 512 * 1024 - 2, 6, 1024, 1, 1),
+         (40_003, 448 * 1024 - 1, 8, 1024, 1, 1), (40_003, 448 * 1024 + 2, 8, 1024, 1, 2), (40_003, 512 * 1024 - 2, 8, 1024, 1, 2),
+         (40_003, 512 * 1024 + 1, 8, 4096, 1, 3), (40_003, 512 * 4096 - 2, 8, 4096, 1, 8), (70_003, 33 * 4096 * 8, 6, 4096, 1, 2),
+         (40_003, 512 * 4096 + 1, 8, 4096, 2, 0), (40_003, 1024 * 4096 + 2, 8, 4096, 2, 0), (70_003, 1025 * 4096 + 1, 6, 4096, 2, 0),
+         (3, 512 * 4096 + 1, 2, 4096, 2, 0), (3, 300 * 1024, 2, 1024, 1, 0)]
+
+
+def _sort_of(cols, nnz):
+    bits = max(1, (cols - 1).bit_length())
+    passes = -(-bits // 8)
+    digit = -(-bits // passes)
+    tile = 1024 if nnz <= 1 << 19 else 4096
+    tiles, parts = -(-nnz // tile), 256 // max(1, (1 << digit) // 8)
+    levels = 2 if tiles > 512 else 1
+    rows = 65535 // tile // 8 * 8 * parts
+    return digit, tile, levels, -(-tiles // rows) if levels == 1 and digit > 2 else 0
+
+
+@pytest.mark.parametrize("n_cols,entries,digit,tile,levels,rounds", SORTS)
+@pytest.mark.parametrize("skew", ["one digit", "spread"])
+def test_sorted_transpose_of_full_tiles(n_cols, entries, digit, tile, levels, rounds, skew):
+    b, n_rel = entries // 3, 3 if n_cols > 3 else 1
+    n_ent = n_cols - n_rel
+    assert 3 * b == entries and _sort_of(n_cols, entries) == (digit, tile, levels, rounds)
     rng = np.random.default_rng(entries)
-    if skew == "one column":                                # every tile's keys fall on two digits, 65,536 of them in 64 tiles
-        h, t, r = np.full(b, 65_000), np.full(b, 65_000), np.zeros(b)
-        h[-1] = 5
+    if skew == "one digit":                                 # all of a tile's keys fall on one first digit, as many as a count can be
+        h, t, r = np.full(b, max(0, n_ent - (1 << digit))), np.full(b, max(0, n_ent - (2 << digit))), np.zeros(b)
+        h[-1] = 5 % n_ent
     else:
         h, t, r = rng.integers(0, n_ent, b), rng.integers(0, n_ent, b), rng.integers(0, n_rel, b)
     ctx = B.Context(B.make_config("transe", "l2", n_ent, n_rel, 4, b, 1), DEV)
@@ -36,7 +56,7 @@ def test_sorted_transpose_of_full_tiles(entries, skew):
     assert np.array_equal(inc.at_row_idx[:nnz].cpu().numpy(), order // 3)
     assert np.array_equal(inc.at_sign[:nnz].cpu().numpy(), np.where(order % 3 == 2, -1, 1))
     u = int(inc.n_touched.item())
-    want, start = np.unique(cols, return_index=False), np.flatnonzero(np.diff(cols[order], prepend=-1))
+    want, start = np.unique(cols), np.flatnonzero(np.diff(cols[order], prepend=-1))
     assert u == len(want) and np.array_equal(inc.at_touched_cols[:u].cpu().numpy(), want)
     assert np.array_equal(inc.at_seg_ptr[:u + 1].cpu().numpy(), np.append(start, nnz))
 
