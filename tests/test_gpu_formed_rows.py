@@ -79,3 +79,34 @@ def test_gradients_are_those_of_the_tables_the_forward_pass_saw():
     m.grads.rows.zero_()
     m.backward()
     assert np.array_equal(m.grad_rows_numpy()[1], want)
+
+
+@pytest.mark.parametrize("mean", [False, True])
+@pytest.mark.parametrize("model,dist,n_ent,n_rel,b,k,dim", CASES)
+def test_sliced_forward_pass_against_64_bits(model, dist, n_ent, n_rel, b, k, dim, mean):
+    wl, tabs, hd, rd, td, neg = _setup(model, dist, n_ent, n_rel, b, k, dim)
+    reduce = B.STX_MEAN if mean else B.STX_SUM
+    ma, mb = (G.GpuModel(wl, tabs, reduce=reduce) for _ in range(2))
+    _forward(ma, hd, rd, td, k, neg)
+    ma.backward_sgd(1e-5)
+    x = mb.params.ent.clone()
+    batch = B.make_batch(hd, rd, td, k, 5, 0, b, 0, neg[0], neg[1])
+    B.stx_train_step(mb.ctx, batch, mb.inc, mb.params, None, 1e-5, mb.scores, mb.loss)
+    assert torch.equal(ma.loss, mb.loss) and torch.equal(ma.params.ent, mb.params.ent)
+    rows = mb.inc.n_rows
+    scores = mb.scores[:rows].double()
+    want = torch.empty_like(scores)
+    weight = mb.params.rel_weight.double()
+    for c in torch.arange(rows, device=G.DEV).split(1 << 16):
+        col = mb.inc.a_colidx[:3 * rows].view(rows, 3)[c].long()
+        y = (x[col[:, 0]] + x[col[:, 1]]) - x[col[:, 2]]  # (rounded as the library rounds it, and so is the torus' fraction)
+        if model == "toruse":
+            f = y - torch.floor(y)
+            y = torch.minimum(f, 1.0 - f)
+        s = y.double().square().sum(1)
+        want[c] = weight[col[:, 1] - n_ent] * (s if dist == "l2_sq" else s.sqrt())
+    # 32-bit sums of non-negative terms: at most dim roundings of 2^-24 each, and those of the term, the root and the weight
+    assert torch.all((scores - want).abs() <= (dim + 4) * 2.0 ** -24 * want)
+    pos, n = scores[:b].float().repeat_interleave(k), scores[b:].float()
+    hinge = ((wl.margin + pos) - n).clamp(min=0.0).double().sum() / (b * k if mean else 1)
+    assert hinge > 0 and abs(mb.loss.double().item() - hinge.item()) <= 1e-6 * hinge.item()
