@@ -1057,13 +1057,22 @@ __global__ __launch_bounds__(kThreads) void k_sgd_rows(const int32_t *__restrict
 //
 // Sums that round (dense rows; the L1 kinds' when a mean over a number of pairs that is no power of two, or weights of relations,
 // scale them) keep short chunks up to a million entries: a training run that adds in another order soon decides some hinge the
-// other way.  Long ones would give TransR's step at d = k = 128 one per cent from 420,000 entries on.
+// other way.  TransR's round as well, but its rows come out of products of bfloat16 operands, whose roundings are 2^15 times
+// larger: its line is 3,600 tiles, 460,800 entries of up to 128 floats and 230,400 of more.  Whole steps with short and with long
+// chunks, three negatives, 1,000 relations: d = k = 128: 189 and 188 us at 300,000 entries, 243 and 241 at 420,000, 272 and 269 at
+// 510,000, 416 and 413 at 900,000; d = k = 256: 506 and 509 at 180,000, 609 and 609 at 240,000, 726 and 719 at 360,000, 1,446 and
+// 1,429 at 900,000; relation columns in a product of their own, d = 128, k = 256: 334 and 340 at 60,000, 699 and 693 at 180,000,
+// 845 and 834 at 240,000, 1,635 and 1,608 at 510,000.
 // Exact sums have the same bits either way.  us of an L1 step with short and with long chunks, 30,000 entities: d = 128: 63.4 and
 // 64.2 at 300,000 entries, 78.1 and 76.1 at 420,000, 111.8 and 108.1 at 720,000; d = 200: 71.7 and 74.6 at 240,000, 82.2 and 82.2 at
 // 300,000, 104.1 and 98.9 at 420,000, 178 and 164 at 900,000; two slices a row, d = 512: 82.5 and 85.4 at 120,000, 103 and 98.5 at
 // 180,000; four, d = 1024: 85.9 and 89.2 at 60,000, 127 and 123 at 120,000.  (Products alone, without the last kernel of the build
 // in their launch, meet their line at half as many entries: d = 200: 14.2 and 16.5 at 120,000, 17.9 and 17.2 at 180,000.)
-static bool short_chunks(int64_t n, int slices, bool exact) { return exact ? n * slices <= 300000 : n <= (1 << 20); }
+static bool short_chunks(const stx_ctx *c, SegRows kind, int64_t n, int slices, int tile)
+{
+    if (kind == SegRows::packed_exact) return n * slices <= 300000;
+    return n <= (c->cfg.model == STX_TRANSR ? 3600 * tile : 1 << 20);
+}
 
 template <int LPR, int ITERS>
 static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_t e_end, const float *src_a,
@@ -1073,7 +1082,7 @@ static void seg_go(stx_ctx *c, const stx_incidence *inc, int32_t e_begin, int32_
     const bool packed_src = kind != SegRows::dense;
     constexpr int CH_LONG = LPR == 64 ? 64 : (LPR < 32 ? LPR : 32), CH_SHORT = LPR < 16 ? LPR : 16;
     constexpr int GROUPS = kThreads / LPR;
-    const bool small = short_chunks(e_end - e_begin, ITERS, kind == SegRows::packed_exact);
+    const bool small = short_chunks(c, kind, e_end - e_begin, ITERS, GROUPS * CH_SHORT);
     const int tile = GROUPS * (small ? CH_SHORT : CH_LONG);
     const int ntiles1 = (e_end - e_begin + tile - 1) / tile;
     SegSecond sec{0x7fffffff, 0, 0, nullptr, nullptr, nullptr, nullptr, 0, 0};
