@@ -110,7 +110,7 @@ __device__ inline bool forward_fast_rows(const int32_t i, const int lig, const F
     auto id = [&](int j) { return __shfl(mine[j / LPR], j % LPR, LPR); };
     const int32_t c0 = id(0), c1 = id(1), c2 = id(2);
     const float wr = a.rel_weight ? a.rel_weight[c1 - a.n_ent] : 1.0f;
-    // (lanes past the row's width hold zeros and take part in the reductions only)
+    // (lanes past the row's width hold its last float4 again, see load_vec: every reduction leaves them out)
     RowVec<ITERS> hr, pr, pt, xp;
     load_vec<LPR, ITERS>(X + (int64_t)c0 * dim, d4, lig, hr);
     load_vec<LPR, ITERS>(X + (int64_t)c1 * dim, d4, lig, pr);

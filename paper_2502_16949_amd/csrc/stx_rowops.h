@@ -118,7 +118,8 @@ __device__ inline float coef_scale(float coef, float dist)
     return coef;
 }
 
-// Sum over 16 neighbouring lanes (in all of them), by data-parallel moves: the bits of group_sum<16>.
+// Sum over 16 neighbouring lanes (in all of them), by data-parallel moves.  Neighbours are added first, where group_sum begins with
+// the lanes farthest apart: sums that are to have the same bits use one of the two (the sliced forward pass and SLICES below: this).
 __device__ inline float sum16(float v)
 {
     auto moved = [](float x, auto ctrl) {
