@@ -1299,11 +1299,15 @@ static void semiring_t_go(stx_ctx *c, const stx_incidence *inc, const float *X, 
     constexpr int CH_LONG = LPR == 64 ? 64 : (LPR < 32 ? LPR : 32), CH_SHORT = LPR < 16 ? LPR : 16;
     constexpr int GROUPS = kThreads / LPR;
     const int32_t nnz = (int32_t)inc->nnz;
-    // Short chunks (see short_chunks) up to where long ones are faster at every size measured; below, either is, by how full the
-    // last workgroups leave the chip.  ComplEx, us with short and with long ones at 162,000, 240,000, 330,000 and 390,000 entries:
-    // d = 128: 32.1 and 34.6, 45.3 and 44.1, 59.6 and 60.8, 67.2 and 64.0; d = 200: 53.5 and 55.7, 75.1 and 72.5, 101 and 103, 116
-    // and 108 (900,000: 254 and 239); two slices a row, d = 512: 114 and 116, 163 and 165, 219 and 221, 257 and 248.
-    const bool small = nnz <= 360000;
+    // Short chunks (see short_chunks) up to 147,456 entries, and up to 360,000 where long ones would leave the 256 compute units with
+    // uneven numbers of workgroups: an eighth more in the fullest than in the mean, a thirty-second where rows have several slices.
+    // ComplEx, us with short and with long ones at 120,000, 162,000, 240,000, 330,000 and 390,000 entries, which are 1.83, 2.47, 3.66,
+    // 5.04 and 5.95 long workgroups a unit: d = 200: 42.5 and 43.3, 53.5 and 55.7, 75.1 and 72.5, 101 and 103, 116 and 108; d = 128:
+    // 26.1 and 27.2, 32.1 and 34.6, 45.3 and 44.1, 59.6 and 60.8, 67.2 and 64.0; two slices a row, d = 512, 180,000, 195,000, 240,000
+    // and 255,000 entries (5.50, 5.95, 7.32 and 7.79): 126 and 128, 135 and 132, 164 and 166, 174 and 168.
+    constexpr int CUS = 256;
+    const int n_long = (nnz + GROUPS * CH_LONG - 1) / (GROUPS * CH_LONG) * ITERS, fullest = (n_long + CUS - 1) / CUS;
+    const bool small = nnz <= 147456 || (nnz <= 360000 && 32 * CUS * fullest > (ITERS > 1 ? 33 : 36) * n_long);
     const int tile = GROUPS * (small ? CH_SHORT : CH_LONG), ntiles = (nnz + tile - 1) / tile;
     const dim3 grid((unsigned)ntiles, (unsigned)ITERS);    // wide rows: column slices of one float4 per lane
     const int d4 = c->cfg.dim / 4;

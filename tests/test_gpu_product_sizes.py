@@ -135,10 +135,11 @@ def test_sums_that_round_keep_their_order(model, dist, dim, mean, weights, b_sma
     assert torch.equal(got[0].view(torch.int32), got[1].view(torch.int32))
 
 
-# The semiring gradient, whose line is 360,000 entries.
+# The semiring gradient: short chunks up to 147,456 entries, and up to 360,000 where long ones fill the chip unevenly (162,000 entries:
+# 2.47 workgroups a unit, and three times that at 520 floats; 180,000: 2.75; 360,000: 5.50; 195,000: 2.98)
 @pytest.mark.parametrize("kind", [B.STX_DISTMULT, B.STX_COMPLEX, B.STX_ROTATE])
 @pytest.mark.parametrize("dim", [128, 200, 520])
-@pytest.mark.parametrize("b", [360_000 // 3, 360_000 // 3 + 1])
+@pytest.mark.parametrize("b", [49_152, 54_000, 60_000, 65_000, 120_000, 120_001])
 def test_semiring_gradient_on_both_sides_of_its_line(kind, dim, b):
     n_ent, n_rel = 9_000, 7
     gen = torch.Generator(device=DEV)
