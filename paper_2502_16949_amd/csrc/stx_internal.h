@@ -446,11 +446,12 @@ inline bool formed_rows(const stx_ctx *c, int64_t n_rows)
     const int64_t cols = c->cfg.n_ent + c->cfg.n_rel, row = (int64_t)c->cfg.dim * 4;
     // (Rows of fewer slices: the launches more and the update of its own take longer to repay.  14,951 entities, L2, us a step
     // with stored rows, with formed ones while every pair is active, and with formed ones once half of them are: d = 128 at
-    // 202 MiB of rows 233, 231 and 189, at 300 MiB 328, 308 and 246, at 384 MiB 435, 377 and 297; d = 256 at 128 MiB 136, 161
-    // and 136, at 202 MiB 235, 215 and 175; d = 512 at 128 MiB 157, 150 and 127, at 202 MiB 227, 194 and 157; d = 1024 at
-    // 128 MiB 156, 160 and 139, at 202 MiB 220, 205 and 172.  So the lines lie where rows are formed faster whatever the share
-    // of active pairs, at d = 128 well behind that point.  d = 100 at 480 MiB 629, 555 and 436; 40,000 entities, whose slices
-    // are 10 MiB, d = 512 at 480 MiB 544, 397 and 310: both outside the lines.)
+    // 128 MiB of rows 168, 166 and 144, at 202 MiB 237, 222 and 186, at 300 MiB 334, 297 and 240, at 384 MiB 440, 360 and 284;
+    // d = 256 at 64 MiB 89, 105 and 95, at 128 MiB 156, 148 and 129, at 202 MiB 238, 198 and 168; d = 512 at 128 MiB 162, 140 and
+    // 121, at 202 MiB 242, 184 and 155; d = 1024 at 128 MiB 167, 156 and 137, at 202 MiB 243, 195 and 168.  The lines lie well
+    // behind the points from which rows are formed faster whatever the share of active pairs: they were drawn for a forward pass
+    // of whole rows, and a lower one would give such steps other bits.  d = 100 at 480 MiB 626, 564 and 439; 40,000 entities,
+    // whose slices are 10 MiB, d = 512 at 480 MiB 564, 398 and 323: both outside the lines.)
     const int64_t least = (int64_t)(c->cfg.dim >= 256 ? 192 : 384) << 20;
     return stacked && !packed_grad(c) && cols * 256 <= ((int64_t)6 << 20) && c->cfg.dim >= 128 && n_rows * row >= least &&
            // room in the buffer of those rows for what replaces them: coefficients, sorted records, their heads, gradient rows
