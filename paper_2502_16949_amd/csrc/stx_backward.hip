@@ -1301,15 +1301,15 @@ static void semiring_t_go(stx_ctx *c, const stx_incidence *inc, const float *X, 
     const int32_t nnz = (int32_t)inc->nnz;
     // Short chunks (see short_chunks) up to 2,304 tiles of them, a little above what the chip holds at once (147,456 entries of more than
     // 128 floats, 294,912 of up to 128), and up to 360,000 entries where long ones would leave the 256 compute units with uneven
-    // numbers of workgroups: an eighth more in the fullest than in the mean, a thirty-second where rows have several slices.
+    // numbers of workgroups: an eighth more in the fullest than in the mean, a sixteenth where rows have several slices.
     // ComplEx, us with short and with long ones at 120,000, 162,000, 240,000, 330,000 and 390,000 entries, which are 1.83, 2.47, 3.66,
     // 5.04 and 5.95 long workgroups a unit: d = 200: 42.5 and 43.3, 53.5 and 55.7, 75.1 and 72.5, 101 and 103, 116 and 108; d = 128:
     // 26.1 and 27.2, 32.1 and 34.6, 45.3 and 44.1 (196,608 of a power law: 43.5 and 43.7), 59.6 and 60.8, 67.2 and 64.0; two slices a
     // row, d = 512, 180,000, 195,000, 240,000 and 255,000 entries (5.50, 5.95, 7.32 and 7.79): 126 and 128, 135 and 132, 164 and 166,
-    // 174 and 168.
+    // 174 and 168; 232,474 entities, d = 368, 317,196 entries (9.69): 237 and 231 for product and gradient.
     constexpr int CUS = 256;
     const int n_long = (nnz + GROUPS * CH_LONG - 1) / (GROUPS * CH_LONG) * ITERS, fullest = (n_long + CUS - 1) / CUS;
-    const bool small = nnz <= 2304 * GROUPS * CH_SHORT || (nnz <= 360000 && 32 * CUS * fullest > (ITERS > 1 ? 33 : 36) * n_long);
+    const bool small = nnz <= 2304 * GROUPS * CH_SHORT || (nnz <= 360000 && 32 * CUS * fullest > (ITERS > 1 ? 34 : 36) * n_long);
     const int tile = GROUPS * (small ? CH_SHORT : CH_LONG), ntiles = (nnz + tile - 1) / tile;
     const dim3 grid((unsigned)ntiles, (unsigned)ITERS);    // wide rows: column slices of one float4 per lane
     const int d4 = c->cfg.dim / 4;
